@@ -124,16 +124,11 @@ struct DeviceGuard {
 };
 
 constexpr int64_t MAX_DCOL = 32768;
-// L^-1 and L^-T L^-1 fused into the factorization launches against the separate recursive-doubling
-// inverse and product, damped inverse of a d x d matrix: 1.1 vs 1.5 ms at d = 2304, even from 4096 to
-// 5120 (3.77 vs 3.80, 6.30 vs 6.29 ms), slower beyond (10.5 vs 9.8 ms at 6144, 25.9 vs 21.2 ms at 8192:
-// three products per inverse tile against one, and the launches are full without them)
-constexpr int FUSED_INVERSE_MAX_D = 4096;
 constexpr int64_t MAX_DROW = 65535;
 constexpr int I8_MIN_D = 384;     // below: too few 128-wide tiles for the digit traffic to pay (measured on 256- and 288-column layers)
 constexpr int64_t I8_MIN_N = 512;
 
-enum { FLAG_NOTPD_H = 0, FLAG_NOTPD_HINV = 1, FLAG_BADPERM = 2, FLAG_COUNT = 4 };
+enum { FLAG_NOTPD_H = 0, FLAG_NOTPD_HINV = 1, FLAG_BADPERM = 2, FLAG_STALLED = 3, FLAG_COUNT = 4 };
 
 // The flag words; all of them start at zero when the buffer is made.
 static int ensure_flags(fobq_ctx* ctx)
@@ -146,47 +141,28 @@ static int ensure_flags(fobq_ctx* ctx)
     return FOBQ_OK;
 }
 
-static int ensure_factor_ws(fobq_ctx* ctx, int64_t d)
+// Scratch of the damped inverse; `rows` > 0: with the per-row loss terms of a layer behind the words of the launch, so
+// that one clearing launch covers both.
+static int ensure_inverse_ws(fobq_ctx* ctx, int64_t d, int64_t rows)
 {
     const size_t dd = (size_t)d * d * sizeof(double);
-    FOBQ_TRY(ctx->Hd.ensure(dd), "workspace Hd");
-    FOBQ_TRY(ctx->Linv.ensure(dd), "workspace Linv");
-    FOBQ_TRY(ctx->T.ensure(dd), "workspace T");
+    FOBQ_TRY(ctx->tiles.ensure(flow_tiles_bytes((int)d)), "workspace tiles");
+    FOBQ_TRY(ctx->gt.ensure(flow_gt_bytes((int)d)), "workspace block inverses");
     FOBQ_TRY(ctx->Hinv.ensure(dd), "workspace Hinv");
-    FOBQ_TRY(ctx->U.ensure(dd), "workspace U");
-    FOBQ_TRY(ctx->Dblk.ensure((4 * 64 * 64 + 128) * sizeof(double)), "workspace Dblk");
-    FOBQ_TRY(ctx->scal.ensure(16 * sizeof(double)), "workspace scal");
+    const size_t words = ((size_t)flow_inverse_words((int)d) * sizeof(int) + 7) / 8 * 8;
+    FOBQ_TRY(ctx->words.ensure(words + (size_t)rows * sizeof(double)), "workspace words and loss terms");
+    ctx->lossrow = reinterpret_cast<double*>(ctx->words.as<unsigned char>() + words);
+    ctx->words_len = (int64_t)(words / sizeof(int)) + 2 * rows;
     return ensure_flags(ctx);
 }
 
-// damped H -> Hinv (upper tiles valid).  Enqueue only.
+// damped H -> Hinv (upper tiles valid).  Enqueue only; the words have been cleared.
 static int enqueue_inverse(fobq_ctx* ctx, const double* H, int d, double damp, double damp_abs)
 {
-    hipStream_t s = ctx->stream;
     int* flags = ctx->flags.as<int>();
-    double* Hd = ctx->Hd.as<double>();
-    double* L = ctx->U.as<double>();       // U is free until the elimination
-    double* Linv = ctx->Linv.as<double>();
-    bool fused = false;
-    {
-        StageScope sc(ctx, FOBQ_STAGE_CHOLESKY);
-        FOBQ_TRY(launch_damp(s, H, d, damp, damp_abs, Hd, ctx->scal.as<double>()), "damp");
-        // the triangular inverse and L^-T L^-1 ride along with the factorization (tiles in the shadow of
-        // its critical path) while the launches are small; for large d the extra tiles would slow the launches down by
-        // more than the separate recursive-doubling inverse costs
-        const bool fused_inverse = d <= FUSED_INVERSE_MAX_D;
-        // nothing reads L itself when the inverse rides along: it is not stored then
-        FOBQ_TRY(cholesky_lower(ctx, Hd, fused_inverse ? nullptr : L, d, Linv, flags + FLAG_NOTPD_H, fused_inverse ? ctx->T.as<double>() : nullptr,
-                                ctx->Hinv.as<double>()), "cholesky");
-        fused = fused_inverse;
-    }
-    {
-        StageScope sc(ctx, FOBQ_STAGE_INVERSE);
-        if (!fused) {
-            FOBQ_TRY(trtri_lower(ctx, L, d, Linv, ctx->T.as<double>()), "trtri");
-            FOBQ_TRY(lauum_upper(ctx, Linv, d, ctx->Hinv.as<double>()), "lauum");
-        }
-    }
+    StageScope sc(ctx, FOBQ_STAGE_CHOLESKY);
+    FOBQ_TRY(launch_flow_inverse(ctx->stream, ctx->cus, H, d, damp, damp_abs, ctx->Hinv.as<double>(), ctx->tiles.as<double>(),
+                                 ctx->gt.as<double>(), ctx->words.as<int>(), flags + FLAG_NOTPD_H, flags + FLAG_STALLED), "inverse");
     return FOBQ_OK;
 }
 
@@ -293,6 +269,7 @@ static int read_flags(fobq_ctx* ctx, const int* dev_flags)
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
     FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
+    if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch stopped making progress and was given up");
     if (h[FLAG_BADPERM]) return set_err(ctx, FOBQ_EINVAL, "perm_in is not a permutation of 0..d_col-1");
     if (h[FLAG_NOTPD_H]) return set_err(ctx, FOBQ_ENOTPD, "damped Hessian is not positive definite (Cholesky pivot <= 0)");
     if (h[FLAG_NOTPD_HINV]) return set_err(ctx, FOBQ_ENOTPD, "shared inverse Hessian lost positive definiteness (elimination pivot <= 0)");
@@ -355,9 +332,9 @@ using namespace fobq;
 
 static std::vector<DevBuf*> all_buffers(fobq_ctx* ctx)
 {
-    return {&ctx->Hpart, &ctx->H, &ctx->Hd, &ctx->Linv, &ctx->T, &ctx->Hinv, &ctx->A, &ctx->U, &ctx->Un,
-            &ctx->Dblk, &ctx->scal, &ctx->flags, &ctx->Wp, &ctx->DT, &ctx->corr, &ctx->codesT, &ctx->scale, &ctx->zero,
-            &ctx->S, &ctx->Spart, &ctx->perm, &ctx->invperm, &ctx->lossrow, &ctx->maps_pad, &ctx->i8planes, &ctx->i8sh, &ctx->i8amax, &ctx->batch_pool, &ctx->batch_desc, &ctx->obq, &ctx->hcorr, &ctx->strips};
+    return {&ctx->Hpart, &ctx->H, &ctx->tiles, &ctx->gt, &ctx->words, &ctx->Hinv, &ctx->A, &ctx->U, &ctx->Un,
+            &ctx->Dblk, &ctx->flags, &ctx->Wp, &ctx->DT, &ctx->corr, &ctx->codesT, &ctx->scale, &ctx->zero,
+            &ctx->S, &ctx->Spart, &ctx->perm, &ctx->invperm, &ctx->maps_pad, &ctx->i8planes, &ctx->i8sh, &ctx->i8amax, &ctx->batch_pool, &ctx->batch_desc, &ctx->obq, &ctx->hcorr, &ctx->strips};
 }
 
 extern "C" {
@@ -712,10 +689,10 @@ int fobq_spd_inverse(fobq_ctx* ctx, const double* H, int64_t d64, double* Hinv)
     DeviceGuard g(ctx->device);
     if (!g.ok) return set_err(ctx, FOBQ_EHIP, "cannot select device %d", ctx->device);
     const int d = (int)d64;
-    int rc = ensure_factor_ws(ctx, d);
+    int rc = ensure_inverse_ws(ctx, d, 0);
     if (rc) return rc;
     rc = [&]() -> int {
-        FOBQ_TRY(launch_clear_words(ctx->stream, ctx->flags.p, FLAG_COUNT, nullptr, 0), "clear flags");
+        FOBQ_TRY(launch_clear_words(ctx->stream, ctx->flags.p, FLAG_COUNT, ctx->words.p, ctx->words_len), "clear flags");
         int r = enqueue_inverse(ctx, H, d, 0.0, 0.0);
         if (r) return r;
         // full symmetric copy out of the upper tiles
@@ -891,7 +868,7 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     const int R = p.R, d = p.d, G = p.G, steps = p.steps, block = p.block, Rp = p.Rp, nblocks = p.nblocks;
     // grid and the W-only part of the column scores: on the side stream, beside the factorization.  The
     // events that order the streams ride on launches (see gemm64's `done`), here on the clearing kernel.
-    FOBQ_TRY(launch_clear_words(s, ctx->flags.p, FLAG_COUNT, ctx->lossrow.p, 2 * (int64_t)R, ctx->sync_ev[EV_FORK]),
+    FOBQ_TRY(launch_clear_words(s, ctx->flags.p, FLAG_COUNT, ctx->words.p, ctx->words_len, ctx->sync_ev[EV_FORK]),
              "clear flags and loss");
     FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
     int rc = enqueue_grid_scores(ctx, ctx->side, p.W, R, d, opts, p.ob, out->scales, out->zeros, ctx->sync_ev[EV_JOIN]);
@@ -917,7 +894,7 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     const double* zero = p.ob.zero;
     int* perm = p.ob.perm;
     uint8_t* codesT = ctx->codesT.as<uint8_t>();
-    double* lossrow = ctx->lossrow.as<double>();
+    double* lossrow = ctx->lossrow;
 
     if (block == 1) {
         // Eq. 9 / 11 and Eq. 12 one column at a time
@@ -1026,15 +1003,16 @@ static int quantize_enqueue(fobq_ctx* ctx, const float* W, int64_t d_row, int64_
 
     // Every allocation (scratch growth, streams, events) comes before the first launch: scratch growth may
     // free a buffer, and a failure in here leaves nothing in flight.
-    rc = ensure_factor_ws(ctx, p.d);
+    rc = ensure_inverse_ws(ctx, p.d, p.R);
     if (rc) return rc;
+    FOBQ_TRY(ctx->U.ensure(dd), "workspace U");
+    FOBQ_TRY(ctx->Dblk.ensure((4 * 64 * 64 + 128) * sizeof(double)), "workspace Dblk");
     FOBQ_TRY(ctx->A.ensure(dd), "workspace A");
     FOBQ_TRY(ctx->Un.ensure(dd), "workspace Un");
     FOBQ_TRY(ctx->Wp.ensure((size_t)p.R * p.d * sizeof(double)), "workspace Wp");
     FOBQ_TRY(ctx->DT.ensure((size_t)p.d * p.Rp * sizeof(double)), "workspace DT");
     FOBQ_TRY(ctx->corr.ensure(2 * (size_t)p.R * 64 * sizeof(double)), "workspace corr");
     FOBQ_TRY(ctx->codesT.ensure((size_t)p.d * p.Rp), "workspace codesT");
-    FOBQ_TRY(ctx->lossrow.ensure((size_t)p.R * sizeof(double)), "workspace lossrow");
     rc = ensure_order_bufs(ctx, p.R, p.d, p.G, &p.ob);
     if (rc) return rc;
     rc = ensure_sync_events(ctx, (size_t)EV_ROWS0 + p.nblocks + 2);

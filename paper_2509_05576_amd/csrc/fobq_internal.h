@@ -112,9 +112,12 @@ struct fobq_ctx {
     fobq::DevBuf H;         // d x d fp64, (2/N) X X^T, full symmetric
 
     // factorization / elimination workspace (all d x d fp64 unless noted)
-    fobq::DevBuf Hd, Linv, T, Hinv, A, U, Un;
+    fobq::DevBuf tiles, gt; // published tiles of a factorization and its transposed block inverses (see flow.hip)
+    fobq::DevBuf words;     // words of its launches, then d_row fp64 per-row loss terms (lossrow); cleared per layer
+    double* lossrow = nullptr;
+    int64_t words_len = 0;  // 4-byte words of that buffer in use
+    fobq::DevBuf Hinv, A, U, Un;
     fobq::DevBuf Dblk;      // diagonal-block scratch: 2 x (64 x 64) L11^-1, 2 x (64 x 64) G, 2 x 64 reciprocal pivots
-    fobq::DevBuf scal;      // a few fp64 scalars (lambda, loss)
     fobq::DevBuf obq;       // running inverses of the per-row baseline (fobq_obq_rows), rows x d x d fp64
     fobq::DevBuf flags;     // FLAG_WORDS int32: status flags written by kernels (cleared per call), then words
                             // that live as long as the context (FLAG_WORD_MATE: see chol_iter_kernel)
@@ -131,7 +134,6 @@ struct fobq_ctx {
     fobq::DevBuf scale, zero;   // d_row x G fp64
     fobq::DevBuf S, Spart;  // d fp64, chunks x d fp64
     fobq::DevBuf perm, invperm; // d int32
-    fobq::DevBuf lossrow;   // d_row fp64
 
     // second stream: the column loop of block k only needs the pivot rows of blocks <= k, so it
     // runs behind the shared-Hinv elimination on its own stream, ordered by one event per block
@@ -214,7 +216,6 @@ hipError_t launch_i8_slice_conv(hipStream_t s, const float* padded, int n_img, i
                                 int ho, int wo, int64_t npix, int64_t pix0, int64_t n, const int* sh, signed char* planes);
 hipError_t launch_xxt_i8(hipStream_t s, const signed char* planes, const int* sh, int d, int64_t n, double* Hpart,
                          int splits, LaunchEvents ev = LaunchEvents(), I8Rect rect = I8Rect());
-hipError_t launch_damp(hipStream_t s, const double* H, int d, double damp, double damp_abs, double* Hd, double* lam_out);
 // hessian_offsets.hip: Hessian of a stride-1 convolution by tap offsets (two block rows from the digit-product kernel,
 // the other blocks by corrections over single rows and columns of the padded maps)
 constexpr int OFFSET_MAX_TAPS = 9, OFFSET_MAX_JOBS = 128, OFFSET_MAX_PAIRS = 81, OFFSET_MAX_TERMS = 384;
@@ -238,14 +239,15 @@ hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_i
 hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, int c,
                                            int k, const double* corr, const int* poison);
 
+// flow.hip: damped H -> upper tiles of Hinv = (H + lambda I)^-1, lambda = damp * mean(diag H) + damp_abs, in one launch.  tiles, gt:
+// scratch; words: flow_inverse_words(d) zeroed words; *notpd / *stalled are set to 1 when a pivot is not positive / the launch gave up
+int64_t flow_inverse_words(int d);
+size_t flow_tiles_bytes(int d);
+size_t flow_gt_bytes(int d);
+hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
+                               double* gt, int* words, int* notpd, int* stalled);
+
 // factor.hip
-// Sacc != null (d x d scratch): L^-1 and the upper tiles of Hinv = L^-T L^-1 are completed alongside the
-// factorization; Sacc == null: only the diagonal blocks of L^-1 are written and Hinv is not touched
-// (trtri_lower and lauum_upper finish the job)
-hipError_t cholesky_lower(fobq_ctx* c, double* Hd, double* L, int d, double* Linv, int* flag, double* Sacc,
-                          double* Hinv);  // Hd = L L^T; Linv gets the diagonal-block inverses
-hipError_t trtri_lower(fobq_ctx* c, const double* L, int d, double* Linv, double* T);      // completes Linv
-hipError_t lauum_upper(fobq_ctx* c, const double* Linv, int d, double* Hinv);              // upper tiles of Linv^T Linv
 // `rows_ready` (may be null): rows_ready[k] is recorded on the context's stream once the pivot rows of
 // block k (rows k*block .. of U and Un) are complete.  In the fused form the event rides on the panel launch
 // as its stop event: a separate hipEventRecord between two dependent launches would be a bubble of about 4 us.

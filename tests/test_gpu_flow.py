@@ -1,0 +1,63 @@
+"""The factorization launches that exchange tiles between workgroups while they run (csrc/flow.hip): the result may not
+depend on which workgroup takes which tile, nor on what else runs on the GPU."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fobq():
+    import paper_2509_05576_amd as f
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU (no CPU fallback exists)")
+    f.load_library()
+    return f
+
+
+def _spd(d, seed):
+    """(2 / n) X X^T + 1 % of its mean diagonal, n < d: the damping alone keeps it positive definite."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    n = max(8, d // 2)
+    X = torch.relu(torch.randn((d, n), generator=g, device="cuda")).double()
+    H = (X @ X.T.contiguous()) * (2.0 / n)
+    H = 0.5 * (H + H.T)
+    H.diagonal().add_(0.01 * H.diagonal().mean())
+    return H.contiguous()
+
+
+# one to two blocks, block edges, more tiles than workgroups, several queue rows in flight
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 128, 129, 500, 1216, 2048])
+def test_inverse_is_the_same_every_time(fobq, d):
+    H = _spd(d, d)
+    with fobq.Ctx(0) as ctx:
+        first = fobq.fobq_spd_inverse(ctx.handle, H)
+        # residual of the first against 64-bit products: eps * kappa * d with kappa <= 1e4 here
+        R = first @ H - torch.eye(d, dtype=torch.float64, device="cuda")
+        assert float(R.abs().max()) <= 1e-9
+        for _ in range(12):
+            assert torch.equal(fobq.fobq_spd_inverse(ctx.handle, H), first)
+
+
+def test_inverses_on_several_contexts_at_once(fobq):
+    dims = [700, 1300, 200, 1000]
+    Hs = [_spd(d, 7 + d) for d in dims]
+    Ws = [torch.randn((40, d), device="cuda") for d in dims]
+    streams = [torch.cuda.Stream() for _ in dims]
+    ctxs = [fobq.Ctx(0, stream=s.cuda_stream) for s in streams]
+    torch.cuda.synchronize()
+    want = []
+    for c, W, H in zip(ctxs, Ws, Hs):
+        o = c.quantize_layer(W, H, bits=4)
+        want.append([t.clone() for t in (o.codes, o.Q, o.perm, o.loss)])
+    for _ in range(6):
+        outs = [c.quantize_layer(W, H, bits=4, wait=False) for c, W, H in zip(ctxs, Ws, Hs)]
+        for c in ctxs:
+            c.finish()
+        for o, w in zip(outs, want):
+            for a, b in zip((o.codes, o.Q, o.perm, o.loss), w):
+                assert torch.equal(a, b)
+    for c in ctxs:
+        c.close()
