@@ -70,22 +70,6 @@ LaunchEvents stage_launch_events(fobq_ctx* c, int stage)
     return ev;
 }
 
-// events (no timing) that order the side stream behind the context's stream and back
-static int ensure_sync_events(fobq_ctx* c, size_t n)
-{
-    if (!c->side && hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
-        c->side = nullptr;
-        return set_err(c, FOBQ_EHIP, "cannot create the side stream");
-    }
-    while (c->sync_ev.size() < n) {
-        hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-            return set_err(c, FOBQ_EHIP, "cannot create an event");
-        c->sync_ev.push_back(e);
-    }
-    return FOBQ_OK;
-}
-
 static void fold_events(fobq_ctx* c)
 {
     for (int st = 0; st < FOBQ_STAGE_COUNT; ++st) {
@@ -112,6 +96,31 @@ static void fold_events(fobq_ctx* c)
             return set_err(ctx, FOBQ_EHIP, "%s: injected failure (test hook)", what);     \
     } while (0)
 
+// the side stream and the events (no timing) that order it behind the context's stream and back; made once
+static hipError_t ensure_side_stream(fobq_ctx* c)
+{
+    if (c->side) return hipSuccess;
+    const hipError_t e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
+    if (e != hipSuccess) c->side = nullptr;
+    return e;
+}
+
+static hipError_t ensure_sync_event(fobq_ctx* c, size_t i)
+{
+    if (i < c->sync_ev.size()) return hipSuccess;
+    hipEvent_t e = nullptr;
+    const hipError_t rc = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+    if (rc == hipSuccess) c->sync_ev.push_back(e);
+    return rc;
+}
+
+static int ensure_sync_events(fobq_ctx* ctx, size_t n)
+{
+    FOBQ_TRY(ensure_side_stream(ctx), "side stream");
+    for (size_t i = 0; i < n; ++i) FOBQ_TRY(ensure_sync_event(ctx, i), "event");
+    return FOBQ_OK;
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool ok = true;
@@ -133,25 +142,27 @@ enum { FLAG_NOTPD_H = 0, FLAG_NOTPD_HINV = 1, FLAG_BADPERM = 2, FLAG_STALLED = 3
 // The flag words; all of them start at zero when the buffer is made.
 static int ensure_flags(fobq_ctx* ctx)
 {
-    static_assert(FLAG_COUNT <= FLAG_WORD_MATE && FLAG_WORD_MATE < FLAG_WORDS, "flag words overlap");
-    if (ctx->flags.cap >= FLAG_WORDS * sizeof(int)) return FOBQ_OK;
+    static_assert(FLAG_COUNT <= FLAG_WORD_NONFINITE && FLAG_WORD_NONFINITE < FLAG_WORDS, "flag words overlap");
+    const bool made = ctx->flags.cap >= FLAG_WORDS * sizeof(int);
     FOBQ_TRY(ctx->flags.ensure(FLAG_WORDS * sizeof(int)), "workspace flags");
-    FOBQ_TRY(launch_clear_words(ctx->stream, ctx->flags.p, FLAG_WORDS, nullptr, 0), "clear flags");
-    ctx->mate_epoch = 0;
+    if (!made) FOBQ_TRY(launch_clear_words(ctx->stream, ctx->flags.p, FLAG_WORDS, nullptr, 0), "clear flags");
     return FOBQ_OK;
 }
 
-// Scratch of the damped inverse; `rows` > 0: with the per-row loss terms of a layer behind the words of the launch, so
-// that one clearing launch covers both.
-static int ensure_inverse_ws(fobq_ctx* ctx, int64_t d, int64_t rows)
+// Scratch of the damped inverse.  The words buffer: the words of its launch, those of the elimination's launch
+// (flow_rows > 0: a layer of that many rows that takes it), the per-row loss terms of `rows` rows; one clearing launch
+// covers them all.
+static int ensure_inverse_ws(fobq_ctx* ctx, int64_t d, int64_t rows, int64_t flow_rows)
 {
     const size_t dd = (size_t)d * d * sizeof(double);
     FOBQ_TRY(ctx->tiles.ensure(flow_tiles_bytes((int)d)), "workspace tiles");
     FOBQ_TRY(ctx->gt.ensure(flow_gt_bytes((int)d)), "workspace block inverses");
     FOBQ_TRY(ctx->Hinv.ensure(dd), "workspace Hinv");
-    const size_t words = ((size_t)flow_inverse_words((int)d) * sizeof(int) + 7) / 8 * 8;
+    const int64_t first = flow_inverse_words((int)d), second = flow_rows > 0 ? flow_eliminate_words((int)d, (int)flow_rows) : 0;
+    const size_t words = ((size_t)(first + second) * sizeof(int) + 7) / 8 * 8;
     FOBQ_TRY(ctx->words.ensure(words + (size_t)rows * sizeof(double)), "workspace words and loss terms");
     ctx->lossrow = reinterpret_cast<double*>(ctx->words.as<unsigned char>() + words);
+    ctx->words2 = ctx->words.as<int>() + first;
     ctx->words_len = (int64_t)(words / sizeof(int)) + 2 * rows;
     return ensure_flags(ctx);
 }
@@ -332,7 +343,7 @@ using namespace fobq;
 
 static std::vector<DevBuf*> all_buffers(fobq_ctx* ctx)
 {
-    return {&ctx->Hpart, &ctx->H, &ctx->tiles, &ctx->gt, &ctx->words, &ctx->Hinv, &ctx->A, &ctx->U, &ctx->Un,
+    return {&ctx->Hpart, &ctx->H, &ctx->tiles, &ctx->gt, &ctx->words, &ctx->tilesN, &ctx->vec, &ctx->Hinv, &ctx->A, &ctx->U, &ctx->Un,
             &ctx->Dblk, &ctx->flags, &ctx->Wp, &ctx->DT, &ctx->corr, &ctx->codesT, &ctx->scale, &ctx->zero,
             &ctx->S, &ctx->Spart, &ctx->perm, &ctx->invperm, &ctx->maps_pad, &ctx->i8planes, &ctx->i8sh, &ctx->i8amax, &ctx->batch_pool, &ctx->batch_desc, &ctx->obq, &ctx->hcorr, &ctx->strips};
 }
@@ -689,7 +700,7 @@ int fobq_spd_inverse(fobq_ctx* ctx, const double* H, int64_t d64, double* Hinv)
     DeviceGuard g(ctx->device);
     if (!g.ok) return set_err(ctx, FOBQ_EHIP, "cannot select device %d", ctx->device);
     const int d = (int)d64;
-    int rc = ensure_inverse_ws(ctx, d, 0);
+    int rc = ensure_inverse_ws(ctx, d, 0, 0);
     if (rc) return rc;
     rc = [&]() -> int {
         FOBQ_TRY(launch_clear_words(ctx->stream, ctx->flags.p, FLAG_COUNT, ctx->words.p, ctx->words_len), "clear flags");
@@ -851,6 +862,7 @@ struct LayerPlan {
     const float* W; const double* H; const fobq_opts* opts; const fobq_out* out;
     int R, d, G, steps, block, Rp, nblocks;
     bool dynamic;
+    bool flow;           // all columns in blocks of 64: elimination and column loop are one launch
     OrderBufs ob;
 };
 
@@ -880,13 +892,16 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     // column scores, order
     rc = enqueue_order(ctx, R, d, opts, ctx->Hinv.as<double>(), p.ob);
     if (rc) return rc;
-    // blocked path: the event that lets the column loop's stream start rides on the gather launch
-    hipEvent_t ev_start = block != 1 ? ctx->sync_ev[EV_ROWS0 + nblocks] : nullptr;
-    hipEvent_t ev_done = block != 1 ? ctx->sync_ev[EV_ROWS0 + nblocks + 1] : nullptr;
+    // general blocked path: the event that lets the column loop's stream start rides on the gather launch
+    const bool blocked = block != 1 && !p.flow;
+    hipEvent_t ev_start = blocked ? ctx->sync_ev[EV_ROWS0 + nblocks] : nullptr;
+    hipEvent_t ev_done = blocked ? ctx->sync_ev[EV_ROWS0 + nblocks + 1] : nullptr;
     {
+        // (the one-launch form gathers inside its launch)
         StageScope sc(ctx, FOBQ_STAGE_PERMUTE);
-        FOBQ_TRY(launch_gather(s, p.W, R, d, p.ob.perm, ctx->Hinv.as<double>(), ctx->Wp.as<double>(),
-                               ctx->A.as<double>(), ev_start), "permute");
+        if (!p.flow)
+            FOBQ_TRY(launch_gather(s, p.W, R, d, p.ob.perm, ctx->Hinv.as<double>(), ctx->Wp.as<double>(),
+                                   ctx->A.as<double>(), ev_start), "permute");
     }
     double* A = ctx->A.as<double>();
     double* Wp = ctx->Wp.as<double>();
@@ -896,7 +911,20 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     uint8_t* codesT = ctx->codesT.as<uint8_t>();
     double* lossrow = ctx->lossrow;
 
-    if (block == 1) {
+    if (p.flow) {
+        FlowElimArgs a;
+        a.d = d; a.R = R; a.G = G; a.gs = opts->group > 0 ? opts->group : d; a.bits = opts->bits; a.Rp = Rp;
+        a.Hinv = ctx->Hinv.as<double>(); a.perm = perm; a.W = p.W; a.scale = scale; a.zero = zero;
+        a.tiles = ctx->tiles.as<double>(); a.tilesN = ctx->tilesN.as<double>(); a.gt = ctx->gt.as<double>(); a.vec = ctx->vec.as<double>();
+        a.wt = Wp; a.dt = ctx->DT.as<double>(); a.corr = ctx->corr.as<double>(); a.lossrow = lossrow; a.Wout = out->W_work;
+        a.codesT = codesT; a.words = ctx->words2;
+        a.notpd = ctx->flags.as<int>() + FLAG_NOTPD_HINV; a.stalled = ctx->flags.as<int>() + FLAG_STALLED;
+        {
+            StageScope sc(ctx, FOBQ_STAGE_ELIMINATE);
+            FOBQ_TRY(launch_flow_eliminate(s, ctx->cus, a), "eliminate and columns");
+        }
+        StageScope columns(ctx, FOBQ_STAGE_COLUMNS);       // part of the launch above
+    } else if (block == 1) {
         // Eq. 9 / 11 and Eq. 12 one column at a time
         StageScope sc(ctx, FOBQ_STAGE_COLUMNS);
         int* pivot_flag = ctx->flags.as<int>() + FLAG_NOTPD_HINV;
@@ -960,9 +988,9 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
         else if (out->loss) FOBQ_TRY(launch_loss(s, lossrow, R, out->loss), "loss");
         if (out->perm)
             FOBQ_TRY(hipMemcpyAsync(out->perm, perm, (size_t)d * sizeof(int), hipMemcpyDeviceToDevice, s), "copy perm");
-        if (out->W_work)
+        if (out->W_work && !p.flow)
             FOBQ_TRY(hipMemcpyAsync(out->W_work, Wp, (size_t)R * d * sizeof(double), hipMemcpyDeviceToDevice, s), "copy W_work");
-        if (out->Hinv_work) FOBQ_TRY(launch_hinv_work(s, A, d, steps, out->Hinv_work), "copy Hinv_work");
+        if (out->Hinv_work) FOBQ_TRY(launch_hinv_work(s, p.flow ? ctx->Hinv.as<double>() : A, d, steps, out->Hinv_work), "copy Hinv_work");
     }
     return FOBQ_OK;
 }
@@ -1003,19 +1031,27 @@ static int quantize_enqueue(fobq_ctx* ctx, const float* W, int64_t d_row, int64_
 
     // Every allocation (scratch growth, streams, events) comes before the first launch: scratch growth may
     // free a buffer, and a failure in here leaves nothing in flight.
-    rc = ensure_inverse_ws(ctx, p.d, p.R);
+    p.flow = p.block == 64 && p.steps == p.d;
+    rc = ensure_inverse_ws(ctx, p.d, p.R, p.flow ? p.R : 0);
     if (rc) return rc;
-    FOBQ_TRY(ctx->U.ensure(dd), "workspace U");
-    FOBQ_TRY(ctx->Dblk.ensure((4 * 64 * 64 + 128) * sizeof(double)), "workspace Dblk");
-    FOBQ_TRY(ctx->A.ensure(dd), "workspace A");
-    FOBQ_TRY(ctx->Un.ensure(dd), "workspace Un");
-    FOBQ_TRY(ctx->Wp.ensure((size_t)p.R * p.d * sizeof(double)), "workspace Wp");
-    FOBQ_TRY(ctx->DT.ensure((size_t)p.d * p.Rp * sizeof(double)), "workspace DT");
-    FOBQ_TRY(ctx->corr.ensure(2 * (size_t)p.R * 64 * sizeof(double)), "workspace corr");
+    if (p.flow) {
+        FOBQ_TRY(ctx->tilesN.ensure(flow_tiles_bytes(p.d)), "workspace tiles of Un");
+        FOBQ_TRY(ctx->vec.ensure((size_t)(p.d + 63) / 64 * 128 * sizeof(double)), "workspace pivots");
+        FOBQ_TRY(ctx->Wp.ensure(flow_rows_bytes(p.d, p.R)), "workspace Wp");
+        FOBQ_TRY(ctx->DT.ensure(flow_rows_bytes(p.d, p.R)), "workspace DT");
+    } else {
+        FOBQ_TRY(ctx->A.ensure(dd), "workspace A");
+        FOBQ_TRY(ctx->U.ensure(dd), "workspace U");
+        FOBQ_TRY(ctx->Un.ensure(dd), "workspace Un");
+        FOBQ_TRY(ctx->Dblk.ensure((64 * 64 + 64) * sizeof(double)), "workspace Dblk");
+        FOBQ_TRY(ctx->Wp.ensure((size_t)p.R * p.d * sizeof(double)), "workspace Wp");
+        FOBQ_TRY(ctx->DT.ensure((size_t)p.d * p.Rp * sizeof(double)), "workspace DT");
+    }
+    FOBQ_TRY(ctx->corr.ensure(2 * (size_t)p.Rp * 64 * sizeof(double)), "workspace corr");
     FOBQ_TRY(ctx->codesT.ensure((size_t)p.d * p.Rp), "workspace codesT");
     rc = ensure_order_bufs(ctx, p.R, p.d, p.G, &p.ob);
     if (rc) return rc;
-    rc = ensure_sync_events(ctx, (size_t)EV_ROWS0 + p.nblocks + 2);
+    rc = ensure_sync_events(ctx, p.flow ? (size_t)EV_ROWS0 : (size_t)EV_ROWS0 + p.nblocks + 2);
     if (rc) return rc;
 
     rc = enqueue_layer_launches(ctx, p);

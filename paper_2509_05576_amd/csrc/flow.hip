@@ -8,10 +8,10 @@
 //
 // Scheme.  A tile is computed once, left-looking: its owner (a workgroup of 8 wavefronts) adds up the products of all
 // earlier panels in registers while their tiles become ready, finishes the tile with the block inverse of its own row
-// and publishes it.  Workgroups take tiles from queues in a fixed order (a ticket each); whatever a tile waits for
-// stands before it in its own queue, or in the queue served first, or is done by the workgroup that walks the chain
-// (the first to start).  The earliest unfinished tile can therefore always proceed, however many workgroups are
-// resident, and every wait ends.  (Should the device stop making progress all the same, every wait gives up after
+// and publishes it.  Workgroups take tiles from queues in a fixed order (a ticket each).  All the work of a launch has one
+// order in which whatever a tile waits for stands before it; each queue is a part of that order, and the workgroup that
+// walks the chain is the first to start, the next ones serve one queue each.  So the earliest unfinished tile has its
+// workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should the device stop making progress all the same, every wait gives up after
 // FLOW_MAX_POLLS looks, the launch drains and the call fails.)
 //
 // Exchange between compute units.  Each XCD has its own L2, which is not coherent with the others inside a launch.
@@ -20,8 +20,11 @@
 // are done, and sets the tile's word after a release fence; the consumer reads the word until it is set and loads.
 // Measured: 1.85 us from the first store of a 32 KB tile to its last load on another XCD, and 16 TB/s when 256
 // workgroups read tiles this way, against 9.6 TB/s that the products want at the full matrix rate.
+#include <algorithm>
+
 #include <hip/hip_ext.h>
 
+#include "column_chain.h"
 #include "tile_block.h"
 
 namespace fobq {
@@ -31,7 +34,7 @@ constexpr int FLOW_LDS = SWEEP_LDS + 4 * NB * DL;    // doubles: two double-buff
 constexpr int FLOW_MAX_POLLS = 1 << 22;              // several seconds
 // words of a launch, all zero before it: counters, then one word per tile (T x T), then two per diagonal block for the
 // sums that are handed to the chain
-enum { FW_ROLE = 0, FW_QUEUE1 = 1, FW_QUEUE2 = 2, FW_ABORT = 3, FW_HEAD = 16 };
+enum { FW_ROLE = 0, FW_QUEUE1 = 1, FW_QUEUE2 = 2, FW_QUEUE3 = 3, FW_ABORT = 4, FW_HEAD = 16 };
 
 __device__ __forceinline__ double ld_shared(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void st_shared(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -41,7 +44,8 @@ __device__ __forceinline__ void st_word(int* p, int v) { __hip_atomic_store(p, v
 // what both launches have: d columns in T blocks; tiles: T x T published tiles, [row of tiles][column of tiles][64][64];
 // gt: T tiles, the transposed block inverses, then T tiles for the sums D(k, 0) (see Queue1); stalled: status word for a launch that gave up
 struct FlowP {
-    int d, T, n1;        // n1: workgroups that serve queue 1 first (the chain's workgroup not counted)
+    int d, T;
+    int n1, n2, n3;      // workgroups that serve queue 1 / 2 / 3 first (the chain's workgroup not counted)
     int* words;
     double* tiles;
     double* gt;
@@ -79,91 +83,145 @@ __device__ __forceinline__ void flow_publish(int* word)
     }
 }
 
-// Operand tiles in LDS: rows of 64 doubles, the two halves of 32 banks exchanged in odd rows, so that the fragment reads
-// of a half wavefront (16 columns of two neighbouring rows) meet no bank conflict.
+// Operand tiles [k][m] in LDS: two rows interleaved, element (k, m) at (k / 2) * 128 + 2 m + (k & 1), so that a fragment read is
+// 16 bytes -- the elements of two MFMAs, the first of rows k = 8 kk + 2 fq, the second of the rows after them -- and meets no
+// bank conflict, and a lane that holds two rows of a column stores 16 bytes.
+typedef double d2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int pair_at(int k, int m) { return (k >> 1) * 128 + 2 * m + (k & 1); }
+__device__ __forceinline__ d2& pair(double* p) { return *reinterpret_cast<d2*>(p); }
+__device__ __forceinline__ const d2& pair(const double* p) { return *reinterpret_cast<const d2*>(p); }
+// the chain's tiles (8-byte reads): rows of 64 doubles, the two halves of 32 banks exchanged in odd rows
 __device__ __forceinline__ int swz(int row, int col) { return row * 64 + (col ^ ((row & 1) << 4)); }
 
-// c -= sum_{q0 <= q < q1} A_q^T B_q, A_q and B_q published 64 x 64 tiles [k][m], [k][n]; c in the accumulator layout: rows
-// wr * 16 + 4 v + fq, columns w2 * 32 + 16 j + fr of wavefront (wr, w2).  src.a(q), src.b(q): the tiles, src.wa(q),
-// src.wb(q): their words.  The loads of the next two steps are in flight during the products of a step as far as their
-// tiles are known to be ready (under load a tile takes longer to arrive than the 1.7 us of a step's products); what is
-// not known to be ready is looked for when its turn comes.  LDS: four tiles, one barrier per step.
+// c += sum_{q0 <= q < q1} A_q^T B_q, A_q and B_q published 64 x 64 tiles [k][m], [k][n]; c in the accumulator layout: rows
+// wr * 16 + 4 v + fq, columns w2 * 32 + 16 j + fr of wavefront (wr, w2).  src.a(q), src.b(q): the tiles; src.ready(q, q1, lane):
+// how many steps from q on have both their tiles (one look, wavefront-uniform).
+// Where several steps are known to be ready they are pipelined: during the products of a step the next one's tiles go
+// from registers to LDS and the loads of the one after the next but one are issued, one or two between any two MFMAs
+// (loads and stores in front of the products cost 0.9 us a step: 2.7 us against 1.7 us of matrix time).  The number
+// of loads in flight must not depend on a branch, or every wait becomes a wait for all of them.
+// LDS: two pairs of tiles, one barrier per step; step number n reads the pair n & 1.
 template <class Src>
 __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src& src, int q0, int q1, d4 (&c)[2])
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
-    int known = q0, loaded = q0;         // the tiles of the steps before `known` are ready, those before `loaded` on their way
-    auto look = [&](int q) {             // wavefront-uniform
-        for (int n = 0;; ++n) {
-            const int s = min(q + (lane & 31), q1 - 1);
-            const unsigned long long m = __ballot(ld_word(lane < 32 ? src.wa(s) : src.wb(s)) != 0);
-            const unsigned both = (unsigned)m & (unsigned)(m >> 32);
-            const int k = both == ~0u ? 32 : __builtin_ctz(~both);
+    const int g0 = wave * 512 + lane;                          // this lane's first element of a tile: rows wave * 8 + u, column lane
+    const int x0 = wave * 512 + 2 * lane;                      // the same in LDS, rows 2 u and 2 u + 1 together
+    const int ra = fq * 128 + 2 * (wr * 16 + fr), rb = fq * 128 + 2 * (w2 * 32 + fr);
+    auto load = [&](int q, double (&pa)[8], double (&pb)[8]) {
+        const double* a = src.a(q) + g0;
+        const double* b = src.b(q) + g0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { pa[u] = ld_shared(a + u * 64); pb[u] = ld_shared(b + u * 64); }
+    };
+    auto store = [&](double* As, const double (&pa)[8], const double (&pb)[8]) {
+        const int x = here(x0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            pair(As + x + u * 128) = d2{pa[2 * u], pa[2 * u + 1]};
+            pair(As + TILE + x + u * 128) = d2{pb[2 * u], pb[2 * u + 1]};
+        }
+    };
+    // rows 8 kk .. 8 kk + 7 of the products of the pair at As
+    auto product = [&](const double* As, int xa, int xb, int kk) {
+        const d2 a = pair(As + xa + kk * 512), b = pair(As + TILE + xb + kk * 512), e = pair(As + TILE + xb + 32 + kk * 512);
+        c[0] = mfma4(a.x, b.x, c[0]);
+        c[1] = mfma4(a.x, e.x, c[1]);
+        c[0] = mfma4(a.y, b.y, c[0]);
+        c[1] = mfma4(a.y, e.y, c[1]);
+    };
+    auto products = [&](const double* As) {
+        const int xa = here(ra), xb = here(rb);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) product(As, xa, xb, kk);
+    };
+    // the products of the pair at As; meanwhile pa, pb to the pair at next and the loads of step q into pa, pb
+    auto step = [&](const double* As, double* next, double (&pa)[8], double (&pb)[8], int q) {
+        const int xa = here(ra), xb = here(rb), x = here(x0);
+        const double* a = src.a(q) + g0;
+        const double* b = src.b(q) + g0;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            product(As, xa, xb, kk);
+            const int u = kk & 3;
+            double (&pp)[8] = kk < 4 ? pa : pb;
+            const double* g = kk < 4 ? a : b;
+            pair(next + (kk < 4 ? 0 : TILE) + x + u * 128) = d2{pp[2 * u], pp[2 * u + 1]};
+            pp[2 * u] = ld_shared(g + 2 * u * 64);
+            pp[2 * u + 1] = ld_shared(g + (2 * u + 1) * 64);
+        }
+    };
+    double pa[8], pb[8], na[8], nb[8];
+    double* cur = lds;                   // pair of LDS tiles of the next step, and the other one
+    double* alt = lds + 2 * TILE;
+    int known = q0;                      // the tiles of the steps before this one are ready
+    for (int q = q0; q < q1;) {
+        for (int n = 0; known <= q; ++n) {                   // wavefront-uniform
+            const int k = src.ready(q, q1, lane);
             if (k > 0) { known = min(q + k, q1); break; }
             if (n >= FLOW_MAX_POLLS) st_word(f.words + FW_ABORT, 1);
             if ((n & 31) == 31 && ld_word(f.words + FW_ABORT) != 0) { known = q1; break; }
             __builtin_amdgcn_s_sleep(1);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    };
-    auto load = [&](double (&pa)[8], double (&pb)[8]) {      // step `loaded`
-        const double* a = src.a(loaded) + wave * 512 + lane;
-        const double* b = src.b(loaded) + wave * 512 + lane;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { pa[u] = ld_shared(a + u * 64); pb[u] = ld_shared(b + u * 64); }
-        ++loaded;
-    };
-    auto step = [&](int q, double* As, double (&pa)[8], double (&pb)[8], double (&na)[8], double (&nb)[8]) {
-        double* Bs = As + TILE;
-        if (loaded == q) {
-            look(q);
-            load(pa, pb);
+        if (known - q < 4) {
+            load(q, pa, pb);
+            store(cur, pa, pb);
+            __syncthreads();
+            products(cur);
+            double* t = cur; cur = alt; alt = t;
+            ++q;
+            continue;
         }
-        const int w0 = here(wave * 512 + lane), w1 = here(wave * 512 + (lane ^ 16));
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            As[(u & 1 ? w1 : w0) + u * 64] = pa[u];
-            Bs[(u & 1 ? w1 : w0) + u * 64] = pb[u];
-        }
+        const int end = known - 1;
+        load(q, pa, pb);
+        load(q + 1, na, nb);
+        store(cur, pa, pb);
+        load(q + 2, pa, pb);
         __syncthreads();
-        if (loaded == q + 1 && q + 1 < known) load(na, nb);
-        if (loaded == q + 2 && q + 2 < known) load(pa, pb);
-        const int ra = here(swz(fq, wr * 16 + fr)), rb = here(swz(fq, w2 * 32 + fr)), rc = here(swz(fq, w2 * 32 + 16 + fr));
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            const double a = -As[ra + ks * 256];
-            c[0] = mfma4(a, Bs[rb + ks * 256], c[0]);
-            c[1] = mfma4(a, Bs[rc + ks * 256], c[1]);
+        while (q + 1 < end) {
+            step(cur, alt, na, nb, min(q + 3, end));
+            __syncthreads();
+            step(alt, cur, pa, pb, min(q + 4, end));
+            __syncthreads();
+            q += 2;
         }
-    };
-    double pa[8], pb[8], na[8], nb[8];
-    int q = q0;
-    for (; q + 1 < q1; q += 2) {
-        step(q, lds, pa, pb, na, nb);
-        step(q + 1, lds + 2 * TILE, na, nb, pa, pb);
+        if (q < end) {
+            step(cur, alt, na, nb, end);
+            __syncthreads();
+            double* t = cur; cur = alt; alt = t;
+            ++q;
+        }
+        products(cur);
+        double* t = cur; cur = alt; alt = t;
+        ++q;
     }
-    if (q < q1) step(q, lds, pa, pb, na, nb);
 }
 
-// u = G c for the finished sum c of a tile in row i of tiles, G = the block inverse of that row (its transpose is
+// u = -G c for the finished sum c of a tile in row i of tiles, G = the block inverse of that row (its transpose is
 // gt[i]).  u: row tiles {w2, 3 - w2} (G is lower triangular: 20 of 32 (k-step, tile) pairs either way), columns
 // wr * 16 ..  steps: how many the sum had (the product takes the pair of LDS tiles that its last step did not read).
 template <int W>
 __device__ __forceinline__ void flow_tri_product(const double* Gs, const double* Cs, int wr, int fr, int fq, d4 (&u)[2])
 {
-    const int rc = here(swz(fq, wr * 16 + fr)), r0 = here(swz(fq, W * 16 + fr)), r1 = here(swz(fq, (3 - W) * 16 + fr));
+    const int rc = here(fq * 128 + 2 * (wr * 16 + fr)), r0 = here(fq * 128 + 2 * (W * 16 + fr)), r1 = here(fq * 128 + 2 * ((3 - W) * 16 + fr));
 #pragma unroll
-    for (int ks = 0; ks < 16 - 4 * W; ++ks) {
-        const double b = Cs[rc + ks * 256];
-        if (ks < 4 * W + 4) u[0] = mfma4(Gs[r0 + ks * 256], b, u[0]);
-        u[1] = mfma4(Gs[r1 + ks * 256], b, u[1]);
+    for (int kk = 0; kk < 8 - 2 * W; ++kk) {
+        const d2 b = pair(Cs + rc + kk * 512), h = pair(Gs + r1 + kk * 512);
+        if (kk < 2 * W + 2) {
+            const d2 g = pair(Gs + r0 + kk * 512);
+            u[0] = mfma4(g.x, b.x, u[0]);
+            u[0] = mfma4(g.y, b.y, u[0]);
+        }
+        u[1] = mfma4(h.x, b.x, u[1]);
+        u[1] = mfma4(h.y, b.y, u[1]);
     }
 }
 
 __device__ __forceinline__ void flow_row_product(const FlowP& f, double* lds, int i, int steps, const d4 (&c)[2], d4 (&u)[2])
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
     double* Gs = lds + (steps & 1) * 2 * TILE;
     double* Cs = Gs + TILE;
@@ -175,15 +233,24 @@ __device__ __forceinline__ void flow_row_product(const FlowP& f, double* lds, in
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Cs[here(swz(wr * 16 + fq, w2 * 32 + 16 * j + fr)) + v * 256] = c[j][v];
-    const int w0 = here(wave * 512 + lane), w1 = here(wave * 512 + (lane ^ 16));
+        for (int v = 0; v < 4; ++v) Cs[here(pair_at(wr * 16 + fq, w2 * 32 + 16 * j + fr)) + v * 256] = -c[j][v];
+    const int x0 = here(wave * 512 + 2 * lane);
 #pragma unroll
-    for (int x = 0; x < 8; ++x) Gs[(x & 1 ? w1 : w0) + x * 64] = pg[x];
+    for (int x = 0; x < 4; ++x) pair(Gs + x0 + x * 128) = d2{pg[2 * x], pg[2 * x + 1]};
     __syncthreads();
     u[0] = d4{0.0, 0.0, 0.0, 0.0};
     u[1] = d4{0.0, 0.0, 0.0, 0.0};
     if (w2 == 0) flow_tri_product<0>(Gs, Cs, wr, fr, fq, u);
     else flow_tri_product<1>(Gs, Cs, wr, fr, fq, u);
+}
+
+// steps q, q + 1, ... whose tiles (q, i) and (q, j) are both published, out of the next 32
+__device__ __forceinline__ int ready_pairs(const FlowP& f, int i, int j, int q, int q1, int lane)
+{
+    const int s = min(q + (lane & 31), q1 - 1);
+    const unsigned long long m = __ballot(ld_word(tile_word(f, s, lane < 32 ? i : j)) != 0);
+    const unsigned both = (unsigned)m & (unsigned)(m >> 32);
+    return both == ~0u ? 32 : __builtin_ctz(~both);
 }
 
 // Queue 1 of both launches, in the order of the rows of tiles: the sums D(1, .) first, then for every row p the tile
@@ -213,6 +280,17 @@ __device__ __forceinline__ int flow_ticket(const FlowP& f, int queue, int* slot)
     if (threadIdx.x == 0) *slot = __hip_atomic_fetch_add(f.words + queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     return *slot;
+}
+
+// the queue that the workgroup with this role (its place in the order of arrival) serves first: one each, then dealt so that
+// however many have arrived, the queues have theirs in proportion (other launches may hold compute units for a while)
+__device__ __forceinline__ int flow_serves(const FlowP& f, int role)
+{
+    if (role <= 3) return role;
+    const int all = f.n1 + f.n2 + f.n3;
+    if ((role + 1) * f.n1 / all > role * f.n1 / all) return 1;
+    const int rest = role - role * f.n1 / all;          // of the others, this one's place among those not on queue 1
+    return (rest + 1) * f.n2 / (f.n2 + f.n3) > rest * f.n2 / (f.n2 + f.n3) ? 2 : 3;
 }
 
 // ---------------------------------------------------------------------------
@@ -247,10 +325,10 @@ __device__ __forceinline__ double flow_lambda(const FlowInverseP& p, double* par
     return lam;
 }
 
-// tile (i, j) of H (0 past d) in the accumulator layout, lambda added on the diagonal
+// minus tile (i, j) of H (0 past d) in the accumulator layout, lambda added on the diagonal
 __device__ __forceinline__ void flow_init_h(const FlowInverseP& p, int i, int j, double lam, d4 (&c)[2])
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
     const int d = p.f.d;
 #pragma unroll
@@ -260,16 +338,15 @@ __device__ __forceinline__ void flow_init_h(const FlowInverseP& p, int i, int j,
             const int gm = NB * i + wr * 16 + 4 * v + fq, gn = NB * j + w2 * 32 + 16 * h + fr;
             double x = (gm < d && gn < d) ? p.H[(int64_t)gm * d + gn] : 0.0;
             if (gm == gn) x += lam;
-            c[h][v] = x;
+            c[h][v] = -x;
         }
 }
 
-struct SumR {      // R_qi^T R_qj
+struct SumR {      // R_qi^T R_qj; X_qi^T X_qj; R_qi^T X_qj
     FlowP f; int i, j;
     __device__ const double* a(int q) const { return tile_at(f, q, i); }
     __device__ const double* b(int q) const { return tile_at(f, q, j); }
-    __device__ const int* wa(int q) const { return tile_word(f, q, i); }
-    __device__ const int* wb(int q) const { return tile_word(f, q, j); }
+    __device__ int ready(int q, int q1, int lane) const { return ready_pairs(f, i, j, q, q1, lane); }
 };
 
 // The chain: the workgroup that walks the diagonal blocks.  For block k it takes the sums D(k, 0), D(k, 1), finishes
@@ -312,62 +389,70 @@ __device__ __forceinline__ void chain_row_product(const double (&g)[20], const d
     }
 }
 
-__device__ __forceinline__ void flow_chain_inverse(const FlowInverseP& p, double* lds)
+// ELIM: the elimination (tiles U, tilesN = Un = U / pivot, vec: see FlowElimP), else the Cholesky factorization (tiles R above and
+// X on the diagonal).  first(m, n): element (m, n) of diagonal block 0.
+template <bool ELIM, class First>
+__device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, double* vec, double* lds, First first)
 {
-    const FlowP& f = p.f;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
     double* Am = lds + SWEEP_LDS;
     double* Xm = Am + NB * DL;
-    double* Vs = Xm + NB * DL;
-    int rt[2], ct[2];
-    chain_tiles(wave, rt, ct);
-    const bool second = wave == 1 || wave == 2;
-    const int t[2] = {w2, 3 - w2};               // row tiles of the product with the block inverse
+    double* Vs = Xm + NB * DL;                   // tile (k - 1, k) of U or R, and (ELIM) of Un
+    double* Vn = ELIM ? Vs + TILE : Vs;
     d4 c[2];
     double vb[16], g[20];
-    auto load_sums = [&](int k) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const double* V = hand_tile(f, k) + fq * 64 + wr * 16 + fr;
-        const double* D = tile_at(f, k, k) + fq * 64 + fr;
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) vb[ks] = ld_shared(V + ks * 256);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (h == 0 || second) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) c[h][v] = ld_shared(D + (rt[h] * 16 + 4 * v) * 64 + ct[h] * 16);
-            }
-    };
-    auto store_diag = [&](int h, int nb) {
-        const int at = here((rt[h] * 16 + fq) * DL + ct[h] * 16 + fr);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int m = rt[h] * 16 + 4 * v + fq, n = ct[h] * 16 + fr;
-            Am[at + 4 * v * DL] = c[h][v];
-            if (nb < NB && (m >= nb || n >= nb)) Am[m * DL + n] = m == n ? 1.0 : 0.0;     // identity padding past d
-        }
-    };
-    auto diag_product = [&](int h) {             // c[h] -= R_{k-1,k}[:, row tile]^T R_{k-1,k}[:, column tile]
-        const int ra = here(swz(fq, rt[h] * 16 + fr)), rb = here(swz(fq, ct[h] * 16 + fr));
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) c[h] = mfma4(-Vs[ra + ks * 256], Vs[rb + ks * 256], c[h]);
-    };
     // chol_block writes the lower triangle of the inverse, whole 16 x 16 tiles on the diagonal included (zeros above it);
     // the tiles above stay as they are.  (Past d the last block's inverse is the identity: its rows meet zeros only.)
-    for (int x = tid; x < NB * NB; x += NT) Xm[(x >> 6) * DL + (x & 63)] = 0.0;
+    for (int x = threadIdx.x; x < NB * NB; x += NT) Xm[(x >> 6) * DL + (x & 63)] = 0.0;
     bool have = false;                           // the sums of the next block are loaded
     for (int k = 0; k < f.T; ++k) {
         const int nb = min(NB, f.d - NB * k);
-        if (k == 0) {
-            const double lam = flow_lambda(p, Am);
+        const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+        int rt[2], ct[2];
+        chain_tiles(wave, rt, ct);
+        if (ELIM) {                                  // elim_block reads the upper triangle, chol_block the lower one
+            const int a0 = rt[0], a1 = rt[1];
+            rt[0] = ct[0]; rt[1] = ct[1];
+            ct[0] = a0; ct[1] = a1;
+        }
+        const bool second = wave == 1 || wave == 2;
+        const int t[2] = {w2, 3 - w2};               // row tiles of the product with the block inverse
+        auto load_sums = [&](int k) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            const double* V = hand_tile(f, k) + fq * 64 + wr * 16 + fr;
+            const double* D = tile_at(f, k, k) + fq * 64 + fr;
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) vb[ks] = ld_shared(V + ks * 256);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
+                if (h == 0 || second) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int m = rt[h] * 16 + 4 * v + fq, n = ct[h] * 16 + fr;
-                    c[h][v] = (m < nb && n < nb) ? p.H[(int64_t)m * f.d + n] : 0.0;
-                    if (m == n) c[h][v] += lam;
+                    for (int v = 0; v < 4; ++v) c[h][v] = ld_shared(D + (rt[h] * 16 + 4 * v) * 64 + ct[h] * 16);
+                }
+        };
+        auto store_diag = [&](int h, int nb) {
+            const int at = here((rt[h] * 16 + fq) * DL + ct[h] * 16 + fr);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = rt[h] * 16 + 4 * v + fq, n = ct[h] * 16 + fr;
+                Am[at + 4 * v * DL] = c[h][v];
+                if (nb < NB && (m >= nb || n >= nb)) Am[m * DL + n] = m == n ? 1.0 : 0.0;     // identity padding past d
+            }
+        };
+        auto diag_product = [&](int h) {             // c[h] -= (tile (k - 1, k) of R or Un)[:, row tile]^T (of R or U)[:, column tile]
+            const int ra = here(swz(fq, rt[h] * 16 + fr)), rb = here(swz(fq, ct[h] * 16 + fr));
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) c[h] = mfma4(-Vn[ra + ks * 256], Vs[rb + ks * 256], c[h]);
+        };
+        if (k == 0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (h == 0 || second) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int m = rt[h] * 16 + 4 * v + fq, n = ct[h] * 16 + fr;
+                        c[h][v] = (m < nb && n < nb) ? first(m, n) : 0.0;
+                    }
                 }
         } else {
             if (!have) {
@@ -379,6 +464,7 @@ __device__ __forceinline__ void flow_chain_inverse(const FlowInverseP& p, double
             if (w2 == 0) chain_row_product<0>(g, vb, u);
             else chain_row_product<1>(g, vb, u);
             double* R = tile_at(f, k - 1, k);
+            double* Rn = tilesN + ((int64_t)(k - 1) * f.T + k) * TILE;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -386,6 +472,11 @@ __device__ __forceinline__ void flow_chain_inverse(const FlowInverseP& p, double
                     const int m = t[i] * 16 + 4 * v + fq, n = wr * 16 + fr;
                     Vs[here(swz(t[i] * 16 + fq, n)) + v * 256] = u[i][v];
                     st_shared(R + m * 64 + n, u[i][v]);
+                    if (ELIM) {
+                        const double un = u[i][v] * lds[m];      // 1 / pivot of the block before
+                        Vn[here(swz(t[i] * 16 + fq, n)) + v * 256] = un;
+                        st_shared(Rn + m * 64 + n, un);
+                    }
                 }
             __syncthreads();
             diag_product(0);
@@ -398,24 +489,33 @@ __device__ __forceinline__ void flow_chain_inverse(const FlowInverseP& p, double
             st_word(tile_word(f, k - 1, k), 1);
         }
         int seen = 1;                            // words of the next block's sums, looked at while the last sweep runs
-        chol_block(Am, Xm, lds, f.notpd, [&]() {
+        auto beside = [&]() {
             if (second) {
                 if (k > 0) diag_product(1);
                 store_diag(1, nb);
             }
-        }, [&]() {
+        };
+        auto ahead = [&]() {
             if (lane < 2 && k + 1 < f.T) seen = ld_word(hand_word(f, k + 1, lane));
-        });
+        };
+        if constexpr (ELIM) elim_block(Am, Xm, lds, f.notpd, beside, ahead);
+        else chol_block(Am, Xm, lds, f.notpd, beside, ahead);
         // the next block's sums: looked for before and after the stores of the block inverse
         have = k + 1 < f.T && __all(seen != 0);
         if (have) load_sums(k + 1);
         double* Gt = f.gt + (int64_t)k * TILE;
         double* G = tile_at(f, k, k);
+        double* Gn = tilesN + ((int64_t)k * f.T + k) * TILE;
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const int y = wave * 8 + x;
             st_shared(Gt + y * 64 + lane, Xm[lane * DL + y]);
-            st_shared(G + y * 64 + lane, Xm[y * DL + lane]);
+            if (ELIM) st_shared(Gn + y * 64 + lane, y < lane ? Am[y * DL + lane] * lds[y] : 0.0);
+            else st_shared(G + y * 64 + lane, Xm[y * DL + lane]);
+        }
+        if (ELIM && wave == 0) {
+            st_shared(vec + 2 * NB * k + lane, lds[lane]);
+            st_shared(vec + 2 * NB * k + NB + lane, 0.5 / Am[lane * DL + lane]);
         }
         if (k + 1 < f.T) {
             if (!have) {
@@ -436,22 +536,24 @@ __device__ __forceinline__ void flow_chain_inverse(const FlowInverseP& p, double
 
 __global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
 {
-    __shared__ double lds[FLOW_LDS];
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
     __shared__ int slot;
     const FlowP& f = p.f;
     const int T = f.T;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
     double* tiles = lds + SWEEP_LDS;
     const int role = flow_ticket(f, FW_ROLE, &slot);
-    if (role == 0) flow_chain_inverse(p, lds);
-    else if (role <= f.n1) {
+    if (role == 0) {
+        const double lam = flow_lambda(p, tiles);
+        flow_chain<false>(f, nullptr, nullptr, lds, [&](int m, int n) { return p.H[(int64_t)m * f.d + n] + (m == n ? lam : 0.0); });
+    } else if (flow_serves(f, role) == 1) {
         Queue1 q1;
         const int n = queue1_length(T);
         for (;;) {
             const int t = flow_ticket(f, FW_QUEUE1, &slot);
             if (t >= n) break;
             const Queue1Item it = q1.at(t, T);
+            const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
             d4 c[2], u[2];
             if (it.kind == 0) {
                 flow_init_h(p, it.i, it.j, 0.0, c);
@@ -472,15 +574,17 @@ __global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, c[h][v]);
+                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, -c[h][v]);
                 flow_publish(hand_word(f, k, it.j));
             }
         }
     }
-    const int nx = T * (T - 1) / 2, nh = T * (T + 1) / 2;
+    const int nx = T * (T - 1) / 2, nh = T * (T + 1) / 2;      // (whoever does not serve queue 1 first serves queue 2)
     for (;;) {
         const int t = flow_ticket(f, FW_QUEUE2, &slot);
         if (t >= nx + nh) break;
+        const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
         d4 c[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}}, u[2];
         if (t < nx) {
             int i, j;
@@ -503,16 +607,326 @@ __global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int gm = NB * m + wr * 16 + 4 * v + fq, gn = NB * n + w2 * 32 + 16 * h + fr;
-                    if (gm < f.d && gn < f.d) p.Hinv[(int64_t)gm * f.d + gn] = -c[h][v];
+                    if (gm < f.d && gn < f.d) p.Hinv[(int64_t)gm * f.d + gn] = c[h][v];
                 }
         }
     }
     if (threadIdx.x == 0 && ld_word(f.words + FW_ABORT) != 0) *f.stalled = 1;
 }
 
+// ---------------------------------------------------------------------------
+// The shared-Hinv elimination (Eq. 12) and the column loop (Section 4.2 steps 4-5) in one launch.  With A = Hinv in
+// processing order (gathered through perm when a tile is started):
+//   U_ij = G_i (A_ij - sum_{q < i} Un_qi^T U_qj), i < j, Un = D^-1 U;  G_i, the pivots and Un_ii from elim_block   (queue 1)
+// and for the rows of W, which do not interact, in groups g of 64 rows and parts s of RS rows:
+//   W(p, g) = W[:, block p] (gathered, widened) - sum_{q < p - 1} D_qg^T Un_qp                                       (queue 3)
+//   C(p, s): the 64 sequential steps of block p for its rows, on W(p, g) less the share of block p - 1 that C(p - 1, s)
+//            computed; leaves D_p (w - q, [column][row]), the codes, the loss terms, and its share for block p + 1.  (queue 2)
+// RS = 8 NR: NR rows per wavefront (see column_rows).
+struct FlowElimP {
+    FlowP f;
+    double* tilesN;        // T x T: Un; on the diagonal Un inside the block (0 on and below its diagonal)
+    double* vec;           // T x 128: reciprocal pivots, 1 / (2 pivot)
+    const double* Hu;      // Hinv (original order, upper triangle)
+    const int* perm;
+    const float* W; int R, G, gs, NG;
+    const double* scale; const double* zero; double maxq;
+    uint8_t* codesT; int Rp; double* lossrow;
+    double* Wout;          // R x d, processing order, or null
+    double* wt;            // T x NG tiles: W(p, g), [row][column]
+    double* dt;            // T x NG tiles: D, [column][row]
+    double* corr;          // 2 x Rp x 64: the share of the block before, by parity of the block
+};
+
+__device__ __forceinline__ int* group_word(const FlowElimP& p, int blk, int g) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 2 * p.f.T + blk * p.NG + g; }
+__device__ __forceinline__ int* part_word(const FlowElimP& p, int blk, int s, int parts) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 2 * p.f.T + p.f.T * p.NG + blk * parts + s; }
+
+struct SumU {      // Un_qi^T U_qj
+    FlowP f; const double* tilesN; int i, j;
+    __device__ const double* a(int q) const { return tilesN + ((int64_t)q * f.T + i) * TILE; }
+    __device__ const double* b(int q) const { return tile_at(f, q, j); }
+    __device__ int ready(int q, int q1, int lane) const { return ready_pairs(f, i, j, q, q1, lane); }
+};
+
+template <int PER>
+struct SumW {      // D_qg^T Un_qp; a step is ready when all PER parts of the group and the tile (q, p) are
+    const FlowElimP& e; int p, g;
+    __device__ const double* a(int q) const { return e.dt + ((int64_t)q * e.NG + g) * TILE; }
+    __device__ const double* b(int q) const { return e.tilesN + ((int64_t)q * e.f.T + p) * TILE; }
+    __device__ int ready(int q, int q1, int lane) const
+    {
+        constexpr int M = PER + 1, STEPS = 64 / M;
+        const int n = min(STEPS, q1 - q), st = lane / M, x = lane % M;
+        int v = 1;
+        if (st < n) v = ld_word(x < PER ? part_word(e, q + st, g * PER + x, e.NG * PER) : tile_word(e.f, q + st, p));
+        const unsigned long long m = __ballot(v != 0);
+        int k = 0;
+        while (k < n && ((m >> (k * M)) & ((1ull << M) - 1)) == (1ull << M) - 1) ++k;
+        return k;
+    }
+};
+
+// element (m, n) of A = Hinv in processing order; flow_init_a: minus tile (i, j) of A (0 past d) in the accumulator layout
+__device__ __forceinline__ double flow_hinv(const FlowElimP& p, int m, int n)
+{
+    const int d = p.f.d;
+    const int pm = min(max(p.perm[m], 0), d - 1), pn = min(max(p.perm[n], 0), d - 1);
+    return p.Hu[(int64_t)min(pm, pn) * d + max(pm, pn)];
+}
+
+__device__ __forceinline__ void flow_init_a(const FlowElimP& p, int i, int j, d4 (&c)[2])
+{
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int gm = NB * i + wr * 16 + 4 * v + fq, gn = NB * j + w2 * 32 + 16 * h + fr;
+            c[h][v] = (gm < p.f.d && gn < p.f.d) ? -flow_hinv(p, gm, gn) : 0.0;
+        }
+}
+
+// C(blk, s) by one workgroup; lds: two tiles, D and the codes of its rows
+template <int NR>
+__device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, int blk, int s)
+{
+    constexpr int RS = 8 * NR, PER = 64 / RS;
+    const FlowP& f = p.f;
+    const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int d = f.d, o = NB * blk, nb = min(NB, d - o), parts = p.NG * PER;
+    const int g = s / PER, r0 = (s % PER) * RS + wave * NR;      // first row of this wavefront inside the group
+    const bool more = blk + 1 < f.T;
+    double* Us = lds;
+    double* Vs = Us + TILE;
+    double* Ds = Vs + TILE;                                      // [column][RS]
+    uint8_t* Cs = reinterpret_cast<uint8_t*>(Ds + NB * RS);      // [column][RS]
+    double ws[NR], w0[NR], sc[NR], ze[NR];
+    const int col = min(o + lane, d - 1);
+    const int gcol = min(max(p.perm[col], 0), d - 1) / p.gs;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int64_t gi = (int64_t)min(NB * g + r0 + r, p.R - 1) * p.G + gcol;
+        sc[r] = p.scale[gi];
+        ze[r] = p.zero[gi];
+    }
+    flow_wait(f, lane == 0 ? tile_word(f, blk, blk) : lane == 1 ? group_word(p, blk, g) : part_word(p, max(blk, 1) - 1, s, parts),
+              lane < (blk > 0 ? 3 : 2));
+    {
+        const double* u = p.tilesN + ((int64_t)blk * f.T + blk) * TILE + wave * 512 + lane;
+        double un[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) un[x] = ld_shared(u + x * 64);
+        const double* wt = p.wt + ((int64_t)blk * p.NG + g) * TILE + r0 * 64 + lane;
+        const double* cin = p.corr + ((int64_t)(blk & 1) * p.NG * NB + NB * g + r0) * 64 + lane;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            w0[r] = ld_shared(wt + r * 64);
+            if (blk > 0) w0[r] -= ld_shared(cin + r * 64);
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) Us[wave * 512 + x * 64 + lane] = un[x];
+    }
+    const double hp = ld_shared(p.vec + 2 * NB * blk + NB + lane);
+    __syncthreads();
+    double mycode[NR], mydiff[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) { ws[r] = w0[r]; mycode[r] = 0.0; mydiff[r] = 0.0; }
+    // what comes after the steps and is there already: the pivot rows above the next block's columns, the loss so far
+    bool ahead = more && __all(lane == 0 ? ld_word(tile_word(f, blk, blk + 1)) != 0 : true);
+    double t[8];
+    auto load_next = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const double* u = p.tilesN + ((int64_t)blk * f.T + blk + 1) * TILE + wave * 512 + lane;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) t[x] = ld_shared(u + x * 64);
+    };
+    if (ahead) load_next();
+    double loss_before[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) loss_before[r] = ld_shared(p.lossrow + min(NB * g + r0 + r, p.R - 1));
+    bool suspect = false;
+    chain_steps<false, NR, NB>(ws, Us, sc, ze, p.maxq, nb, lane, mycode, mydiff, suspect);
+    if (__any(suspect)) {                    // wavefront-uniform; practically never taken
+#pragma unroll
+        for (int r = 0; r < NR; ++r) ws[r] = w0[r];
+        chain_steps<true, NR, NB>(ws, Us, sc, ze, p.maxq, nb, lane, mycode, mydiff, suspect);
+    }
+    if (more) {
+        if (!ahead) {
+            flow_wait(f, tile_word(f, blk, blk + 1), lane == 0);
+            load_next();
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) Vs[wave * 512 + x * 64 + lane] = t[x];
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        if (lane >= nb) { mydiff[r] = 0.0; mycode[r] = 0.0; }
+        Ds[lane * RS + wave * NR + r] = mydiff[r];
+        Cs[lane * RS + wave * NR + r] = (uint8_t)mycode[r];
+    }
+    __syncthreads();
+    if (more) {
+        double acc[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) acc[r] = 0.0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const double v = Vs[k * 64 + lane];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = fma(chain_readlane(mydiff[r], k), v, acc[r]);
+        }
+        double* cout = p.corr + ((int64_t)((blk + 1) & 1) * p.NG * NB + NB * g + r0) * 64 + lane;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) st_shared(cout + r * 64, acc[r]);
+        if (blk + 2 < f.T) {
+            double* dt = p.dt + ((int64_t)blk * p.NG + g) * TILE + (s % PER) * RS;
+#pragma unroll
+            for (int x = 0; x < NR; ++x) {
+                const int e = tid + NT * x;
+                st_shared(dt + (e / RS) * 64 + e % RS, Ds[e]);
+            }
+        }
+    }
+    // the codes, 8 rows at a time (codesT is padded to whole groups of rows)
+    if (tid < NB * NR && tid / NR < nb)
+        *reinterpret_cast<unsigned long long*>(p.codesT + (int64_t)(o + tid / NR) * p.Rp + NB * g + (s % PER) * RS + 8 * (tid % NR)) =
+            reinterpret_cast<const unsigned long long*>(Cs)[tid];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int row = NB * g + r0 + r;
+        double loss = mydiff[r] * mydiff[r] * hp;
+        if (lane >= nb) loss = 0.0;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+        if (row < p.R) {
+            if (lane == 0) st_shared(p.lossrow + row, loss_before[r] + loss);
+            if (p.Wout && lane < nb) p.Wout[(int64_t)row * d + o + lane] = ws[r];
+        }
+    }
+    flow_publish(part_word(p, blk, s, parts));
+}
+
+template <int NR>
+__global__ __launch_bounds__(NT, 2) void flow_eliminate_kernel(FlowElimP p)
+{
+    constexpr int PER = 64 / (8 * NR);
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
+    __shared__ int slot;
+    const FlowP& f = p.f;
+    const int T = f.T;
+    double* tiles = lds + SWEEP_LDS;
+    const int role = flow_ticket(f, FW_ROLE, &slot);
+    if (role == 0) flow_chain<true>(f, p.tilesN, p.vec, lds, [&](int m, int n) { return flow_hinv(p, m, n); });
+    else if (flow_serves(f, role) == 1) {
+        Queue1 q1;
+        const int n = queue1_length(T);
+        for (;;) {
+            const int t = flow_ticket(f, FW_QUEUE1, &slot);
+            if (t >= n) break;
+            const Queue1Item it = q1.at(t, T);
+            const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+            d4 c[2], u[2];
+            if (it.kind == 0) {
+                flow_init_a(p, it.i, it.j, c);
+                flow_sum(f, tiles, SumU{f, p.tilesN, it.i, it.j}, 0, it.i, c);
+                flow_row_product(f, tiles, it.i, it.i, c, u);
+                double* out = tile_at(f, it.i, it.j) + wr * 16 + fr;
+                double* outn = p.tilesN + ((int64_t)it.i * T + it.j) * TILE + wr * 16 + fr;
+                const double* rv = p.vec + 2 * NB * it.i;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int m = (h ? 3 - w2 : w2) * 16 + 4 * v + fq;
+                        st_shared(out + m * 64, u[h][v]);
+                        st_shared(outn + m * 64, u[h][v] * ld_shared(rv + m));
+                    }
+                flow_publish(tile_word(f, it.i, it.j));
+            } else {
+                const int k = it.i, ti = it.j ? k : k - 1;
+                flow_init_a(p, ti, k, c);
+                flow_sum(f, tiles, SumU{f, p.tilesN, ti, k}, 0, k - 1, c);
+                double* out = it.j ? tile_at(f, k, k) : hand_tile(f, k);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, -c[h][v]);
+                flow_publish(hand_word(f, k, it.j));
+            }
+        }
+    }
+    // a workgroup whose own queue is empty helps with the others
+    for (int turn = 0; turn < 2; ++turn) {
+        if ((flow_serves(f, role) == 3) == (turn == 0)) {
+            for (;;) {
+                const int t = flow_ticket(f, FW_QUEUE3, &slot);
+                if (t >= T * p.NG) break;
+                const int blk = t / p.NG, x = t - blk * p.NG;
+                const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+                const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+                d4 c[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int gm = NB * x + wr * 16 + 4 * v + fq, gn = NB * blk + w2 * 32 + 16 * h + fr;
+                        c[h][v] = (gm < p.R && gn < f.d) ? -(double)p.W[(int64_t)gm * f.d + min(max(p.perm[gn], 0), f.d - 1)] : 0.0;
+                    }
+                flow_sum(f, tiles, SumW<PER>{p, blk, x}, 0, blk - 1, c);
+                double* out = p.wt + ((int64_t)blk * p.NG + x) * TILE;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, -c[h][v]);
+                flow_publish(group_word(p, blk, x));
+            }
+        } else {
+            const int parts = p.NG * PER;
+            for (;;) {
+                const int t = flow_ticket(f, FW_QUEUE2, &slot);
+                if (t >= T * parts) break;
+                const int blk = t / parts;
+                flow_columns<NR>(p, tiles, blk, t - blk * parts);
+            }
+        }
+    }
+    if (threadIdx.x == 0 && ld_word(f.words + FW_ABORT) != 0) *f.stalled = 1;
+}
+
 int64_t flow_inverse_words(int d) { return flow_words((d + NB - 1) / NB); }
+// Rows per wavefront of a part of columns (1, 2 or 4).  A part takes 7.5 / 11 / 18 us (measured), on top of which its successor
+// waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15 us
+// each), with many the workgroups are all busy and what counts is the time per row.  Twice the pure work over all
+// workgroups against the chains; measured at 1 / 2 / 4 rows, elimination and columns: 256 x 2304 0.54 / 0.58 / 0.74 ms,
+// 2048 x 512 0.16 / 0.15 / 0.19, 1024 x 4608 2.10 / 1.90 / 1.81, 8192 x 256 0.35 / 0.32 / 0.22.
+static int column_rows(int64_t R, int64_t T)
+{
+    const double cost[3] = {7.5, 11.0, 18.0};
+    const double NG = (double)((R + NB - 1) / NB), t = (double)T, products = 2.4 * (t * t * t / 6.0 + NG * t * t / 2.0);
+    int best = 1;
+    double least = 0.0;
+    for (int i = 0; i < 3; ++i) {
+        const int nr = 1 << i;
+        const double chains = t * std::max(15.3, cost[i] + 2.5), work = 2.0 / 255.0 * (products + t * NG * (8 / nr) * cost[i]);
+        const double time = std::max(chains, work);
+        if (i == 0 || time < least) { least = time; best = nr; }
+    }
+    return best;
+}
+int64_t flow_eliminate_words(int d, int R)
+{
+    const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
+    return flow_words((int)T) + T * NG * (1 + 8 / column_rows(R, T));
+}
 size_t flow_tiles_bytes(int d) { const size_t T = (d + NB - 1) / NB; return T * T * TILE * sizeof(double); }
 size_t flow_gt_bytes(int d) { const size_t T = (d + NB - 1) / NB; return 2 * T * TILE * sizeof(double); }
+size_t flow_rows_bytes(int d, int R) { const size_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB; return T * NG * TILE * sizeof(double); }
+
+// One workgroup per compute unit at most (its LDS), no more than there are tiles to start with.
+static int flow_grid(int cus, int64_t tasks) { return (int)(1 + tasks < cus ? 1 + tasks : cus); }
 
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
                                double* gt, int* words, int* notpd, int* stalled)
@@ -520,15 +934,49 @@ hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, d
     FlowInverseP p;
     p.f.d = d;
     p.f.T = (d + NB - 1) / NB;
-    const int T = p.f.T;
-    // One workgroup per compute unit at most (its LDS), no more than there are tiles in flight.
-    const int64_t total = 1 + 2 * (int64_t)T * T;
-    const int wgs = (int)(total < cus ? total : cus);
-    p.f.n1 = 2 * T < wgs / 2 ? 2 * T : wgs / 2;
-    if (p.f.n1 < 1) p.f.n1 = 1;
+    const int T = p.f.T, wgs = flow_grid(cus, 2 * (int64_t)T * T);
+    // two rows of tiles in flight keep the chain fed (64 to 160 workgroups give the same times at d = 2304 .. 4608)
+    p.f.n1 = std::max(1, std::min(2 * T, wgs / 2));
+    p.f.n2 = std::max(1, wgs - 1 - p.f.n1);          // the others: queue 2 (there is no third)
+    p.f.n3 = 0;
     p.f.words = words; p.f.tiles = tiles; p.f.gt = gt; p.f.notpd = notpd; p.f.stalled = stalled;
     p.H = H; p.damp = damp; p.damp_abs = damp_abs; p.Hinv = Hinv;
     hipLaunchKernelGGL(flow_inverse_kernel, dim3(wgs), dim3(NT), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
+{
+    FlowElimP p;
+    p.f.d = a.d;
+    p.f.T = (a.d + NB - 1) / NB;
+    p.R = a.R; p.G = a.G; p.gs = a.gs; p.NG = (a.R + NB - 1) / NB;
+    // Where the chain of the diagonal blocks bounds the launch: what keeps up with it (two rows of tiles on queue 1, which feeds
+    // everything else; half as many again as there are parts in a block; the groups' sums a few blocks ahead), and no more, so
+    // that other launches find compute units.  Otherwise all, in proportion to the work of the queues in rank-64 products of a
+    // tile (a part of columns: what it takes, measured, in such products).
+    const int64_t T = p.f.T, nr = column_rows(a.R, T), parts = p.NG * (8 / nr);
+    const double w1 = (double)T * T * T / 6.0, w2 = (double)T * parts * (nr == 1 ? 3.0 : nr == 2 ? 5.0 : 8.0), w3 = (double)p.NG * T * T / 2.0;
+    const int64_t k1 = 2 * T, k2 = parts + (parts + 1) / 2, k3 = p.NG + p.NG * T / 6;
+    int avail = flow_grid(cus, T * (T + 9 * p.NG)) - 1;
+    if (k1 + k2 + k3 <= avail) {
+        p.f.n1 = (int)k1; p.f.n2 = (int)k2; p.f.n3 = (int)k3;
+    } else {
+        p.f.n1 = std::max<int>((int)(avail * w1 / (w1 + w2 + w3)), (int)std::min<int64_t>(k1, avail / 3));
+        p.f.n1 = std::max(1, std::min(p.f.n1, avail - 2));
+        p.f.n2 = std::max(1, std::min(avail - p.f.n1 - 1, (int)((avail - p.f.n1) * w2 / (w2 + w3) + 0.5)));
+        p.f.n3 = avail - p.f.n1 - p.f.n2;
+    }
+    const int wgs = 1 + p.f.n1 + p.f.n2 + p.f.n3;
+    p.f.words = a.words; p.f.tiles = a.tiles; p.f.gt = a.gt; p.f.notpd = a.notpd; p.f.stalled = a.stalled;
+    p.tilesN = a.tilesN; p.vec = a.vec; p.Hu = a.Hinv; p.perm = a.perm; p.W = a.W; p.scale = a.scale; p.zero = a.zero;
+    p.maxq = (double)((1 << a.bits) - 1);
+    p.codesT = a.codesT; p.Rp = a.Rp; p.lossrow = a.lossrow; p.Wout = a.Wout; p.wt = a.wt; p.dt = a.dt; p.corr = a.corr;
+    switch (nr) {
+    case 1: hipLaunchKernelGGL(flow_eliminate_kernel<1>, dim3(wgs), dim3(NT), 0, s, p); break;
+    case 2: hipLaunchKernelGGL(flow_eliminate_kernel<2>, dim3(wgs), dim3(NT), 0, s, p); break;
+    default: hipLaunchKernelGGL(flow_eliminate_kernel<4>, dim3(wgs), dim3(NT), 0, s, p); break;
+    }
     return hipGetLastError();
 }
 

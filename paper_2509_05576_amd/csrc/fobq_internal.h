@@ -80,7 +80,7 @@ struct StageTimer {
 
 }  // namespace fobq
 
-constexpr int FLAG_WORDS = 16, FLAG_WORD_MATE = 8, FLAG_WORD_NONFINITE = 9;
+constexpr int FLAG_WORDS = 16, FLAG_WORD_NONFINITE = 9;
 
 struct fobq_ctx {
     int device = 0;
@@ -113,23 +113,26 @@ struct fobq_ctx {
 
     // factorization / elimination workspace (all d x d fp64 unless noted)
     fobq::DevBuf tiles, gt; // published tiles of a factorization and its transposed block inverses (see flow.hip)
-    fobq::DevBuf words;     // words of its launches, then d_row fp64 per-row loss terms (lossrow); cleared per layer
+    fobq::DevBuf words;     // words of the two launches, then d_row fp64 per-row loss terms (lossrow); cleared per layer
     double* lossrow = nullptr;
+    int* words2 = nullptr;  // the elimination's words inside that buffer
     int64_t words_len = 0;  // 4-byte words of that buffer in use
-    fobq::DevBuf Hinv, A, U, Un;
-    fobq::DevBuf Dblk;      // diagonal-block scratch: 2 x (64 x 64) L11^-1, 2 x (64 x 64) G, 2 x 64 reciprocal pivots
+    fobq::DevBuf tilesN;    // a second set of published tiles (Un of the elimination)
+    fobq::DevBuf vec;       // 128 fp64 per 64 columns: reciprocal pivots, half reciprocal pivots
+    fobq::DevBuf Hinv;
+    fobq::DevBuf A, U, Un;  // general elimination (block != 64, or not all columns)
+    fobq::DevBuf Dblk;      // general elimination: one block's G (64 x 64) and 64 reciprocal pivots
     fobq::DevBuf obq;       // running inverses of the per-row baseline (fobq_obq_rows), rows x d x d fp64
     fobq::DevBuf flags;     // FLAG_WORDS int32: status flags written by kernels (cleared per call), then words
-                            // that live as long as the context (FLAG_WORD_MATE: see chol_iter_kernel)
-    int mate_epoch = 0;     // number of the last launch that used FLAG_WORD_MATE
+                            // that live longer (FLAG_WORD_NONFINITE: an accumulation)
     int cus = 256;          // compute units of the device (fobq_create)
     int* h_flags = nullptr; // pinned host memory that the status flags are read back into (made by fobq_create)
     unsigned char* static_scratch = nullptr;   // this GPU's copy of the library's static scratch array
     int fail_countdown = 0; // test hook: > 0 = the n-th status check from now reports an injected failure
     // quantization workspace
-    fobq::DevBuf Wp;        // d_row x d fp64, columns in processing order
-    fobq::DevBuf DT;        // d x Rp fp64: (w - q) per processed column
-    fobq::DevBuf corr;      // 2 x d_row x 64 fp64: compensation handed from one column block to the next
+    fobq::DevBuf Wp;        // d_row x d fp64, columns in processing order (one-launch form: in tiles)
+    fobq::DevBuf DT;        // d x Rp fp64: (w - q) per processed column (one-launch form: in tiles)
+    fobq::DevBuf corr;      // 2 x Rp x 64 fp64: compensation handed from one column block to the next
     fobq::DevBuf codesT;    // d x Rp u8
     fobq::DevBuf scale, zero;   // d_row x G fp64
     fobq::DevBuf S, Spart;  // d fp64, chunks x d fp64
@@ -244,6 +247,19 @@ hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, i
 int64_t flow_inverse_words(int d);
 size_t flow_tiles_bytes(int d);
 size_t flow_gt_bytes(int d);
+// The shared-Hinv elimination and the column loop of a whole layer in one launch.  words: flow_eliminate_words(d, R) zeroed words;
+// tiles, tilesN: flow_tiles_bytes(d); gt: flow_gt_bytes(d); vec: 128 doubles per 64 columns; wt, dt: flow_rows_bytes(d, R);
+// corr: 2 x Rp x 64; lossrow: zeroed; Wout may be null.
+struct FlowElimArgs {
+    int d, R, G, gs, bits, Rp;
+    const double* Hinv; const int* perm; const float* W; const double *scale, *zero;
+    double *tiles, *tilesN, *gt, *vec, *wt, *dt, *corr, *lossrow, *Wout;
+    uint8_t* codesT;
+    int *words, *notpd, *stalled;
+};
+int64_t flow_eliminate_words(int d, int R);
+size_t flow_rows_bytes(int d, int R);
+hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a);
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
                                double* gt, int* words, int* notpd, int* stalled);
 

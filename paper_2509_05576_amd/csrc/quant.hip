@@ -1,7 +1,7 @@
 // Grid, sensitivity, ordering, permutation and the column loop (Section 4.2).
 #include <hip/hip_ext.h>
 
-#include "fobq_internal.h"
+#include "column_chain.h"
 
 namespace fobq {
 
@@ -266,56 +266,7 @@ hipError_t launch_gather(hipStream_t s, const float* W, int R, int d, const int*
 // the one that counts and is broadcast with v_readlane.  The loop is fully
 // unrolled, so there is no memory access on the sequential chain.  diff is stored
 // (DT) for the deferred rank-nb update of the columns right of the block.
-constexpr int CB = 64;
 constexpr int CHAIN_WAVES = 8;
-
-__device__ __forceinline__ double readlane_f64(double v, int lane)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
-// The 64 sequential steps of one row.  EXACT = false forms the quotient w / s as w * (1 / s)
-// (the product is within 2 ulp of the true quotient, so rint of it can differ from
-// rint(w / s) only when it lies within 2 ulp of a half-integer) and reports through `suspect`
-// whether any lane came that close; EXACT = true uses the true division.  The dependent chain
-// per step is: multiply, rint, max, min, fma, readlane, fma.
-template <bool EXACT>
-__device__ __forceinline__ void chain_steps(double& w, const double (*Us)[CB + 1], double s, double z, double maxq,
-                                            int nb, int lane, double& mycode, double& mydiff, bool& suspect)
-{
-    const double rcp_s = 1.0 / s;
-    const double lo = -z, hi = maxq - z;          // clamp(c + z, 0, maxq) - z = clamp(c, -z, maxq - z)
-    // This lane's pivot-row entries u_j = Us[j][lane] (0 for lanes <= j: they keep the value they were
-    // quantized at) come from LDS 16 steps ahead of their use, so that no memory access sits on the
-    // sequential chain and only 32 of the 64 are in registers at a time.
-    double ub[2][16];
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) ub[0][jj] = Us[jj][lane];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        if (g < 3) {
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) ub[(g + 1) & 1][jj] = Us[16 * (g + 1) + jj][lane];
-        }
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int j = 16 * g + jj;
-            if (j < nb) {                             // uniform
-                const double tq = EXACT ? w / s : w * rcp_s;
-                const double c0 = rint(tq);
-                if (!EXACT) suspect = suspect || (fabs(fabs(tq - c0) - 0.5) < 1.0e-9 * fmax(1.0, fabs(tq)));
-                const double cz = fmin(fmax(c0, lo), hi);        // code - zero
-                const double df = w - s * cz;
-                const double dj = readlane_f64(df, j);
-                if (lane == j) { mycode = cz + z; mydiff = df; }
-                w -= dj * ub[g & 1][jj];
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);            // keeps the loads of the group after the next from moving up here
-    }
-}
 
 // One launch per column block k does two things that do not depend on each other:
 //   (chain role, workgroups 0 .. n_chain-1)   the 64 sequential steps of block k, one row of W per wavefront;
@@ -375,13 +326,15 @@ __device__ __forceinline__ void col_chain_role(const ColChainP& c, double* lds, 
     const double hp = 0.5 / c.U[(int64_t)(o + cl) * d + o + cl];
     __syncthreads();
     if (row >= c.R) return;                  // whole wavefront leaves; no barrier after this point
-    double w = w0, mycode = 0.0, mydiff = 0.0;
+    double ws[1] = {w0}, codes[1] = {0.0}, diffs[1] = {0.0};
+    const double ss[1] = {s}, zs[1] = {z};
     bool suspect = false;
-    chain_steps<false>(w, Us, s, z, c.maxq, nb, lane, mycode, mydiff, suspect);
+    chain_steps<false, 1, CB + 1>(ws, &Us[0][0], ss, zs, c.maxq, nb, lane, codes, diffs, suspect);
     if (__any(suspect)) {                    // wavefront-uniform; practically never taken
-        w = w0;
-        chain_steps<true>(w, Us, s, z, c.maxq, nb, lane, mycode, mydiff, suspect);
+        ws[0] = w0;
+        chain_steps<true, 1, CB + 1>(ws, &Us[0][0], ss, zs, c.maxq, nb, lane, codes, diffs, suspect);
     }
+    const double w = ws[0], mycode = codes[0], mydiff = diffs[0];
     if (col_ok) {
         c.codesT[(int64_t)(o + lane) * c.Rp + row] = (uint8_t)mycode;
         c.DT[(int64_t)(o + lane) * c.Rp + row] = mydiff;
@@ -392,7 +345,7 @@ __device__ __forceinline__ void col_chain_role(const ColChainP& c, double* lds, 
         const double dk = col_ok ? mydiff : 0.0;
         double acc = 0.0;
 #pragma unroll
-        for (int k = 0; k < CB; ++k) acc = fma(readlane_f64(dk, k), Vs[k][lane], acc);
+        for (int k = 0; k < CB; ++k) acc = fma(chain_readlane(dk, k), Vs[k][lane], acc);
         if (lane < c.nb_next) c.corr_out[(int64_t)row * CB + lane] = acc;
     }
     double loss = col_ok ? mydiff * mydiff * hp : 0.0;
@@ -965,7 +918,7 @@ __global__ __launch_bounds__(64 * CHAIN_WAVES) void batch_columns_kernel(const B
             __syncthreads();
             double acc = 0.0;
 #pragma unroll
-            for (int j = 0; j < CB; ++j) acc = fma(readlane_f64(dj, j), Us[j][lane], acc);
+            for (int j = 0; j < CB; ++j) acc = fma(chain_readlane(dj, j), Us[j][lane], acc);
             if (row_ok && lane < nk) L.Wp[(int64_t)row * d + k0 + lane] -= acc;
             __syncthreads();
         }

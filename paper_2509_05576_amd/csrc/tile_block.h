@@ -120,7 +120,7 @@ struct Nothing { __device__ void operator()() const {} };
 template <class SW, class TI, class TR, class TF, class BS, class AH>
 __device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TI tinv, TR trail, TF tf, BS beside, AH ahead)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int fr = lane & 15, fq = lane >> 4;
     d4 t = {0.0, 0.0, 0.0, 0.0};
     const int j3 = wave - 3;                       // wavefronts 3, 4, 5: column tile of X_3j
@@ -160,7 +160,7 @@ __device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TI tinv, TR
 template <class BS = Nothing, class AH = Nothing>
 __device__ __forceinline__ void chol_block(double* Am, double* Xm, double* rq, int* __restrict__ flag, BS beside = BS(), AH ahead = AH())
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, fq = lane >> 4;
     // The columns of the running sweep: column k at cb[CB0 + 16 k + r], r = row - tile base.  Only the
     // 16 tile rows are read; what the other lanes write falls into the slots of neighbouring columns,
@@ -281,7 +281,7 @@ __device__ __forceinline__ void chol_block(double* Am, double* Xm, double* rq, i
 template <class BS = Nothing, class AH = Nothing>
 __device__ __forceinline__ void elim_block(double* Am, double* Xm, double* rv, int* __restrict__ flag, BS beside = BS(), AH ahead = AH())
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, fq = lane >> 4;
     double* cb = rv + NB;      // the pivot rows of the running sweep, laid out as in chol_block
     double* idt = cb + CB_LEN; // 16 rows of the identity, row stride DL (read from the second sweep on)

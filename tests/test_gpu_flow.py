@@ -61,3 +61,24 @@ def test_inverses_on_several_contexts_at_once(fobq):
                 assert torch.equal(a, b)
     for c in ctxs:
         c.close()
+
+
+# single rows, ragged groups of rows, one and several rows per wavefront, ragged last block, grids per group: the launch that
+# eliminates and quantizes against the general form (other blocks, other kernels); both are fp64, sums in another order
+@pytest.mark.parametrize("r,d,group", [(1, 1, 0), (7, 64, 0), (9, 65, 0), (65, 129, 43), (300, 577, 0), (1030, 320, 64),
+                                       (2100, 512, 128), (8200, 256, 0), (260, 2304, 0)])
+def test_elimination_and_columns_match_the_general_form(fobq, r, d, group):
+    H = _spd(d, 3 * d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(r + d)
+    W = torch.randn((r, d), generator=g, device="cuda") * (2.0 / d) ** 0.5
+    with fobq.Ctx(0) as ctx:
+        want = ctx.quantize_layer(W, H, bits=4, group=group, block=32, debug=True)
+        got = ctx.quantize_layer(W, H, bits=4, group=group, debug=True)
+        assert torch.equal(got.perm, want.perm) and torch.equal(got.codes, want.codes) and torch.equal(got.Q, want.Q)
+        assert torch.allclose(got.W_work, want.W_work, rtol=1e-9, atol=1e-12)
+        assert torch.allclose(got.loss, want.loss, rtol=1e-11)
+        assert not got.Hinv_work.any()
+        for _ in range(3):
+            again = ctx.quantize_layer(W, H, bits=4, group=group)
+            assert torch.equal(again.codes, got.codes) and torch.equal(again.loss, got.loss)
