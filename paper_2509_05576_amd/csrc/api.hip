@@ -613,18 +613,22 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
     ctx->h_conv_k = k;
     if (first_call) ctx->h_offsets = offsets;
     // the padded copy is stream-ordered: a later call reuses the buffer only after this call's launches
-    FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>()),
-             "pad maps");
+    int* nonfinite = ctx->flags.as<int>() + FLAG_WORD_NONFINITE;
+    bool have_amax = false;
+    if (i8) {
+        // the channel maxima start at zero; an accumulation's first call also lowers the flag
+        FOBQ_TRY(launch_clear_words(ctx->stream, ctx->i8amax.p, c, nonfinite, ctx->h_i8_used ? 0 : 1), "clear channel maxima and flag");
+        ctx->h_i8_used = true;
+    }
+    FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>(),
+                             i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax), "pad maps");
     if (i8) {
         // the digits of the unfolded input are written out (1.25 bytes per element of the unfolded X, a block of
         // columns at a time) and the matrix kernel runs on them as it does on a plain X
-        int* nonfinite = ctx->flags.as<int>() + FLAG_WORD_NONFINITE;
-        if (!ctx->h_i8_used) FOBQ_TRY(launch_clear_words(ctx->stream, nonfinite, 1, nullptr, 0), "clear flag");
-        ctx->h_i8_used = true;
         {
             StageScope sc(ctx, FOBQ_STAGE_SLICE);
             FOBQ_TRY(launch_i8_chan_shifts(ctx->stream, ctx->maps_pad.as<float>(), (n_img + 1) * hp * wp, (int)c, d,
-                                           ctx->i8amax.as<unsigned>(), ctx->i8sh.as<int>(), nonfinite), "channel exponents");
+                                           ctx->i8amax.as<unsigned>(), have_amax, ctx->i8sh.as<int>(), nonfinite), "channel exponents");
         }
         for (int64_t p0 = 0; p0 < npix; p0 += blk) {
             const int64_t nb = npix - p0 < blk ? npix - p0 : blk;

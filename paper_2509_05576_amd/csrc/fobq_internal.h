@@ -190,7 +190,7 @@ hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t 
 int xxt_pick_splits(int d);
 int xxt_slabs_touched(int d, int64_t n, int splits, bool conv);
 hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, int count);
-hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out);
+hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took);
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                            int ho, int wo, int64_t npix, double* Hpart, int splits,
                            LaunchEvents ev = LaunchEvents());
@@ -213,8 +213,8 @@ int xxt_i8_wanted_splits(int d, int64_t n, I8Rect rect = I8Rect());
 int64_t i8_block_columns(int d);      // most columns one launch of the matrix kernel takes (bounds the digit scratch)
 hipError_t launch_i8_row_shifts(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, int* sh, int* nonfinite);
 hipError_t launch_i8_slice(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, const int* sh, signed char* planes);
-hipError_t launch_i8_chan_shifts(hipStream_t s, const float* padded, int64_t pixels, int c, int d, unsigned* amax, int* sh,
-                                 int* nonfinite);
+hipError_t launch_i8_chan_shifts(hipStream_t s, const float* padded, int64_t pixels, int c, int d, unsigned* amax, bool have_amax,
+                                 int* sh, int* nonfinite);
 hipError_t launch_i8_slice_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                                 int ho, int wo, int64_t npix, int64_t pix0, int64_t n, const int* sh, signed char* planes);
 hipError_t launch_xxt_i8(hipStream_t s, const signed char* planes, const int* sh, int d, int64_t n, double* Hpart,

@@ -65,31 +65,77 @@ struct ConvP {
     FastDiv div_k;      // by k
 };
 
-// out: (n_img + 1) x hp x wp x c, hp = h + 2 pad, wp = w + 2 pad; image n_img is all zeros
-__global__ __launch_bounds__(256) void pad_maps_kernel(const float* __restrict__ maps, int n_img, int h, int w, int c,
-                                                       int pad, float* __restrict__ out, int64_t total)
+// out: (n_img + 1) x hp x wp x c, hp = h + 2 pad, wp = w + 2 pad; image n_img is all zeros.  Bound by memory: a workgroup takes
+// whole rows of the padded copy (zeros, the row of the map, zeros: no division per element), 16 bytes per lane where the
+// channels come in fours (VEC: c % 4 == 0, both pointers 16-byte aligned).  AMAX: the maxima |.| of every channel (bit
+// patterns) are taken on the way: the first `active` threads walk a row in steps of a multiple of c, so that a thread stays on
+// its channels; one atomic per channel and workgroup.  The 64-image 56 x 56 x 128 maps (103 MB): 85 us for a copy by elements
+// and 139 us for a second pass over it with an atomic per thread, 61 us together now.
+template <bool VEC, bool AMAX>
+__global__ __launch_bounds__(256) void pad_maps_kernel(const float* __restrict__ maps, int n_img, int h, int w, int c, int pad,
+                                                       float* __restrict__ out, int64_t rows, int active, unsigned* __restrict__ amax)
 {
-    const int hp = h + 2 * pad, wp = w + 2 * pad;
-    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-        const int ch = (int)(idx % c);
-        int64_t r = idx / c;
-        const int x = (int)(r % wp) - pad;
-        r /= wp;
-        const int y = (int)(r % hp) - pad;
-        const int64_t img = r / hp;
-        float v = 0.f;
-        if (img < n_img && (unsigned)y < (unsigned)h && (unsigned)x < (unsigned)w)
-            v = maps[((img * h + y) * w + x) * c + ch];
-        out[idx] = v;
+    typedef typename std::conditional<VEC, float4, float>::type V;
+    constexpr int VL = VEC ? 4 : 1;
+    const int hp = h + 2 * pad;
+    const int lead = pad * c / VL, len = w * c / VL, total = len + 2 * lead;
+    V zero{};
+    unsigned m[VL];
+#pragma unroll
+    for (int e = 0; e < VL; ++e) m[e] = 0;
+    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+        const int64_t img = row / hp;
+        const int y = (int)(row - img * hp) - pad;
+        V* __restrict__ dst = reinterpret_cast<V*>(out) + row * total;
+        if (img >= n_img || (unsigned)y >= (unsigned)h) {
+            for (int x = threadIdx.x; x < total; x += 256) dst[x] = zero;
+            continue;
+        }
+        const V* __restrict__ src = reinterpret_cast<const V*>(maps) + (img * h + y) * len;
+        for (int x = threadIdx.x; x < lead; x += 256) {
+            dst[x] = zero;
+            dst[lead + len + x] = zero;
+        }
+        if ((int)threadIdx.x < active) {
+#pragma unroll 4
+            for (int x = threadIdx.x; x < len; x += active) {
+                const V v = src[x];
+                if (AMAX) {
+                    const float* f = reinterpret_cast<const float*>(&v);
+#pragma unroll
+                    for (int e = 0; e < VL; ++e) m[e] = max(m[e], __float_as_uint(f[e]) & 0x7fffffffu);
+                }
+                dst[lead + x] = v;
+            }
+        }
+    }
+    if (AMAX) {
+        __shared__ unsigned part[256 * VL];
+#pragma unroll
+        for (int e = 0; e < VL; ++e) part[threadIdx.x * VL + e] = m[e];      // thread t: channels (t VL + e) % c
+        __syncthreads();
+        for (int ch = threadIdx.x; ch < c; ch += 256) {
+            unsigned best = 0;
+            for (int i = ch; i < active * VL; i += c) best = max(best, part[i]);
+            atomicMax(&amax[ch], best);
+        }
     }
 }
 
-hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out)
+// amax: null, or c words that hold zeros; *took (if amax): whether the maxima were taken (else the caller's own pass does it)
+hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took)
 {
-    const int64_t total = (int64_t)(n_img + 1) * (h + 2 * pad) * (w + 2 * pad) * c;
-    const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(pad_maps_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, maps, n_img, h,
-                       w, c, pad, out, total);
+    const int64_t rows = (int64_t)(n_img + 1) * (h + 2 * pad);
+    const bool vec = c % 4 == 0 && ((reinterpret_cast<uintptr_t>(maps) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+    const int unit = vec ? c / 4 : c;                  // steps of a row after which the channels repeat
+    const bool max_too = amax && unit <= 256;
+    const int active = max_too ? unit * (256 / unit) : 256;
+    const dim3 grid((unsigned)(rows < 2048 ? rows : 2048)), block(256);
+    if (took) *took = max_too;
+    if (vec && max_too)  hipLaunchKernelGGL((pad_maps_kernel<true, true>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
+    else if (vec)        hipLaunchKernelGGL((pad_maps_kernel<true, false>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
+    else if (max_too)    hipLaunchKernelGGL((pad_maps_kernel<false, true>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
+    else                 hipLaunchKernelGGL((pad_maps_kernel<false, false>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
     return hipGetLastError();
 }
 

@@ -204,27 +204,18 @@ struct SliceConvP {
     int64_t npix;            // output pixels of the whole call
 };
 
-// amax[c] = max over all pixels of |maps[.][c]| as a bit pattern (integer max: order-free).  blockIdx.x = chunk of
-// pixels.  c <= 256: the workgroup walks its chunk T = c * (256 / c) elements at a time, so a thread stays on one
-// channel; c > 256: thread = channel (strided), one pixel at a time.
+// amax[c] = max over all pixels of |maps[.][c]| as a bit pattern (integer max: order-free), for channel counts that the padding
+// launch does not take along (see pad_maps_kernel).  blockIdx.x = chunk of pixels, thread = channel (strided).
 __global__ __launch_bounds__(256) void chan_amax_kernel(const float* __restrict__ padded, int64_t pixels, int c,
                                                         unsigned* __restrict__ amax)
 {
     const int64_t per = (pixels + gridDim.x - 1) / gridDim.x;
     const int64_t p0 = (int64_t)blockIdx.x * per, p1 = min(pixels, p0 + per);
     if (p0 >= p1) return;
-    if (c <= 256) {
-        const int T = c * (256 / c);
-        if ((int)threadIdx.x >= T) return;
+    for (int ch = threadIdx.x; ch < c; ch += 256) {
         unsigned m = 0;
-        for (int64_t e = p0 * c + threadIdx.x; e < p1 * c; e += T) m = max(m, __float_as_uint(padded[e]) & 0x7fffffffu);
-        atomicMax(&amax[threadIdx.x % c], m);
-    } else {
-        for (int ch = threadIdx.x; ch < c; ch += 256) {
-            unsigned m = 0;
-            for (int64_t p = p0; p < p1; ++p) m = max(m, __float_as_uint(padded[p * c + ch]) & 0x7fffffffu);
-            atomicMax(&amax[ch], m);
-        }
+        for (int64_t p = p0; p < p1; ++p) m = max(m, __float_as_uint(padded[p * c + ch]) & 0x7fffffffu);
+        atomicMax(&amax[ch], m);
     }
 }
 
@@ -626,16 +617,16 @@ hipError_t launch_i8_slice(hipStream_t s, const float* X, int64_t ld, int d, int
     return hipGetLastError();
 }
 
-// Convolution input, per call: channel maxima over the padded copy ((n_img + 1) x hp x wp x c), then sh for the
-// d = c k^2 tap-major rows.  amax: c words of scratch.
-hipError_t launch_i8_chan_shifts(hipStream_t s, const float* padded, int64_t pixels, int c, int d, unsigned* amax, int* sh,
+// Convolution input, per call: sh for the d = c k^2 tap-major rows from the channel maxima; those over the padded copy
+// ((n_img + 1) x hp x wp x c) first unless the padding launch has taken them (have_amax).  amax: c words of scratch.
+hipError_t launch_i8_chan_shifts(hipStream_t s, const float* padded, int64_t pixels, int c, int d, unsigned* amax, bool have_amax, int* sh,
                                  int* nonfinite)
 {
-    hipError_t e = launch_clear_words(s, amax, c, nullptr, 0);
-    if (e != hipSuccess) return e;
-    const int64_t chunks = (pixels + 63) / 64;           // at least 64 pixels per workgroup
-    hipLaunchKernelGGL(chan_amax_kernel, dim3((unsigned)(chunks < 4096 ? (chunks < 1 ? 1 : chunks) : 4096)), dim3(256), 0, s,
-                       padded, pixels, c, amax);
+    if (!have_amax) {
+        const int64_t chunks = (pixels + 63) / 64;           // at least 64 pixels per workgroup
+        hipLaunchKernelGGL(chan_amax_kernel, dim3((unsigned)(chunks < 4096 ? (chunks < 1 ? 1 : chunks) : 4096)), dim3(256), 0, s,
+                           padded, pixels, c, amax);
+    }
     hipLaunchKernelGGL(chan_shift_kernel, dim3((d + 255) / 256), dim3(256), 0, s, amax, c, d, sh, nonfinite);
     return hipGetLastError();
 }
