@@ -212,11 +212,11 @@ int fobq_finish(fobq_ctx* ctx);
 /*
  * Several small layers in one call (Section 3: "each layer is quantized independently").  A layer of up
  * to 256 columns is a chain of short dependent steps that leaves the GPU idle; here every stage of the
- * path is ONE launch for all layers of the batch (grid and column sums, damped inverse, scores and order,
- * shared-Hinv elimination, column loop with emit, loss), one workgroup per layer walking the factor path
- * of its layer, so the cost of a batch is about that of one small layer.  Results per layer are those of
- * fobq_quantize_layer (same arithmetic in fp64; sums inside the deferred updates are taken in a
- * different order).
+ * path is ONE launch for all layers of the batch (grid, column sums, damped inverse, scores and order,
+ * shared-Hinv elimination with the column loop, emit with the loss), in the two factorization launches with
+ * several workgroups to a layer, so the cost of a batch is about that of one small layer while the GPU
+ * holds it.  Results per layer are those of fobq_quantize_layer (same arithmetic in fp64; the loss is summed
+ * in a different order).
  *   layers   host array of n_layers entries: W (device fp32 d_row x d_col), H (device fp64 d_col x d_col,
  *            full symmetric, undamped: e.g. from fobq_hessian_finalize(ctx, H)), out (device pointers as in
  *            fobq_out; W_work and Hinv_work must be NULL)

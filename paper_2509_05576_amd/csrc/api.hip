@@ -1075,22 +1075,26 @@ static void* pool_take(unsigned char* base, size_t* off, size_t bytes)
 // scratch pointers of one batched layer (or, with base == null, just the size it needs)
 static void batch_layout(BatchLayer* L, unsigned char* base, size_t* off)
 {
-    const size_t dd = (size_t)L->d * L->d * sizeof(double);
-    double** mats[] = {&L->Hd, &L->Linv, &L->T, &L->Hinv, &L->A, &L->U, &L->Un};
-    for (double** m : mats) *m = static_cast<double*>(pool_take(base, off, dd));
-    L->Gs = static_cast<double*>(pool_take(base, off, 64 * 64 * sizeof(double)));
-    L->rinv = static_cast<double*>(pool_take(base, off, 64 * sizeof(double)));
-    L->Wp = static_cast<double*>(pool_take(base, off, (size_t)L->R * L->d * sizeof(double)));
-    L->DT = static_cast<double*>(pool_take(base, off, (size_t)L->d * L->Rp * sizeof(double)));
+    auto doubles = [&](size_t n) { return static_cast<double*>(pool_take(base, off, n * sizeof(double))); };
+    L->nwords1 = (int)flow_inverse_words(L->d);
+    L->nwords = L->nwords1 + (int)flow_eliminate_words_most(L->d, L->R) + 2;
+    L->words = static_cast<int*>(pool_take(base, off, (size_t)L->nwords * sizeof(int)));
+    L->Hinv = doubles((size_t)L->d * L->d);
+    L->tiles = static_cast<double*>(pool_take(base, off, flow_tiles_bytes(L->d)));
+    L->tilesN = static_cast<double*>(pool_take(base, off, flow_tiles_bytes(L->d)));
+    L->gt = static_cast<double*>(pool_take(base, off, flow_gt_bytes(L->d)));
+    L->vec = doubles((size_t)(L->d + 63) / 64 * 128);
+    L->wt = static_cast<double*>(pool_take(base, off, flow_rows_bytes(L->d, L->R)));
+    L->dt = static_cast<double*>(pool_take(base, off, flow_rows_bytes(L->d, L->R)));
+    L->corr = doubles((size_t)2 * L->Rp * 64);
     L->codesT = static_cast<uint8_t*>(pool_take(base, off, (size_t)L->d * L->Rp));
-    L->scale = static_cast<double*>(pool_take(base, off, (size_t)L->R * L->G * sizeof(double)));
-    L->zero = static_cast<double*>(pool_take(base, off, (size_t)L->R * L->G * sizeof(double)));
-    L->S = static_cast<double*>(pool_take(base, off, (size_t)L->d * sizeof(double)));
-    L->Spart = static_cast<double*>(pool_take(base, off, (size_t)L->chunks * L->d * sizeof(double)));
-    L->lossrow = static_cast<double*>(pool_take(base, off, (size_t)L->R * sizeof(double)));
+    L->scale = doubles((size_t)L->R * L->G);
+    L->zero = doubles((size_t)L->R * L->G);
+    L->S = doubles(L->d);
+    L->Spart = doubles((size_t)L->chunks * L->d);
+    L->lossrow = doubles(L->R);
     L->perm = static_cast<int*>(pool_take(base, off, (size_t)L->d * sizeof(int)));
     L->invperm = static_cast<int*>(pool_take(base, off, (size_t)L->d * sizeof(int)));
-    L->flags = static_cast<int*>(pool_take(base, off, 4 * sizeof(int)));
 }
 
 int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_layer* layers, const fobq_opts* opts)
@@ -1124,16 +1128,32 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     if (!g.ok) return set_err(ctx, FOBQ_EHIP, "cannot select device %d", ctx->device);
     ctx->err.clear();
 
-    // descriptors: pinned host staging (also receives the status words), device copy, scratch pool
-    const size_t desc_bytes = (size_t)BATCH_MAX_LAYERS * sizeof(BatchLayer), flag_bytes = (size_t)BATCH_MAX_LAYERS * 4 * sizeof(int);
+    // descriptors: pinned host staging (also receives the status words), device copy, scratch pool.  In both: the layers, the
+    // descriptors of the two factorization launches, the layer of every workgroup of either, and (host) the status words.
+    auto packed = [&](int layers, size_t* at) {      // offsets of the two descriptors and the two tables; the length of all
+        const size_t most_wgs = (size_t)flow_batch_most_wgs(ctx->cus, layers);
+        at[0] = (size_t)layers * sizeof(BatchLayer);
+        at[1] = at[0] + layers * FLOW_DESC_BYTES;
+        at[2] = at[1] + layers * FLOW_DESC_BYTES;
+        at[3] = at[2] + most_wgs * sizeof(uint16_t);
+        return (at[3] + most_wgs * sizeof(uint16_t) + 255) / 256 * 256;
+    };
+    size_t at[4];
+    const size_t desc_bytes = packed(BATCH_MAX_LAYERS, at);
+    const size_t flag_bytes = (size_t)BATCH_MAX_LAYERS * 4 * sizeof(int);
+    const size_t sent_bytes = packed(n_layers, at);
+    const size_t off_inv = at[0], off_elim = at[1], off_inv_of = at[2], off_elim_of = at[3];
     if (!ctx->h_batch && hipHostMalloc(&ctx->h_batch, desc_bytes + flag_bytes, hipHostMallocDefault) != hipSuccess) {
         ctx->h_batch = nullptr;
         return set_err(ctx, FOBQ_ENOMEM, "cannot allocate pinned host memory for the batch descriptors");
     }
-    FOBQ_TRY(ctx->batch_desc.ensure(desc_bytes + flag_bytes), "workspace batch descriptors");
+    FOBQ_TRY(ctx->batch_desc.ensure(desc_bytes), "workspace batch descriptors");
+    unsigned char* hb = static_cast<unsigned char*>(ctx->h_batch);
     BatchLayer* hd = static_cast<BatchLayer*>(ctx->h_batch);
-    int max_pairs = 1, max_chunks = 1, max_rows = 1;
+    int max_pairs = 1, max_chunks = 1;
+    int64_t max_weights = 1;
     size_t pool = 0;
+    pool_take(nullptr, &pool, (size_t)n_layers * 4 * sizeof(int));          // status words
     for (int l = 0; l < n_layers; ++l) {
         const fobq_layer& in = layers[l];
         BatchLayer& L = hd[l];
@@ -1145,7 +1165,6 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         L.Rp = (L.R + 63) / 64 * 64;
         L.chunks = sens_chunks(L.R);
         L.maxq = (double)((1 << opts->bits) - 1);
-        L.damp = opts->damp; L.damp_abs = opts->damp_abs;
         L.order = opts->order; L.kind = order_kind(opts);
         L.ascending = opts->order >= FOBQ_ORDER_SENSI_ASC && opts->order <= FOBQ_ORDER_W_ASC;
         L.codes = in.out.codes; L.scales = in.out.scales; L.zeros = in.out.zeros; L.Q = in.out.Q;
@@ -1153,30 +1172,51 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         batch_layout(&L, nullptr, &pool);
         max_pairs = std::max(max_pairs, L.R * L.G);
         max_chunks = std::max(max_chunks, L.chunks);
-        max_rows = std::max(max_rows, L.R);
+        max_weights = std::max(max_weights, (int64_t)L.R * L.d);
     }
     FOBQ_TRY(ctx->batch_pool.ensure(pool), "workspace batch pool");
     size_t off = 0;
-    for (int l = 0; l < n_layers; ++l) batch_layout(&hd[l], ctx->batch_pool.as<unsigned char>(), &off);
+    int* flags = static_cast<int*>(pool_take(ctx->batch_pool.as<unsigned char>(), &off, (size_t)n_layers * 4 * sizeof(int)));
+    FlowElimArgs ea[BATCH_MAX_LAYERS];
+    const double* Hs[BATCH_MAX_LAYERS];
+    int *words[BATCH_MAX_LAYERS], *notpd[BATCH_MAX_LAYERS];
+    for (int l = 0; l < n_layers; ++l) {
+        BatchLayer& L = hd[l];
+        batch_layout(&L, ctx->batch_pool.as<unsigned char>(), &off);
+        L.flags = flags + 4 * l;
+        FlowElimArgs& a = ea[l];
+        a.d = L.d; a.R = L.R; a.G = L.G; a.gs = L.gs; a.bits = opts->bits; a.Rp = L.Rp;
+        a.Hinv = L.Hinv; a.perm = L.perm; a.W = L.W; a.scale = L.scale; a.zero = L.zero;
+        a.tiles = L.tiles; a.tilesN = L.tilesN; a.gt = L.gt; a.vec = L.vec; a.wt = L.wt; a.dt = L.dt; a.corr = L.corr;
+        a.lossrow = L.lossrow; a.Wout = nullptr; a.codesT = L.codesT;
+        a.words = L.words + L.nwords1;
+        a.notpd = L.flags + FLAG_NOTPD_HINV; a.stalled = L.flags + FLAG_STALLED;
+        Hs[l] = L.H; words[l] = L.words; notpd[l] = L.flags + FLAG_NOTPD_H;
+    }
+    FlowBatchPlan plan;
+    flow_batch_plan(ctx->cus, n_layers, ea, Hs, opts->damp, opts->damp_abs, words, hb + off_inv, hb + off_elim,
+                    reinterpret_cast<uint16_t*>(hb + off_inv_of), reinterpret_cast<uint16_t*>(hb + off_elim_of), notpd, &plan);
 
+    int* arrivals = hd[0].words + hd[0].nwords - 2;
     hipStream_t s = ctx->stream;
-    const BatchLayer* dl = ctx->batch_desc.as<BatchLayer>();
+    const unsigned char* db = ctx->batch_desc.as<unsigned char>();
+    const BatchLayer* dl = reinterpret_cast<const BatchLayer*>(db);
     int rc = [&]() -> int {
-        FOBQ_TRY(hipMemcpyAsync(ctx->batch_desc.p, hd, (size_t)n_layers * sizeof(BatchLayer), hipMemcpyHostToDevice, s),
-                 "upload batch descriptors");
+        FOBQ_TRY(hipMemcpyAsync(ctx->batch_desc.p, hb, sent_bytes, hipMemcpyHostToDevice, s), "upload batch descriptors");
         FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs), "grid (batch)");
         FOBQ_TRY(launch_batch_sens_partial(s, dl, n_layers, max_chunks), "sensitivity (batch)");
-        FOBQ_TRY(launch_batch_inverse(s, dl, n_layers), "inverse (batch)");
+        FOBQ_TRY(launch_flow_batch_inverse(s, db + off_inv, reinterpret_cast<const uint16_t*>(db + off_inv_of), arrivals, plan.inv_wgs), "inverse (batch)");
         FOBQ_TRY(launch_batch_order(s, dl, n_layers), "order (batch)");
-        FOBQ_TRY(launch_batch_eliminate(s, dl, n_layers), "eliminate (batch)");
-        FOBQ_TRY(launch_batch_columns(s, dl, n_layers, max_rows), "column loop (batch)");
-        FOBQ_TRY(launch_batch_loss(s, dl, n_layers), "loss (batch)");
-        // status words of every layer, gathered by one strided copy into the staging area behind the descriptors
-        int* hflags = reinterpret_cast<int*>(static_cast<unsigned char*>(ctx->h_batch) + desc_bytes);
-        for (int l = 0; l < n_layers; ++l)
-            FOBQ_TRY(hipMemcpyAsync(hflags + 4 * l, hd[l].flags, 4 * sizeof(int), hipMemcpyDeviceToHost, s), "read status flags");
+        FOBQ_TRY(launch_flow_batch_eliminate(s, db + off_elim, reinterpret_cast<const uint16_t*>(db + off_elim_of), arrivals + 1,
+                                            plan.elim_wgs, plan.nr),
+                 "eliminate and columns (batch)");
+        FOBQ_TRY(launch_batch_emit(s, dl, n_layers, max_weights), "emit (batch)");
+        int* hflags = reinterpret_cast<int*>(hb + desc_bytes);      // behind the descriptors
+        FOBQ_TRY(hipMemcpyAsync(hflags, flags, (size_t)n_layers * 4 * sizeof(int), hipMemcpyDeviceToHost, s), "read status flags");
         FOBQ_TRY(hipStreamSynchronize(s), "synchronize");
         for (int l = 0; l < n_layers; ++l) {
+            if (hflags[4 * l + FLAG_STALLED])
+                return set_err(ctx, FOBQ_EHIP, "layer %d: a factorization launch stopped making progress and was given up", l);
             if (hflags[4 * l + FLAG_NOTPD_H])
                 return set_err(ctx, FOBQ_ENOTPD, "layer %d: damped Hessian is not positive definite (Cholesky pivot <= 0)", l);
             if (hflags[4 * l + FLAG_NOTPD_HINV])

@@ -1,6 +1,8 @@
 // The two factorizations of the path as ONE launch each, by dependencies between 64 x 64 tiles instead of a launch per
 // 64-column panel:
 //   flow_inverse    H_d = R^T R (R = L^T), R^-T = L^-1 and Hinv = L^-T L^-1              (Section 5, item 1)
+//   flow_eliminate  the shared-Hinv elimination with the column loop that follows it     (Eq. 8, 9, 12, Section 4.2)
+// and of several small layers at once (the *_batch kernels: the same bodies, each workgroup on one layer).
 // A factorization is a chain of T = d / 64 diagonal blocks, each a few microseconds of sequential pivots, and between
 // two of them only two tiles matter; everything else is product work that needs a fraction of the chip.  A launch per
 // panel puts the launch gap, the loads and the recomputed panel products on that chain, and makes it wait for the
@@ -11,8 +13,8 @@
 // and publishes it.  Workgroups take tiles from queues in a fixed order (a ticket each).  All the work of a launch has one
 // order in which whatever a tile waits for stands before it; each queue is a part of that order, and the workgroup that
 // walks the chain is the first to start, the next ones serve one queue each.  So the earliest unfinished tile has its
-// workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should the device stop making progress all the same, every wait gives up after
-// FLOW_MAX_POLLS looks, the launch drains and the call fails.)
+// workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should the device
+// stop making progress all the same, every wait gives up after FLOW_MAX_POLLS looks, the launch drains and the call fails.)
 //
 // Exchange between compute units.  Each XCD has its own L2, which is not coherent with the others inside a launch.
 // Everything that one workgroup hands to another during a launch goes through relaxed agent-scope atomic accesses
@@ -20,6 +22,8 @@
 // are done, and sets the tile's word after a release fence; the consumer reads the word until it is set and loads.
 // Measured: 1.85 us from the first store of a 32 KB tile to its last load on another XCD, and 16 TB/s when 256
 // workgroups read tiles this way, against 9.6 TB/s that the products want at the full matrix rate.
+#include <string.h>
+
 #include <algorithm>
 
 #include <hip/hip_ext.h>
@@ -534,10 +538,8 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
     }
 }
 
-__global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
+__device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds, int& slot)
 {
-    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
-    __shared__ int slot;
     const FlowP& f = p.f;
     const int T = f.T;
     double* tiles = lds + SWEEP_LDS;
@@ -612,6 +614,34 @@ __global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
         }
     }
     if (threadIdx.x == 0 && ld_word(f.words + FW_ABORT) != 0) *f.stalled = 1;
+}
+
+__global__ __launch_bounds__(NT, 2) void flow_inverse_kernel(FlowInverseP p)
+{
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
+    __shared__ int slot;
+    flow_inverse(p, lds, slot);
+}
+
+// Several layers in one launch: the b-th workgroup to arrive works on layer layer_of[b].  A layer's entries are consecutive
+// and the number is drawn, not the workgroup's index, so the workgroups that wait are never those of a layer whose others
+// cannot become resident.
+__device__ __forceinline__ int batch_layer(int* arrivals, const uint16_t* layer_of, int& slot)
+{
+    if (threadIdx.x == 0) slot = layer_of[min(atomicAdd(arrivals, 1), (int)gridDim.x - 1)];
+    __syncthreads();
+    const int l = __builtin_amdgcn_readfirstlane(slot);
+    __syncthreads();
+    return l;
+}
+
+__global__ __launch_bounds__(NT, 2) void flow_inverse_batch_kernel(const FlowInverseP* __restrict__ layers, const uint16_t* __restrict__ layer_of,
+                                                                   int* __restrict__ arrivals)
+{
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
+    __shared__ int slot;
+    const FlowInverseP p = layers[batch_layer(arrivals, layer_of, slot)];
+    flow_inverse(p, lds, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -809,11 +839,9 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
 }
 
 template <int NR>
-__global__ __launch_bounds__(NT, 2) void flow_eliminate_kernel(FlowElimP p)
+__device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, int& slot)
 {
     constexpr int PER = 64 / (8 * NR);
-    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
-    __shared__ int slot;
     const FlowP& f = p.f;
     const int T = f.T;
     double* tiles = lds + SWEEP_LDS;
@@ -896,6 +924,24 @@ __global__ __launch_bounds__(NT, 2) void flow_eliminate_kernel(FlowElimP p)
     if (threadIdx.x == 0 && ld_word(f.words + FW_ABORT) != 0) *f.stalled = 1;
 }
 
+template <int NR>
+__global__ __launch_bounds__(NT, 2) void flow_eliminate_kernel(FlowElimP p)
+{
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
+    __shared__ int slot;
+    flow_eliminate<NR>(p, lds, slot);
+}
+
+template <int NR>
+__global__ __launch_bounds__(NT, 2) void flow_eliminate_batch_kernel(const FlowElimP* __restrict__ layers, const uint16_t* __restrict__ layer_of,
+                                                                     int* __restrict__ arrivals)
+{
+    __shared__ __attribute__((aligned(16))) double lds[FLOW_LDS];
+    __shared__ int slot;
+    const FlowElimP p = layers[batch_layer(arrivals, layer_of, slot)];
+    flow_eliminate<NR>(p, lds, slot);
+}
+
 int64_t flow_inverse_words(int d) { return flow_words((d + NB - 1) / NB); }
 // Rows per wavefront of a part of columns (1, 2 or 4).  A part takes 7.5 / 11 / 18 us (measured), on top of which its successor
 // waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15 us
@@ -921,6 +967,11 @@ int64_t flow_eliminate_words(int d, int R)
     const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
     return flow_words((int)T) + T * NG * (1 + 8 / column_rows(R, T));
 }
+int64_t flow_eliminate_words_most(int d, int R)
+{
+    const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
+    return flow_words((int)T) + T * NG * 9;
+}
 size_t flow_tiles_bytes(int d) { const size_t T = (d + NB - 1) / NB; return T * T * TILE * sizeof(double); }
 size_t flow_gt_bytes(int d) { const size_t T = (d + NB - 1) / NB; return 2 * T * TILE * sizeof(double); }
 size_t flow_rows_bytes(int d, int R) { const size_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB; return T * NG * TILE * sizeof(double); }
@@ -928,29 +979,46 @@ size_t flow_rows_bytes(int d, int R) { const size_t T = (d + NB - 1) / NB, NG = 
 // One workgroup per compute unit at most (its LDS), no more than there are tiles to start with.
 static int flow_grid(int cus, int64_t tasks) { return (int)(1 + tasks < cus ? 1 + tasks : cus); }
 
-hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
-                               double* gt, int* words, int* notpd, int* stalled)
+static FlowInverseP inverse_params(const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles, double* gt, int* words,
+                                   int* notpd, int* stalled, int wgs)
 {
     FlowInverseP p;
     p.f.d = d;
     p.f.T = (d + NB - 1) / NB;
-    const int T = p.f.T, wgs = flow_grid(cus, 2 * (int64_t)T * T);
     // two rows of tiles in flight keep the chain fed (64 to 160 workgroups give the same times at d = 2304 .. 4608)
-    p.f.n1 = std::max(1, std::min(2 * T, wgs / 2));
+    p.f.n1 = std::max(1, std::min(2 * p.f.T, wgs / 2));
     p.f.n2 = std::max(1, wgs - 1 - p.f.n1);          // the others: queue 2 (there is no third)
     p.f.n3 = 0;
     p.f.words = words; p.f.tiles = tiles; p.f.gt = gt; p.f.notpd = notpd; p.f.stalled = stalled;
     p.H = H; p.damp = damp; p.damp_abs = damp_abs; p.Hinv = Hinv;
+    return p;
+}
+
+static FlowElimP eliminate_params(const FlowElimArgs& a)     // all but the numbers of workgroups
+{
+    FlowElimP p;
+    p.f.d = a.d;
+    p.f.T = (a.d + NB - 1) / NB;
+    p.f.words = a.words; p.f.tiles = a.tiles; p.f.gt = a.gt; p.f.notpd = a.notpd; p.f.stalled = a.stalled;
+    p.R = a.R; p.G = a.G; p.gs = a.gs; p.NG = (a.R + NB - 1) / NB;
+    p.tilesN = a.tilesN; p.vec = a.vec; p.Hu = a.Hinv; p.perm = a.perm; p.W = a.W; p.scale = a.scale; p.zero = a.zero;
+    p.maxq = (double)((1 << a.bits) - 1);
+    p.codesT = a.codesT; p.Rp = a.Rp; p.lossrow = a.lossrow; p.Wout = a.Wout; p.wt = a.wt; p.dt = a.dt; p.corr = a.corr;
+    return p;
+}
+
+hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
+                               double* gt, int* words, int* notpd, int* stalled)
+{
+    const int T = (d + NB - 1) / NB, wgs = flow_grid(cus, 2 * (int64_t)T * T);
+    const FlowInverseP p = inverse_params(H, d, damp, damp_abs, Hinv, tiles, gt, words, notpd, stalled, wgs);
     hipLaunchKernelGGL(flow_inverse_kernel, dim3(wgs), dim3(NT), 0, s, p);
     return hipGetLastError();
 }
 
 hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
 {
-    FlowElimP p;
-    p.f.d = a.d;
-    p.f.T = (a.d + NB - 1) / NB;
-    p.R = a.R; p.G = a.G; p.gs = a.gs; p.NG = (a.R + NB - 1) / NB;
+    FlowElimP p = eliminate_params(a);
     // Where the chain of the diagonal blocks bounds the launch: what keeps up with it (two rows of tiles on queue 1, which feeds
     // everything else; half as many again as there are parts in a block; the groups' sums a few blocks ahead), and no more, so
     // that other launches find compute units.  Otherwise all, in proportion to the work of the queues in rank-64 products of a
@@ -968,14 +1036,79 @@ hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
         p.f.n3 = avail - p.f.n1 - p.f.n2;
     }
     const int wgs = 1 + p.f.n1 + p.f.n2 + p.f.n3;
-    p.f.words = a.words; p.f.tiles = a.tiles; p.f.gt = a.gt; p.f.notpd = a.notpd; p.f.stalled = a.stalled;
-    p.tilesN = a.tilesN; p.vec = a.vec; p.Hu = a.Hinv; p.perm = a.perm; p.W = a.W; p.scale = a.scale; p.zero = a.zero;
-    p.maxq = (double)((1 << a.bits) - 1);
-    p.codesT = a.codesT; p.Rp = a.Rp; p.lossrow = a.lossrow; p.Wout = a.Wout; p.wt = a.wt; p.dt = a.dt; p.corr = a.corr;
     switch (nr) {
     case 1: hipLaunchKernelGGL(flow_eliminate_kernel<1>, dim3(wgs), dim3(NT), 0, s, p); break;
     case 2: hipLaunchKernelGGL(flow_eliminate_kernel<2>, dim3(wgs), dim3(NT), 0, s, p); break;
     default: hipLaunchKernelGGL(flow_eliminate_kernel<4>, dim3(wgs), dim3(NT), 0, s, p); break;
+    }
+    return hipGetLastError();
+}
+
+// ---- several small layers (fobq_quantize_layers_batched) ----------------------------------------------------------
+// A layer of at most 4 blocks is bound by its chain (about 18 us a block in the inverse, 15 to 20 in the elimination); the
+// layers' chains run side by side, and the launch ends when the device has worked off the parts of the longest ones.  20
+// layers of 64 .. 1024 rows and 64 .. 256 columns: inverse 75 us (one workgroup per layer, a panel at a time: 311),
+// elimination with columns 169 us (191 + 311 before, in launches of their own); the call 398 us, 1033 before.
+static_assert(sizeof(FlowInverseP) <= FLOW_DESC_BYTES && sizeof(FlowElimP) <= FLOW_DESC_BYTES, "descriptor size");
+constexpr int BATCH_INVERSE_WGS = 8;      // a layer of 4 blocks: the chain, and 25 tiles of R, X and Hinv
+
+int flow_batch_most_wgs(int cus, int n) { return cus + n * (BATCH_INVERSE_WGS + 8); }
+
+void flow_batch_plan(int cus, int n, const FlowElimArgs* a, const double* const* H, double damp, double damp_abs, int* const* words, void* inv_desc,
+                     void* elim_desc, uint16_t* inv_of, uint16_t* elim_of, int* const* notpd_h, FlowBatchPlan* plan)
+{
+    // Rows per wavefront for all layers: the longest chains against twice the pure work over the device (see column_rows).
+    const double cost[3] = {7.5, 11.0, 18.0};
+    double least = 0.0, total = 0.0;
+    plan->nr = 1;
+    for (int i = 0; i < 3; ++i) {
+        double chains = 0.0, work = 0.0;
+        for (int l = 0; l < n; ++l) {
+            const double T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB;
+            chains = std::max(chains, T * std::max(15.3, cost[i] + 2.5));
+            work += T * NG * (8 >> i) * cost[i] * 2.0 / (cus - 1);
+        }
+        const double time = std::max(chains, work);
+        if (i == 0 || time < least) { least = time; plan->nr = 1 << i; }
+    }
+    int fixed = 0;
+    for (int l = 0; l < n; ++l) {
+        const int T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB;
+        total += (double)T * NG;
+        fixed += 1 + std::min(T, 4) + std::min(NG, 4);
+    }
+    // the device's workgroups, less those that every layer needs, in proportion to the layers' blocks of rows and columns
+    const int budget = std::max(cus - fixed, n);
+    plan->inv_wgs = plan->elim_wgs = 0;
+    for (int l = 0; l < n; ++l) {
+        const int T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB, parts = NG * (8 / plan->nr);
+        const int wi = std::min(1 + 2 * T * T, BATCH_INVERSE_WGS);
+        const FlowInverseP ip = inverse_params(H[l], a[l].d, damp, damp_abs, const_cast<double*>(a[l].Hinv), a[l].tiles, a[l].gt, words[l], notpd_h[l],
+                                               a[l].stalled, wi);
+        memcpy(static_cast<unsigned char*>(inv_desc) + (size_t)l * sizeof(FlowInverseP), &ip, sizeof ip);
+        for (int w = 0; w < wi; ++w) inv_of[plan->inv_wgs++] = (uint16_t)l;
+        FlowElimP ep = eliminate_params(a[l]);
+        ep.f.n1 = std::min(T, 4);
+        ep.f.n2 = std::max(1, std::min(parts, (int)(budget * (double)T * NG / total)));
+        ep.f.n3 = std::min(NG, 4);
+        memcpy(static_cast<unsigned char*>(elim_desc) + (size_t)l * sizeof(FlowElimP), &ep, sizeof ep);
+        for (int w = 0; w < 1 + ep.f.n1 + ep.f.n2 + ep.f.n3; ++w) elim_of[plan->elim_wgs++] = (uint16_t)l;
+    }
+}
+
+hipError_t launch_flow_batch_inverse(hipStream_t s, const void* desc, const uint16_t* layer_of, int* arrivals, int wgs)
+{
+    hipLaunchKernelGGL(flow_inverse_batch_kernel, dim3(wgs), dim3(NT), 0, s, static_cast<const FlowInverseP*>(desc), layer_of, arrivals);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_batch_eliminate(hipStream_t s, const void* desc, const uint16_t* layer_of, int* arrivals, int wgs, int nr)
+{
+    const FlowElimP* d = static_cast<const FlowElimP*>(desc);
+    switch (nr) {
+    case 1: hipLaunchKernelGGL(flow_eliminate_batch_kernel<1>, dim3(wgs), dim3(NT), 0, s, d, layer_of, arrivals); break;
+    case 2: hipLaunchKernelGGL(flow_eliminate_batch_kernel<2>, dim3(wgs), dim3(NT), 0, s, d, layer_of, arrivals); break;
+    default: hipLaunchKernelGGL(flow_eliminate_batch_kernel<4>, dim3(wgs), dim3(NT), 0, s, d, layer_of, arrivals); break;
     }
     return hipGetLastError();
 }

@@ -155,15 +155,16 @@ namespace fobq {
 struct BatchLayer {
     const float* W; const double* H;          // inputs
     int R, d, G, gs, Rp, chunks;              // G grids per row of gs columns; Rp = R rounded up to 64; chunks = sens_chunks(R)
-    double maxq, damp, damp_abs;
+    double maxq;
     int order, kind, ascending;               // fobq_order; sort key (0 sensi, 1 err, 2 w); direction
-    double *Hd, *Linv, *T, *Hinv, *A, *U, *Un;    // d x d each
-    double *Gs, *rinv;                        // 64 x 64 and 64: diagonal-block scratch of the elimination
-    double *Wp, *DT;                          // R x d; d x Rp
+    double *Hinv;                             // d x d
+    double *tiles, *tilesN, *gt, *vec, *wt, *dt, *corr;   // scratch of the two factorization launches (see FlowElimArgs)
+    int *words; int nwords, nwords1;          // their words: nwords in all, the inverse's nwords1 first,
+                                              // last the launches' two counts of workgroups (used: layer 0's)
     uint8_t* codesT;                          // d x Rp
     double *scale, *zero;                     // R x G
     double *S, *Spart, *lossrow;              // d; chunks x d; R
-    int *perm, *invperm, *flags;              // d; d; 4 status words (not positive definite: H, running Hinv)
+    int *perm, *invperm, *flags;              // d; d; 4 status words (as FLAG_* of a single layer)
     uint8_t* codes; float *scales, *zeros, *Q; int* perm_out; double* loss;   // outputs (may be null)
 };
 constexpr int BATCH_MAX_D = 256;      // columns of a layer in a batched call (4 panels of 64)
@@ -258,6 +259,7 @@ struct FlowElimArgs {
     int *words, *notpd, *stalled;
 };
 int64_t flow_eliminate_words(int d, int R);
+int64_t flow_eliminate_words_most(int d, int R);     // however many rows a wavefront takes
 size_t flow_rows_bytes(int d, int R);
 hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a);
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
@@ -270,14 +272,21 @@ hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, d
 hipError_t eliminate_blocked(fobq_ctx* c, double* A, int d, int steps, int block, double* U, double* Un, int* flag,
                              const std::vector<hipEvent_t>* rows_ready);
 
-// batched small layers: factor.hip (batch_factor), quant.hip (the rest); grids have one dimension over the layers
-hipError_t launch_batch_inverse(hipStream_t s, const BatchLayer* layers, int n);
+// several small layers in one launch of each kind: descriptors (FLOW_DESC_BYTES each at most, packed as the kernels read them) and
+// the layer of every workgroup, for both launches
+constexpr size_t FLOW_DESC_BYTES = 320;
+struct FlowBatchPlan { int inv_wgs, elim_wgs, nr; };
+int flow_batch_most_wgs(int cus, int n);
+void flow_batch_plan(int cus, int n, const FlowElimArgs* a, const double* const* H, double damp, double damp_abs, int* const* words, void* inv_desc,
+                     void* elim_desc, uint16_t* inv_of, uint16_t* elim_of, int* const* notpd_h, FlowBatchPlan* plan);
+hipError_t launch_flow_batch_inverse(hipStream_t s, const void* desc, const uint16_t* layer_of, int* arrivals, int wgs);
+hipError_t launch_flow_batch_eliminate(hipStream_t s, const void* desc, const uint16_t* layer_of, int* arrivals, int wgs, int nr);
+
+// the rest of a batched call: quant.hip; grids have one dimension over the layers
 hipError_t launch_batch_order(hipStream_t s, const BatchLayer* layers, int n);
-hipError_t launch_batch_eliminate(hipStream_t s, const BatchLayer* layers, int n);
 hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs);
 hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks);
-hipError_t launch_batch_columns(hipStream_t s, const BatchLayer* layers, int n, int max_rows);
-hipError_t launch_batch_loss(hipStream_t s, const BatchLayer* layers, int n);
+hipError_t launch_batch_emit(hipStream_t s, const BatchLayer* layers, int n, int64_t max_weights);
 
 // per-row baseline (obq.hip)
 constexpr int OBQ_MAX_D = 4096;        // columns: a row's weights, pivot row and flags live in LDS

@@ -784,17 +784,18 @@ hipError_t launch_fill_i32(hipStream_t s, int* p, int64_t n, int v)
 }
 
 // ---------------------------------------------------------------------------
-// Batched small layers (see batch_inverse_kernel): the same stages with one grid dimension over the layers
+// Batched small layers: the same stages with one grid dimension over the layers
 // of the batch, each layer's shapes and pointers in its BatchLayer; workgroups past a layer's own extent leave.
 
-// Grid per (row, group) as grid_kernel; the first workgroup of a layer also clears its status words and
-// per-row loss terms.
+// Grid per (row, group) as grid_kernel; the first workgroup of a layer also clears its status words, the words of its
+// factorization launches and its per-row loss terms.
 __global__ __launch_bounds__(256) void batch_grid_kernel(const BatchLayer* __restrict__ layers)
 {
     const BatchLayer L = layers[blockIdx.y];
     if (blockIdx.x == 0) {
         if (threadIdx.x < 4) L.flags[threadIdx.x] = 0;
         for (int i = threadIdx.x; i < L.R; i += 256) L.lossrow[i] = 0.0;
+        for (int i = threadIdx.x; i < L.nwords; i += 256) L.words[i] = 0;
     }
     const int lane = threadIdx.x & 63;
     const int64_t pair = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -874,80 +875,34 @@ __global__ __launch_bounds__(256) void batch_order_kernel(const BatchLayer* __re
     if (L.perm_out && j < d) L.perm_out[j] = L.perm[j];
 }
 
-// The whole column loop of a small layer in one launch.  Rows never interact (Section 4.2 step 4: all rows
-// at once), and with the pivot rows complete a workgroup of 8 wavefronts owns 8 rows from the first column to
-// the last: it gathers them into processing order, then block by block runs the 64 sequential steps
-// (col_chain_role) and applies the block's deferred compensation (Eq. 9 / 11) to its own rows' later columns;
-// at the end it writes its rows' codes and dequantized weights in the original column order.
-__global__ __launch_bounds__(64 * CHAIN_WAVES) void batch_columns_kernel(const BatchLayer* __restrict__ layers)
+// Codes and dequantized weights of all layers in original column order, and the losses (as emit_kernel); blockIdx.x: 1024
+// weights of a layer
+__global__ __launch_bounds__(256) void batch_emit_kernel(const BatchLayer* __restrict__ layers)
 {
-    __shared__ double lds[2 * CB * (CB + 2)];
     const BatchLayer L = layers[blockIdx.y];
-    const int wg = blockIdx.x;
-    if (wg * CHAIN_WAVES >= L.R) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = wg * CHAIN_WAVES + wave, d = L.d;
-    const bool row_ok = row < L.R;
-    if (row_ok) {
-        for (int t = lane; t < d; t += 64) {
-            const int pt = min(max(L.perm[t], 0), d - 1);
-            L.Wp[(int64_t)row * d + t] = (double)L.W[(int64_t)row * d + pt];
-        }
-    }
-    __syncthreads();
-    ColChainP c;
-    c.Wp = L.Wp; c.R = L.R; c.d = d; c.Un = L.Un; c.U = L.U; c.scale = L.scale; c.zero = L.zero;
-    c.G = L.G; c.gs = L.gs; c.perm = L.perm; c.maxq = L.maxq; c.codesT = L.codesT; c.DT = L.DT; c.Rp = L.Rp;
-    c.lossrow = L.lossrow; c.corr_in = nullptr; c.corr_out = nullptr; c.nb_next = 0;
-    for (int o = 0; o < d; o += CB) {
-        const int nb = min(CB, d - o);
-        c.o = o; c.nb = nb;
-        col_chain_role(c, lds, wg);
-        __syncthreads();               // the chain's stores of this workgroup's rows are visible to it
-        // W[row][k] -= sum_j diff_j Un[o + j][k] for the columns k right of the block, 64 columns at a time: the
-        // block's pivot rows above those columns go through LDS once for the workgroup's 8 rows; lane j holds diff_j
-        const double dj = (row_ok && lane < nb) ? L.DT[(int64_t)(o + lane) * L.Rp + row] : 0.0;
-        double (*Us)[CB + 1] = reinterpret_cast<double (*)[CB + 1]>(lds);
-        for (int k0 = o + nb; k0 < d; k0 += CB) {
-            const int nk = min(CB, d - k0);
-#pragma unroll
-            for (int i = 0; i < CB / CHAIN_WAVES; ++i) {
-                const int j = wave + CHAIN_WAVES * i;
-                Us[j][lane] = (j < nb && lane < nk) ? L.Un[(int64_t)(o + j) * d + k0 + lane] : 0.0;
-            }
-            __syncthreads();
-            double acc = 0.0;
-#pragma unroll
-            for (int j = 0; j < CB; ++j) acc = fma(chain_readlane(dj, j), Us[j][lane], acc);
-            if (row_ok && lane < nk) L.Wp[(int64_t)row * d + k0 + lane] -= acc;
-            __syncthreads();
-        }
-    }
-    if (!row_ok) return;
-    for (int cidx = lane; cidx < d; cidx += 64) {
-        const int t = min(max(L.invperm[cidx], 0), d - 1);
-        const uint8_t code = L.codesT[(int64_t)t * L.Rp + row];
-        const int g = cidx / L.gs;
-        const double q = L.scale[(int64_t)row * L.G + g] * ((double)code - L.zero[(int64_t)row * L.G + g]);
-        if (L.codes) L.codes[(int64_t)row * d + cidx] = code;
-        if (L.Q) L.Q[(int64_t)row * d + cidx] = (float)q;
-    }
-}
-
-__global__ __launch_bounds__(256) void batch_loss_kernel(const BatchLayer* __restrict__ layers)
-{
-    __shared__ double part[256];
-    const BatchLayer L = layers[blockIdx.x];
-    if (!L.loss) return;
-    double s = 0.0;
-    for (int i = threadIdx.x; i < L.R; i += 256) s += L.lossrow[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    if (blockIdx.x == 0 && L.loss) {
+        __shared__ double part[256];
+        double s = 0.0;
+        for (int i = threadIdx.x; i < L.R; i += 256) s += L.lossrow[i];
+        part[threadIdx.x] = s;
         __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *L.loss = part[0];
     }
-    if (threadIdx.x == 0) *L.loss = part[0];
+    const int64_t all = (int64_t)L.R * L.d;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const int64_t e = (int64_t)blockIdx.x * 1024 + 256 * x + threadIdx.x;
+        if (e >= all) return;
+        const int i = (int)(e / L.d), c = (int)(e - (int64_t)i * L.d), g = c / L.gs;
+        const int t = min(max(L.invperm[c], 0), L.d - 1);
+        const uint8_t code = L.codesT[(int64_t)t * L.Rp + i];
+        if (L.codes) L.codes[e] = code;
+        if (L.Q) L.Q[e] = (float)(L.scale[(int64_t)i * L.G + g] * ((double)code - L.zero[(int64_t)i * L.G + g]));
+    }
 }
 
 hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs)
@@ -968,16 +923,9 @@ hipError_t launch_batch_order(hipStream_t s, const BatchLayer* layers, int n)
     return hipGetLastError();
 }
 
-hipError_t launch_batch_columns(hipStream_t s, const BatchLayer* layers, int n, int max_rows)
+hipError_t launch_batch_emit(hipStream_t s, const BatchLayer* layers, int n, int64_t max_weights)
 {
-    hipLaunchKernelGGL(batch_columns_kernel, dim3((max_rows + CHAIN_WAVES - 1) / CHAIN_WAVES, n), dim3(64 * CHAIN_WAVES), 0, s,
-                       layers);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_loss(hipStream_t s, const BatchLayer* layers, int n)
-{
-    hipLaunchKernelGGL(batch_loss_kernel, dim3(n), dim3(256), 0, s, layers);
+    hipLaunchKernelGGL(batch_emit_kernel, dim3((unsigned)((max_weights + 1023) / 1024), n), dim3(256), 0, s, layers);
     return hipGetLastError();
 }
 

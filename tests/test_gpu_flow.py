@@ -82,3 +82,20 @@ def test_elimination_and_columns_match_the_general_form(fobq, r, d, group):
         for _ in range(3):
             again = ctx.quantize_layer(W, H, bits=4, group=group)
             assert torch.equal(again.codes, got.codes) and torch.equal(again.loss, got.loss)
+
+
+# one layer, one to four blocks, ragged sizes, more workgroups than the GPU holds, many rows (several rows per wavefront):
+# layers that share the launches against the same layers one by one; sums in the same order, so the bits are the same
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(40, 63), (64, 64), (3, 65), (130, 129), (9, 256)], [(17 + i % 50, 1 + i) for i in range(256)],
+                                    [(3000, 250), (1, 2), (5000, 100)]])
+def test_batched_layers_match_single_layers(fobq, shapes):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(shapes))
+    Hs = [_spd(d, 11 + d) for _, d in shapes]
+    Ws = [torch.randn((r, d), generator=g, device="cuda") * (2.0 / d) ** 0.5 for r, d in shapes]
+    with fobq.Ctx(0) as ctx:
+        want = [ctx.quantize_layer(W, H, bits=3) for W, H in zip(Ws, Hs)]
+        for _ in range(3):
+            for o, w in zip(ctx.quantize_layers_batched(Ws, Hs, bits=3), want):
+                assert torch.equal(o.perm, w.perm) and torch.equal(o.codes, w.codes) and torch.equal(o.Q, w.Q)
+                assert torch.allclose(o.loss, w.loss, rtol=1e-11)
