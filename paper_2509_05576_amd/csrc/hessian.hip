@@ -139,53 +139,93 @@ hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, i
     return hipGetLastError();
 }
 
-// Tile edge XT: 128 (each of the 4 wavefronts owns 64 x 64 = 4 x 4 MFMA tiles) or, for small d where
-// 128-wide tiles are mostly padding, 64 (32 x 32 = 2 x 2 MFMA tiles per wavefront; twice the operand
-// traffic and conversions per MFMA, but up to 4x less padding).
+// Tile edge XT: 128 (each of the 4 wavefronts owns 64 x 64 = 4 x 4 MFMA tiles); 96 (48 x 48 = 3 x 3) or 64 (32 x 32 =
+// 2 x 2; twice the operand traffic and conversions per MFMA) where 128-wide tiles are mostly padding; 160 for a d that a
+// single tile holds, which is a diagonal one: 8 wavefronts share the 55 MFMA tiles of its lower triangle and X is read once.
 constexpr int XK = 32;           // calibration columns per LDS stage
 constexpr int XLD = XK + 4;      // fp32 row stride in LDS: 16B-aligned rows, conflict-free 16B fragment reads
-constexpr int xxt_wgs(int xt) { return xt == 128 ? 512 : 1024; }   // persistent workgroups: 2 or 4 per compute unit
-
-// 64-wide tiles when they cut the padded area (tiles on or below the diagonal) by more than the ~20 % that
-// the smaller tile costs in matrix-pipe efficiency.
-static int xxt_tile(int d)
-{
-    const int64_t n128 = (d + 127) / 128, n64 = (d + 63) / 64;
-    const int64_t a128 = n128 * (n128 + 1) / 2 * 128 * 128, a64 = n64 * (n64 + 1) / 2 * 64 * 64;
-    return a64 * 6 < a128 * 5 ? 64 : 128;
-}
+constexpr int xxt_waves(int xt) { return xt == 160 ? 8 : 4; }
+constexpr int xxt_wgs(int xt) { return xt == 64 ? 1024 : xt == 160 ? 256 : 512; }   // persistent workgroups: 4, 1 or 2 per compute unit
 
 // Price of one chunk of a diagonal tile in units of 1/16 of another tile's chunk.  A 128 x 128 diagonal tile
 // is 8 x 8 MFMA tiles of which the 36 on and below its diagonal are needed: 9 per wavefront (diag_mma), and one
 // operand panel instead of two.  By MFMA count that is 9/16; the loads, LDS stores and barriers per chunk stay,
 // and the ranges come out equally long in time at 10/16 (plain loader) and 12/16 (convolution loader: more
-// address arithmetic per chunk) -- measured: with 9 the workgroups on the diagonal tiles finish last.
+// address arithmetic per chunk) -- measured: with 9 the workgroups on the diagonal tiles finish last.  A 96 x 96
+// diagonal tile has 6 per wavefront of the 9 of a full one.
 // A 64 x 64 tile has 4 x 4 MFMA tiles, 10 needed: no split over 4 wavefronts beats the 4 each of the full tile.
-constexpr int XXT_WD_PLAIN = 10, XXT_WD_CONV = 12;
-constexpr int xxt_diag_cost(int xt, bool conv) { return xt == 128 ? (conv ? XXT_WD_CONV : XXT_WD_PLAIN) : 16; }
-constexpr int xxt_diag_cost_min(int xt) { return xt == 128 ? (XXT_WD_CONV < XXT_WD_PLAIN ? XXT_WD_CONV : XXT_WD_PLAIN) : 16; }
+constexpr int xxt_diag_cost(int xt, bool conv) { return xt == 128 ? (conv ? 12 : 10) : xt == 96 ? (conv ? 13 : 12) : 16; }
+constexpr int xxt_diag_cost_min(int xt) { return xxt_diag_cost(xt, false); }
 
-// One group of 16 calibration columns of a diagonal 128 x 128 tile for wavefront W (0..3): the MFMA tiles
-// (W, 0..W) and (7 - W, 0..7 - W) of the 8 x 8 grid -- rows W and 7 - W of its lower triangle, 9 tiles for
-// every W.  acc[0..W] are row W's, acc[W+1..8] row 7 - W's.  Both operands come from the one panel At.
-template <int W, class F>
-__device__ __forceinline__ void diag_mma(const float (*At)[XLD], int g, int fr, int fk, d4 (&acc)[9], F after_step)
+// Tile edge for d columns, by the MFMA tiles per chunk that each choice spends (a diagonal tile by its price), over the
+// part of the matrix rate that it reaches on long inputs: 64: 0.73, 96: 0.66, 128: 0.92, 160: 0.60.  d = 147 with 401408
+// columns: 367 us with tiles of 64, 244 with one of 160; d = 288 with 409600: 850 with 64, 722 with 96.
+static int xxt_tile(int d)
 {
-    constexpr int RS = W, RL = 7 - W;
-    float4 fb[RL + 1];
+    auto cost = [&](int xt) {
+        const int64_t n = (d + xt - 1) / xt, mt = xt / 16, full = mt * mt;
+        return xt == 160 ? (n == 1 ? 56.0 : 1e30) : (double)(n * full * xxt_diag_cost(xt, true) / 16 + n * (n - 1) / 2 * full);
+    };
+    const int64_t n128 = (d + 127) / 128, n64 = (d + 63) / 64;
+    const int64_t a128 = n128 * (n128 + 1) / 2 * 128 * 128, a64 = n64 * (n64 + 1) / 2 * 64 * 64;
+    const int base = a64 * 6 < a128 * 5 ? 64 : 128;
+    if (d <= 128) return base;               // few products: a tile is cut into so many pieces that their sums weigh more
+    const double own = cost(base) / (base == 64 ? 0.73 : 0.92);
+    if (cost(160) / 0.60 < own) return 160;
+    return cost(96) / 0.66 < 0.95 * own ? 96 : base;
+}
+
+// The MFMA tiles on and below the diagonal of a B x B grid in the order in which they are dealt to the wavefronts, K
+// consecutive ones each: rows 0, B - 1, 1, B - 2, ...  (B = 8, K = 9: rows w and 7 - w for wavefront w).
+template <int B>
+struct TriOrder {
+    signed char r[B * (B + 1) / 2], c[B * (B + 1) / 2];
+    constexpr TriOrder() : r(), c()
+    {
+        int t = 0;
+        for (int x = 0; x < B; ++x) {
+            const int row = x % 2 == 0 ? x / 2 : B - 1 - x / 2;
+            for (int col = 0; col <= row; ++col, ++t) { r[t] = (signed char)row; c[t] = (signed char)col; }
+        }
+    }
+    constexpr bool needs(int t0, int t1, int row) const      // fragment `row` is an operand of the tiles t0 .. t1 - 1
+    {
+        for (int t = t0; t < t1 && t < B * (B + 1) / 2; ++t)
+            if (r[t] == row || c[t] == row) return true;
+        return false;
+    }
+};
+
+// the place of tile t in that order (two consecutive rows from an even x on have B + 1 tiles, the first of them x / 2 + 1)
+template <int B>
+__device__ __forceinline__ bool tri_place(int t, int& r, int& c)
+{
+    const int pair = t / (B + 1), u = t - pair * (B + 1);
+    const bool second = u > pair;
+    r = second ? B - 1 - pair : pair;
+    c = second ? u - pair - 1 : u;
+    return t < B * (B + 1) / 2;
+}
+
+// One group of 16 calibration columns of a diagonal tile for wavefront W: its K MFMA tiles in TriOrder's order.  Both
+// operands come from the one panel At.
+template <int W, int B, int K, class F>
+__device__ __forceinline__ void diag_mma(const float (*At)[XLD], int g, int fr, int fk, d4 (&acc)[K], F after_step)
+{
+    constexpr TriOrder<B> o;
+    constexpr int T0 = W * K, T1 = T0 + K < B * (B + 1) / 2 ? T0 + K : B * (B + 1) / 2;
+    float4 f[B];
 #pragma unroll
-    for (int j = 0; j <= RL; ++j) fb[j] = *reinterpret_cast<const float4*>(&At[j * 16 + fr][g * 16 + fk]);
+    for (int j = 0; j < B; ++j)
+        if (o.needs(T0, T1, j)) f[j] = *reinterpret_cast<const float4*>(&At[j * 16 + fr][g * 16 + fk]);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-        double b[RL + 1];
+        double b[B];
 #pragma unroll
-        for (int j = 0; j <= RL; ++j)
-            b[j] = (double)(ks == 0 ? fb[j].x : ks == 1 ? fb[j].y : ks == 2 ? fb[j].z : fb[j].w);
+        for (int j = 0; j < B; ++j)
+            if (o.needs(T0, T1, j)) b[j] = (double)(ks == 0 ? f[j].x : ks == 1 ? f[j].y : ks == 2 ? f[j].z : f[j].w);
 #pragma unroll
-        for (int j = 0; j <= RS; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[RS], b[j], acc[j], 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j <= RL; ++j)
-            acc[RS + 1 + j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[RL], b[j], acc[RS + 1 + j], 0, 0, 0);
+        for (int t = T0; t < T1; ++t) acc[t - T0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[o.r[t]], b[o.c[t]], acc[t - T0], 0, 0, 0);
         after_step(ks);     // the convolution loader's share of this k-step
     }
 }
@@ -210,21 +250,27 @@ __device__ __forceinline__ void tile_decode(int t, int nt, int& I, int& J)
 // MODE 0: X rows are 16-byte aligned (ld % 4 == 0, base aligned) -> float4 loads.
 // MODE 1: any ld / alignment.  MODE 2: X = feature maps, n = images * ho * wo (convolution mode).
 template <int MODE, int XT>
-__global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float* __restrict__ X, int64_t ld, int d, int64_t n,
+__global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kernel(const float* __restrict__ X, int64_t ld, int d, int64_t n,
                                                      double* __restrict__ Hpart, int chunks, int64_t range_cost,
                                                      int64_t total_items, int classes, int splits, ConvP cp)
 {
     constexpr bool FAST = MODE == 0;
     constexpr bool CONV = MODE == 2;
-    constexpr int RG = XT / 32;       // groups of 32 rows per operand tile (plain loader: one float4 per group)
+    constexpr int NW = xxt_waves(XT);
+    constexpr int RW = 8 * NW;        // rows per group of the plain loader (one float4 per row and 8 threads)
+    constexpr int RG = (XT + RW - 1) / RW;
+    constexpr int PX = XK / NW;       // pixels per wavefront and chunk (convolution loader)
+    constexpr bool SINGLE = XT == 160;   // the one tile is a diagonal one
+    constexpr bool LOWER = XT != 64;  // of a diagonal tile only the lower triangle is formed, from one panel
     constexpr int WT = XT / 2;        // edge of a wavefront's part of the tile
-    constexpr int MT = WT / 16;       // MFMA tiles per edge of that part
+    constexpr int MT = SINGLE ? 1 : WT / 16;       // MFMA tiles per edge of that part
+    constexpr int TB = XT / 16, TK = (TB * (TB + 1) / 2 + NW - 1) / NW;   // diagonal tile: MFMA tiles per edge, per wavefront
     __shared__ float As[2][XT][XLD];
-    __shared__ float Bs[2][XT][XLD];
+    __shared__ float Bs[2][SINGLE ? 1 : XT][XLD];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int lr = tid >> 3;          // 0..31: row within a group of 32 rows
+    const int lr = tid >> 3;          // row within a group of RW rows
     const int lk = (tid & 7) * 4;     // 0..28: first of 4 consecutive calibration columns
     const int fr = lane & 15;         // fragment row
     const int fk = (lane >> 4) * 4;   // fragment: 4 consecutive columns, one per k-step (the sum over k is order-free)
@@ -280,7 +326,7 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
         const int len = c_end - c_begin;
         const bool diag = tile < nt;
         const int64_t per_wg = max((int64_t)1, range_cost / (diag ? WD : 16));   // nominal range length in this tile's chunks
-        const bool load_b = !(XT == 128 && diag);     // a diagonal tile's two operand panels are one: only As is filled
+        const bool load_b = !SINGLE && !(LOWER && diag);     // a diagonal tile's two operand panels are one: only As is filled
         int rot = 0;
         if (npieces == 1) {
             const int64_t aligned = (c_begin + per_wg - 1) / per_wg * per_wg;
@@ -302,15 +348,15 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
         const int i0 = I * XT, j0 = J * XT;
 
         // plain modes: clamped row pointers (rows past d produce outputs that are never stored);
-        // thread = (row lr + 32 u, 4 consecutive columns)
+        // thread = (row lr + RW u, 4 consecutive columns)
         const float* __restrict__ arow[RG];
         const float* __restrict__ brow[RG];
-        // convolution mode: thread = (rows lane + 64 q, pixels 8 wave + j): a load covers 64
+        // convolution mode: thread = (rows lane + 64 q, pixels PX wave + j): a load covers 64
         // consecutive channels (256 contiguous bytes) of ONE pixel, so the pixel's decoding and its
         // window origin are wavefront-uniform (scalar unit).  Per tile: the offset of this thread's
         // two rows (ky, kx, channel) of each operand from the window's top-left element in the
         // padded copy.  Rows past d stand in as row d - 1.
-        constexpr int QN = XT / 64;    // rows per operand and thread in convolution mode
+        constexpr int QN = (XT + 63) / 64;    // rows per operand and thread in convolution mode (those past the tile are not stored)
         uint32_t offA[QN], offB[QN];
         if (CONV) {
 #pragma unroll
@@ -324,13 +370,14 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
         } else {
 #pragma unroll
             for (int u = 0; u < RG; ++u) {
-                arow[u] = X + (int64_t)min(i0 + lr + 32 * u, d - 1) * ld;
-                brow[u] = X + (int64_t)min(j0 + lr + 32 * u, d - 1) * ld;
+                arow[u] = X + (int64_t)min(i0 + lr + RW * u, d - 1) * ld;
+                brow[u] = X + (int64_t)min(j0 + lr + RW * u, d - 1) * ld;
             }
         }
-        float4 pa[RG], pb[RG];
-        // Convolution mode: the loads of pixel j (0..7) of chunk c for this thread's rows; called
-        // with j = 0, 1, ..., 7 in this order.  Pixel 0 is decoded in full (two divisions by
+        constexpr int PN = CONV ? QN * PX / 4 : RG;
+        float4 pa[PN], pb[PN];
+        // Convolution mode: the loads of pixel j (0..PX-1) of chunk c for this thread's rows; called
+        // with j = 0, 1, ..., PX - 1 in this order.  Pixel 0 is decoded in full (two divisions by
         // invariant integers), the others by stepping (image, y, x) one pixel on; a pixel past the
         // last one takes the all-zero image.  All of it is wavefront-uniform, i.e. scalar-unit
         // work with no branch: arithmetic on the vector unit takes cycles from the fp64 matrix
@@ -339,7 +386,7 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
         auto gload_px = [&](int c, int j) {
             float* fa = reinterpret_cast<float*>(pa);
             float* fb = reinterpret_cast<float*>(pb);
-            const int p = c * XK + 8 * wave_s + j;               // < 2^31 (checked by the caller)
+            const int p = c * XK + PX * wave_s + j;              // < 2^31 (checked by the caller)
             const bool pv = p < (int)n;
             if (j == 0) {
                 const uint32_t pc = (uint32_t)min(p, (int)n - 1);
@@ -362,14 +409,14 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
             const float* __restrict__ win = X + (pv ? origin : cp.zero_origin);
 #pragma unroll
             for (int q = 0; q < QN; ++q) {
-                fa[q * 8 + j] = win[offA[q]];
-                if (load_b) fb[q * 8 + j] = win[offB[q]];
+                fa[q * PX + j] = win[offA[q]];
+                if (load_b) fb[q * PX + j] = win[offB[q]];
             }
         };
         auto gload = [&](int c) {
             if (CONV) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) gload_px(c, j);
+                for (int j = 0; j < PX; ++j) gload_px(c, j);
                 return;
             }
             const int64_t k = (int64_t)c * XK + lk;
@@ -394,38 +441,38 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
         };
         auto sstore = [&](int buf) {
             if (CONV) {
-                // 8 consecutive pixels of a row: two 16-byte stores per row
+                // PX consecutive pixels of a row: 16 bytes per store
 #pragma unroll
-                for (int q = 0; q < QN; ++q) {
-                    *reinterpret_cast<float4*>(&As[buf][lane + 64 * q][8 * wave]) = pa[2 * q];
-                    *reinterpret_cast<float4*>(&As[buf][lane + 64 * q][8 * wave + 4]) = pa[2 * q + 1];
-                    if (load_b) {
-                        *reinterpret_cast<float4*>(&Bs[buf][lane + 64 * q][8 * wave]) = pb[2 * q];
-                        *reinterpret_cast<float4*>(&Bs[buf][lane + 64 * q][8 * wave + 4]) = pb[2 * q + 1];
-                    }
-                }
+                for (int q = 0; q < QN; ++q)
+                    if (64 * q + 64 <= XT || lane + 64 * q < XT)
+#pragma unroll
+                        for (int x = 0; x < PX / 4; ++x) {
+                            *reinterpret_cast<float4*>(&As[buf][lane + 64 * q][PX * wave + 4 * x]) = pa[q * PX / 4 + x];
+                            if (load_b) *reinterpret_cast<float4*>(&Bs[buf][lane + 64 * q][PX * wave + 4 * x]) = pb[q * PX / 4 + x];
+                        }
                 return;
             }
 #pragma unroll
-            for (int u = 0; u < RG; ++u) {
-                *reinterpret_cast<float4*>(&As[buf][lr + 32 * u][lk]) = pa[u];
-                if (load_b) *reinterpret_cast<float4*>(&Bs[buf][lr + 32 * u][lk]) = pb[u];
-            }
+            for (int u = 0; u < RG; ++u)
+                if (RW * u + RW <= XT || lr + RW * u < XT) {
+                    *reinterpret_cast<float4*>(&As[buf][lr + RW * u][lk]) = pa[u];
+                    if (load_b) *reinterpret_cast<float4*>(&Bs[buf][lr + RW * u][lk]) = pb[u];
+                }
         };
 
         double* __restrict__ out = Hpart + (int64_t)piece * d * d;
-        // The pipeline over the piece's chunks; DG: diagonal tile of XT = 128 (only the MFMA tiles on and
-        // below its diagonal are formed, 9 per wavefront instead of 16).
+        // The pipeline over the piece's chunks; DG: diagonal tile of which only the MFMA tiles on and below
+        // its diagonal are formed (XT = 128: 9 per wavefront instead of 16).
         auto run_piece = [&](auto dg_tag) {
             constexpr bool DG = decltype(dg_tag)::value;
             d4 acc[MT][MT];
-            d4 accd[DG ? 9 : 1];
+            d4 accd[DG ? TK : 1];
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
                 for (int j = 0; j < MT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int i = 0; i < (DG ? 9 : 1); ++i) accd[i] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int i = 0; i < (DG ? TK : 1); ++i) accd[i] = d4{0.0, 0.0, 0.0, 0.0};
 
             __syncthreads();              // LDS free (previous tile's last stage consumed)
             gload(chunk_at(0));
@@ -442,11 +489,17 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
 #pragma unroll
                 for (int g = 0; g < XK / 16; ++g) {
                     if constexpr (DG) {
-                        auto after = [&](int ks) { if (CONV) gload_px(cn, g * 4 + ks); };
-                        if (wave_s == 0) diag_mma<0>(As[cur], g, fr, fk, accd, after);
-                        else if (wave_s == 1) diag_mma<1>(As[cur], g, fr, fk, accd, after);
-                        else if (wave_s == 2) diag_mma<2>(As[cur], g, fr, fk, accd, after);
-                        else diag_mma<3>(As[cur], g, fr, fk, accd, after);
+                        auto after = [&](int ks) { if (CONV && g * 4 + ks < PX) gload_px(cn, g * 4 + ks); };
+                        if (wave_s == 0) diag_mma<0, TB, TK>(As[cur], g, fr, fk, accd, after);
+                        else if (wave_s == 1) diag_mma<1, TB, TK>(As[cur], g, fr, fk, accd, after);
+                        else if (wave_s == 2) diag_mma<2, TB, TK>(As[cur], g, fr, fk, accd, after);
+                        else if (NW == 4 || wave_s == 3) diag_mma<3, TB, TK>(As[cur], g, fr, fk, accd, after);
+                        else if constexpr (NW == 8) {
+                            if (wave_s == 4) diag_mma<4, TB, TK>(As[cur], g, fr, fk, accd, after);
+                            else if (wave_s == 5) diag_mma<5, TB, TK>(As[cur], g, fr, fk, accd, after);
+                            else if (wave_s == 6) diag_mma<6, TB, TK>(As[cur], g, fr, fk, accd, after);
+                            else diag_mma<7, TB, TK>(As[cur], g, fr, fk, accd, after);
+                        }
                     } else {
                         float4 fa[MT], fb[MT];
 #pragma unroll
@@ -469,7 +522,7 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
 #pragma unroll
                                 for (int j = 0; j < MT; ++j)
                                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-                            if (CONV) gload_px(cn, g * 4 + ks);
+                            if (CONV && g * 4 + ks < PX) gload_px(cn, g * 4 + ks);
                         }
                     }
                 }
@@ -479,16 +532,16 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
             }
 
             if constexpr (DG) {
-                // wavefront w holds the MFMA tiles (w, 0..w) and (7 - w, 0..7 - w): see diag_mma
+                // wavefront w holds K consecutive MFMA tiles of the triangle: see TriOrder
 #pragma unroll
-                for (int q = 0; q < 9; ++q) {
-                    const int sr = q <= wave_s ? wave_s : 7 - wave_s;
-                    const int sc = q <= wave_s ? q : q - wave_s - 1;
+                for (int q = 0; q < TK; ++q) {
+                    int sr, sc;
+                    const bool mine = tri_place<TB>(wave_s * TK + q, sr, sc);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int gr = i0 + sr * 16 + 4 * v + (lane >> 4);
                         const int gc = j0 + sc * 16 + (lane & 15);
-                        if (gr < d && gc < d) out[(int64_t)gr * d + gc] += accd[q][v];
+                        if (mine && gr < d && gc < d) out[(int64_t)gr * d + gc] += accd[q][v];
                     }
                 }
             } else {
@@ -504,7 +557,9 @@ __global__ __launch_bounds__(256, XT == 128 ? 2 : 4) void xxt_kernel(const float
                         }
             }
         };
-        if constexpr (XT == 128) {
+        if constexpr (SINGLE) {
+            run_piece(std::true_type{});
+        } else if constexpr (LOWER) {
             if (diag) run_piece(std::true_type{});
             else run_piece(std::false_type{});
         } else {
@@ -590,12 +645,16 @@ static void xxt_launch(hipStream_t s, const XxtPlan& pl, const float* X, int64_t
     const int64_t tile_cost = 16 * (int64_t)pl.chunks;
     int classes = (int)((tile_cost + pl.range_cost / 2) / pl.range_cost);
     classes = classes < 1 ? 1 : (classes > pl.wgs ? pl.wgs : classes);
-    if (pl.xt == 128)
-        hipExtLaunchKernelGGL((xxt_kernel<MODE, 128>), dim3(pl.wgs), dim3(256), 0, s, ev.start, ev.stop, 0, X, ld, d, n,
-                              Hpart, pl.chunks, pl.range_cost, pl.items, classes, splits, cp);
-    else
-        hipExtLaunchKernelGGL((xxt_kernel<MODE, 64>), dim3(pl.wgs), dim3(256), 0, s, ev.start, ev.stop, 0, X, ld, d, n,
-                              Hpart, pl.chunks, pl.range_cost, pl.items, classes, splits, cp);
+    auto launch = [&](auto kernel) {
+        hipExtLaunchKernelGGL(kernel, dim3(pl.wgs), dim3(64 * xxt_waves(pl.xt)), 0, s, ev.start, ev.stop, 0, X, ld, d, n, Hpart,
+                              pl.chunks, pl.range_cost, pl.items, classes, splits, cp);
+    };
+    switch (pl.xt) {
+    case 64: launch(xxt_kernel<MODE, 64>); break;
+    case 96: launch(xxt_kernel<MODE, 96>); break;
+    case 128: launch(xxt_kernel<MODE, 128>); break;
+    default: launch(xxt_kernel<MODE, 160>); break;
+    }
 }
 
 hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits,
