@@ -447,12 +447,14 @@ int fobq_hessian_begin(fobq_ctx* ctx, int64_t d_col)
     return FOBQ_OK;
 }
 
-// clears the slabs of Hpart that a launch over n calibration columns can touch for the first time
-static int clear_slabs(fobq_ctx* ctx, int64_t n, bool conv, bool i8 = false)
+// clears the slabs of Hpart that a launch over n calibration columns can touch for the first time; *fresh: the fp64 kernel's
+// first launch needs no clearing, but the number of its slabs (h_zeroed once it is enqueued)
+static int clear_slabs(fobq_ctx* ctx, int64_t n, bool conv, bool i8, int* fresh)
 {
     const int need = i8 ? xxt_i8_slabs_touched((int)ctx->h_d, n, ctx->h_splits)
                         : xxt_slabs_touched((int)ctx->h_d, n, ctx->h_splits, conv);
-    if (need > ctx->h_zeroed) {
+    *fresh = !i8 && ctx->h_zeroed == 0 ? need : 0;
+    if (need > ctx->h_zeroed && *fresh == 0) {
         FOBQ_TRY(launch_clear_slabs(ctx->stream, ctx->Hpart.as<double>(), (int)ctx->h_d, ctx->h_zeroed, need - ctx->h_zeroed),
                  "clear Hessian accumulator");
         ctx->h_zeroed = need;
@@ -499,8 +501,9 @@ int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld
         const int grc = grow_i8_slabs(ctx, n < blk ? n : blk);
         if (grc) return grc;
     }
-    int rc = clear_slabs(ctx, n < blk ? n : blk, false, i8);
-    if (!rc && n > blk && n % blk) rc = clear_slabs(ctx, n % blk, false, i8);    // the shorter last launch
+    int fresh = 0;
+    int rc = clear_slabs(ctx, n < blk ? n : blk, false, i8, &fresh);
+    if (!rc && n > blk && n % blk) rc = clear_slabs(ctx, n % blk, false, i8, &fresh);    // the shorter last launch
     if (rc) return rc;
     ctx->h_conv_c = -1;
     if (i8) {
@@ -522,8 +525,9 @@ int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld
                                    ctx->Hpart.as<double>(), ctx->h_splits, stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (int8)");
         }
     } else {
-        FOBQ_TRY(launch_xxt(ctx->stream, X, ld, d, n, ctx->Hpart.as<double>(), ctx->h_splits,
+        FOBQ_TRY(launch_xxt(ctx->stream, X, ld, d, n, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
                             stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt");
+        if (fresh > 0) ctx->h_zeroed = fresh;
     }
     ctx->h_n += n;
     return FOBQ_OK;
@@ -586,6 +590,7 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         const int grc = grow_i8_slabs(ctx, npix < blk ? npix : blk, rect);
         if (grc) return grc;
     }
+    int fresh = 0;
     if (offsets) {
         FOBQ_TRY(ctx->hcorr.ensure((size_t)d * d * sizeof(double)), "workspace corrections");
         FOBQ_TRY(ctx->strips.ensure(offset_strips_bytes(tab.njobs, (int)c)), "workspace strips");
@@ -605,8 +610,8 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         if (!rc && npix > blk && npix % blk) rc = clear_rect(npix % blk);
         if (rc) return rc;
     } else {
-        int rc = clear_slabs(ctx, npix < blk ? npix : blk, true, i8);
-        if (!rc && npix > blk && npix % blk) rc = clear_slabs(ctx, npix % blk, true, i8);    // the shorter last launch
+        int rc = clear_slabs(ctx, npix < blk ? npix : blk, true, i8, &fresh);
+        if (!rc && npix > blk && npix % blk) rc = clear_slabs(ctx, npix % blk, true, i8, &fresh);    // the shorter last launch
         if (rc) return rc;
     }
     ctx->h_conv_c = (int)c;
@@ -648,8 +653,9 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         }
     } else {
         FOBQ_TRY(launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
-                                 (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits,
+                                 (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
                                  stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
+        if (fresh > 0) ctx->h_zeroed = fresh;
     }
     ctx->h_n += npix;
     return FOBQ_OK;

@@ -185,15 +185,16 @@ struct StageScope {
     ~StageScope();
 };
 
-// hessian.hip
-hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits,
+// hessian.hip; fresh: 0, or on the first launch of an accumulation the slabs that it then has (xxt_slabs_touched), which need
+// not hold anything before
+hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits, int fresh,
                       LaunchEvents ev = LaunchEvents());
 int xxt_pick_splits(int d);
 int xxt_slabs_touched(int d, int64_t n, int splits, bool conv);
 hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, int count);
 hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took);
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
-                           int ho, int wo, int64_t npix, double* Hpart, int splits,
+                           int ho, int wo, int64_t npix, double* Hpart, int splits, int fresh,
                            LaunchEvents ev = LaunchEvents());
 hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H,
                                    int conv_c, int conv_kk, const int* poison);   // *poison != 0: H = NaN

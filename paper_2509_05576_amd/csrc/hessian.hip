@@ -12,8 +12,8 @@
 // all ranges equally expensive (an item of a diagonal tile is priced below one of
 // another tile), so every workgroup does the same amount of work whatever d and n are.  A
 // range can cross tile boundaries; the part of a tile done by one workgroup is a
-// "piece".  Piece p of a tile is added into slab p of Hpart (XXT_SLABS slabs of
-// d x d), and exactly one workgroup owns a given (tile, piece) in a launch, so
+// "piece".  Piece p of a tile is added into slab p of Hpart (d x d each; the first
+// launch of an accumulation stores it there), and exactly one workgroup owns a given (tile, piece) in a launch, so
 // the sums do not depend on the order in which workgroups finish.
 //
 // Convolution mode: the same kernel with a loader that reads the unfolded input of a k x k
@@ -252,7 +252,7 @@ __device__ __forceinline__ void tile_decode(int t, int nt, int& I, int& J)
 template <int MODE, int XT>
 __global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kernel(const float* __restrict__ X, int64_t ld, int d, int64_t n,
                                                      double* __restrict__ Hpart, int chunks, int64_t range_cost,
-                                                     int64_t total_items, int classes, int splits, ConvP cp)
+                                                     int64_t total_items, int classes, int splits, int fresh, ConvP cp)
 {
     constexpr bool FAST = MODE == 0;
     constexpr bool CONV = MODE == 2;
@@ -531,31 +531,37 @@ __global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kern
                 cur ^= 1;
             }
 
-            if constexpr (DG) {
-                // wavefront w holds K consecutive MFMA tiles of the triangle: see TriOrder
+            auto flush = [&](auto add_tag) {
+                constexpr bool ADD = decltype(add_tag)::value;
+                int fl = lane;
+                asm volatile("" : "+v"(fl));       // addresses formed here, not kept over the pipeline
+                auto put = [&](int gr, int gc, double v) {
+                    if (gr >= d || gc >= d) return;
+                    double* __restrict__ o = out + (int64_t)gr * d + gc;
+                    *o = ADD ? *o + v : v;
+                };
+                if constexpr (DG) {
+                    // wavefront w holds K consecutive MFMA tiles of the triangle: see TriOrder
 #pragma unroll
-                for (int q = 0; q < TK; ++q) {
-                    int sr, sc;
-                    const bool mine = tri_place<TB>(wave_s * TK + q, sr, sc);
+                    for (int q = 0; q < TK; ++q) {
+                        int sr, sc;
+                        const bool mine = tri_place<TB>(wave_s * TK + q, sr, sc);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int gr = i0 + sr * 16 + 4 * v + (lane >> 4);
-                        const int gc = j0 + sc * 16 + (lane & 15);
-                        if (mine && gr < d && gc < d) out[(int64_t)gr * d + gc] += accd[q][v];
+                        for (int v = 0; v < 4; ++v)
+                            if (mine) put(i0 + sr * 16 + 4 * v + (fl >> 4), j0 + sc * 16 + (fl & 15), accd[q][v]);
                     }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < MT; ++j)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                put(i0 + wm * WT + i * 16 + 4 * v + (fl >> 4), j0 + wn * WT + j * 16 + (fl & 15), acc[i][j][v]);
                 }
-            } else {
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < MT; ++j)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int gr = i0 + wm * WT + i * 16 + 4 * v + (lane >> 4);
-                            const int gc = j0 + wn * WT + j * 16 + (lane & 15);
-                            if (gr < d && gc < d) out[(int64_t)gr * d + gc] += acc[i][j][v];
-                        }
-            }
+            };
+            if (fresh > 0) flush(std::false_type{});
+            else flush(std::true_type{});
         };
         if constexpr (SINGLE) {
             run_piece(std::true_type{});
@@ -564,6 +570,23 @@ __global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kern
             else run_piece(std::false_type{});
         } else {
             run_piece(std::false_type{});
+        }
+
+        // An accumulation's first launch finds nothing in its slabs and stores; where a tile has fewer pieces than the launch
+        // has slabs (fresh), its workgroups put zeros into the others in turn.  (d = 512, 50176 columns: 295 us with a launch
+        // that clears 61 slabs and the sums read and written, 260 so.)
+        if (fresh > 0) {
+            const int64_t tile_last = tile_first + chunks - 1;
+            int64_t last_range = (diag ? (tile_last + 1) * WD : diag_cost + (tile_last + 1 - diag_items) * 16) / range_cost;
+            while (item_at(last_range * range_cost) > tile_last) --last_range;
+            const int pieces = (int)(last_range - first_range) + 1;
+            for (int p = piece + pieces; p < fresh; p += pieces) {
+                double* __restrict__ rest = Hpart + (int64_t)p * d * d;
+                for (int e = tid; e < XT * XT; e += 64 * NW) {
+                    const int gr = i0 + e / XT, gc = j0 + e % XT;
+                    if (gr < d && gc < d) rest[(int64_t)gr * d + gc] = 0.0;
+                }
+            }
         }
     }
 }
@@ -639,7 +662,7 @@ hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, in
 
 template <int MODE>
 static void xxt_launch(hipStream_t s, const XxtPlan& pl, const float* X, int64_t ld, int d, int64_t n, double* Hpart,
-                       int splits, const ConvP& cp, LaunchEvents ev)
+                       int splits, int fresh, const ConvP& cp, LaunchEvents ev)
 {
     // pieces per tile (below the diagonal), rounded: the number of classes of ranges (see the kernel)
     const int64_t tile_cost = 16 * (int64_t)pl.chunks;
@@ -647,7 +670,7 @@ static void xxt_launch(hipStream_t s, const XxtPlan& pl, const float* X, int64_t
     classes = classes < 1 ? 1 : (classes > pl.wgs ? pl.wgs : classes);
     auto launch = [&](auto kernel) {
         hipExtLaunchKernelGGL(kernel, dim3(pl.wgs), dim3(64 * xxt_waves(pl.xt)), 0, s, ev.start, ev.stop, 0, X, ld, d, n, Hpart,
-                              pl.chunks, pl.range_cost, pl.items, classes, splits, cp);
+                              pl.chunks, pl.range_cost, pl.items, classes, splits, fresh, cp);
     };
     switch (pl.xt) {
     case 64: launch(xxt_kernel<MODE, 64>); break;
@@ -657,21 +680,21 @@ static void xxt_launch(hipStream_t s, const XxtPlan& pl, const float* X, int64_t
     }
 }
 
-hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits,
+hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits, int fresh,
                       LaunchEvents ev)
 {
     const XxtPlan pl = xxt_plan(d, n, splits, false);
     const bool fast = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
     ConvP none{};
-    if (fast) xxt_launch<0>(s, pl, X, ld, d, n, Hpart, splits, none, ev);
-    else      xxt_launch<1>(s, pl, X, ld, d, n, Hpart, splits, none, ev);
+    if (fast) xxt_launch<0>(s, pl, X, ld, d, n, Hpart, splits, fresh, none, ev);
+    else      xxt_launch<1>(s, pl, X, ld, d, n, Hpart, splits, fresh, none, ev);
     return hipGetLastError();
 }
 
 // Convolution mode: padded = the copy written by launch_pad_maps ((n_img + 1) x hp x wp x c),
 // d = c k^2, one calibration column per output pixel; npix = n_img * ho * wo < 2^31 - 64.
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
-                           int ho, int wo, int64_t npix, double* Hpart, int splits,
+                           int ho, int wo, int64_t npix, double* Hpart, int splits, int fresh,
                            LaunchEvents ev)
 {
     const int d = c * k * k;
@@ -683,7 +706,7 @@ hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp
     cp.div_row = fastdiv_make((uint32_t)wo);
     cp.div_c = fastdiv_make((uint32_t)c);
     cp.div_k = fastdiv_make((uint32_t)k);
-    xxt_launch<2>(s, pl, padded, 0, d, npix, Hpart, splits, cp, ev);
+    xxt_launch<2>(s, pl, padded, 0, d, npix, Hpart, splits, fresh, cp, ev);
     return hipGetLastError();
 }
 

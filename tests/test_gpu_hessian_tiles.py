@@ -53,3 +53,28 @@ def test_hessian_from_maps_at_tile_edges(ctx, n, side, c, k, stride, pad):
     X = torch.stack([M[:, y:y + stride * (o - 1) + 1:stride, x:x + stride * (o - 1) + 1:stride, :].reshape(-1, c)
                      for y in range(k) for x in range(k)], 2).reshape(n * o * o, -1)
     _close(H, X.T.contiguous())
+
+
+# the first call of an accumulation stores its sums, later ones add: a later call with more slabs than the first, with fewer,
+# and (int8 mode takes short calls in fp64) one in the integer form after an fp64 one; scratch that held another accumulation's sums before
+@pytest.mark.parametrize("d", [100, 147, 192, 288, 512, 640])
+@pytest.mark.parametrize("cuts", [[40, 20040], [20000, 20033], [1, 2, 5002, 20002]])
+def test_calls_of_one_accumulation(ctx, d, cuts):
+    import paper_2509_05576_amd as f
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    X = torch.randn((d, cuts[-1]), generator=g, device="cuda")
+    H = torch.empty((d, d), dtype=torch.float64, device="cuda")
+    ctx.hessian(1e6 * X, H_out=H)
+    for int8 in (False, True):
+        ctx.set_hessian_mode(f.HESSIAN_INT8_SLICES if int8 else f.HESSIAN_FP64)
+        f.fobq_hessian_begin(ctx.handle, d)
+        lo = 0
+        for hi in cuts:
+            f.fobq_hessian_accumulate(ctx.handle, X[:, lo:hi])
+            lo = hi
+        f.fobq_hessian_finalize(ctx.handle, H)
+        ctx.set_hessian_mode(f.HESSIAN_FP64)
+        want = (X.double() @ X.double().T.contiguous()) * (2.0 / X.shape[1])
+        scale = torch.sqrt(want.diagonal()[:, None] * want.diagonal()[None, :])
+        assert float(((H - want).abs() / scale).max()) <= (1e-12 if int8 else 1e-13)      # the integer form's bar; eps * sqrt(n)
