@@ -104,7 +104,7 @@ struct fobq_ctx {
     fobq::DevBuf i8sh;      // per-row shifts of that call
     fobq::DevBuf i8amax;    // per-channel maxima (convolution input)
     fobq::DevBuf batch_pool;    // scratch of all layers of a batched call
-    fobq::DevBuf batch_desc;    // BatchLayer[n] + status words
+    fobq::DevBuf batch_desc;    // descriptors and workgroup tables of a batched call
     void* h_batch = nullptr;    // pinned host staging for the descriptors and the status read-back
 
     fobq::DevBuf Hpart;     // h_splits x d x d fp64 partial sums of X X^T (lower tiles)

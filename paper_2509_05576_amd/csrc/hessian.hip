@@ -2,9 +2,10 @@
 //
 // xxt_kernel: fp32 X is read from HBM, staged through LDS as fp32, widened to
 // fp64 when the MFMA fragments are formed (products of two fp32 values are
-// exact in fp64), and accumulated with v_mfma_f64_16x16x4_f64.  Only the 128 x 128
-// tiles on or below the diagonal are computed, and of a diagonal tile only the
-// 16 x 16 MFMA tiles on or below its diagonal (36 of 64).
+// exact in fp64), and accumulated with v_mfma_f64_16x16x4_f64.  Only the tiles (128 x 128;
+// 96, 64 or 160 wide where that spends fewer matrix instructions) on or below the diagonal are
+// computed, and of a diagonal tile only the 16 x 16 MFMA tiles on or below its diagonal (36 of 64;
+// not at 64, see xxt_diag_cost).
 //
 // Work decomposition ("stream-K"): the work items are (tile, 32-column chunk of
 // the calibration dimension) pairs in tile-major order, diagonal tiles first; a
@@ -70,7 +71,7 @@ struct ConvP {
 // channels come in fours (VEC: c % 4 == 0, both pointers 16-byte aligned).  AMAX: the maxima |.| of every channel (bit
 // patterns) are taken on the way: the first `active` threads walk a row in steps of a multiple of c, so that a thread stays on
 // its channels; one atomic per channel and workgroup.  The 64-image 56 x 56 x 128 maps (103 MB): 85 us for a copy by elements
-// and 139 us for a second pass over it with an atomic per thread, 61 us together now.
+// and 139 us for a second pass over it with an atomic per thread, 42 us together now.
 template <bool VEC, bool AMAX>
 __global__ __launch_bounds__(256) void pad_maps_kernel(const float* __restrict__ maps, int n_img, int h, int w, int c, int pad,
                                                        float* __restrict__ out, int64_t rows, int active, unsigned* __restrict__ amax)
@@ -130,7 +131,10 @@ hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, i
     const int unit = vec ? c / 4 : c;                  // steps of a row after which the channels repeat
     const bool max_too = amax && unit <= 256;
     const int active = max_too ? unit * (256 / unit) : 256;
-    const dim3 grid((unsigned)(rows < 2048 ? rows : 2048)), block(256);
+    // the maxima cost an atomic per channel and workgroup: 2048 workgroups 61 us, 768 42 us (64 x 56 x 56 x 128; 128 x 14 x 14 x
+    // 256: 43 and 23)
+    const int64_t most = max_too ? 768 : 2048;
+    const dim3 grid((unsigned)(rows < most ? rows : most)), block(256);
     if (took) *took = max_too;
     if (vec && max_too)  hipLaunchKernelGGL((pad_maps_kernel<true, true>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
     else if (vec)        hipLaunchKernelGGL((pad_maps_kernel<true, false>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kern
     // over two tiles takes the head of the later tile (chunks 0 ...) before the tail of the earlier
     // one.  The order of the sum over chunks is free; it stays fixed, so results are reproducible.
     // Items are laid out with the nt diagonal tiles first, then the tiles below the diagonal.  A chunk of
-    // a diagonal tile costs WD units of work (36 of the 64 MFMA tiles, see diag_mma), any other 16; the
+    // a diagonal tile costs WD units of work (see xxt_diag_cost), any other 16; the
     // ranges are equally long in cost, and both ends of a range are rounded down to an item in the same way.
     constexpr int WD = xxt_diag_cost(XT, CONV);
     const int64_t diag_items = (int64_t)nt * chunks, diag_cost = diag_items * WD;
