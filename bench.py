@@ -423,16 +423,15 @@ def main() -> int:
                     "avg_launch_ms": round(avg_ms, 6), "algorithmic_bytes_per_launch": bytes_per_launch,
                     "moved_bytes_per_launch": moved_per_launch, "moved_GBs": round(moved, 1),
                     "moved_frac": round(moved / PEAK_HBM_GBS, 4)}
-    # The other contractions of the path, from the stage events of the second pass (each stage is many short
-    # dependent launches, so these are stage-level rates, launch gaps included), against the fp64 matrix
-    # peak: shared-Hinv elimination d^3 / 3 flop (symmetric trailing updates), column loop R d^2 (deferred
-    # compensation), Cholesky + triangular inverse + L^-T L^-1 d^3.
+    # The other contractions of the path, from the stage events of the second pass, against the fp64 matrix peak (each is
+    # one launch that is bound by its chain of d / 64 dependent diagonal blocks): Cholesky + triangular inverse +
+    # L^-T L^-1 d^3; shared-Hinv elimination d^3 / 3 flop (symmetric trailing updates) with the column loop's R d^2
+    # (deferred compensation).
     secondary = []
     if args.block != 1:
-        for name, stage_names, flops in (("eliminate (elim_iter_kernel)", ("eliminate",), d ** 3 / 3.0),
-                                         ("columns (col_block_kernel)", ("columns",), float(R) * d * d),
-                                         ("cholesky + inverse (chol_iter_kernel, gemm64_kernel)",
-                                          ("cholesky", "inverse"), float(d) ** 3)):
+        for name, stage_names, flops in (("eliminate + columns (flow_eliminate_kernel)", ("eliminate", "columns"),
+                                          d ** 3 / 3.0 + float(R) * d * d),
+                                         ("cholesky + inverse (flow_inverse_kernel)", ("cholesky", "inverse"), float(d) ** 3)):
             ms = sum(stages[n][0] for n in stage_names) / args.steps
             if ms > 0:
                 tf = flops / (ms * 1e-3) / 1e12

@@ -329,12 +329,12 @@ int fobq_probe_int8_matrix_rate(fobq_ctx* ctx, int operand_kind, double* tera_op
 typedef enum {
     FOBQ_STAGE_XXT = 0,      /* the X X^T kernel launches only                              */
     FOBQ_STAGE_FINALIZE = 1, /* split reduction, 2/N, mirror                                */
-    FOBQ_STAGE_CHOLESKY = 2, /* damping + H = L L^T (d_col <= 4096: also L^-1, L^-T L^-1)   */
-    FOBQ_STAGE_INVERSE = 3,  /* L^-1 and L^-T L^-1 where they are separate launches         */
+    FOBQ_STAGE_CHOLESKY = 2, /* damping, H = L L^T, L^-1 and L^-T L^-1 (one launch)         */
+    FOBQ_STAGE_INVERSE = 3,  /* reads 0: the inverse is part of the launch above            */
     FOBQ_STAGE_ORDER = 4,    /* column scores and sort (the grid runs beside the Cholesky)  */
-    FOBQ_STAGE_PERMUTE = 5,  /* gather W and Hinv into processing order                     */
-    FOBQ_STAGE_ELIMINATE = 6,/* shared-Hinv elimination (blocked form only)                 */
-    FOBQ_STAGE_COLUMNS = 7,  /* column loop: quantize + compensate (+ Eq. 12 when unblocked)*/
+    FOBQ_STAGE_PERMUTE = 5,  /* gather W and Hinv into processing order (general path only) */
+    FOBQ_STAGE_ELIMINATE = 6,/* shared-Hinv elimination; default block: with the column loop*/
+    FOBQ_STAGE_COLUMNS = 7,  /* column loop in launches of its own (general path, unblocked)*/
     FOBQ_STAGE_EMIT = 8,     /* scatter to original order, loss                             */
     FOBQ_STAGE_SLICE = 9,    /* integer-slice mode: row exponents and digits of X           */
     FOBQ_STAGE_COUNT = 10
