@@ -39,7 +39,8 @@ typedef enum {
     FOBQ_OK = 0,
     FOBQ_EINVAL = -1, /* bad argument (shape, bits, group, NULL pointer, bad permutation)  */
     FOBQ_ENOMEM = -2, /* device or host allocation failed                                   */
-    FOBQ_EHIP = -3,   /* a HIP call failed; fobq_last_error has the HIP error string        */
+    FOBQ_EHIP = -3,   /* a HIP call failed (fobq_last_error has the HIP error string), or a
+                         factorization launch gave up after many seconds without progress  */
     FOBQ_ENOTPD = -4, /* a Cholesky / elimination pivot was <= 0 or not finite              */
     FOBQ_ESTATE = -5  /* call sequence error (e.g. accumulate before begin)                 */
 } fobq_status;

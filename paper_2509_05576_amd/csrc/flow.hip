@@ -35,7 +35,7 @@ namespace fobq {
 
 constexpr int TILE = NB * NB;                        // doubles of a published tile
 constexpr int FLOW_LDS = SWEEP_LDS + 4 * NB * DL;    // doubles: two double-buffered operand tiles, or the chain's blocks
-constexpr int FLOW_MAX_POLLS = 1 << 22;              // several seconds
+constexpr int FLOW_MAX_POLLS = 1 << 24;              // more than ten seconds: longer than other work keeps the device full
 // words of a launch, all zero before it: counters, then one word per tile (T x T), then two per diagonal block for the
 // sums that are handed to the chain
 enum { FW_ROLE = 0, FW_QUEUE1 = 1, FW_QUEUE2 = 2, FW_QUEUE3 = 3, FW_ABORT = 4, FW_HEAD = 16 };
