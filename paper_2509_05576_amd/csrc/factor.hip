@@ -7,8 +7,6 @@
 //                    for step t is  W[:, k] -= (w_t - q_t) * Un[t, k].
 // The 64 x 64 diagonal blocks are handled by one workgroup in LDS (tile_block.h); everything
 // else is products on the matrix cores (gemm64).
-#include <hip/hip_ext.h>
-
 #include "fobq_internal.h"
 #include "tile_block.h"
 
@@ -80,7 +78,7 @@ hipError_t eliminate_blocked(fobq_ctx* c, double* A, int d, int steps, int block
         p.B = A + (int64_t)o * d + (o + nb); p.ldb = d;
         p.C = U + (int64_t)o * d + (o + nb); p.ldc = d;
         p.C2 = Un + (int64_t)o * d + (o + nb); p.rowscale = rinv;
-        hipError_t e = gemm64(s, p, false, false);
+        hipError_t e = gemm64(s, p, false);
         if (e != hipSuccess) return e;
         // trailing update  A22 -= Un12^T U12  (tiles on or above the diagonal)
         GemmP q;
@@ -88,8 +86,8 @@ hipError_t eliminate_blocked(fobq_ctx* c, double* A, int d, int steps, int block
         q.A = Un + (int64_t)o * d + (o + nb); q.lda = d;
         q.B = U + (int64_t)o * d + (o + nb); q.ldb = d;
         q.C = A + (int64_t)(o + nb) * d + (o + nb); q.ldc = d;
-        q.alpha = -1.0; q.beta = 1.0; q.cmode = CMODE_UPPER;
-        e = gemm64(s, q, true, false);
+        q.alpha = -1.0; q.beta = 1.0; q.upper = true;
+        e = gemm64(s, q, true);
         if (e != hipSuccess) return e;
         ready(it);
     }

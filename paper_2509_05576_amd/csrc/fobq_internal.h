@@ -36,17 +36,9 @@ struct DevBuf {
 };
 
 // ---------------------------------------------------------------------------
-// Generic fp64 MFMA GEMM:  C = beta*C + alpha * op(A) * op(B), row-major.
-//   op(A) is M x K:  TA=false -> A[m*lda + k],  TA=true -> A[k*lda + m]
-//   op(B) is K x N:  TB=false -> B[k*ldb + n],  TB=true -> B[n*ldb + k]
-// Tiles of 64 x 64 per workgroup; tiles can be restricted to one triangle and
-// the K range of a tile can be restricted when an operand is triangular.
-enum { CMODE_ALL = 0, CMODE_LOWER = 1, CMODE_UPPER = 2 };
-enum { KMODE_FULL = 0,      // k in [0, K)
-       KMODE_GE_MAX_MN = 1, // k >= max(m0, n0)   (both operands zero above)
-       KMODE_GE_N = 2,      // k >= n0            (op(B) lower triangular)
-       KMODE_LT_M = 3 };    // k <  m0 + 64       (op(A) lower triangular)
-
+// fp64 MFMA GEMM:  C = beta*C + alpha * op(A) * B, row-major.
+//   op(A) is M x K:  TA=false -> A[m*lda + k],  TA=true -> A[k*lda + m];  B is K x N
+// Tiles of 64 x 64 per workgroup; `upper`: only those on or above the diagonal.
 struct GemmP {
     int M = 0, N = 0, K = 0;
     const double* A = nullptr; int64_t lda = 0;
@@ -55,19 +47,13 @@ struct GemmP {
     double* C2 = nullptr;              // optional second output: rowscale[m] * result
     const double* rowscale = nullptr;
     double alpha = 1.0, beta = 0.0;
-    int cmode = CMODE_ALL, kmode = KMODE_FULL;
-    int kmin = 0;                      // k starts no lower than this (a multiple of 64)
-    int beta_ncols = -1;               // >= 0: beta applies only to the tiles left of this column (0 elsewhere)
-    // batching (blockIdx.z): element strides and per-batch clamps
-    int batches = 1;
-    int64_t sA = 0, sB = 0, sC = 0;
-    int Mtot = -1, mstep = 0;          // M_eff = min(M, Mtot - b*mstep) when Mtot >= 0
-    int Ktot = -1, kstep = 0;          // K_eff likewise
+    bool upper = false;
 };
-// `done` (here and in the launchers below that take one; may be null): an event that is recorded when the launch
+hipError_t gemm64(hipStream_t s, const GemmP& p, bool TA);
+
+// `done` (in the launchers below that take one; may be null): an event that is recorded when the launch
 // completes.  It rides on the launch as its stop event (hipExtLaunchKernelGGL): a separate hipEventRecord
 // between two dependent launches is a bubble of about 4 us on the stream.
-hipError_t gemm64(hipStream_t s, const GemmP& p, bool TA, bool TB, hipEvent_t done = nullptr);
 
 // ---------------------------------------------------------------------------
 // Stage timing (hipEvents on the context's stream), off by default.
