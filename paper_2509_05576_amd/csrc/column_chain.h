@@ -20,7 +20,9 @@ __device__ __forceinline__ double chain_readlane(double v, int lane)
 // and every lane takes its code and its difference w - q from its final value afterwards, by the same operations.
 // EXACT = false forms the quotient w / s as w * (1 / s) (the product is within 2 ulp of the true quotient, so rint of it can
 // differ from rint(w / s) only when it lies within 2 ulp of a half-integer) and reports through `suspect` whether any
-// column came that close when it was quantized; EXACT = true uses the true division.
+// column came that close when it was quantized, or ended with a difference that is not finite: such a difference times the
+// 0 of a column quantized before it is NaN, and that column's final value is no longer what it was quantized at.
+// EXACT = true uses the true division and takes code and difference at the column's own step.
 template <bool EXACT, int NR, int LDU>
 __device__ __forceinline__ void chain_steps(double (&w)[NR], const double* Us, const double (&s)[NR], const double (&z)[NR],
                                             double maxq, int nb, int lane, double (&mycode)[NR], double (&mydiff)[NR],
@@ -53,20 +55,22 @@ __device__ __forceinline__ void chain_steps(double (&w)[NR], const double* Us, c
                     const double tq = EXACT ? w[r] / s[r] : w[r] * rcp_s[r];
                     const double cz = fmin(fmax(rint(tq), lo[r]), hi[r]);        // code - zero
                     const double df = w[r] - s[r] * cz;
+                    if (EXACT && lane == j) { mycode[r] = cz + z[r]; mydiff[r] = df; }
                     w[r] -= chain_readlane(df, j) * ub[g & 1][jj];
                 }
             }
         }
         __builtin_amdgcn_sched_barrier(0);            // keeps the loads of the group after the next from moving up here
     }
+    if (EXACT) return;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const double tq = EXACT ? w[r] / s[r] : w[r] * rcp_s[r];
+        const double tq = w[r] * rcp_s[r];
         const double c0 = rint(tq);
-        if (!EXACT) suspect = suspect || (fabs(fabs(tq - c0) - 0.5) < 1.0e-9 * fmax(1.0, fabs(tq)));
         const double cz = fmin(fmax(c0, lo[r]), hi[r]);
         mycode[r] = cz + z[r];
         mydiff[r] = w[r] - s[r] * cz;
+        suspect = suspect || (fabs(fabs(tq - c0) - 0.5) < 1.0e-9 * fmax(1.0, fabs(tq))) || !(fabs(mydiff[r]) <= 1.7976931348623157e308);
     }
 }
 
