@@ -329,7 +329,9 @@ __device__ __forceinline__ double flow_lambda(const FlowInverseP& p, double* par
     return lam;
 }
 
-// minus tile (i, j) of H (0 past d) in the accumulator layout, lambda added on the diagonal
+// minus tile (i, j), i <= j, of H (0 past d) in the accumulator layout, lambda added on the diagonal.  H is read on and below its
+// diagonal only (of a diagonal tile the chain uses that part): the mirrored tile, 16 lanes a row apart, each line of 128
+// bytes in four loads of the same wavefront.
 __device__ __forceinline__ void flow_init_h(const FlowInverseP& p, int i, int j, double lam, d4 (&c)[2])
 {
     const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -340,7 +342,7 @@ __device__ __forceinline__ void flow_init_h(const FlowInverseP& p, int i, int j,
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int gm = NB * i + wr * 16 + 4 * v + fq, gn = NB * j + w2 * 32 + 16 * h + fr;
-            double x = (gm < d && gn < d) ? p.H[(int64_t)gm * d + gn] : 0.0;
+            double x = (gm < d && gn < d) ? p.H[(int64_t)max(gm, gn) * d + min(gm, gn)] : 0.0;
             if (gm == gn) x += lam;
             c[h][v] = -x;
         }
@@ -546,7 +548,7 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
     const int role = flow_ticket(f, FW_ROLE, &slot);
     if (role == 0) {
         const double lam = flow_lambda(p, tiles);
-        flow_chain<false>(f, nullptr, nullptr, lds, [&](int m, int n) { return p.H[(int64_t)m * f.d + n] + (m == n ? lam : 0.0); });
+        flow_chain<false>(f, nullptr, nullptr, lds, [&](int m, int n) { return p.H[(int64_t)max(m, n) * f.d + min(m, n)] + (m == n ? lam : 0.0); });
     } else if (flow_serves(f, role) == 1) {
         Queue1 q1;
         const int n = queue1_length(T);
