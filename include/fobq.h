@@ -39,8 +39,10 @@ typedef enum {
     FOBQ_OK = 0,
     FOBQ_EINVAL = -1, /* bad argument (shape, bits, group, NULL pointer, bad permutation)  */
     FOBQ_ENOMEM = -2, /* device or host allocation failed                                   */
-    FOBQ_EHIP = -3,   /* a HIP call failed (fobq_last_error has the HIP error string), or a
-                         factorization launch gave up after many seconds without progress  */
+    FOBQ_EHIP = -3,   /* a HIP call failed (fobq_last_error has the HIP error string), or the
+                         workgroups of a factorization launch that were running waited for about
+                         a minute during which none of that launch started or finished a tile:
+                         other work may delay a call without limit as long as it moves at all  */
     FOBQ_ENOTPD = -4, /* a Cholesky / elimination pivot was <= 0 or not finite              */
     FOBQ_ESTATE = -5  /* call sequence error (e.g. accumulate before begin)                 */
 } fobq_status;
@@ -292,6 +294,12 @@ int fobq_obq_rows(fobq_ctx* ctx, const float* W, int64_t d_row, int64_t d_col, c
  * A call that fails this way with work already enqueued waits for that work before it returns and
  * leaves the context usable. */
 int fobq_debug_fail_after(fobq_ctx* ctx, int n);
+
+/* Test hook for the waits inside the factorization launches: from now on a launch of this context gives up
+ * (FOBQ_EHIP, outputs unspecified, the context stays usable) after `looks` looks of a waiting wavefront (about
+ * a microsecond each) during which no workgroup of the launch drew a tile; 0: at its first wait; < 0: the
+ * library's own limit. */
+int fobq_debug_wait_looks(fobq_ctx* ctx, int looks);
 
 /* Test hook for the host side of the tap-offset form of fobq_hessian_accumulate_conv (stride 1; needs no GPU
  * and no context): the list of single-row / single-column correlations ("strips") and, for every pair of

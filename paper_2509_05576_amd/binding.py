@@ -75,6 +75,7 @@ def load_library() -> ctypes.CDLL:
     lib.fobq_sensitivity.argtypes = [vp, vp, i64, i64, vp, ctypes.POINTER(FobqOpts), vp, vp]
     lib.fobq_sensitivity_static.argtypes = lib.fobq_sensitivity.argtypes
     lib.fobq_debug_fail_after.argtypes = [vp, i32]
+    lib.fobq_debug_wait_looks.argtypes = [vp, i32]
     lib.fobq_debug_offset_tables.argtypes = [i32, i32, i64, i64, ctypes.POINTER(i32), i64, ctypes.POINTER(i64)]
     lib.fobq_workspace_bytes.argtypes = [vp, ctypes.POINTER(i64)]
     lib.fobq_hessian_form.argtypes = [vp, ctypes.POINTER(i32)]
@@ -86,7 +87,7 @@ def load_library() -> ctypes.CDLL:
     for name in ("fobq_create", "fobq_destroy", "fobq_hessian_begin", "fobq_hessian_set_mode", "fobq_hessian_accumulate",
                  "fobq_hessian_accumulate_conv", "fobq_hessian_finalize", "fobq_quantize_layer",
                  "fobq_quantize_layer_enqueue", "fobq_quantize_layers_batched", "fobq_finish", "fobq_spd_inverse", "fobq_sensitivity",
-                 "fobq_sensitivity_static", "fobq_debug_fail_after", "fobq_debug_offset_tables", "fobq_workspace_bytes", "fobq_probe_int8_matrix_rate", "fobq_obq_rows", "fobq_hessian_form",
+                 "fobq_sensitivity_static", "fobq_debug_fail_after", "fobq_debug_wait_looks", "fobq_debug_offset_tables", "fobq_workspace_bytes", "fobq_probe_int8_matrix_rate", "fobq_obq_rows", "fobq_hessian_form",
                  "fobq_profile_enable", "fobq_profile_get", "fobq_profile_reset"):
         getattr(lib, name).restype = i32
     _lib = lib
@@ -334,6 +335,10 @@ def fobq_probe_int8_matrix_rate(ctx: int, operand_kind: int) -> float:
 
 def fobq_debug_fail_after(ctx: int, n: int) -> None:
     _check(ctx, load_library().fobq_debug_fail_after(ctypes.c_void_p(ctx), n))
+
+
+def fobq_debug_wait_looks(ctx: int, looks: int) -> None:
+    _check(ctx, load_library().fobq_debug_wait_looks(ctypes.c_void_p(ctx), looks))
 
 
 def fobq_debug_offset_tables(k: int, pad: int, h: int, w: int):

@@ -173,7 +173,7 @@ static int enqueue_inverse(fobq_ctx* ctx, const double* H, int d, double damp, d
     int* flags = ctx->flags.as<int>();
     StageScope sc(ctx, FOBQ_STAGE_CHOLESKY);
     FOBQ_TRY(launch_flow_inverse(ctx->stream, ctx->cus, H, d, damp, damp_abs, ctx->Hinv.as<double>(), ctx->tiles.as<double>(),
-                                 ctx->gt.as<double>(), ctx->words.as<int>(), flags + FLAG_NOTPD_H, flags + FLAG_STALLED), "inverse");
+                                 ctx->gt.as<double>(), ctx->words.as<int>(), flags + FLAG_NOTPD_H, flags + FLAG_STALLED, ctx->flow_looks), "inverse");
     return FOBQ_OK;
 }
 
@@ -280,7 +280,7 @@ static int read_flags(fobq_ctx* ctx, const int* dev_flags)
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
     FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
-    if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch stopped making progress and was given up");
+    if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for about a minute and was given up");
     if (h[FLAG_BADPERM]) return set_err(ctx, FOBQ_EINVAL, "perm_in is not a permutation of 0..d_col-1");
     if (h[FLAG_NOTPD_H]) return set_err(ctx, FOBQ_ENOTPD, "damped Hessian is not positive definite (Cholesky pivot <= 0)");
     if (h[FLAG_NOTPD_HINV]) return set_err(ctx, FOBQ_ENOTPD, "shared inverse Hessian lost positive definiteness (elimination pivot <= 0)");
@@ -867,6 +867,13 @@ int fobq_debug_fail_after(fobq_ctx* ctx, int n)
     return FOBQ_OK;
 }
 
+int fobq_debug_wait_looks(fobq_ctx* ctx, int looks)
+{
+    if (!ctx) return FOBQ_EINVAL;
+    ctx->flow_looks = looks < 0 ? FLOW_LOOKS : looks;
+    return FOBQ_OK;
+}
+
 // What one layer's launches need, fixed before the first of them is enqueued.
 struct LayerPlan {
     const float* W; const double* H; const fobq_opts* opts; const fobq_out* out;
@@ -929,6 +936,7 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
         a.wt = Wp; a.dt = ctx->DT.as<double>(); a.corr = ctx->corr.as<double>(); a.lossrow = lossrow; a.Wout = out->W_work;
         a.codesT = codesT; a.words = ctx->words2;
         a.notpd = ctx->flags.as<int>() + FLAG_NOTPD_HINV; a.stalled = ctx->flags.as<int>() + FLAG_STALLED;
+        a.looks = ctx->flow_looks;
         {
             StageScope sc(ctx, FOBQ_STAGE_ELIMINATE);
             FOBQ_TRY(launch_flow_eliminate(s, ctx->cus, a), "eliminate and columns");
@@ -1196,7 +1204,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         a.tiles = L.tiles; a.tilesN = L.tilesN; a.gt = L.gt; a.vec = L.vec; a.wt = L.wt; a.dt = L.dt; a.corr = L.corr;
         a.lossrow = L.lossrow; a.Wout = nullptr; a.codesT = L.codesT;
         a.words = L.words + L.nwords1;
-        a.notpd = L.flags + FLAG_NOTPD_HINV; a.stalled = L.flags + FLAG_STALLED;
+        a.notpd = L.flags + FLAG_NOTPD_HINV; a.stalled = L.flags + FLAG_STALLED; a.looks = ctx->flow_looks;
         Hs[l] = L.H; words[l] = L.words; notpd[l] = L.flags + FLAG_NOTPD_H;
     }
     FlowBatchPlan plan;
@@ -1222,7 +1230,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         FOBQ_TRY(hipStreamSynchronize(s), "synchronize");
         for (int l = 0; l < n_layers; ++l) {
             if (hflags[4 * l + FLAG_STALLED])
-                return set_err(ctx, FOBQ_EHIP, "layer %d: a factorization launch stopped making progress and was given up", l);
+                return set_err(ctx, FOBQ_EHIP, "layer %d: a factorization launch drew no tile for about a minute and was given up", l);
             if (hflags[4 * l + FLAG_NOTPD_H])
                 return set_err(ctx, FOBQ_ENOTPD, "layer %d: damped Hessian is not positive definite (Cholesky pivot <= 0)", l);
             if (hflags[4 * l + FLAG_NOTPD_HINV])

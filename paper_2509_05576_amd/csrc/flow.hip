@@ -13,8 +13,9 @@
 // and publishes it.  Workgroups take tiles from queues in a fixed order (a ticket each).  All the work of a launch has one
 // order in which whatever a tile waits for stands before it; each queue is a part of that order, and the workgroup that
 // walks the chain is the first to start, the next ones serve one queue each.  So the earliest unfinished tile has its
-// workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should the device
-// stop making progress all the same, every wait gives up after FLOW_MAX_POLLS looks, the launch drains and the call fails.)
+// workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should a launch stop
+// all the same -- nobody draws a ticket for about a minute, see flow_gives_up -- its waits give up, it drains and the call
+// fails.  A wait may be as long as it likes while tickets are drawn: foreign work on the device only delays it.)
 //
 // Exchange between compute units.  Each XCD has its own L2, which is not coherent with the others inside a launch.
 // Everything that one workgroup hands to another during a launch goes through relaxed agent-scope atomic accesses
@@ -35,7 +36,6 @@ namespace fobq {
 
 constexpr int TILE = NB * NB;                        // doubles of a published tile
 constexpr int FLOW_LDS = SWEEP_LDS + 4 * NB * DL;    // doubles: two double-buffered operand tiles, or the chain's blocks
-constexpr int FLOW_MAX_POLLS = 1 << 24;              // more than ten seconds: longer than other work keeps the device full
 // words of a launch, all zero before it: counters, then one word per tile (T x T), then two per diagonal block for the
 // sums that are handed to the chain
 enum { FW_ROLE = 0, FW_QUEUE1 = 1, FW_QUEUE2 = 2, FW_QUEUE3 = 3, FW_ABORT = 4, FW_HEAD = 16 };
@@ -50,6 +50,7 @@ __device__ __forceinline__ void st_word(int* p, int v) { __hip_atomic_store(p, v
 struct FlowP {
     int d, T;
     int n1, n2, n3;      // workgroups that serve queue 1 / 2 / 3 first (the chain's workgroup not counted)
+    int looks;           // see flow_gives_up
     int* words;
     double* tiles;
     double* gt;
@@ -63,15 +64,34 @@ __device__ __forceinline__ int* hand_word(const FlowP& f, int k, int which) { re
 __device__ __forceinline__ double* hand_tile(const FlowP& f, int k) { return f.gt + (int64_t)(f.T + k) * TILE; }
 static int flow_words(int T) { return FW_HEAD + T * T + 2 * T; }
 
+// One wavefront, after a look that found nothing: whether to stop waiting.  n counts the looks since the launch was last seen
+// to move, that is to draw tickets (roles or tiles: whoever finishes a tile draws the next); after f.looks of them the
+// launch is given up, for all its wavefronts.  seen: the counters at the last check (per lane; both start as in FlowPatience).
+struct FlowPatience { int n = 0, seen = -1; };
+__device__ __forceinline__ bool flow_gives_up(const FlowP& f, FlowPatience& w)
+{
+    ++w.n;
+    if ((w.n & 31) == 0 || w.n >= f.looks) {
+        const int lane = threadIdx.x & 63;
+        const int v = ld_word(f.words + min(lane, (int)FW_ABORT));
+        if (__builtin_amdgcn_readlane(v, FW_ABORT) != 0) return true;
+        if (__any(lane < FW_ABORT && v != w.seen)) w.n = 0;
+        else if (w.n >= f.looks) {
+            st_word(f.words + FW_ABORT, 1);
+            return true;
+        }
+        w.seen = v;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    return false;
+}
+
 // One wavefront: waits until the word of every lane that has one is set.
 __device__ __forceinline__ void flow_wait(const FlowP& f, const int* word, bool has)
 {
-    for (int n = 0;; ++n) {
+    for (FlowPatience w;;) {
         const int v = has ? ld_word(word) : 1;
-        if (__all(v != 0)) break;
-        if (n >= FLOW_MAX_POLLS) st_word(f.words + FW_ABORT, 1);
-        if ((n & 31) == 31 && ld_word(f.words + FW_ABORT) != 0) break;
-        __builtin_amdgcn_s_sleep(1);
+        if (__all(v != 0) || flow_gives_up(f, w)) break;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");    // (keeps the loads that follow behind the last look)
 }
@@ -161,12 +181,10 @@ __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src&
     double* alt = lds + 2 * TILE;
     int known = q0;                      // the tiles of the steps before this one are ready
     for (int q = q0; q < q1;) {
-        for (int n = 0; known <= q; ++n) {                   // wavefront-uniform
+        for (FlowPatience w; known <= q;) {                  // wavefront-uniform
             const int k = src.ready(q, q1, lane);
-            if (k > 0) { known = min(q + k, q1); break; }
-            if (n >= FLOW_MAX_POLLS) st_word(f.words + FW_ABORT, 1);
-            if ((n & 31) == 31 && ld_word(f.words + FW_ABORT) != 0) { known = q1; break; }
-            __builtin_amdgcn_s_sleep(1);
+            if (k > 0) known = min(q + k, q1);
+            else if (flow_gives_up(f, w)) known = q1;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         if (known - q < 4) {
@@ -982,9 +1000,10 @@ size_t flow_rows_bytes(int d, int R) { const size_t T = (d + NB - 1) / NB, NG = 
 static int flow_grid(int cus, int64_t tasks) { return (int)(1 + tasks < cus ? 1 + tasks : cus); }
 
 static FlowInverseP inverse_params(const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles, double* gt, int* words,
-                                   int* notpd, int* stalled, int wgs)
+                                   int* notpd, int* stalled, int looks, int wgs)
 {
     FlowInverseP p;
+    p.f.looks = looks;
     p.f.d = d;
     p.f.T = (d + NB - 1) / NB;
     // two rows of tiles in flight keep the chain fed (64 to 160 workgroups give the same times at d = 2304 .. 4608)
@@ -999,6 +1018,7 @@ static FlowInverseP inverse_params(const double* H, int d, double damp, double d
 static FlowElimP eliminate_params(const FlowElimArgs& a)     // all but the numbers of workgroups
 {
     FlowElimP p;
+    p.f.looks = a.looks;
     p.f.d = a.d;
     p.f.T = (a.d + NB - 1) / NB;
     p.f.words = a.words; p.f.tiles = a.tiles; p.f.gt = a.gt; p.f.notpd = a.notpd; p.f.stalled = a.stalled;
@@ -1010,10 +1030,10 @@ static FlowElimP eliminate_params(const FlowElimArgs& a)     // all but the numb
 }
 
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
-                               double* gt, int* words, int* notpd, int* stalled)
+                               double* gt, int* words, int* notpd, int* stalled, int looks)
 {
     const int T = (d + NB - 1) / NB, wgs = flow_grid(cus, 2 * (int64_t)T * T);
-    const FlowInverseP p = inverse_params(H, d, damp, damp_abs, Hinv, tiles, gt, words, notpd, stalled, wgs);
+    const FlowInverseP p = inverse_params(H, d, damp, damp_abs, Hinv, tiles, gt, words, notpd, stalled, looks, wgs);
     hipLaunchKernelGGL(flow_inverse_kernel, dim3(wgs), dim3(NT), 0, s, p);
     return hipGetLastError();
 }
@@ -1086,7 +1106,7 @@ void flow_batch_plan(int cus, int n, const FlowElimArgs* a, const double* const*
         const int T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB, parts = NG * (8 / plan->nr);
         const int wi = std::min(1 + 2 * T * T, BATCH_INVERSE_WGS);
         const FlowInverseP ip = inverse_params(H[l], a[l].d, damp, damp_abs, const_cast<double*>(a[l].Hinv), a[l].tiles, a[l].gt, words[l], notpd_h[l],
-                                               a[l].stalled, wi);
+                                               a[l].stalled, a[l].looks, wi);
         memcpy(static_cast<unsigned char*>(inv_desc) + (size_t)l * sizeof(FlowInverseP), &ip, sizeof ip);
         for (int w = 0; w < wi; ++w) inv_of[plan->inv_wgs++] = (uint16_t)l;
         FlowElimP ep = eliminate_params(a[l]);

@@ -18,6 +18,10 @@ __device__ __forceinline__ double grid_code(double w, double scale, double zero,
     return c;
 }
 
+// Looks (about a microsecond each) that a wavefront inside a factorization launch waits while nobody in that launch draws a tile
+// before the launch is given up: about a minute.
+constexpr int FLOW_LOOKS = 1 << 26;
+
 // ---------------------------------------------------------------------------
 // Device buffer owned by the context; grows, never shrinks.
 struct DevBuf {
@@ -114,6 +118,7 @@ struct fobq_ctx {
     int cus = 256;          // compute units of the device (fobq_create)
     int* h_flags = nullptr; // pinned host memory that the status flags are read back into (made by fobq_create)
     unsigned char* static_scratch = nullptr;   // this GPU's copy of the library's static scratch array
+    int flow_looks = fobq::FLOW_LOOKS;   // (test hook: fobq_debug_wait_looks)
     int fail_countdown = 0; // test hook: > 0 = the n-th status check from now reports an injected failure
     // quantization workspace
     fobq::DevBuf Wp;        // d_row x d fp64, columns in processing order (one-launch form: in tiles)
@@ -232,6 +237,7 @@ hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, i
 
 // flow.hip: damped H -> upper tiles of Hinv = (H + lambda I)^-1, lambda = damp * mean(diag H) + damp_abs, in one launch.  tiles, gt:
 // scratch; words: flow_inverse_words(d) zeroed words; *notpd / *stalled are set to 1 when a pivot is not positive / the launch gave up
+// after `looks` looks of a waiting wavefront during which nobody drew a tile (FLOW_LOOKS)
 int64_t flow_inverse_words(int d);
 size_t flow_tiles_bytes(int d);
 size_t flow_gt_bytes(int d);
@@ -244,13 +250,14 @@ struct FlowElimArgs {
     double *tiles, *tilesN, *gt, *vec, *wt, *dt, *corr, *lossrow, *Wout;
     uint8_t* codesT;
     int *words, *notpd, *stalled;
+    int looks;
 };
 int64_t flow_eliminate_words(int d, int R);
 int64_t flow_eliminate_words_most(int d, int R);     // however many rows a wavefront takes
 size_t flow_rows_bytes(int d, int R);
 hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a);
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
-                               double* gt, int* words, int* notpd, int* stalled);
+                               double* gt, int* words, int* notpd, int* stalled, int looks);
 
 // factor.hip
 // `rows_ready` (may be null): rows_ready[k] is recorded on the context's stream once the pivot rows of
