@@ -317,6 +317,13 @@ int fobq_debug_wait_looks(fobq_ctx* ctx, int looks);
  * fobq_hessian_accumulate_conv takes the general path). */
 int fobq_debug_offset_tables(int32_t k, int32_t pad, int64_t h, int64_t w, int32_t* out, int64_t cap, int64_t* used);
 
+/* Test hook for the rules by which launches are cut into workgroups (host code: needs no GPU and no context).
+ * in, out: n_in / n_out words as listed; EINVAL for others or values out of range.
+ *   FOBQ_PLAN_PAD  in: images, h, w, channels, pad, both pointers 16-byte aligned (0 / 1), channel maxima wanted (0 / 1)
+ *                  out: parts that each padded row is cut into, workgroups */
+typedef enum { FOBQ_PLAN_PAD = 0 } fobq_plan;
+int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out, int32_t n_out);
+
 /* Measurement aid for the X X^T kernel of the int8-slice mode (no part of the method): the rate, in
  * 1e12 int8 operations per second (multiply and add counted separately), at which this GPU's matrix
  * cores run that kernel's inner loop -- the 19 digit products of a k-step on 32 x 32 x 32 int8

@@ -76,6 +76,7 @@ def load_library() -> ctypes.CDLL:
     lib.fobq_sensitivity_static.argtypes = lib.fobq_sensitivity.argtypes
     lib.fobq_debug_fail_after.argtypes = [vp, i32]
     lib.fobq_debug_wait_looks.argtypes = [vp, i32]
+    lib.fobq_debug_plan.argtypes = [i32, ctypes.POINTER(i64), i32, ctypes.POINTER(i64), i32]
     lib.fobq_debug_offset_tables.argtypes = [i32, i32, i64, i64, ctypes.POINTER(i32), i64, ctypes.POINTER(i64)]
     lib.fobq_workspace_bytes.argtypes = [vp, ctypes.POINTER(i64)]
     lib.fobq_hessian_form.argtypes = [vp, ctypes.POINTER(i32)]
@@ -87,7 +88,7 @@ def load_library() -> ctypes.CDLL:
     for name in ("fobq_create", "fobq_destroy", "fobq_hessian_begin", "fobq_hessian_set_mode", "fobq_hessian_accumulate",
                  "fobq_hessian_accumulate_conv", "fobq_hessian_finalize", "fobq_quantize_layer",
                  "fobq_quantize_layer_enqueue", "fobq_quantize_layers_batched", "fobq_finish", "fobq_spd_inverse", "fobq_sensitivity",
-                 "fobq_sensitivity_static", "fobq_debug_fail_after", "fobq_debug_wait_looks", "fobq_debug_offset_tables", "fobq_workspace_bytes", "fobq_probe_int8_matrix_rate", "fobq_obq_rows", "fobq_hessian_form",
+                 "fobq_sensitivity_static", "fobq_debug_fail_after", "fobq_debug_wait_looks", "fobq_debug_plan", "fobq_debug_offset_tables", "fobq_workspace_bytes", "fobq_probe_int8_matrix_rate", "fobq_obq_rows", "fobq_hessian_form",
                  "fobq_profile_enable", "fobq_profile_get", "fobq_profile_reset"):
         getattr(lib, name).restype = i32
     _lib = lib
@@ -339,6 +340,18 @@ def fobq_debug_fail_after(ctx: int, n: int) -> None:
 
 def fobq_debug_wait_looks(ctx: int, looks: int) -> None:
     _check(ctx, load_library().fobq_debug_wait_looks(ctypes.c_void_p(ctx), looks))
+
+
+PLAN_PAD = 0
+
+
+def fobq_debug_plan(what: int, args, n_out: int):
+    """fobq_debug_plan: the list of its n_out words.  Host code only: no GPU, no context."""
+    a, out = (ctypes.c_int64 * len(args))(*args), (ctypes.c_int64 * n_out)()
+    rc = load_library().fobq_debug_plan(what, a, len(args), out, n_out)
+    if rc != OK:
+        raise FobqError(rc, "fobq_debug_plan: bad argument")
+    return list(out)
 
 
 def fobq_debug_offset_tables(k: int, pad: int, h: int, w: int):

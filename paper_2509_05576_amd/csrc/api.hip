@@ -860,6 +860,20 @@ int fobq_debug_offset_tables(int32_t k, int32_t pad, int64_t h, int64_t w, int32
     return FOBQ_OK;
 }
 
+int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out, int32_t n_out)
+{
+    if (!in || !out) return FOBQ_EINVAL;
+    if (what == FOBQ_PLAN_PAD && n_in == 7 && n_out == 2) {
+        for (int i = 0; i < 5; ++i)
+            if (in[i] < (i == 4 ? 0 : 1) || in[i] > (1 << 20)) return FOBQ_EINVAL;
+        if ((in[2] + 2 * in[4]) * in[3] >= (1ll << 31)) return FOBQ_EINVAL;
+        const PadPlan p = pad_maps_plan(in[0], (int)in[1], (int)in[2], (int)in[3], (int)in[4], in[5] != 0, in[6] != 0);
+        out[0] = p.parts; out[1] = p.wgs;
+        return FOBQ_OK;
+    }
+    return FOBQ_EINVAL;
+}
+
 int fobq_debug_fail_after(fobq_ctx* ctx, int n)
 {
     if (!ctx || n < 0) return FOBQ_EINVAL;

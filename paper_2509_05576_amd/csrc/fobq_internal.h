@@ -183,6 +183,10 @@ hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t 
 int xxt_pick_splits(int d);
 int xxt_slabs_touched(int d, int64_t n, int splits, bool conv);
 hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, int count);
+// the padding launch: `parts` runs of `run` pixels (the last one the rest) of each of `rows` rows, wgs workgroups of 256 threads; whether it moves 16 bytes per lane and takes
+// the channel maxima along
+struct PadPlan { int64_t rows; int parts, run, wgs, active; bool vec, maxima; };
+PadPlan pad_maps_plan(int64_t n_img, int h, int w, int c, int pad, bool aligned, bool maxima);
 hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took);
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                            int ho, int wo, int64_t npix, double* Hpart, int splits, int fresh,

@@ -67,39 +67,49 @@ struct ConvP {
 };
 
 // out: (n_img + 1) x hp x wp x c, hp = h + 2 pad, wp = w + 2 pad; image n_img is all zeros.  Bound by memory: a workgroup takes
-// whole rows of the padded copy (zeros, the row of the map, zeros: no division per element), 16 bytes per lane where the
-// channels come in fours (VEC: c % 4 == 0, both pointers 16-byte aligned).  AMAX: the maxima |.| of every channel (bit
-// patterns) are taken on the way: the first `active` threads walk a row in steps of a multiple of c, so that a thread stays on
-// its channels; one atomic per channel and workgroup.  The 64-image 56 x 56 x 128 maps (103 MB): 85 us for a copy by elements
-// and 139 us for a second pass over it with an atomic per thread, 42 us together now.
-template <bool VEC, bool AMAX>
+// rows of the padded copy (zeros, the row of the map, zeros: no division per element) or (SPLIT), where the rows are few and long,
+// one of `parts` runs of `run` pixels of a row; 16 bytes per lane where the channels come in fours (VEC: c % 4 == 0, both pointers
+// 16-byte aligned).  AMAX: the maxima |.| of every channel (bit patterns) are taken on the way: the first `active` threads walk a
+// run in steps of a multiple of c, so that a thread stays on its channels; one atomic per channel and workgroup.  The 64-image
+// 56 x 56 x 128 maps (103 MB): 85 us for a copy by elements and 139 us for a second pass over it with an atomic per thread, 42 us
+// together now.  One image of 1 x 100352 x 256 (two rows of 103 MB; the whole accumulate call, 1 x 1): 3.56 ms with undivided
+// rows, 0.36 with the copy by elements, 0.23 in runs.
+template <bool VEC, bool AMAX, bool SPLIT>
 __global__ __launch_bounds__(256) void pad_maps_kernel(const float* __restrict__ maps, int n_img, int h, int w, int c, int pad,
-                                                       float* __restrict__ out, int64_t rows, int active, unsigned* __restrict__ amax)
+                                                       float* __restrict__ out, int64_t rows, int parts, int run, int active,
+                                                       unsigned* __restrict__ amax)
 {
     typedef typename std::conditional<VEC, float4, float>::type V;
     constexpr int VL = VEC ? 4 : 1;
     const int hp = h + 2 * pad;
-    const int lead = pad * c / VL, len = w * c / VL, total = len + 2 * lead;
+    const int unit = c / VL, lead = pad * unit, len = w * unit, total = len + 2 * lead;
     V zero{};
     unsigned m[VL];
 #pragma unroll
     for (int e = 0; e < VL; ++e) m[e] = 0;
-    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+    const int64_t items = SPLIT ? rows * parts : rows;
+    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const int64_t row = SPLIT ? (int)item / parts : item;       // (SPLIT: at most 2048 items)
+        const int part = SPLIT ? (int)item - (int)row * parts : 0;
+        const bool first = !SPLIT || part == 0, last = !SPLIT || part == parts - 1;
         const int64_t img = row / hp;
         const int y = (int)(row - img * hp) - pad;
         V* __restrict__ dst = reinterpret_cast<V*>(out) + row * total;
         if (img >= n_img || (unsigned)y >= (unsigned)h) {
-            for (int x = threadIdx.x; x < total; x += 256) dst[x] = zero;
+            const int end = last ? total : (part + 1) * run * unit;
+            for (int x = part * run * unit + threadIdx.x; x < end; x += 256) dst[x] = zero;
             continue;
         }
         const V* __restrict__ src = reinterpret_cast<const V*>(maps) + (img * h + y) * len;
-        for (int x = threadIdx.x; x < lead; x += 256) {
-            dst[x] = zero;
-            dst[lead + len + x] = zero;
-        }
+        if (first || last)
+            for (int x = threadIdx.x; x < lead; x += 256) {
+                if (first) dst[x] = zero;
+                if (last) dst[lead + len + x] = zero;
+            }
         if ((int)threadIdx.x < active) {
+            const int end = last ? len : (part + 1) * run * unit;
 #pragma unroll 4
-            for (int x = threadIdx.x; x < len; x += active) {
+            for (int x = part * run * unit + threadIdx.x; x < end; x += active) {
                 const V v = src[x];
                 if (AMAX) {
                     const float* f = reinterpret_cast<const float*>(&v);
@@ -123,23 +133,40 @@ __global__ __launch_bounds__(256) void pad_maps_kernel(const float* __restrict__
     }
 }
 
+// aligned: both pointers to 16 bytes
+PadPlan pad_maps_plan(int64_t n_img, int h, int w, int c, int pad, bool aligned, bool maxima)
+{
+    PadPlan p;
+    p.rows = (n_img + 1) * (h + 2 * pad);
+    p.vec = aligned && c % 4 == 0;
+    const int unit = p.vec ? c / 4 : c;                // steps of a row after which the channels repeat
+    p.maxima = maxima && unit <= 256;
+    p.active = p.maxima ? unit * (256 / unit) : 256;
+    // the maxima cost an atomic per channel and workgroup: 2048 workgroups 61 us, 768 42 us (64 x 56 x 56 x 128; 128 x 14 x 14 x
+    // 256: 43 and 23)
+    const int64_t most = p.maxima ? 768 : 2048;
+    // fewer rows than that: cut into parts of at least four steps of a whole workgroup
+    const int64_t fill = most / p.rows, steps = (int64_t)w * unit / (4 * 256);
+    p.parts = (int)std::max<int64_t>(1, std::min(std::min(fill, steps), (int64_t)w));
+    p.run = (w + p.parts - 1) / p.parts;
+    p.parts = (w + p.run - 1) / p.run;                // none of them empty
+    p.wgs = (int)std::min(p.rows * p.parts, most);
+    return p;
+}
+
 // amax: null, or c words that hold zeros; *took (if amax): whether the maxima were taken (else the caller's own pass does it)
 hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took)
 {
-    const int64_t rows = (int64_t)(n_img + 1) * (h + 2 * pad);
-    const bool vec = c % 4 == 0 && ((reinterpret_cast<uintptr_t>(maps) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    const int unit = vec ? c / 4 : c;                  // steps of a row after which the channels repeat
-    const bool max_too = amax && unit <= 256;
-    const int active = max_too ? unit * (256 / unit) : 256;
-    // the maxima cost an atomic per channel and workgroup: 2048 workgroups 61 us, 768 42 us (64 x 56 x 56 x 128; 128 x 14 x 14 x
-    // 256: 43 and 23)
-    const int64_t most = max_too ? 768 : 2048;
-    const dim3 grid((unsigned)(rows < most ? rows : most)), block(256);
-    if (took) *took = max_too;
-    if (vec && max_too)  hipLaunchKernelGGL((pad_maps_kernel<true, true>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
-    else if (vec)        hipLaunchKernelGGL((pad_maps_kernel<true, false>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
-    else if (max_too)    hipLaunchKernelGGL((pad_maps_kernel<false, true>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
-    else                 hipLaunchKernelGGL((pad_maps_kernel<false, false>), grid, block, 0, s, maps, n_img, h, w, c, pad, out, rows, active, amax);
+    const PadPlan p = pad_maps_plan(n_img, h, w, c, pad, ((reinterpret_cast<uintptr_t>(maps) | reinterpret_cast<uintptr_t>(out)) & 15) == 0, amax != nullptr);
+    if (took) *took = p.maxima;
+    auto launch = [&](auto whole, auto split) {
+        hipLaunchKernelGGL((p.parts > 1 ? split : whole), dim3(p.wgs), dim3(256), 0, s, maps, n_img, h, w, c, pad, out, p.rows, p.parts, p.run,
+                           p.active, amax);
+    };
+    if (p.vec && p.maxima) launch(pad_maps_kernel<true, true, false>, pad_maps_kernel<true, true, true>);
+    else if (p.vec)        launch(pad_maps_kernel<true, false, false>, pad_maps_kernel<true, false, true>);
+    else if (p.maxima)     launch(pad_maps_kernel<false, true, false>, pad_maps_kernel<false, true, true>);
+    else                   launch(pad_maps_kernel<false, false, false>, pad_maps_kernel<false, false, true>);
     return hipGetLastError();
 }
 
