@@ -158,7 +158,7 @@ static int ensure_inverse_ws(fobq_ctx* ctx, int64_t d, int64_t rows, int64_t flo
     FOBQ_TRY(ctx->tiles.ensure(flow_tiles_bytes((int)d)), "workspace tiles");
     FOBQ_TRY(ctx->gt.ensure(flow_gt_bytes((int)d)), "workspace block inverses");
     FOBQ_TRY(ctx->Hinv.ensure(dd), "workspace Hinv");
-    const int64_t first = flow_inverse_words((int)d), second = flow_rows > 0 ? flow_eliminate_words((int)d, (int)flow_rows) : 0;
+    const int64_t first = flow_inverse_words((int)d), second = flow_rows > 0 ? flow_eliminate_words(ctx->cus, (int)d, (int)flow_rows) : 0;
     const size_t words = ((size_t)(first + second) * sizeof(int) + 7) / 8 * 8;
     FOBQ_TRY(ctx->words.ensure(words + (size_t)rows * sizeof(double)), "workspace words and loss terms");
     ctx->lossrow = reinterpret_cast<double*>(ctx->words.as<unsigned char>() + words);
@@ -869,6 +869,21 @@ int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out,
         if ((in[2] + 2 * in[4]) * in[3] >= (1ll << 31)) return FOBQ_EINVAL;
         const PadPlan p = pad_maps_plan(in[0], (int)in[1], (int)in[2], (int)in[3], (int)in[4], in[5] != 0, in[6] != 0);
         out[0] = p.parts; out[1] = p.wgs;
+        return FOBQ_OK;
+    }
+    if (what == FOBQ_PLAN_ELIMINATE && n_in >= 3 && n_in % 2 == 1 && n_in / 2 <= BATCH_MAX_LAYERS && n_out == 4 * (n_in / 2)) {
+        const int n = n_in / 2;
+        if (in[0] < 16 || in[0] > 4096) return FOBQ_EINVAL;
+        int d[BATCH_MAX_LAYERS], R[BATCH_MAX_LAYERS];
+        FlowElimPlan p[BATCH_MAX_LAYERS];
+        for (int l = 0; l < n; ++l) {
+            if (in[1 + 2 * l] < 1 || in[1 + 2 * l] > MAX_DROW || in[2 + 2 * l] < 1 || in[2 + 2 * l] > (n == 1 ? MAX_DCOL : BATCH_MAX_D)) return FOBQ_EINVAL;
+            R[l] = (int)in[1 + 2 * l];
+            d[l] = (int)in[2 + 2 * l];
+        }
+        if (n == 1) p[0] = flow_eliminate_plan((int)in[0], d[0], R[0]);
+        else flow_batch_deal((int)in[0], n, d, R, p);
+        for (int l = 0; l < n; ++l) { out[4 * l] = p[l].nr; out[4 * l + 1] = p[l].n1; out[4 * l + 2] = p[l].n2; out[4 * l + 3] = p[l].n3; }
         return FOBQ_OK;
     }
     return FOBQ_EINVAL;

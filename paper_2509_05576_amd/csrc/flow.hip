@@ -27,8 +27,6 @@
 
 #include <algorithm>
 
-#include <hip/hip_ext.h>
-
 #include "column_chain.h"
 #include "tile_block.h"
 
@@ -963,29 +961,30 @@ __global__ __launch_bounds__(NT, 2) void flow_eliminate_batch_kernel(const FlowE
 }
 
 int64_t flow_inverse_words(int d) { return flow_words((d + NB - 1) / NB); }
-// Rows per wavefront of a part of columns (1, 2 or 4).  A part takes 7.5 / 11 / 18 us (measured), on top of which its successor
+// A part of columns with 1, 2 or 4 rows per wavefront.
+static const double PART_US[3] = {7.5, 11.0, 18.0};
+// Rows per wavefront of a part of columns (1, 2 or 4).  A part takes PART_US (measured), on top of which its successor
 // waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15 us
 // each), with many the workgroups are all busy and what counts is the time per row.  Twice the pure work over all
 // workgroups against the chains; measured at 1 / 2 / 4 rows, elimination and columns: 256 x 2304 0.54 / 0.58 / 0.74 ms,
 // 2048 x 512 0.16 / 0.15 / 0.19, 1024 x 4608 2.10 / 1.90 / 1.81, 8192 x 256 0.35 / 0.32 / 0.22.
-static int column_rows(int64_t R, int64_t T)
+static int column_rows(int cus, int64_t R, int64_t T)
 {
-    const double cost[3] = {7.5, 11.0, 18.0};
     const double NG = (double)((R + NB - 1) / NB), t = (double)T, products = 2.4 * (t * t * t / 6.0 + NG * t * t / 2.0);
     int best = 1;
     double least = 0.0;
     for (int i = 0; i < 3; ++i) {
         const int nr = 1 << i;
-        const double chains = t * std::max(15.3, cost[i] + 2.5), work = 2.0 / 255.0 * (products + t * NG * (8 / nr) * cost[i]);
+        const double chains = t * std::max(15.3, PART_US[i] + 2.5), work = 2.0 / (cus - 1) * (products + t * NG * (8 / nr) * PART_US[i]);
         const double time = std::max(chains, work);
         if (i == 0 || time < least) { least = time; best = nr; }
     }
     return best;
 }
-int64_t flow_eliminate_words(int d, int R)
+int64_t flow_eliminate_words(int cus, int d, int R)
 {
     const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
-    return flow_words((int)T) + T * NG * (1 + 8 / column_rows(R, T));
+    return flow_words((int)T) + T * NG * (1 + 8 / column_rows(cus, R, T));
 }
 int64_t flow_eliminate_words_most(int d, int R)
 {
@@ -1038,25 +1037,50 @@ hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, d
     return hipGetLastError();
 }
 
+// What the queues of an elimination have to do, in units of 2.3 us, a rank-64 product of a tile near the chain: tiles of U; parts of
+// columns (measured; of a layer narrower than a block their steps are fewer); sums of 64 rows.  Where there are more groups of
+// rows than blocks, the launch consists of parts and sums, and a sum is its products (1.5 units: their tiles come from farther
+// away) and, whatever their number, a ticket, the gather of its weights and its publication (5 us).  Otherwise the products
+// alone: queue 1's workgroups are free for the rest in the later half.  The best share of queue 3 in what queues 2 and 3 have,
+// measured / by these: 65535 x 64 from 0.16 on / 0.16, 65535 x 512 0.30 / 0.34, 4000 x 1024 0.46 / 0.47, 8000 x 2048 0.69 / 0.62;
+// 4096 x 4608 0.68 / 0.69 (6.80 ms; at 0.76 6.99), 2048 x 4608 0.70 to 0.76 / 0.69.  (With the products alone counted everywhere
+// 8 workgroups had the sums of 65535 x 64 and 245 waited for them: 986 us for the layer, 666 with a launch per block, 580 so.)
+static double work_u(double T) { return T * T * T / 6.0; }
+static double work_columns(double T, double NG, int nr, int d)
+{
+    return T * NG * (8 / nr) * (nr == 1 ? 3.0 : nr == 2 ? 5.0 : 8.0) * (0.3 + 0.7 * d / (64.0 * T));
+}
+static double work_groups(double T, double NG) { return NG * T * (NG > T ? 0.75 * T + 2.2 : 0.5 * T); }
+
+FlowElimPlan flow_eliminate_plan(int cus, int d, int R)
+{
+    // Where the chain of the diagonal blocks bounds the launch: what keeps up with it (two rows of tiles on queue 1, which feeds
+    // everything else; half as many again as there are parts in a block; the groups' sums a few blocks ahead), and no more, so
+    // that other launches find compute units.  Otherwise all, in proportion to the work of the queues.
+    FlowElimPlan p;
+    const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
+    p.nr = column_rows(cus, R, T);
+    const int64_t parts = NG * (8 / p.nr);
+    const double w1 = work_u((double)T), w2 = work_columns((double)T, (double)NG, p.nr, d), w3 = work_groups((double)T, (double)NG);
+    const int64_t k1 = 2 * T, k2 = parts + (parts + 1) / 2, k3 = NG + NG * T / 6;
+    const int avail = flow_grid(cus, T * (T + 9 * NG)) - 1;
+    if (k1 + k2 + k3 <= avail) {
+        p.n1 = (int)k1; p.n2 = (int)k2; p.n3 = (int)k3;
+    } else {
+        p.n1 = std::max<int>((int)(avail * w1 / (w1 + w2 + w3)), (int)std::min<int64_t>(k1, avail / 3));
+        p.n1 = std::max(1, std::min(p.n1, avail - 2));
+        p.n2 = std::max(1, std::min(avail - p.n1 - 1, (int)((avail - p.n1) * w2 / (w2 + w3) + 0.5)));
+        p.n3 = avail - p.n1 - p.n2;
+    }
+    return p;
+}
+
 hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
 {
     FlowElimP p = eliminate_params(a);
-    // Where the chain of the diagonal blocks bounds the launch: what keeps up with it (two rows of tiles on queue 1, which feeds
-    // everything else; half as many again as there are parts in a block; the groups' sums a few blocks ahead), and no more, so
-    // that other launches find compute units.  Otherwise all, in proportion to the work of the queues in rank-64 products of a
-    // tile (a part of columns: what it takes, measured, in such products).
-    const int64_t T = p.f.T, nr = column_rows(a.R, T), parts = p.NG * (8 / nr);
-    const double w1 = (double)T * T * T / 6.0, w2 = (double)T * parts * (nr == 1 ? 3.0 : nr == 2 ? 5.0 : 8.0), w3 = (double)p.NG * T * T / 2.0;
-    const int64_t k1 = 2 * T, k2 = parts + (parts + 1) / 2, k3 = p.NG + p.NG * T / 6;
-    int avail = flow_grid(cus, T * (T + 9 * p.NG)) - 1;
-    if (k1 + k2 + k3 <= avail) {
-        p.f.n1 = (int)k1; p.f.n2 = (int)k2; p.f.n3 = (int)k3;
-    } else {
-        p.f.n1 = std::max<int>((int)(avail * w1 / (w1 + w2 + w3)), (int)std::min<int64_t>(k1, avail / 3));
-        p.f.n1 = std::max(1, std::min(p.f.n1, avail - 2));
-        p.f.n2 = std::max(1, std::min(avail - p.f.n1 - 1, (int)((avail - p.f.n1) * w2 / (w2 + w3) + 0.5)));
-        p.f.n3 = avail - p.f.n1 - p.f.n2;
-    }
+    const FlowElimPlan plan = flow_eliminate_plan(cus, a.d, a.R);
+    const int nr = plan.nr;
+    p.f.n1 = plan.n1; p.f.n2 = plan.n2; p.f.n3 = plan.n3;
     const int wgs = 1 + p.f.n1 + p.f.n2 + p.f.n3;
     switch (nr) {
     case 1: hipLaunchKernelGGL(flow_eliminate_kernel<1>, dim3(wgs), dim3(NT), 0, s, p); break;
@@ -1076,43 +1100,62 @@ constexpr int BATCH_INVERSE_WGS = 8;      // a layer of 4 blocks: the chain, and
 
 int flow_batch_most_wgs(int cus, int n) { return cus + n * (BATCH_INVERSE_WGS + 8); }
 
-void flow_batch_plan(int cus, int n, const FlowElimArgs* a, const double* const* H, double damp, double damp_abs, int* const* words, void* inv_desc,
-                     void* elim_desc, uint16_t* inv_of, uint16_t* elim_of, int* const* notpd_h, FlowBatchPlan* plan)
+// How the workgroups of the batched elimination are dealt, and the rows per wavefront (the same for all layers).
+void flow_batch_deal(int cus, int n, const int* d, const int* R, FlowElimPlan* out)
 {
-    // Rows per wavefront for all layers: the longest chains against twice the pure work over the device (see column_rows).
-    const double cost[3] = {7.5, 11.0, 18.0};
+    // Rows per wavefront: the longest chains against twice the pure work over the device (see column_rows).
     double least = 0.0, total = 0.0;
-    plan->nr = 1;
+    int nr = 1;
     for (int i = 0; i < 3; ++i) {
         double chains = 0.0, work = 0.0;
         for (int l = 0; l < n; ++l) {
-            const double T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB;
-            chains = std::max(chains, T * std::max(15.3, cost[i] + 2.5));
-            work += T * NG * (8 >> i) * cost[i] * 2.0 / (cus - 1);
+            const double T = (d[l] + NB - 1) / NB, NG = (R[l] + NB - 1) / NB;
+            chains = std::max(chains, T * std::max(15.3, PART_US[i] + 2.5));
+            work += T * NG * (8 >> i) * PART_US[i] * 2.0 / (cus - 1);
         }
         const double time = std::max(chains, work);
-        if (i == 0 || time < least) { least = time; plan->nr = 1 << i; }
+        if (i == 0 || time < least) { least = time; nr = 1 << i; }
     }
     int fixed = 0;
     for (int l = 0; l < n; ++l) {
-        const int T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB;
+        const int T = (d[l] + NB - 1) / NB, NG = (R[l] + NB - 1) / NB;
         total += (double)T * NG;
         fixed += 1 + std::min(T, 4) + std::min(NG, 4);
     }
-    // the device's workgroups, less those that every layer needs, in proportion to the layers' blocks of rows and columns
+    // the device's workgroups, less those that every layer needs, in proportion to the layers' blocks of rows and columns; of a
+    // layer's, what the sums of its rows want beyond the four (by work: one layer of 16000 x 256 1494 us with four, 1159 with
+    // a launch per stage, 490 so)
     const int budget = std::max(cus - fixed, n);
+    for (int l = 0; l < n; ++l) {
+        const int T = (d[l] + NB - 1) / NB, NG = (R[l] + NB - 1) / NB, parts = NG * (8 / nr);
+        const int base = std::min(NG, 4), share = (int)(budget * (double)T * NG / total);
+        const double w2 = work_columns(T, NG, nr, d[l]), w3 = work_groups(T, NG);
+        const int more = std::max(0, std::min(std::min((int)((base + share) * w3 / (w2 + w3)), NG) - base, share - 1));
+        out[l].nr = nr;
+        out[l].n1 = std::min(T, 4);
+        out[l].n2 = std::max(1, std::min(parts, share - more));
+        out[l].n3 = base + more;
+    }
+}
+
+void flow_batch_plan(int cus, int n, const FlowElimArgs* a, const double* const* H, double damp, double damp_abs, int* const* words, void* inv_desc,
+                     void* elim_desc, uint16_t* inv_of, uint16_t* elim_of, int* const* notpd_h, FlowBatchPlan* plan)
+{
+    FlowElimPlan deal[BATCH_MAX_LAYERS];
+    int ds[BATCH_MAX_LAYERS], Rs[BATCH_MAX_LAYERS];
+    for (int l = 0; l < n; ++l) { ds[l] = a[l].d; Rs[l] = a[l].R; }
+    flow_batch_deal(cus, n, ds, Rs, deal);
+    plan->nr = deal[0].nr;
     plan->inv_wgs = plan->elim_wgs = 0;
     for (int l = 0; l < n; ++l) {
-        const int T = (a[l].d + NB - 1) / NB, NG = (a[l].R + NB - 1) / NB, parts = NG * (8 / plan->nr);
+        const int T = (a[l].d + NB - 1) / NB;
         const int wi = std::min(1 + 2 * T * T, BATCH_INVERSE_WGS);
         const FlowInverseP ip = inverse_params(H[l], a[l].d, damp, damp_abs, const_cast<double*>(a[l].Hinv), a[l].tiles, a[l].gt, words[l], notpd_h[l],
                                                a[l].stalled, a[l].looks, wi);
         memcpy(static_cast<unsigned char*>(inv_desc) + (size_t)l * sizeof(FlowInverseP), &ip, sizeof ip);
         for (int w = 0; w < wi; ++w) inv_of[plan->inv_wgs++] = (uint16_t)l;
         FlowElimP ep = eliminate_params(a[l]);
-        ep.f.n1 = std::min(T, 4);
-        ep.f.n2 = std::max(1, std::min(parts, (int)(budget * (double)T * NG / total)));
-        ep.f.n3 = std::min(NG, 4);
+        ep.f.n1 = deal[l].n1; ep.f.n2 = deal[l].n2; ep.f.n3 = deal[l].n3;
         memcpy(static_cast<unsigned char*>(elim_desc) + (size_t)l * sizeof(FlowElimP), &ep, sizeof ep);
         for (int w = 0; w < 1 + ep.f.n1 + ep.f.n2 + ep.f.n3; ++w) elim_of[plan->elim_wgs++] = (uint16_t)l;
     }

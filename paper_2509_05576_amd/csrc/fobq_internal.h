@@ -245,7 +245,7 @@ hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, i
 int64_t flow_inverse_words(int d);
 size_t flow_tiles_bytes(int d);
 size_t flow_gt_bytes(int d);
-// The shared-Hinv elimination and the column loop of a whole layer in one launch.  words: flow_eliminate_words(d, R) zeroed words;
+// The shared-Hinv elimination and the column loop of a whole layer in one launch.  words: flow_eliminate_words(cus, d, R) zeroed words;
 // tiles, tilesN: flow_tiles_bytes(d); gt: flow_gt_bytes(d); vec: 128 doubles per 64 columns; wt, dt: flow_rows_bytes(d, R);
 // corr: 2 x Rp x 64; lossrow: zeroed; Wout may be null.
 struct FlowElimArgs {
@@ -256,9 +256,13 @@ struct FlowElimArgs {
     int *words, *notpd, *stalled;
     int looks;
 };
-int64_t flow_eliminate_words(int d, int R);
+int64_t flow_eliminate_words(int cus, int d, int R);
 int64_t flow_eliminate_words_most(int d, int R);     // however many rows a wavefront takes
 size_t flow_rows_bytes(int d, int R);
+// rows per wavefront of a part of columns, and the workgroups that serve each queue first
+struct FlowElimPlan { int nr, n1, n2, n3; };
+FlowElimPlan flow_eliminate_plan(int cus, int d, int R);
+void flow_batch_deal(int cus, int n, const int* d, const int* R, FlowElimPlan* out);
 hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a);
 hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, double damp, double damp_abs, double* Hinv, double* tiles,
                                double* gt, int* words, int* notpd, int* stalled, int looks);

@@ -25,3 +25,35 @@ def test_bad_plans_are_refused():
     for args in ([0, 1, 1, 1, 0, 1, 1], [1, 1, 1, 1, -1, 1, 1], [1, 1, 1 << 20, 4096, 0, 1, 1], [1, 1, 1]):
         with pytest.raises(fobq.FobqError):
             fobq.fobq_debug_plan(fobq.PLAN_PAD, args, 2)
+
+
+PART_US, GROUP_US, PRODUCT_US = {1: 7.5, 2: 11.0, 4: 18.0}, 5.0, 3.4       # measured on an MI355X: a part of columns, a sum's own time, one of its products
+
+
+def _queue_us(r, d, nr, n1, n2, n3):
+    """What every workgroup of queues 2 and 3 has to do, and the chain."""
+    t, ng = -(-d // 64), -(-r // 64)
+    return t * ng * (8 // nr) * PART_US[nr] / n2, t * ng * (t / 2 * PRODUCT_US + GROUP_US) / n3, t * 15.3
+
+
+# from one block to many, from one row to the most, and a smaller device
+@pytest.mark.parametrize("cus", [256, 64])
+@pytest.mark.parametrize("d", [1, 64, 65, 200, 256, 512, 1024, 4608])
+@pytest.mark.parametrize("r", [1, 64, 300, 2000, 16000, 65535])
+def test_no_queue_of_an_elimination_is_left_without_workgroups(r, d, cus):
+    nr, n1, n2, n3 = fobq.fobq_debug_plan(fobq.PLAN_ELIMINATE, [cus, r, d], 4)
+    assert min(n1, n2, n3) >= 1 and 1 + n1 + n2 + n3 <= cus
+    parts, groups, chain = _queue_us(r, d, nr, n1, n2, n3)
+    assert groups <= 2.0 * max(parts, chain) + 2 * GROUP_US, (parts, groups, chain)
+
+
+@pytest.mark.parametrize("layers", [[(40000, 256), (1, 1)], [(65535, 64), (64, 64)], [(20000, 256)] + [(64, 64)] * 30, [(1024, 256)] * 6 + [(64, 100)] * 14,
+                                    [(64, 256)] * 256])
+def test_no_queue_of_a_batched_elimination_is_left_without_workgroups(layers):
+    out = fobq.fobq_debug_plan(fobq.PLAN_ELIMINATE, [256] + [x for layer in layers for x in layer], 4 * len(layers))
+    for l, (r, d) in enumerate(layers):
+        nr, n1, n2, n3 = out[4 * l:4 * l + 4]
+        assert min(n1, n2, n3) >= 1 and nr == out[0]
+        parts, groups, chain = _queue_us(r, d, nr, n1, n2, n3)
+        assert groups <= 1.5 * max(parts, chain) + 2 * GROUP_US, (r, d, parts, groups, chain)
+    assert sum(1 + out[4 * l + 1] + out[4 * l + 2] + out[4 * l + 3] for l in range(len(layers))) <= 256 + 16 * len(layers)
