@@ -670,14 +670,15 @@ __global__ __launch_bounds__(NT, 2) void flow_inverse_batch_kernel(const FlowInv
 //   W(p, g) = W[:, block p] (gathered, widened) - sum_{q < p - 1} D_qg^T Un_qp                                       (queue 3)
 //   C(p, s): the 64 sequential steps of block p for its rows, on W(p, g) less the share of block p - 1 that C(p - 1, s)
 //            computed; leaves D_p (w - q, [column][row]), the codes, the loss terms, and its share for block p + 1.  (queue 2)
-// RS = 8 NR: NR rows per wavefront (see column_rows).
+// RS = 8 NR: NR rows per wavefront (see column_rows).  Queues 2 and 3 go through the blocks for NGC groups of rows at a time (see
+// group_run), the last run the rest.
 struct FlowElimP {
     FlowP f;
     double* tilesN;        // T x T: Un; on the diagonal Un inside the block (0 on and below its diagonal)
     double* vec;           // T x 128: reciprocal pivots, 1 / (2 pivot)
     const double* Hu;      // Hinv (original order, upper triangle)
     const int* perm;
-    const float* W; int R, G, gs, NG;
+    const float* W; int R, G, gs, NG, NGC;
     const double* scale; const double* zero; double maxq;
     uint8_t* codesT; int Rp; double* lossrow;
     double* Wout;          // R x d, processing order, or null
@@ -856,6 +857,20 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
     flow_publish(part_word(p, blk, s, parts));
 }
 
+// Ticket t of queue 2 (per = 64 / RS parts to a group) or 3 (per = 1): block and part / group.
+__device__ __forceinline__ void flow_rows_item(const FlowElimP& p, int t, int per, int& blk, int& x)
+{
+    int n = p.NG * per, x0 = 0;
+    if (p.NGC < p.NG) {
+        const int run = t / (p.f.T * p.NGC * per);
+        x0 = run * p.NGC * per;
+        n = min(p.NGC * per, n - x0);
+        t -= p.f.T * x0;
+    }
+    blk = t / n;
+    x = x0 + t - blk * n;
+}
+
 template <int NR>
 __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, int& slot)
 {
@@ -910,7 +925,8 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
             for (;;) {
                 const int t = flow_ticket(f, FW_QUEUE3, &slot);
                 if (t >= T * p.NG) break;
-                const int blk = t / p.NG, x = t - blk * p.NG;
+                int blk, x;
+                flow_rows_item(p, t, 1, blk, x);
                 const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
                 const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
                 d4 c[2];
@@ -934,8 +950,9 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
             for (;;) {
                 const int t = flow_ticket(f, FW_QUEUE2, &slot);
                 if (t >= T * parts) break;
-                const int blk = t / parts;
-                flow_columns<NR>(p, tiles, blk, t - blk * parts);
+                int blk, x;
+                flow_rows_item(p, t, PER, blk, x);
+                flow_columns<NR>(p, tiles, blk, x);
             }
         }
     }
@@ -1014,6 +1031,17 @@ static FlowInverseP inverse_params(const double* H, int d, double damp, double d
     return p;
 }
 
+// Groups of 64 rows that go through all blocks together: rows do not interact, and what a run of them keeps for its later
+// blocks (W and D, 64 KB a block and group) should stay in the 256 MB cache on the memory's side; at least 64 groups, which
+// keep the workgroups busy, and runs of equal length.  The layer in one run and in runs by this rule: 65535 x 512 3.33 and 3.05 ms
+// (2 runs), 65535 x 1024 7.55 and 6.20 (4), 65535 x 2048 19.3 and 16.9 (8), 30000 x 4608 33.2 and 30.4 (9); more runs
+// than that lose: 32000 x 512 1.47 in one, 1.55 in two.
+static int group_run(int64_t T, int64_t NG)
+{
+    const int64_t most = std::max<int64_t>(64, (256 << 20) / (64 << 10) / T), runs = (NG + most - 1) / most;
+    return (int)((NG + runs - 1) / runs);
+}
+
 static FlowElimP eliminate_params(const FlowElimArgs& a)     // all but the numbers of workgroups
 {
     FlowElimP p;
@@ -1021,7 +1049,7 @@ static FlowElimP eliminate_params(const FlowElimArgs& a)     // all but the numb
     p.f.d = a.d;
     p.f.T = (a.d + NB - 1) / NB;
     p.f.words = a.words; p.f.tiles = a.tiles; p.f.gt = a.gt; p.f.notpd = a.notpd; p.f.stalled = a.stalled;
-    p.R = a.R; p.G = a.G; p.gs = a.gs; p.NG = (a.R + NB - 1) / NB;
+    p.R = a.R; p.G = a.G; p.gs = a.gs; p.NG = (a.R + NB - 1) / NB; p.NGC = group_run(p.f.T, p.NG);
     p.tilesN = a.tilesN; p.vec = a.vec; p.Hu = a.Hinv; p.perm = a.perm; p.W = a.W; p.scale = a.scale; p.zero = a.zero;
     p.maxq = (double)((1 << a.bits) - 1);
     p.codesT = a.codesT; p.Rp = a.Rp; p.lossrow = a.lossrow; p.Wout = a.Wout; p.wt = a.wt; p.dt = a.dt; p.corr = a.corr;
