@@ -323,8 +323,11 @@ int fobq_debug_offset_tables(int32_t k, int32_t pad, int64_t h, int64_t w, int32
  *                  out: parts that each padded row is cut into, workgroups
  *   FOBQ_PLAN_ELIMINATE  in: compute units, then d_row, d_col of one layer, or of two or more of a batched call
  *                  out, per layer: rows per wavefront of a part of columns, then the workgroups that first serve the
- *                  tiles of the pivot rows, the parts of columns, the sums of 64 rows */
-typedef enum { FOBQ_PLAN_PAD = 0, FOBQ_PLAN_ELIMINATE = 1 } fobq_plan;
+ *                  tiles of the pivot rows, the parts of columns, the sums of 64 rows
+ *   FOBQ_PLAN_HESSIAN  in: d_col, calibration columns of one fp64 accumulate call, from feature maps (0 / 1)
+ *                  out: tile edge, slabs of an accumulation, slabs that this call can touch */
+typedef enum { FOBQ_PLAN_PAD = 0, FOBQ_PLAN_ELIMINATE = 1, FOBQ_PLAN_HESSIAN = 2 } fobq_plan;
+
 int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out, int32_t n_out);
 
 /* Measurement aid for the X X^T kernel of the int8-slice mode (no part of the method): the rate, in

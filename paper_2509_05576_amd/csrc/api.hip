@@ -871,6 +871,12 @@ int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out,
         out[0] = p.parts; out[1] = p.wgs;
         return FOBQ_OK;
     }
+    if (what == FOBQ_PLAN_HESSIAN && n_in == 3 && n_out == 3) {
+        if (in[0] < 1 || in[0] > MAX_DCOL || in[1] < 1 || in[1] >= (1ll << 31) - 64) return FOBQ_EINVAL;
+        const int splits = xxt_pick_splits((int)in[0]);
+        out[0] = xxt_tile((int)in[0], in[1]); out[1] = splits; out[2] = xxt_slabs_touched((int)in[0], in[1], splits, in[2] != 0);
+        return FOBQ_OK;
+    }
     if (what == FOBQ_PLAN_ELIMINATE && n_in >= 3 && n_in % 2 == 1 && n_in / 2 <= BATCH_MAX_LAYERS && n_out == 4 * (n_in / 2)) {
         const int n = n_in / 2;
         if (in[0] < 16 || in[0] > 4096) return FOBQ_EINVAL;

@@ -181,6 +181,7 @@ struct StageScope {
 hipError_t launch_xxt(hipStream_t s, const float* X, int64_t ld, int d, int64_t n, double* Hpart, int splits, int fresh,
                       LaunchEvents ev = LaunchEvents());
 int xxt_pick_splits(int d);
+int xxt_tile(int d, int64_t n);       // tile edge of a launch over n calibration columns
 int xxt_slabs_touched(int d, int64_t n, int splits, bool conv);
 hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, int count);
 // the padding launch: `parts` runs of `run` pixels (the last one the rest) of each of `rows` rows, wgs workgroups of 256 threads; whether it moves 16 bytes per lane and takes

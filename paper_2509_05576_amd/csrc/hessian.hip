@@ -2,8 +2,8 @@
 //
 // xxt_kernel: fp32 X is read from HBM, staged through LDS as fp32, widened to
 // fp64 when the MFMA fragments are formed (products of two fp32 values are
-// exact in fp64), and accumulated with v_mfma_f64_16x16x4_f64.  Only the tiles (128 x 128;
-// 96, 64 or 160 wide where that spends fewer matrix instructions) on or below the diagonal are
+// exact in fp64), and accumulated with v_mfma_f64_16x16x4_f64.  Only the tiles (128 or 64 wide;
+// in long calls 160 for 129 to 160 columns and 96 for 257 to 288, see xxt_tile) on or below the diagonal are
 // computed, and of a diagonal tile only the 16 x 16 MFMA tiles on or below its diagonal (36 of 64;
 // not at 64, see xxt_diag_cost).
 //
@@ -28,6 +28,7 @@
 // H back into the (c, ky, kx) order.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fobq_internal.h"
@@ -188,22 +189,38 @@ constexpr int xxt_wgs(int xt) { return xt == 64 ? 1024 : xt == 160 ? 256 : 512; 
 constexpr int xxt_diag_cost(int xt, bool conv) { return xt == 128 ? (conv ? 12 : 10) : xt == 96 ? (conv ? 13 : 12) : 16; }
 constexpr int xxt_diag_cost_min(int xt) { return xxt_diag_cost(xt, false); }
 
-// Tile edge for d columns, by the MFMA tiles per chunk that each choice spends (a diagonal tile by its price), over the
-// part of the matrix rate that it reaches on long inputs: 64: 0.73, 96: 0.66, 128: 0.92, 160: 0.60.  d = 147 with 401408
-// columns: 367 us with tiles of 64, 244 with one of 160; d = 288 with 409600: 850 with 64, 722 with 96.
-static int xxt_tile(int d)
+// Tile edge for d columns: 128, or 64 where that spends less than 5/6 of the MFMA tiles ...
+static int xxt_base_tile(int d)
+{
+    const int64_t n128 = (d + 127) / 128, n64 = (d + 63) / 64;
+    const int64_t a128 = n128 * (n128 + 1) / 2 * 128 * 128, a64 = n64 * (n64 + 1) / 2 * 64 * 64;
+    return a64 * 6 < a128 * 5 ? 64 : 128;
+}
+
+// ... and in long calls 160 or 96, by the MFMA tiles per chunk that each choice spends (a diagonal tile by its price), over the
+// part of the matrix rate that it reaches there (measured at d = 128, 147, 288, 1024): 64: 0.73, 96: 0.66, 128: 0.92, 160: 0.60;
+// 5 % in favour of the choice above.  That comes to 160 for 129 to 160 columns and 96 for 257 to 288.
+static int xxt_long_tile(int d)
 {
     auto cost = [&](int xt) {
         const int64_t n = (d + xt - 1) / xt, mt = xt / 16, full = mt * mt;
         return xt == 160 ? (n == 1 ? 56.0 : 1e30) : (double)(n * full * xxt_diag_cost(xt, true) / 16 + n * (n - 1) / 2 * full);
     };
-    const int64_t n128 = (d + 127) / 128, n64 = (d + 63) / 64;
-    const int64_t a128 = n128 * (n128 + 1) / 2 * 128 * 128, a64 = n64 * (n64 + 1) / 2 * 64 * 64;
-    const int base = a64 * 6 < a128 * 5 ? 64 : 128;
+    const int base = xxt_base_tile(d);
     if (d <= 128) return base;               // few products: a tile is cut into so many pieces that their sums weigh more
     const double own = cost(base) / (base == 64 ? 0.73 : 0.92);
     if (cost(160) / 0.60 < own) return 160;
     return cost(96) / 0.66 < 0.95 * own ? 96 : base;
+}
+
+// A short call is over before the wide tiles' matrix rate counts, and their longer prologue and epilogue, on fewer workgroups, remain.
+// Accumulate calls after the first, 64 wide and wide: 147 columns of X, n = 256 6.9 and 12.7 us, 2048 12.8 and 17.5, 4096 23.2 and
+// 23.3, 6144 35.6 and 30.0, 65536 76 and 65; 288 columns, n = 256 7.1 and 11.7, 8192 33.5 and 39.6, 16384 49.7 and 48.7, 24576
+// 64.2 and 60.1, from 32-channel maps 16384 56.8 and 60.6, 25600 74.4 and 74.6, 51200 126 and 113, 400000 826 and 685.
+int xxt_tile(int d, int64_t n)
+{
+    const int wide = xxt_long_tile(d);
+    return n < (wide == 160 ? 4096 : wide == 96 ? 24576 : 0) ? xxt_base_tile(d) : wide;
 }
 
 // The MFMA tiles on and below the diagonal of a B x B grid in the order in which they are dealt to the wavefronts, K
@@ -641,16 +658,19 @@ static int64_t xxt_cost_per_chunk_column(int xt, int nt, int wd)     // cost of 
 // starts inside a range; the range cost is at least the total cost / W.
 int xxt_pick_splits(int d)
 {
-    const int xt = xxt_tile(d);
-    const int nt = (d + xt - 1) / xt;
-    const int64_t per_column = xxt_cost_per_chunk_column(xt, nt, xxt_diag_cost_min(xt));   // either mode fits
-    return (int)((16 * (int64_t)xxt_wgs(xt) + per_column - 1) / per_column) + 1;
+    int most = 0;
+    for (int xt : {xxt_base_tile(d), xxt_long_tile(d)}) {          // calls of either length fit
+        const int nt = (d + xt - 1) / xt;
+        const int64_t per_column = xxt_cost_per_chunk_column(xt, nt, xxt_diag_cost_min(xt));   // either mode fits
+        most = std::max(most, (int)((16 * (int64_t)xxt_wgs(xt) + per_column - 1) / per_column) + 1);
+    }
+    return most;
 }
 
 static XxtPlan xxt_plan(int d, int64_t n, int splits, bool conv)
 {
     XxtPlan p;
-    p.xt = xxt_tile(d);
+    p.xt = xxt_tile(d, n);
     p.nt = (d + p.xt - 1) / p.xt;
     p.chunks = (int)((n + XK - 1) / XK);
     p.items = ((int64_t)p.nt * (p.nt + 1) / 2) * p.chunks;
@@ -674,12 +694,12 @@ int xxt_slabs_touched(int d, int64_t n, int splits, bool conv)
     return (int)(p < splits ? p : splits);
 }
 
-// Zero the part of the slabs [first, first + count) that xxt_kernel adds into and the finalize kernels read:
-// the tiles on and below the diagonal, i.e. in row a the columns up to the end of its diagonal tile.
-__global__ __launch_bounds__(256) void clear_slabs_kernel(double* __restrict__ Hpart, int d, int xt, int first)
+// Zero the part of the slabs [first, first + count) that the finalize kernels read, the lower triangle, whole tiles of 64 on the
+// diagonal.  (A wider diagonal tile adds into entries above that part too; nothing reads those.)
+__global__ __launch_bounds__(256) void clear_slabs_kernel(double* __restrict__ Hpart, int d, int first)
 {
     const int a = blockIdx.x;
-    const int lim = min(d, (a / xt + 1) * xt);
+    const int lim = min(d, (a / 64 + 1) * 64);
     double* __restrict__ row = Hpart + ((int64_t)(first + blockIdx.y) * d + a) * d;
     for (int c = threadIdx.x; c < lim; c += 256) row[c] = 0.0;
 }
@@ -687,7 +707,7 @@ __global__ __launch_bounds__(256) void clear_slabs_kernel(double* __restrict__ H
 hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, int count)
 {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(clear_slabs_kernel, dim3(d, count), dim3(256), 0, s, Hpart, d, xxt_tile(d), first);
+    hipLaunchKernelGGL(clear_slabs_kernel, dim3(d, count), dim3(256), 0, s, Hpart, d, first);
     return hipGetLastError();
 }
 

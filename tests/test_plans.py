@@ -57,3 +57,14 @@ def test_no_queue_of_a_batched_elimination_is_left_without_workgroups(layers):
         parts, groups, chain = _queue_us(r, d, nr, n1, n2, n3)
         assert groups <= 1.5 * max(parts, chain) + 2 * GROUP_US, (r, d, parts, groups, chain)
     assert sum(1 + out[4 * l + 1] + out[4 * l + 2] + out[4 * l + 3] for l in range(len(layers))) <= 256 + 16 * len(layers)
+
+
+# the wide tiles of the fp64 Hessian are for long calls: in short ones (an image, a small batch) they were 1.3 to 1.9 times as slow
+@pytest.mark.parametrize("conv", [0, 1])
+@pytest.mark.parametrize("d", list(range(120, 300, 3)) + [129, 160, 161, 257, 288, 289, 512, 2304, 8192])
+def test_short_hessian_calls_take_the_small_tiles(d, conv):
+    wide = 160 if 129 <= d <= 160 else 96 if 257 <= d <= 288 else 0
+    for n in (1, 196, 2048, 4095, 4096, 8192, 24575, 24576, 400000, (1 << 31) - 65):
+        tile, slabs, touched = fobq.fobq_debug_plan(fobq.PLAN_HESSIAN, [d, n, conv], 3)
+        assert tile == wide if wide and n >= (4096 if wide == 160 else 24576) else tile in (64, 128)
+        assert 1 <= touched <= slabs
