@@ -72,8 +72,8 @@ def sweep(model: str, steps: int, warmup: int, concurrency: int, iid: bool, int8
 
     Two measurements, each the MEDIAN over `steps` whole-model runs after `warmup`: (1) one layer after the
     other on one context (`sequential_ms`); (2) up to `concurrency` layers in flight on as many contexts /
-    streams (layers are independent of each other; most of a layer is a chain of short dependent launches
-    that leaves the GPU nearly idle, so layers overlap): `ms_per_step`, the whole-model time.
+    streams (layers are independent of each other; most of a layer is a chain of short dependent steps
+    that needs a part of the GPU, so layers overlap): `ms_per_step`, the whole-model time.
     After the timed region every layer is run once more and checked on the device: `perm` is a permutation,
     Q = scale * (code - zero), codes within the grid, and the loss the path reports equals
     1/2 tr(dW H_d dW^T) evaluated from the path's own Hessian; a miss fails the run."""

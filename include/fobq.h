@@ -184,7 +184,7 @@ int fobq_hessian_form(fobq_ctx* ctx, int32_t* form);
  *   e = (w - q) / [Hinv]_tt into the columns not yet quantized (Eq. 9 / 11) and
  *   eliminate the column from the one shared Hinv (Eq. 12).
  * W: device fp32 d_row x d_col.  H: device fp64 d_col x d_col full symmetric
- * undamped Hessian, or NULL to use the one accumulated in the context
+ * undamped Hessian (its lower triangle is read), or NULL to use the one accumulated in the context
  * (fobq_hessian_finalize must have been called with the same d_col).
  * The call enqueues all work on the context's stream, then SYNCHRONISES the
  * stream and reports device-detected failures (ENOTPD, bad custom permutation).
@@ -198,7 +198,7 @@ int fobq_quantize_layer(fobq_ctx* ctx, const float* W, int64_t d_row, int64_t d_
 /*
  * The same in two halves, for callers that keep several contexts busy at once (layers are
  * independent of each other, Section 3; most of a layer's work is a chain of short dependent
- * launches that leaves the GPU nearly idle, so layers on different contexts / streams overlap well):
+ * steps that needs a part of the GPU, so layers on different contexts / streams overlap well):
  *   fobq_quantize_layer_enqueue  checks the arguments, enqueues all work and returns without
  *                                waiting; W, H, perm_in and the outputs must stay valid until
  *                                fobq_finish returns.  Only Hessian accumulation for the next

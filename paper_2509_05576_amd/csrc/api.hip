@@ -931,7 +931,8 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     const fobq_out* out = p.out;
     const int R = p.R, d = p.d, G = p.G, steps = p.steps, block = p.block, Rp = p.Rp, nblocks = p.nblocks;
     // grid and the W-only part of the column scores: on the side stream, beside the factorization.  The
-    // events that order the streams ride on launches (see gemm64's `done`), here on the clearing kernel.
+    // events that order the streams ride on launches as their stop events (`done`; recorded between two dependent
+    // launches each would be a bubble of about 4 us), here on the clearing kernel.
     FOBQ_TRY(launch_clear_words(s, ctx->flags.p, FLAG_COUNT, ctx->words.p, ctx->words_len, ctx->sync_ev[EV_FORK]),
              "clear flags and loss");
     FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");

@@ -21,8 +21,11 @@
 // Everything that one workgroup hands to another during a launch goes through relaxed agent-scope atomic accesses
 // (loads and stores that bypass the caches which are not shared): the producer stores a tile, waits until its stores
 // are done, and sets the tile's word after a release fence; the consumer reads the word until it is set and loads.
-// Measured: 1.85 us from the first store of a 32 KB tile to its last load on another XCD, and 16 TB/s when 256
-// workgroups read tiles this way, against 9.6 TB/s that the products want at the full matrix rate.
+// Measured with a kernel that does nothing else: 1.85 us from the first store of a 32 KB tile to its last load by a workgroup on
+// another XCD, and 16 TB/s when 256 workgroups read published tiles this way, against 9.6 TB/s that the products want at the
+// full matrix rate.
+// Registers: the inverse 198 VGPRs; the elimination, with the chain, the tiles and the column parts in one body, 252, and 144 to
+// 157 SGPRs kept in lanes of vector registers (no scratch in either).
 #include <string.h>
 
 #include <algorithm>

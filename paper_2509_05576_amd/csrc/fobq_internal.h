@@ -270,8 +270,8 @@ hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, d
 
 // factor.hip
 // `rows_ready` (may be null): rows_ready[k] is recorded on the context's stream once the pivot rows of
-// block k (rows k*block .. of U and Un) are complete.  In the fused form the event rides on the panel launch
-// as its stop event: a separate hipEventRecord between two dependent launches would be a bubble of about 4 us.
+// block k (rows k*block .. of U and Un) are complete (hipEventRecord: about 4 us on the stream, in a path of three launches a
+// block).
 hipError_t eliminate_blocked(fobq_ctx* c, double* A, int d, int steps, int block, double* U, double* Un, int* flag,
                              const std::vector<hipEvent_t>* rows_ready);
 

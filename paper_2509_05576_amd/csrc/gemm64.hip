@@ -10,8 +10,6 @@
 // then stored to LDS.  The C tile is prefetched with the first chunk.  The rank-64
 // updates (K = 64) are latency bound -- a few tiles per launch -- so a single
 // exposed memory round trip is what matters there.
-#include <hip/hip_ext.h>
-
 #include "fobq_internal.h"
 
 namespace fobq {

@@ -621,8 +621,8 @@ __global__ __launch_bounds__(64 * xxt_waves(XT), XT == 64 ? 4 : 2) void xxt_kern
         }
 
         // An accumulation's first launch finds nothing in its slabs and stores; where a tile has fewer pieces than the launch
-        // has slabs (fresh), its workgroups put zeros into the others in turn.  (d = 512, 50176 columns: 295 us with a launch
-        // that clears 61 slabs and the sums read and written, 260 so.)
+        // has slabs (fresh), its workgroups put zeros into the others in turn.  (d = 512, 50176 columns, accumulate and
+        // finalize: 295 us with a launch that clears 61 slabs and the sums read and written, 251 so.)
         if (fresh > 0) {
             const int64_t tile_last = tile_first + chunks - 1;
             int64_t last_range = (diag ? (tile_last + 1) * WD : diag_cost + (tile_last + 1 - diag_items) * 16) / range_cost;
