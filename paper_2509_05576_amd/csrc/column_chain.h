@@ -70,7 +70,7 @@ __device__ __forceinline__ void chain_steps(double (&w)[NR], const double* Us, c
         const double cz = fmin(fmax(c0, lo[r]), hi[r]);
         mycode[r] = cz + z[r];
         mydiff[r] = w[r] - s[r] * cz;
-        suspect = suspect || (fabs(fabs(tq - c0) - 0.5) < 1.0e-9 * fmax(1.0, fabs(tq))) || !(fabs(mydiff[r]) <= 1.7976931348623157e308);
+        suspect |= (fabs(fabs(tq - c0) - 0.5) < 1.0e-9 * fmax(1.0, fabs(tq))) | __builtin_amdgcn_class(mydiff[r], 0x207);      // NaN, -inf, inf
     }
 }
 
