@@ -40,8 +40,8 @@ typedef enum {
     FOBQ_EINVAL = -1, /* bad argument (shape, bits, group, NULL pointer, bad permutation)  */
     FOBQ_ENOMEM = -2, /* device or host allocation failed                                   */
     FOBQ_EHIP = -3,   /* a HIP call failed (fobq_last_error has the HIP error string), or the
-                         workgroups of a factorization launch that were running waited for about
-                         a minute during which none of that launch started or finished a tile:
+                         workgroups of a factorization launch that were running waited for some
+                         45 s during which none of that launch started or finished a tile:
                          other work may delay a call without limit as long as it moves at all  */
     FOBQ_ENOTPD = -4, /* a Cholesky / elimination pivot was <= 0 or not finite              */
     FOBQ_ESTATE = -5  /* call sequence error (e.g. accumulate before begin)                 */
@@ -297,7 +297,7 @@ int fobq_debug_fail_after(fobq_ctx* ctx, int n);
 
 /* Test hook for the waits inside the factorization launches: from now on a launch of this context gives up
  * (FOBQ_EHIP, outputs unspecified, the context stays usable) after `looks` looks of a waiting wavefront (about
- * a microsecond each) during which no workgroup of the launch drew a tile; 0: at its first wait; < 0: the
+ * 0.2 us each) during which no workgroup of the launch drew a tile; 0: at its first wait; < 0: the
  * library's own limit. */
 int fobq_debug_wait_looks(fobq_ctx* ctx, int looks);
 

@@ -280,7 +280,7 @@ static int read_flags(fobq_ctx* ctx, const int* dev_flags)
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
     FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
-    if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for about a minute and was given up");
+    if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for three quarters of a minute and was given up");
     if (h[FLAG_BADPERM]) return set_err(ctx, FOBQ_EINVAL, "perm_in is not a permutation of 0..d_col-1");
     if (h[FLAG_NOTPD_H]) return set_err(ctx, FOBQ_ENOTPD, "damped Hessian is not positive definite (Cholesky pivot <= 0)");
     if (h[FLAG_NOTPD_HINV]) return set_err(ctx, FOBQ_ENOTPD, "shared inverse Hessian lost positive definiteness (elimination pivot <= 0)");
@@ -1266,7 +1266,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         FOBQ_TRY(hipStreamSynchronize(s), "synchronize");
         for (int l = 0; l < n_layers; ++l) {
             if (hflags[4 * l + FLAG_STALLED])
-                return set_err(ctx, FOBQ_EHIP, "layer %d: a factorization launch drew no tile for about a minute and was given up", l);
+                return set_err(ctx, FOBQ_EHIP, "layer %d: a factorization launch drew no tile for three quarters of a minute and was given up", l);
             if (hflags[4 * l + FLAG_NOTPD_H])
                 return set_err(ctx, FOBQ_ENOTPD, "layer %d: damped Hessian is not positive definite (Cholesky pivot <= 0)", l);
             if (hflags[4 * l + FLAG_NOTPD_HINV])

@@ -14,7 +14,7 @@
 // order in which whatever a tile waits for stands before it; each queue is a part of that order, and the workgroup that
 // walks the chain is the first to start, the next ones serve one queue each.  So the earliest unfinished tile has its
 // workgroup as soon as one workgroup per queue is resident, it can always proceed, and every wait ends.  (Should a launch stop
-// all the same -- nobody draws a ticket for about a minute, see flow_gives_up -- its waits give up, it drains and the call
+// all the same -- nobody draws a ticket for three quarters of a minute, see flow_gives_up -- its waits give up, it drains and the call
 // fails.  A wait may be as long as it likes while tickets are drawn: foreign work on the device only delays it.)
 //
 // Exchange between compute units.  Each XCD has its own L2, which is not coherent with the others inside a launch.

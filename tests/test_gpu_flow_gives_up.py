@@ -51,14 +51,14 @@ def test_a_launch_that_is_given_up_fails_the_call_only(fobq, form):
                 assert torch.equal(a, b)
 
 
-# most of these launches' wavefronts wait for several of the chain's blocks, 15 us each, at a time: far more than 256 looks; the launch
-# as a whole draws tiles all the while
+# most of these launches' wavefronts wait for many of the chain's blocks, 15 us each, at a time: more than 768 looks of 0.16 us or
+# more; the launch as a whole draws tiles all the while
 @pytest.mark.parametrize("r,d", [(64, 3000), (300, 4608)])
 def test_long_waits_of_a_launch_that_moves_are_waited_for(fobq, r, d):
     W, H = _layer(r, d)
     with fobq.Ctx(0) as ctx:
         want = ctx.quantize_layer(W, H, bits=4)
-        fobq.fobq_debug_wait_looks(ctx.handle, 256)
+        fobq.fobq_debug_wait_looks(ctx.handle, 768)
         got = ctx.quantize_layer(W, H, bits=4)
     for a, b in zip((got.codes, got.Q, got.perm, got.loss), (want.codes, want.Q, want.perm, want.loss)):
         assert torch.equal(a, b)
