@@ -1,6 +1,8 @@
 // 64 x 64 diagonal blocks of the factorizations, held in LDS by one workgroup (device code shared by factor.hip and
 // flow.hip).
 #pragma once
+#include <type_traits>
+
 #include "fobq_internal.h"
 
 namespace fobq {
@@ -12,20 +14,19 @@ constexpr int NB = 64;
 // work on it as a 4 x 4 grid of 16 x 16 tiles.  The only sequential arithmetic is
 // the unblocked sweep over the 16 pivots of a diagonal tile: one wavefront, one
 // row (Cholesky) or column (elimination) of the whole block per lane, so the same
-// sweep also produces the tiles below (right of) the diagonal tile; pivot rows are
-// broadcast with v_readlane (next column) and LDS reads (the columns after it).  A
-// wavefront on its own issues one instruction of any kind per 5 to 8 cycles, so the
-// sweep costs its instruction count.  The triangular inverse of a diagonal tile comes out
-// of the same sweep, in lanes it would leave idle (the first tile's: a forward
-// substitution on a second wavefront during the next sweep).  Everything else --
+// sweep also produces the tiles below (right of) the diagonal tile, and, in lanes it
+// would leave idle, the triangular inverse of the diagonal tile.  A wavefront on its
+// own issues one instruction of any kind per 5 to 8 cycles, and a value that goes
+// through v_readlane or LDS to other lanes is late by as much again; so every row of 16
+// lanes keeps a copy of the diagonal tile, and pivots and multipliers reach the lanes as
+// DPP operands of the multiply-adds themselves.  Everything else --
 // trailing update, assembly of the 64 x 64 triangular inverse from the tile
 // inverses -- is 16 x 16 x 16 products on the matrix cores (4 MFMAs each), one tile
 // per wavefront, one interval behind the sweeps.
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int NT = 512;   // threads per workgroup of every kernel that uses these routines (8 wavefronts)
 constexpr int DL = 66;    // LDS row stride (doubles): conflict-free 8-byte MFMA fragment reads per half-wave
-constexpr int CB0 = 48, CB_LEN = CB0 + 16 * 16 + 48;   // sweep column buffer: see chol_block
-constexpr int SWEEP_LDS = NB + CB_LEN + 16 * DL;   // doubles of LDS that chol_block / elim_block need besides the two tiles
+constexpr int SWEEP_LDS = NB + 16 * DL + 2;   // doubles of LDS that chol_block / elim_block need besides the two tiles
 
 __device__ __forceinline__ double readlane_f64(double v, int lane)
 {
@@ -52,6 +53,44 @@ __device__ __forceinline__ double pivot_rsqrt(double x)
     const double y0 = __builtin_amdgcn_rsq(x);
     const double e = fma(-(x * y0), y0, 1.0);
     return fma(y0 * e, fma(0.375, e, 0.5), y0);
+}
+
+// Lane K of every row of 16 lanes, to the whole row (DPP row_newbcast, which 64-bit operations take).  The compiler does not see
+// into the asm and so does not keep the two wait states that DPP wants between a vector instruction and the one that reads its
+// result across lanes: every statement brings its own where the value may be that young, and row_product hands on a factor
+// that is old enough for any number of uses.
+template <int K>
+__device__ __forceinline__ double row_lane(double v)
+{
+    double x;
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "=v"(x) : "v"(v), "n"(K));
+    return x;
+}
+__device__ __forceinline__ double row_factor(double a, double b)      // a * b
+{
+    double x;
+    asm("v_mul_f64 %0, %1, %2\n\ts_nop 1" : "=v"(x) : "v"(a), "v"(b));
+    return x;
+}
+// acc -= (lane K of f) * m
+template <int K>
+__device__ __forceinline__ void row_update(double& acc, double f, double m)
+{
+    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(f), "v"(m), "n"(K));
+}
+template <int K, int N, class F>
+__device__ __forceinline__ void unroll(F f)           // f(integral_constant<K>) .. f(integral_constant<N - 1>)
+{
+    if constexpr (K < N) {
+        f(std::integral_constant<int, K>{});
+        unroll<K + 1, N>(f);
+    }
+}
+
+__device__ __forceinline__ void identity_rows(double* idt, int fr, int fq)
+{
+#pragma unroll
+    for (int u = 0; u < 4; ++u) idt[(4 * u + fq) * DL + fr] = 4 * u + fq == fr ? 1.0 : 0.0;
 }
 
 // The same value, which the compiler computes where it stands and does not know: keeps lane-dependent constants from being
@@ -100,15 +139,14 @@ __device__ __forceinline__ void inv_tile(double* Xm, TF tfetch, int i, int j, in
     inv_tile_finish(Xm, i, j, inv_tile_sum(Xm, tfetch, i, j, j, i, d4{0.0, 0.0, 0.0, 0.0}, fr, fq), fr, fq);
 }
 
-// Schedule shared by chol_block and elim_block.  sweep(b): pivots of diagonal tile b and the
-// tiles below / right of it -- and, for b >= 1, the inverse X_bb of the diagonal tile, carried along in
-// 16 lanes that the sweep leaves idle; tinv(0): triangular inverse of diagonal tile 0 into Xm;
-// trail(b): update of the tiles behind tile row/column b; tf: tile fetch for inv_tile.
+// Schedule shared by chol_block and elim_block.  sweep(b): pivots of diagonal tile b, the
+// tiles below / right of it and the inverse X_bb of the diagonal tile; trail(b): update of the tiles
+// behind tile row/column b; tf: tile fetch for inv_tile.
 //   interval   wavefront 0        wavefront 1   wavefront 2   wavefronts 3, 4, 5
 //   b = 0      sweep(0)
-//   b = 1      sweep(1) + X_11    tinv(0)
-//   b = 2      sweep(2) + X_22                  X_10
-//   b = 3      sweep(3) + X_33    X_21          X_20          the sums of X_30, X_31, X_32 as far as they
+//   b = 1      sweep(1)
+//   b = 2      sweep(2)                         X_10
+//   b = 3      sweep(3)           X_21          X_20          the sums of X_30, X_31, X_32 as far as they
 //                                                             do not need this interval's tiles
 //   then                                                      rest of the sums, times -X_33
 //   (after each of b = 0..2: trail(b) on all wavefronts)
@@ -117,8 +155,8 @@ __device__ __forceinline__ void inv_tile(double* Xm, TF tfetch, int i, int j, in
 // not read (it reads the first tile column / row only; the diagonal entries of later tiles that its lanes carry along are not
 // used).  `ahead` is called by every wavefront about 2 us before the end (wavefront 0: after the last sweep).
 struct Nothing { __device__ void operator()() const {} };
-template <class SW, class TI, class TR, class TF, class BS, class AH>
-__device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TI tinv, TR trail, TF tf, BS beside, AH ahead)
+template <class SW, class TR, class TF, class BS, class AH>
+__device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TR trail, TF tf, BS beside, AH ahead)
 {
     const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int fr = lane & 15, fq = lane >> 4;
@@ -129,7 +167,6 @@ __device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TI tinv, TR
         if (b == 3 && wave != 0) ahead();
         if (wave == 0) sweep(b);
         else if (b == 0) beside();
-        else if (wave == 1 && b == 1) tinv(0);
         else if (wave == 2 && b == 2) inv_tile(Xm, tf, 1, 0, fr, fq);
         else if (wave == 1 && b == 3) inv_tile(Xm, tf, 2, 1, fr, fq);
         else if (wave == 2 && b == 3) inv_tile(Xm, tf, 2, 0, fr, fq);
@@ -153,101 +190,64 @@ __device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TI tinv, TR
 //   in : Am lower triangle = the block (identity padding past its size); Xm need not be initialised (every
 //        entry of its lower triangle, whole diagonal 16 x 16 tiles included, is written before it is read)
 //   out: Am = L (lower; what is above the diagonal is not defined),
-//        Xm = L^-1 (lower);  rq (SWEEP_LDS doubles of LDS) is scratch: 1 / L[k][k], then the sweep columns
+//        Xm = L^-1 (lower);  scratch: SWEEP_LDS doubles of LDS
 //   flag: set to 1 when a pivot is <= 0 or not finite (the pivot is replaced by 1 so that
 //         the arithmetic stays finite; the caller reports ENOTPD).
 // Called by all NT threads of the workgroup; ends with a barrier.
 template <class BS = Nothing, class AH = Nothing>
-__device__ __forceinline__ void chol_block(double* Am, double* Xm, double* rq, int* __restrict__ flag, BS beside = BS(), AH ahead = AH())
+__device__ __forceinline__ void chol_block(double* Am, double* Xm, double* scratch, int* __restrict__ flag, BS beside = BS(), AH ahead = AH())
 {
     const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, fq = lane >> 4;
-    // The columns of the running sweep: column k at cb[CB0 + 16 k + r], r = row - tile base.  Only the
-    // 16 tile rows are read; what the other lanes write falls into the slots of neighbouring columns,
-    // which is harmless: a column is read right after it is written, before the next one is written.
-    double* cb = rq + NB;
-    double* idt = cb + CB_LEN; // 16 rows of the identity, row stride DL (read from the second sweep on)
-    if (tid < 256) idt[(tid >> 4) * DL + (tid & 15)] = (tid >> 4) == (tid & 15) ? 1.0 : 0.0;
+    double* idt = scratch;     // 16 rows of the identity, row stride DL: written and read by the wavefront of the sweeps
+    if (wave == 0) identity_rows(idt, fr, fq);
 
-    // Right-looking Cholesky of the 16 columns base .. base+15 of the block over all rows
-    // >= base: lane rho holds row rho.  Rows inside the diagonal tile (0 <= r < 16) hold the
-    // tile row (what lies right of its diagonal is carried along and never used); rows below it
-    // (r >= 16) get their part of L in the same sweep (l_rho,k = (a_rho,k - sum l l) / l_kk);
-    // rows above (r < 0) idle on harmless values.
+    // Right-looking Cholesky of the 16 columns base .. base+15 of the block over all rows >= base.  Every row of 16
+    // lanes holds the diagonal tile (lane s tile row s; what lies right of its diagonal is carried along and never
+    // used), so the pivot and the multipliers of the columns are operands of the instructions that use them, and beside
+    // it, lane rho, row rho of the block below the tile (their part of L: l_rho,k = (a_rho,k - sum l l) / l_kk), or,
+    // in the lanes of the tile itself, the rows of the identity, which become I L_bb^-T: lane s ends with column s of
+    // X_bb = L_bb^-1.  The lanes above idle on rows of the identity.
     auto sweep = [&](int b) {
-        const int base = 16 * b, rho = lane, r = rho - base;
-        // For b >= 1 the lanes 0..15 (rows above the tile, otherwise idle) carry the rows of the identity
-        // as if they were rows below the tile: those become I L_bb^-T, i.e. lane c ends with column c of
-        // X_bb = L_bb^-1, for the price of no extra instruction.
-        const bool idl = b > 0 && lane < 16;
-        // one row of 16 per lane: its own (columns j > r of a tile row are never used), or a row of the identity
-        const double* src = idl ? idt + lane * DL : Am + rho * DL + base;
-        double a[16];
+        const int base = 16 * b, own = lane >> 4;
+        const double* tile = Am + (base + fr) * DL + base;
+        const double* src = own > b ? Am + lane * DL + base : idt + fr * DL;
+        double t[16], a[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t[j] = tile[j];
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] = src[j];
-        // Each lane of the tile also keeps its own diagonal entry in `dg` and updates it locally
-        // (dg -= l_rk^2), so the pivot of step k+1 is available one fma after l_rk: the
-        // sequential chain per step is readlane, reciprocal square root, multiply, fma.  A wavefront on
-        // its own issues an instruction of any kind every 5 to 8 cycles, so the sweep costs its
-        // instruction count: nothing sits in the loop that can be done once after it.
-        double dg = Am[rho * DL + rho];
-        double tp = 0.0, lb[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const double rs = pivot_rsqrt(readlane_f64(dg, base + k));     // 1 / L[k][k]
-            // l_rk for r >= k (lane k's a[k] has had the same updates as its dg: it is the pivot).  Lanes
-            // of rows above the pivot go through the same arithmetic on entries that are never stored.
-            const double t = a[k] * rs;
-            dg -= t * t;
-            a[k] = t;
-            // Rank-1 update of the columns behind: the next column takes l_jk by readlane (it is on the
-            // sequential path), the others take it one step late as a broadcast read of the column that
-            // every lane leaves in LDS: half an instruction per column instead of two readlanes.
-            cb[CB0 + 16 * k + r] = t;
-            if (k > 0) {
-#pragma unroll
-                for (int j = k + 1; j < 16; ++j) a[j] -= tp * lb[j];
+        // The chain per pivot: broadcast, reciprocal square root, multiply, multiply-add.  Beside it the updates by
+        // the pivot before of the columns that are not next.
+        double tp = 0.0;
+        unroll<0, 16>([&](auto K) {
+            constexpr int k = K;
+            const double rs = pivot_rsqrt(row_lane<k>(t[k]));              // 1 / L[k][k]
+            if constexpr (k > 0) {
+                row_update<k>(a[k], tp, a[k - 1]);
+                unroll<k + 1, 16>([&](auto J) {
+                    row_update<J>(t[J], tp, t[k - 1]);
+                    row_update<J>(a[J], tp, a[k - 1]);
+                });
             }
-            if (k < 15) a[k + 1] -= t * readlane_f64(t, base + k + 1);
+            t[k] = row_factor(t[k], rs);                                   // l_sk (a pivot's own lane: sqrt)
+            a[k] *= rs;
+            if constexpr (k < 15) row_update<k + 1>(t[k + 1], t[k], t[k]);
+            tp = t[k];
+        });
+        if (own > b) {
 #pragma unroll
-            for (int j = k + 2; j < 16; ++j) lb[j] = cb[CB0 + 16 * k + j];   // in flight during the next pivot
-            tp = t;
+            for (int j = 0; j < 16; ++j) Am[lane * DL + base + j] = a[j];
+        } else if (own == b) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) Am[lane * DL + base + j] = t[j];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) Xm[(base + k) * DL + lane] = a[k];
+            // A pivot that is not a positive normal number (nor anything after it) leaves no positive
+            // finite L[r][r] behind: one test per tile row after the sweep instead of one per pivot.
+            const double lrr = Am[lane * DL + lane];
+            if (!(lrr > 0.0) || !(lrr < 1.0e300)) *flag = 1;
         }
-        if (r >= 0) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) Am[rho * DL + base + j] = a[j];
-            if (r < 16) {
-                // A pivot that is not a positive normal number (nor anything after it) leaves no positive
-                // finite L[r][r] behind: one test per tile row after the sweep instead of one per pivot.
-                const double lrr = Am[rho * DL + rho];
-                if (!(lrr > 0.0) || !(lrr < 1.0e300)) *flag = 1;
-                rq[rho] = pivot_rcp(lrr);
-            }
-        }
-        if (idl) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) Xm[(base + k) * DL + base + lane] = a[k];
-        }
-    };
-    // the diagonal tile's inverse by forward substitution: lane c (mod 16) solves L x = e_c;
-    // the entries of L and the pivot reciprocals are wavefront-uniform LDS reads
-    auto tinv = [&](int b) {
-        const int base = 16 * b, c = here(fr);
-        double sv[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sv[i] = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const double xm = sv[m] * rq[base + m];
-            sv[m] = xm;
-#pragma unroll
-            for (int i = m + 1; i < 16; ++i) sv[i] -= Am[(base + i) * DL + base + m] * xm;
-        }
-        if (lane < 16) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Xm[(base + i) * DL + base + c] = sv[i];
-        }
-        __builtin_amdgcn_wave_barrier();
     };
     // trailing tiles: A_ij -= L_ib L_jb^T for b < j <= i
     auto trail = [&](int b) {
@@ -266,7 +266,7 @@ __device__ __forceinline__ void chol_block(double* Am, double* Xm, double* rq, i
                 for (int v = 0; v < 4; ++v) Am[(16 * i + 4 * v + fq) * DL + 16 * j + fr] = acc[v];
             }
     };
-    block_schedule(Xm, sweep, tinv, trail,
+    block_schedule(Xm, sweep, trail,
                    [&](int i, int m, int ks) { return Am[(16 * i + fr) * DL + 16 * m + 4 * ks + fq]; }, beside, ahead);
 }
 
@@ -283,82 +283,50 @@ __device__ __forceinline__ void elim_block(double* Am, double* Xm, double* rv, i
 {
     const int tid = here(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, fq = lane >> 4;
-    double* cb = rv + NB;      // the pivot rows of the running sweep, laid out as in chol_block
-    double* idt = cb + CB_LEN; // 16 rows of the identity, row stride DL (read from the second sweep on)
-    if (tid < 256) idt[(tid >> 4) * DL + (tid & 15)] = (tid >> 4) == (tid & 15) ? 1.0 : 0.0;
+    double* idt = rv + NB;     // as in chol_block
+    if (wave == 0) identity_rows(idt, fr, fq);
 
-    // Elimination of the 16 pivots base .. base+15 over all columns >= base: lane c holds
-    // column c of the 16 pivot rows.  Columns inside the diagonal tile (0 <= r < 16) hold the
-    // tile column (what lies below its diagonal is carried along and never used); columns right
-    // of it (r >= 16) get their part of the pivot rows
-    // in the same sweep; columns left of it (r < 0) idle on harmless values.
+    // Elimination of the 16 pivots base .. base+15 over all columns >= base, laid out as in chol_block by columns: every row
+    // of 16 lanes holds the diagonal tile (lane s tile column s; what lies below its diagonal is carried along and
+    // never used), beside it lane c column c of the pivot rows right of the tile, or in the lanes of the tile
+    // itself the columns of the identity, which become G_bb I: lane s ends with column s of G_bb = (Un_bb^T)^-1.
     auto sweep = [&](int b) {
-        const int base = 16 * b, c = lane, r = c - base;
-        // For b >= 1 the lanes 0..15 (columns left of the tile, otherwise idle) carry the columns of the
-        // identity as if they were columns right of the tile: those become G_bb I, i.e. lane c ends with
-        // column c of G_bb = (Un_bb^T)^-1.
-        const bool idl = b > 0 && lane < 16;
-        // one column of 16 per lane: its own (rows j > r of a tile column are never used), or one of the identity
-        const double* src = idl ? idt + lane : Am + base * DL + c;
-        double a[16];
+        const int base = 16 * b, own = lane >> 4;
+        const double* tile = Am + base * DL + base + fr;
+        const double* src = own > b ? Am + base * DL + lane : idt + fr;
+        double t[16], a[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t[j] = tile[j * DL];
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] = src[j * DL];
-        // as in chol_block: every lane of the tile keeps its own diagonal entry in `dg`
-        double dg = Am[c * DL + c];
-        double fp = 0.0, lb[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const double pi = pivot_rcp(readlane_f64(dg, base + k));
-            // A[k][c] = U[k][c] for c >= k (lane k's a[k] has had the same updates as its dg: it is the
-            // pivot).  Lanes of columns left of the pivot go through the same arithmetic on entries that
-            // are never stored.
-            const double cr = a[k];
-            const double fm = cr * pi;                        // Un[k][c]
-            dg -= fm * cr;
-            // as in chol_block: the next row by readlane, the others one step late from LDS
-            cb[CB0 + 16 * k + r] = cr;
-            if (k > 0) {
-#pragma unroll
-                for (int j = k + 1; j < 16; ++j) a[j] -= fp * lb[j];
+        double tp = 0.0, ap = 0.0;                                         // Un of the pivot row before
+        unroll<0, 16>([&](auto K) {
+            constexpr int k = K;
+            const double pi = pivot_rcp(row_lane<k>(t[k]));
+            if constexpr (k > 0) {
+                row_update<k>(a[k], t[k - 1], ap);
+                unroll<k + 1, 16>([&](auto J) {
+                    row_update<J>(t[J], t[k - 1], tp);
+                    row_update<J>(a[J], t[k - 1], ap);
+                });
             }
-            if (k < 15) a[k + 1] -= fm * readlane_f64(cr, base + k + 1);
+            tp = t[k] * pi;                                                // Un[k][s]; t[k] = U[k][s]
+            ap = a[k] * pi;
+            if constexpr (k < 15) row_update<k + 1>(t[k + 1], t[k], tp);
+        });
+        if (own > b) {
 #pragma unroll
-            for (int j = k + 2; j < 16; ++j) lb[j] = cb[CB0 + 16 * k + j];   // in flight during the next pivot
-            fp = fm;
+            for (int k = 0; k < 16; ++k) Am[(base + k) * DL + lane] = a[k];
+        } else if (own == b) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) Am[(base + k) * DL + lane] = t[k];   // U[k][c] for k <= c
+#pragma unroll
+            for (int k = 0; k < 16; ++k) Xm[(base + k) * DL + lane] = a[k];
+            // a pivot that is not a positive normal number leaves such a value, or a NaN, on the diagonal
+            const double piv = Am[lane * DL + lane];
+            if (!(piv > 0.0) || !(piv < 1.0e300)) *flag = 1;
+            rv[lane] = pivot_rcp(piv);
         }
-        if (r >= 0) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) Am[(base + k) * DL + c] = a[k];   // U[k][c] for k <= c
-            if (r < 16) {
-                // a pivot that is not a positive normal number leaves such a value, or a NaN, on the diagonal
-                const double piv = Am[c * DL + c];
-                if (!(piv > 0.0) || !(piv < 1.0e300)) *flag = 1;
-                rv[c] = pivot_rcp(piv);
-            }
-        }
-        if (idl) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) Xm[(base + k) * DL + base + lane] = a[k];
-        }
-    };
-    // G_bb = (Un_bb^T)^-1 (unit lower) by forward substitution: lane c (mod 16) solves
-    // Un_bb^T x = e_c; entry [i][m] of Un_bb^T is Un[m][i], a wavefront-uniform LDS read
-    auto tinv = [&](int b) {
-        const int base = 16 * b, c = here(fr);
-        double sv[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sv[i] = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const double xm = sv[m] * rv[base + m];
-#pragma unroll
-            for (int i = m + 1; i < 16; ++i) sv[i] -= Am[(base + m) * DL + base + i] * xm;
-        }
-        if (lane < 16) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Xm[(base + i) * DL + base + c] = sv[i];
-        }
-        __builtin_amdgcn_wave_barrier();
     };
     // trailing tiles: A_ij -= Un_bi^T U_bj for b < i <= j
     auto trail = [&](int b) {
@@ -379,7 +347,7 @@ __device__ __forceinline__ void elim_block(double* Am, double* Xm, double* rv, i
             }
     };
     // G = (Un11^T)^-1: tile T_im of Un11^T is Un_mi transposed
-    block_schedule(Xm, sweep, tinv, trail, [&](int i, int m, int ks) {
+    block_schedule(Xm, sweep, trail, [&](int i, int m, int ks) {
         return Am[(16 * m + 4 * ks + fq) * DL + 16 * i + fr] * rv[16 * m + 4 * ks + fq]; }, beside, ahead);
 }
 
