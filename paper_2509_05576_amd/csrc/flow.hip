@@ -61,9 +61,10 @@ struct FlowP {
 
 __device__ __forceinline__ double* tile_at(const FlowP& f, int i, int j) { return f.tiles + ((int64_t)i * f.T + j) * TILE; }
 __device__ __forceinline__ int* tile_word(const FlowP& f, int i, int j) { return f.words + FW_HEAD + i * f.T + j; }
-__device__ __forceinline__ int* hand_word(const FlowP& f, int k, int which) { return f.words + FW_HEAD + f.T * f.T + 2 * k + which; }
+__device__ __forceinline__ int* hand_word(const FlowP& f, int k, int which) { return f.words + FW_HEAD + f.T * f.T + 3 * k + which; }
 __device__ __forceinline__ double* hand_tile(const FlowP& f, int k) { return f.gt + (int64_t)(f.T + k) * TILE; }
-static int flow_words(int T) { return FW_HEAD + T * T + 2 * T; }
+__device__ __forceinline__ double* sum_tile(const FlowP& f, int k) { return f.gt + (int64_t)(2 * f.T + k) * TILE; }
+static int flow_words(int T) { return FW_HEAD + T * T + 3 * T; }
 
 // One wavefront, after a look that found nothing: whether to stop waiting.  n counts the looks since the launch was last seen
 // to move, that is to draw tickets (roles or tiles: whoever finishes a tile draws the next); after f.looks of them the
@@ -126,6 +127,15 @@ __device__ __forceinline__ int swz(int row, int col) { return row * 64 + (col ^ 
 // (loads and stores in front of the products cost 0.9 us a step: 2.7 us against 1.7 us of matrix time).  The number
 // of loads in flight must not depend on a branch, or every wait becomes a wait for all of them.
 // LDS: two pairs of tiles, one barrier per step; step number n reads the pair n & 1.
+__device__ __forceinline__ void flow_product(const double* As, const double* Bs, int xa, int xb, int kk, d4 (&c)[2])   // rows 8 kk .. 8 kk + 7
+{
+    const d2 a = pair(As + xa + kk * 512), b = pair(Bs + xb + kk * 512), e = pair(Bs + xb + 32 + kk * 512);
+    c[0] = mfma4(a.x, b.x, c[0]);
+    c[1] = mfma4(a.x, e.x, c[1]);
+    c[0] = mfma4(a.y, b.y, c[0]);
+    c[1] = mfma4(a.y, e.y, c[1]);
+}
+
 template <class Src>
 __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src& src, int q0, int q1, d4 (&c)[2])
 {
@@ -148,18 +158,10 @@ __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src&
             pair(As + TILE + x + u * 128) = d2{pb[2 * u], pb[2 * u + 1]};
         }
     };
-    // rows 8 kk .. 8 kk + 7 of the products of the pair at As
-    auto product = [&](const double* As, int xa, int xb, int kk) {
-        const d2 a = pair(As + xa + kk * 512), b = pair(As + TILE + xb + kk * 512), e = pair(As + TILE + xb + 32 + kk * 512);
-        c[0] = mfma4(a.x, b.x, c[0]);
-        c[1] = mfma4(a.x, e.x, c[1]);
-        c[0] = mfma4(a.y, b.y, c[0]);
-        c[1] = mfma4(a.y, e.y, c[1]);
-    };
     auto products = [&](const double* As) {
         const int xa = here(ra), xb = here(rb);
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) product(As, xa, xb, kk);
+        for (int kk = 0; kk < 8; ++kk) flow_product(As, As + TILE, xa, xb, kk, c);
     };
     // the products of the pair at As; meanwhile pa, pb to the pair at next and the loads of step q into pa, pb
     auto step = [&](const double* As, double* next, double (&pa)[8], double (&pb)[8], int q) {
@@ -168,7 +170,7 @@ __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src&
         const double* b = src.b(q) + g0;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
-            product(As, xa, xb, kk);
+            flow_product(As, As + TILE, xa, xb, kk, c);
             const int u = kk & 3;
             double (&pp)[8] = kk < 4 ? pa : pb;
             const double* g = kk < 4 ? a : b;
@@ -265,6 +267,66 @@ __device__ __forceinline__ void flow_row_product(const FlowP& f, double* lds, in
     u[1] = d4{0.0, 0.0, 0.0, 0.0};
     if (w2 == 0) flow_tri_product<0>(Gs, Cs, wr, fr, fq, u);
     else flow_tri_product<1>(Gs, Cs, wr, fr, fq, u);
+}
+
+// The last panel, that of row p = k - 2 of tiles, of the sum c for D(k, which) (see Queue1).  Tile (p, k) is wanted here as soon as
+// the chain has the block inverse of row p; taking it from the workgroup that owns it would put its publication and another
+// look between that inverse and the chain's next block but one.  So its sum is handed over before it meets the inverse
+// (sum_tile), and the product with the inverse is formed here too.  tilesN, vec: of the elimination.  steps: as in flow_row_product.
+template <bool ELIM>
+__device__ __forceinline__ void flow_last_panel(const FlowP& f, const double* tilesN, const double* vec, double* lds, int k, int which, int steps,
+                                                d4 (&c)[2])
+{
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+    const int p = k - 2;
+    flow_wait(f, hand_word(f, k, 2), lane == 0);
+    const double* S = sum_tile(f, k) + (wr * 16 + fq) * 64 + w2 * 32 + fr;
+    d4 s[2], u[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[h][v] = ld_shared(S + v * 256 + 16 * h);
+    flow_row_product(f, lds, p, steps, s, u);
+    double* As = lds + ((steps + 1) & 1) * 2 * TILE;             // (the pair that the last step of the sum has read)
+    double* Bs = As + TILE;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int m = (h ? 3 - w2 : w2) * 16 + 4 * v + fq, n = wr * 16 + fr;
+            Bs[pair_at(m, n)] = u[h][v];
+            if (ELIM && which == 1) As[pair_at(m, n)] = u[h][v] * ld_shared(vec + 2 * NB * p + m);
+        }
+    if (which == 0) {
+        flow_wait(f, tile_word(f, p, p + 1), lane == 0);
+        const double* a = (ELIM ? tilesN + ((int64_t)p * f.T + p + 1) * TILE : tile_at(f, p, p + 1)) + wave * 512 + lane;
+        double pa[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) pa[x] = ld_shared(a + x * 64);
+        const int x0 = here(wave * 512 + 2 * lane);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) pair(As + x0 + x * 128) = d2{pa[2 * x], pa[2 * x + 1]};
+    } else if (!ELIM) {
+        As = Bs;
+    }
+    __syncthreads();
+    const int xa = here(fq * 128 + 2 * (wr * 16 + fr)), xb = here(fq * 128 + 2 * (w2 * 32 + fr));
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) flow_product(As, Bs, xa, xb, kk, c);
+}
+
+// The sum of tile (i, i + 2) before its product with the block inverse of row i, for those who wait for the tile (flow_last_panel).
+__device__ __forceinline__ void flow_hand_sum(const FlowP& f, int i, const d4 (&c)[2])
+{
+    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
+    double* S = sum_tile(f, i + 2) + (wr * 16 + fq) * 64 + w2 * 32 + fr;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st_shared(S + v * 256 + 16 * h, c[h][v]);
+    flow_publish(hand_word(f, i + 2, 2));
 }
 
 // steps q, q + 1, ... whose tiles (q, i) and (q, j) are both published, out of the next 32
@@ -428,6 +490,20 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
     // chol_block writes the lower triangle of the inverse, whole 16 x 16 tiles on the diagonal included (zeros above it);
     // the tiles above stay as they are.  (Past d the last block's inverse is the identity: its rows meet zeros only.)
     for (int x = threadIdx.x; x < NB * NB; x += NT) Xm[(x >> 6) * DL + (x & 63)] = 0.0;
+    // The word of a block inverse: whichever wavefront is the last to know its stores done sets it (a count in LDS), so that
+    // none waits for another's before it goes on.  (Its own it does wait for here: with the word put off behind the next
+    // product, 2 us later, the chain is that much shorter, but the sums it needs come later too, 1036 against 1071 us for a
+    // layer of 1000 x 2048.)
+    int* stored = reinterpret_cast<int*>(lds + SWEEP_LDS) - 1;
+    if (threadIdx.x == 0) *stored = 0;
+    auto publish_inverse = [&](int k) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        if ((threadIdx.x & 63) == 0 && __hip_atomic_fetch_add(stored, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == (NT / 64) * (k + 1) - 1) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            st_word(tile_word(f, k, k), 1);
+        }
+    };
     bool have = false;                           // the sums of the next block are loaded
     for (int k = 0; k < f.T; ++k) {
         const int nb = min(NB, f.d - NB * k);
@@ -550,12 +626,7 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
             if (w2 == 0) chain_load_inverse<0>(Xm, fr, fq, g);
             else chain_load_inverse<1>(Xm, fr, fq, g);
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == NT - 64) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            st_word(tile_word(f, k, k), 1);
-        }
+        publish_inverse(k);
     }
 }
 
@@ -581,6 +652,7 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
             if (it.kind == 0) {
                 flow_init_h(p, it.i, it.j, 0.0, c);
                 flow_sum(f, tiles, SumR{f, it.i, it.j}, 0, it.i, c);
+                if (it.j == it.i + 2) flow_hand_sum(f, it.i, c);
                 flow_row_product(f, tiles, it.i, it.i, c, u);
                 double* out = tile_at(f, it.i, it.j);
 #pragma unroll
@@ -592,7 +664,8 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
                 const int k = it.i, ti = it.j ? k : k - 1;
                 const double lam = it.j ? flow_lambda(p, tiles) : 0.0;
                 flow_init_h(p, ti, k, lam, c);
-                flow_sum(f, tiles, SumR{f, ti, k}, 0, k - 1, c);
+                flow_sum(f, tiles, SumR{f, ti, k}, 0, k - 2, c);
+                if (k > 1) flow_last_panel<false>(f, nullptr, nullptr, tiles, k, it.j, k - 2, c);
                 double* out = it.j ? tile_at(f, k, k) : hand_tile(f, k);
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
@@ -690,8 +763,8 @@ struct FlowElimP {
     double* corr;          // 2 x Rp x 64: the share of the block before, by parity of the block
 };
 
-__device__ __forceinline__ int* group_word(const FlowElimP& p, int blk, int g) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 2 * p.f.T + blk * p.NG + g; }
-__device__ __forceinline__ int* part_word(const FlowElimP& p, int blk, int s, int parts) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 2 * p.f.T + p.f.T * p.NG + blk * parts + s; }
+__device__ __forceinline__ int* group_word(const FlowElimP& p, int blk, int g) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 3 * p.f.T + blk * p.NG + g; }
+__device__ __forceinline__ int* part_word(const FlowElimP& p, int blk, int s, int parts) { return p.f.words + FW_HEAD + p.f.T * p.f.T + 3 * p.f.T + p.f.T * p.NG + blk * parts + s; }
 
 struct SumU {      // Un_qi^T U_qj
     FlowP f; const double* tilesN; int i, j;
@@ -896,6 +969,7 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
             if (it.kind == 0) {
                 flow_init_a(p, it.i, it.j, c);
                 flow_sum(f, tiles, SumU{f, p.tilesN, it.i, it.j}, 0, it.i, c);
+                if (it.j == it.i + 2) flow_hand_sum(f, it.i, c);
                 flow_row_product(f, tiles, it.i, it.i, c, u);
                 double* out = tile_at(f, it.i, it.j) + wr * 16 + fr;
                 double* outn = p.tilesN + ((int64_t)it.i * T + it.j) * TILE + wr * 16 + fr;
@@ -912,7 +986,8 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
             } else {
                 const int k = it.i, ti = it.j ? k : k - 1;
                 flow_init_a(p, ti, k, c);
-                flow_sum(f, tiles, SumU{f, p.tilesN, ti, k}, 0, k - 1, c);
+                flow_sum(f, tiles, SumU{f, p.tilesN, ti, k}, 0, k - 2, c);
+                if (k > 1) flow_last_panel<true>(f, p.tilesN, p.vec, tiles, k, it.j, k - 2, c);
                 double* out = it.j ? tile_at(f, k, k) : hand_tile(f, k);
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
@@ -1012,7 +1087,7 @@ int64_t flow_eliminate_words_most(int d, int R)
     return flow_words((int)T) + T * NG * 9;
 }
 size_t flow_tiles_bytes(int d) { const size_t T = (d + NB - 1) / NB; return T * T * TILE * sizeof(double); }
-size_t flow_gt_bytes(int d) { const size_t T = (d + NB - 1) / NB; return 2 * T * TILE * sizeof(double); }
+size_t flow_gt_bytes(int d) { const size_t T = (d + NB - 1) / NB; return 3 * T * TILE * sizeof(double); }
 size_t flow_rows_bytes(int d, int R) { const size_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB; return T * NG * TILE * sizeof(double); }
 
 // One workgroup per compute unit at most (its LDS), no more than there are tiles to start with.

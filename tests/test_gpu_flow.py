@@ -28,8 +28,8 @@ def _spd(d, seed):
     return H.contiguous()
 
 
-# one to two blocks, block edges, more tiles than workgroups, several queue rows in flight
-@pytest.mark.parametrize("d", [1, 63, 64, 65, 128, 129, 500, 1216, 2048])
+# one to five blocks, block edges, more tiles than workgroups, several queue rows in flight
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 128, 129, 192, 193, 257, 500, 1216, 2048])
 def test_inverse_is_the_same_every_time(fobq, d):
     H = _spd(d, d)
     with fobq.Ctx(0) as ctx:
