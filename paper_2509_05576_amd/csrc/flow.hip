@@ -24,8 +24,8 @@
 // Measured with a kernel that does nothing else: 1.85 us from the first store of a 32 KB tile to its last load by a workgroup on
 // another XCD, and 16 TB/s when 256 workgroups read published tiles this way, against 9.6 TB/s that the products want at the
 // full matrix rate.
-// Registers: the inverse 198 VGPRs; the elimination, with the chain, the tiles and the column parts in one body, 252, and 141 to
-// 157 SGPRs kept in lanes of vector registers (no scratch in either).
+// Registers: the inverse 166 VGPRs; the elimination, with the chain, the tiles and the column parts in one body, 192, and 145 to
+// 165 SGPRs kept in lanes of vector registers (no scratch in either).
 #include <string.h>
 
 #include <algorithm>
@@ -116,6 +116,33 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int pair_at(int k, int m) { return (k >> 1) * 128 + 2 * m + (k & 1); }
 __device__ __forceinline__ d2& pair(double* p) { return *reinterpret_cast<d2*>(p); }
 __device__ __forceinline__ const d2& pair(const double* p) { return *reinterpret_cast<const d2*>(p); }
+// Published tiles are laid out the same way in memory, so that a lane moves 16 bytes at a time: rows k and k + 1 (k even) of a
+// column.  They are read and written past the caches that are not shared (bit 4: sc1), as ld_shared and st_shared do.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(const double* tile)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(tile), 0, TILE * (int)sizeof(double), 0x00020000);
+}
+__device__ __forceinline__ d2 ld_pair(const double* tile, int at)
+{
+    return __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(tile_buffer(tile), at * 8, 0, 16));
+}
+__device__ __forceinline__ void st_pair(double* tile, int at, d2 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), tile_buffer(tile), at * 8, 0, 16);
+}
+// Rows m0 + 4 v + fq (v = 0 .. 3) of column n in a tile, from the accumulator layout: lanes fq and fq + 1 (fq even) hold the rows
+// of a pair, and exchange what makes two pairs of theirs whole.
+__device__ __forceinline__ void st_rows(double* tile, int m0, int n, int fq, const d4& x)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x[2 * i]), __double2loint(x[2 * i + 1]), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x[2 * i]), __double2hiint(x[2 * i + 1]), false, false);
+        const d2 y = {__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
+        st_pair(tile, ((m0 >> 1) + 4 * i + 2 * (fq & 1) + (fq >> 1)) * 128 + 2 * n, y);
+    }
+}
 // the chain's tiles (8-byte reads): rows of 64 doubles, the two halves of 32 banks exchanged in odd rows
 __device__ __forceinline__ int swz(int row, int col) { return row * 64 + (col ^ ((row & 1) << 4)); }
 
@@ -141,21 +168,20 @@ __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src&
 {
     const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
-    const int g0 = wave * 512 + lane;                          // this lane's first element of a tile: rows wave * 8 + u, column lane
-    const int x0 = wave * 512 + 2 * lane;                      // the same in LDS, rows 2 u and 2 u + 1 together
+    const int x0 = wave * 512 + 2 * lane;                      // this lane's first pair of a tile: rows wave * 8 + 2 u and the next, column lane
     const int ra = fq * 128 + 2 * (wr * 16 + fr), rb = fq * 128 + 2 * (w2 * 32 + fr);
-    auto load = [&](int q, double (&pa)[8], double (&pb)[8]) {
-        const double* a = src.a(q) + g0;
-        const double* b = src.b(q) + g0;
+    auto load = [&](int q, d2 (&pa)[4], d2 (&pb)[4]) {
+        const double* a = src.a(q);
+        const double* b = src.b(q);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) { pa[u] = ld_shared(a + u * 64); pb[u] = ld_shared(b + u * 64); }
+        for (int u = 0; u < 4; ++u) { pa[u] = ld_pair(a, x0 + u * 128); pb[u] = ld_pair(b, x0 + u * 128); }
     };
-    auto store = [&](double* As, const double (&pa)[8], const double (&pb)[8]) {
+    auto store = [&](double* As, const d2 (&pa)[4], const d2 (&pb)[4]) {
         const int x = here(x0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            pair(As + x + u * 128) = d2{pa[2 * u], pa[2 * u + 1]};
-            pair(As + TILE + x + u * 128) = d2{pb[2 * u], pb[2 * u + 1]};
+            pair(As + x + u * 128) = pa[u];
+            pair(As + TILE + x + u * 128) = pb[u];
         }
     };
     auto products = [&](const double* As) {
@@ -164,22 +190,20 @@ __device__ __forceinline__ void flow_sum(const FlowP& f, double* lds, const Src&
         for (int kk = 0; kk < 8; ++kk) flow_product(As, As + TILE, xa, xb, kk, c);
     };
     // the products of the pair at As; meanwhile pa, pb to the pair at next and the loads of step q into pa, pb
-    auto step = [&](const double* As, double* next, double (&pa)[8], double (&pb)[8], int q) {
+    auto step = [&](const double* As, double* next, d2 (&pa)[4], d2 (&pb)[4], int q) {
         const int xa = here(ra), xb = here(rb), x = here(x0);
-        const double* a = src.a(q) + g0;
-        const double* b = src.b(q) + g0;
+        const double* a = src.a(q);
+        const double* b = src.b(q);
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             flow_product(As, As + TILE, xa, xb, kk, c);
             const int u = kk & 3;
-            double (&pp)[8] = kk < 4 ? pa : pb;
-            const double* g = kk < 4 ? a : b;
-            pair(next + (kk < 4 ? 0 : TILE) + x + u * 128) = d2{pp[2 * u], pp[2 * u + 1]};
-            pp[2 * u] = ld_shared(g + 2 * u * 64);
-            pp[2 * u + 1] = ld_shared(g + (2 * u + 1) * 64);
+            d2 (&pp)[4] = kk < 4 ? pa : pb;
+            pair(next + (kk < 4 ? 0 : TILE) + x + u * 128) = pp[u];
+            pp[u] = ld_pair(kk < 4 ? a : b, x0 + u * 128);
         }
     };
-    double pa[8], pb[8], na[8], nb[8];
+    d2 pa[4], pb[4], na[4], nb[4];
     double* cur = lds;                   // pair of LDS tiles of the next step, and the other one
     double* alt = lds + 2 * TILE;
     int known = q0;                      // the tiles of the steps before this one are ready
@@ -251,17 +275,16 @@ __device__ __forceinline__ void flow_row_product(const FlowP& f, double* lds, in
     double* Gs = lds + (steps & 1) * 2 * TILE;
     double* Cs = Gs + TILE;
     flow_wait(f, tile_word(f, i, i), lane == 0);
-    const double* g = f.gt + (int64_t)i * TILE + wave * 512 + lane;
-    double pg[8];
+    const int x0 = here(wave * 512 + 2 * lane);
+    d2 pg[4];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) pg[x] = ld_shared(g + x * 64);
+    for (int x = 0; x < 4; ++x) pg[x] = ld_pair(f.gt + (int64_t)i * TILE, x0 + x * 128);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) Cs[here(pair_at(wr * 16 + fq, w2 * 32 + 16 * j + fr)) + v * 256] = -c[j][v];
-    const int x0 = here(wave * 512 + 2 * lane);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) pair(Gs + x0 + x * 128) = d2{pg[2 * x], pg[2 * x + 1]};
+    for (int x = 0; x < 4; ++x) pair(Gs + x0 + x * 128) = pg[x];
     __syncthreads();
     u[0] = d4{0.0, 0.0, 0.0, 0.0};
     u[1] = d4{0.0, 0.0, 0.0, 0.0};
@@ -281,12 +304,13 @@ __device__ __forceinline__ void flow_last_panel(const FlowP& f, const double* ti
     const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
     const int p = k - 2;
     flow_wait(f, hand_word(f, k, 2), lane == 0);
-    const double* S = sum_tile(f, k) + (wr * 16 + fq) * 64 + w2 * 32 + fr;
     d4 s[2], u[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[h][v] = ld_shared(S + v * 256 + 16 * h);
+    for (int x = 0; x < 4; ++x) {
+        const d2 y = ld_pair(sum_tile(f, k), x * 2 * NT + 2 * here(threadIdx.x));
+        s[x >> 1][2 * (x & 1)] = y.x;
+        s[x >> 1][2 * (x & 1) + 1] = y.y;
+    }
     flow_row_product(f, lds, p, steps, s, u);
     double* As = lds + ((steps + 1) & 1) * 2 * TILE;             // (the pair that the last step of the sum has read)
     double* Bs = As + TILE;
@@ -300,13 +324,13 @@ __device__ __forceinline__ void flow_last_panel(const FlowP& f, const double* ti
         }
     if (which == 0) {
         flow_wait(f, tile_word(f, p, p + 1), lane == 0);
-        const double* a = (ELIM ? tilesN + ((int64_t)p * f.T + p + 1) * TILE : tile_at(f, p, p + 1)) + wave * 512 + lane;
-        double pa[8];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) pa[x] = ld_shared(a + x * 64);
+        const double* a = ELIM ? tilesN + ((int64_t)p * f.T + p + 1) * TILE : tile_at(f, p, p + 1);
         const int x0 = here(wave * 512 + 2 * lane);
+        d2 pa[4];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) pair(As + x0 + x * 128) = d2{pa[2 * x], pa[2 * x + 1]};
+        for (int x = 0; x < 4; ++x) pa[x] = ld_pair(a, x0 + x * 128);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) pair(As + x0 + x * 128) = pa[x];
     } else if (!ELIM) {
         As = Bs;
     }
@@ -316,16 +340,13 @@ __device__ __forceinline__ void flow_last_panel(const FlowP& f, const double* ti
     for (int kk = 0; kk < 8; ++kk) flow_product(As, Bs, xa, xb, kk, c);
 }
 
-// The sum of tile (i, i + 2) before its product with the block inverse of row i, for those who wait for the tile (flow_last_panel).
+// The sum of tile (i, i + 2) before its product with the block inverse of row i, for those who wait for the tile (flow_last_panel);
+// every thread finds its own values again.
 __device__ __forceinline__ void flow_hand_sum(const FlowP& f, int i, const d4 (&c)[2])
 {
-    const int lane = here(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, w2 = wave & 1, fr = lane & 15, fq = lane >> 4;
-    double* S = sum_tile(f, i + 2) + (wr * 16 + fq) * 64 + w2 * 32 + fr;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) st_shared(S + v * 256 + 16 * h, c[h][v]);
+    for (int x = 0; x < 4; ++x)
+        st_pair(sum_tile(f, i + 2), x * 2 * NT + 2 * here(threadIdx.x), d2{c[x >> 1][2 * (x & 1)], c[x >> 1][2 * (x & 1) + 1]});
     flow_publish(hand_word(f, i + 2, 2));
 }
 
@@ -364,7 +385,7 @@ __device__ __forceinline__ int flow_ticket(const FlowP& f, int queue, int* slot)
     __syncthreads();                                 // the LDS of the tile before is free, the slot has been read
     if (threadIdx.x == 0) *slot = __hip_atomic_fetch_add(f.words + queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    return *slot;
+    return __builtin_amdgcn_readfirstlane(*slot);
 }
 
 // the queue that the workgroup with this role (its place in the order of arrival) serves first: one each, then dealt so that
@@ -454,25 +475,28 @@ __device__ __forceinline__ void chain_tiles(int wave, int (&rt)[2], int (&ct)[2]
 }
 
 // The block inverse G (lower triangular, DL-strided in LDS) as A operand of the row tiles {W, 3 - W}: row tile t needs the
-// k-steps 0 .. 4 t + 3 only, 20 of 32 (k-step, tile) pairs for either W: g[0 .. 4 W + 3] are tile W's, the rest 3 - W's.
+// k-steps 0 .. 4 t + 3 only, 20 of 32 (k-step, tile) pairs for either W, two k-steps (rows 8 kk + 2 fq and the next) at a time:
+// g[0 .. 2 W + 1] are tile W's, the rest 3 - W's.
 template <int W>
-__device__ __forceinline__ void chain_load_inverse(const double* Xm, int fr, int fq, double (&g)[20])
+__device__ __forceinline__ void chain_load_inverse(const double* Xm, int fr, int fq, d2 (&g)[10])
 {
-    const int r0 = here((W * 16 + fr) * DL + fq), r1 = here(((3 - W) * 16 + fr) * DL + fq);
+    const int r0 = here((W * 16 + fr) * DL + 2 * fq), r1 = here(((3 - W) * 16 + fr) * DL + 2 * fq);
 #pragma unroll
-    for (int x = 0; x < 20; ++x) {
-        const bool lo = x < 4 * W + 4;
-        g[x] = Xm[(lo ? r0 : r1) + 4 * (lo ? x : x - 4 * W - 4)];
+    for (int x = 0; x < 10; ++x) {
+        const bool lo = x < 2 * W + 2;
+        g[x] = pair(Xm + (lo ? r0 : r1) + 8 * (lo ? x : x - 2 * W - 2));
     }
 }
 
 template <int W>
-__device__ __forceinline__ void chain_row_product(const double (&g)[20], const double (&vb)[16], d4 (&u)[2])
+__device__ __forceinline__ void chain_row_product(const d2 (&g)[10], const d2 (&vb)[8], d4 (&u)[2])
 {
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks) {
-        if (ks < 4 * W + 4) u[0] = mfma4(g[ks], vb[ks], u[0]);
-        if (ks < 16 - 4 * W) u[1] = mfma4(g[4 * W + 4 + ks], vb[ks], u[1]);
+    for (int kk = 0; kk < 8; ++kk) {
+        if (kk < 2 * W + 2) u[0] = mfma4(g[kk].x, vb[kk].x, u[0]);
+        if (kk < 8 - 2 * W) u[1] = mfma4(g[2 * W + 2 + kk].x, vb[kk].x, u[1]);
+        if (kk < 2 * W + 2) u[0] = mfma4(g[kk].y, vb[kk].y, u[0]);
+        if (kk < 8 - 2 * W) u[1] = mfma4(g[2 * W + 2 + kk].y, vb[kk].y, u[1]);
     }
 }
 
@@ -486,7 +510,7 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
     double* Vs = Xm + NB * DL;                   // tile (k - 1, k) of U or R, and (ELIM) of Un
     double* Vn = ELIM ? Vs + TILE : Vs;
     d4 c[2];
-    double vb[16], g[20];
+    d2 vb[8], g[10];
     // chol_block writes the lower triangle of the inverse, whole 16 x 16 tiles on the diagonal included (zeros above it);
     // the tiles above stay as they are.  (Past d the last block's inverse is the identity: its rows meet zeros only.)
     for (int x = threadIdx.x; x < NB * NB; x += NT) Xm[(x >> 6) * DL + (x & 63)] = 0.0;
@@ -520,15 +544,14 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
         const int t[2] = {w2, 3 - w2};               // row tiles of the product with the block inverse
         auto load_sums = [&](int k) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            const double* V = hand_tile(f, k) + fq * 64 + wr * 16 + fr;
-            const double* D = tile_at(f, k, k) + fq * 64 + fr;
+            const double* D = tile_at(f, k, k);
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) vb[ks] = ld_shared(V + ks * 256);
+            for (int kk = 0; kk < 8; ++kk) vb[kk] = ld_pair(hand_tile(f, k), (4 * kk + fq) * 128 + 2 * (wr * 16 + fr));
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 if (h == 0 || second) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) c[h][v] = ld_shared(D + (rt[h] * 16 + 4 * v) * 64 + ct[h] * 16);
+                    for (int v = 0; v < 4; ++v) c[h][v] = ld_shared(D + pair_at(rt[h] * 16 + 4 * v + fq, ct[h] * 16 + fr));
                 }
         };
         auto store_diag = [&](int h, int nb) {
@@ -567,18 +590,20 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
             double* R = tile_at(f, k - 1, k);
             double* Rn = tilesN + ((int64_t)(k - 1) * f.T + k) * TILE;
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i) {
+                const int n = wr * 16 + fr, at = here(swz(t[i] * 16 + fq, n));
+                d4 un;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int m = t[i] * 16 + 4 * v + fq, n = wr * 16 + fr;
-                    Vs[here(swz(t[i] * 16 + fq, n)) + v * 256] = u[i][v];
-                    st_shared(R + m * 64 + n, u[i][v]);
+                    Vs[at + v * 256] = u[i][v];
                     if (ELIM) {
-                        const double un = u[i][v] * lds[m];      // 1 / pivot of the block before
-                        Vn[here(swz(t[i] * 16 + fq, n)) + v * 256] = un;
-                        st_shared(Rn + m * 64 + n, un);
+                        un[v] = u[i][v] * lds[t[i] * 16 + 4 * v + fq];      // 1 / pivot of the block before
+                        Vn[at + v * 256] = un[v];
                     }
                 }
+                st_rows(R, t[i] * 16, n, fq, u[i]);
+                if (ELIM) st_rows(Rn, t[i] * 16, n, fq, un);
+            }
             __syncthreads();
             diag_product(0);
             __builtin_amdgcn_s_waitcnt(0);
@@ -608,11 +633,11 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
         double* G = tile_at(f, k, k);
         double* Gn = tilesN + ((int64_t)k * f.T + k) * TILE;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int y = wave * 8 + x;
-            st_shared(Gt + y * 64 + lane, Xm[lane * DL + y]);
-            if (ELIM) st_shared(Gn + y * 64 + lane, y < lane ? Am[y * DL + lane] * lds[y] : 0.0);
-            else st_shared(G + y * 64 + lane, Xm[y * DL + lane]);
+        for (int x = 0; x < 4; ++x) {
+            const int y = wave * 8 + 2 * x, at = y * 64 + 2 * lane;
+            st_pair(Gt, at, pair(Xm + lane * DL + y));
+            if (ELIM) st_pair(Gn, at, d2{y < lane ? Am[y * DL + lane] * lds[y] : 0.0, y + 1 < lane ? Am[(y + 1) * DL + lane] * lds[y + 1] : 0.0});
+            else st_pair(G, at, d2{Xm[y * DL + lane], Xm[(y + 1) * DL + lane]});
         }
         if (ELIM && wave == 0) {
             st_shared(vec + 2 * NB * k + lane, lds[lane]);
@@ -656,9 +681,7 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
                 flow_row_product(f, tiles, it.i, it.i, c, u);
                 double* out = tile_at(f, it.i, it.j);
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) st_shared(out + ((h ? 3 - w2 : w2) * 16 + 4 * v + fq) * 64 + wr * 16 + fr, u[h][v]);
+                for (int h = 0; h < 2; ++h) st_rows(out, (h ? 3 - w2 : w2) * 16, wr * 16 + fr, fq, u[h]);
                 flow_publish(tile_word(f, it.i, it.j));
             } else {
                 const int k = it.i, ti = it.j ? k : k - 1;
@@ -668,9 +691,7 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
                 if (k > 1) flow_last_panel<false>(f, nullptr, nullptr, tiles, k, it.j, k - 2, c);
                 double* out = it.j ? tile_at(f, k, k) : hand_tile(f, k);
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, -c[h][v]);
+                for (int h = 0; h < 2; ++h) st_rows(out, wr * 16, w2 * 32 + 16 * h + fr, fq, -c[h]);
                 flow_publish(hand_word(f, k, it.j));
             }
         }
@@ -690,9 +711,7 @@ __device__ __forceinline__ void flow_inverse(const FlowInverseP& p, double* lds,
             flow_row_product(f, tiles, i, i - j, c, u);
             double* out = tile_at(f, i, j);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) st_shared(out + ((h ? 3 - w2 : w2) * 16 + 4 * v + fq) * 64 + wr * 16 + fr, u[h][v]);
+            for (int h = 0; h < 2; ++h) st_rows(out, (h ? 3 - w2 : w2) * 16, wr * 16 + fr, fq, u[h]);
             flow_publish(tile_word(f, i, j));
         } else {
             int m, n;
@@ -838,10 +857,9 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
     flow_wait(f, lane == 0 ? tile_word(f, blk, blk) : lane == 1 ? group_word(p, blk, g) : part_word(p, max(blk, 1) - 1, s, parts),
               lane < (blk > 0 ? 3 : 2));
     {
-        const double* u = p.tilesN + ((int64_t)blk * f.T + blk) * TILE + wave * 512 + lane;
-        double un[8];
+        d2 un[4];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) un[x] = ld_shared(u + x * 64);
+        for (int x = 0; x < 4; ++x) un[x] = ld_pair(p.tilesN + ((int64_t)blk * f.T + blk) * TILE, wave * 512 + x * 128 + 2 * lane);
         const double* wt = p.wt + ((int64_t)blk * p.NG + g) * TILE + r0 * 64 + lane;
         const double* cin = p.corr + ((int64_t)(blk & 1) * p.NG * NB + NB * g + r0) * 64 + lane;
 #pragma unroll
@@ -850,7 +868,10 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
             if (blk > 0) w0[r] -= ld_shared(cin + r * 64);
         }
 #pragma unroll
-        for (int x = 0; x < 8; ++x) Us[wave * 512 + x * 64 + lane] = un[x];
+        for (int x = 0; x < 4; ++x) {
+            Us[wave * 512 + x * 128 + lane] = un[x].x;
+            Us[wave * 512 + x * 128 + 64 + lane] = un[x].y;
+        }
     }
     const double hp = ld_shared(p.vec + 2 * NB * blk + NB + lane);
     __syncthreads();
@@ -859,12 +880,11 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
     for (int r = 0; r < NR; ++r) { ws[r] = w0[r]; mycode[r] = 0.0; mydiff[r] = 0.0; }
     // what comes after the steps and is there already: the pivot rows above the next block's columns, the loss so far
     bool ahead = more && __all(lane == 0 ? ld_word(tile_word(f, blk, blk + 1)) != 0 : true);
-    double t[8];
+    d2 t[4];
     auto load_next = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const double* u = p.tilesN + ((int64_t)blk * f.T + blk + 1) * TILE + wave * 512 + lane;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) t[x] = ld_shared(u + x * 64);
+        for (int x = 0; x < 4; ++x) t[x] = ld_pair(p.tilesN + ((int64_t)blk * f.T + blk + 1) * TILE, wave * 512 + x * 128 + 2 * lane);
     };
     if (ahead) load_next();
     double loss_before[NR];
@@ -883,7 +903,10 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
             load_next();
         }
 #pragma unroll
-        for (int x = 0; x < 8; ++x) Vs[wave * 512 + x * 64 + lane] = t[x];
+        for (int x = 0; x < 4; ++x) {
+            Vs[wave * 512 + x * 128 + lane] = t[x].x;
+            Vs[wave * 512 + x * 128 + 64 + lane] = t[x].y;
+        }
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -906,11 +929,11 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
 #pragma unroll
         for (int r = 0; r < NR; ++r) st_shared(cout + r * 64, acc[r]);
         if (blk + 2 < f.T) {
-            double* dt = p.dt + ((int64_t)blk * p.NG + g) * TILE + (s % PER) * RS;
+            double* dt = p.dt + ((int64_t)blk * p.NG + g) * TILE;
 #pragma unroll
-            for (int x = 0; x < NR; ++x) {
-                const int e = tid + NT * x;
-                st_shared(dt + (e / RS) * 64 + e % RS, Ds[e]);
+            for (int x = 0; x < (NR + 1) / 2; ++x) {
+                const int e = tid + NT * x, c2 = e / RS, r = e % RS;      // columns 2 c2 and 2 c2 + 1 of row r
+                if (c2 < NB / 2) st_pair(dt, c2 * 128 + 2 * ((s % PER) * RS + r), d2{Ds[2 * c2 * RS + r], Ds[(2 * c2 + 1) * RS + r]});
             }
         }
     }
@@ -971,17 +994,17 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
                 flow_sum(f, tiles, SumU{f, p.tilesN, it.i, it.j}, 0, it.i, c);
                 if (it.j == it.i + 2) flow_hand_sum(f, it.i, c);
                 flow_row_product(f, tiles, it.i, it.i, c, u);
-                double* out = tile_at(f, it.i, it.j) + wr * 16 + fr;
-                double* outn = p.tilesN + ((int64_t)it.i * T + it.j) * TILE + wr * 16 + fr;
+                double* outn = p.tilesN + ((int64_t)it.i * T + it.j) * TILE;
                 const double* rv = p.vec + 2 * NB * it.i;
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < 2; ++h) {
+                    const int m0 = (h ? 3 - w2 : w2) * 16;
+                    d4 un;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int m = (h ? 3 - w2 : w2) * 16 + 4 * v + fq;
-                        st_shared(out + m * 64, u[h][v]);
-                        st_shared(outn + m * 64, u[h][v] * ld_shared(rv + m));
-                    }
+                    for (int v = 0; v < 4; ++v) un[v] = u[h][v] * ld_shared(rv + m0 + 4 * v + fq);
+                    st_rows(tile_at(f, it.i, it.j), m0, wr * 16 + fr, fq, u[h]);
+                    st_rows(outn, m0, wr * 16 + fr, fq, un);
+                }
                 flow_publish(tile_word(f, it.i, it.j));
             } else {
                 const int k = it.i, ti = it.j ? k : k - 1;
@@ -990,9 +1013,7 @@ __device__ __forceinline__ void flow_eliminate(const FlowElimP& p, double* lds, 
                 if (k > 1) flow_last_panel<true>(f, p.tilesN, p.vec, tiles, k, it.j, k - 2, c);
                 double* out = it.j ? tile_at(f, k, k) : hand_tile(f, k);
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) st_shared(out + (wr * 16 + 4 * v + fq) * 64 + w2 * 32 + 16 * h + fr, -c[h][v]);
+                for (int h = 0; h < 2; ++h) st_rows(out, wr * 16, w2 * 32 + 16 * h + fr, fq, -c[h]);
                 flow_publish(hand_word(f, k, it.j));
             }
         }
