@@ -20,7 +20,10 @@
 // Exchange between compute units.  Each XCD has its own L2, which is not coherent with the others inside a launch.
 // Everything that one workgroup hands to another during a launch goes through relaxed agent-scope atomic accesses
 // (loads and stores that bypass the caches which are not shared): the producer stores a tile, waits until its stores
-// are done, and sets the tile's word after a release fence; the consumer reads the word until it is set and loads.
+// are done, and sets the tile's word; the consumer reads the word until it is set and loads.  Stores that are done are
+// where every compute unit finds them, and nothing else crosses, so the word needs no release at agent scope in front of it:
+// that writes the XCD's whole L2 back, for every tile of every workgroup (4.76 against 4.61 ms for a layer of 2048 x 4608, 1046 against
+// 990 us for 1000 x 2048).
 // Measured with a kernel that does nothing else: 1.85 us from the first store of a 32 KB tile to its last load by a workgroup on
 // another XCD, and 16 TB/s when 256 workgroups read published tiles this way, against 9.6 TB/s that the products want at the
 // full matrix rate.
@@ -104,7 +107,7 @@ __device__ __forceinline__ void flow_publish(int* word)
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         st_word(word, 1);
     }
 }
@@ -524,7 +527,7 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);
         if ((threadIdx.x & 63) == 0 && __hip_atomic_fetch_add(stored, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == (NT / 64) * (k + 1) - 1) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             st_word(tile_word(f, k, k), 1);
         }
     };
@@ -611,7 +614,7 @@ __device__ __forceinline__ void flow_chain(const FlowP& f, double* tilesN, doubl
         store_diag(0, nb);
         __syncthreads();
         if (k > 0 && tid == NT - 64) {           // a wavefront that the sweeps leave idle
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             st_word(tile_word(f, k - 1, k), 1);
         }
         int seen = 1;                            // words of the next block's sums, looked at while the last sweep runs
