@@ -381,8 +381,8 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
             if (c >= len) c -= len;
             return c_begin + c;
         };
-        // tile -> (I, J): I >= J, row-major over the lower triangle; or, for a list of tile rows (rect.cb > 0: two
-        // groups of rect.cb tile rows, the second starting at tile row rect.gap), all tile columns of those rows;
+        // tile -> (I, J): I >= J, row-major over the lower triangle; or (rect.cb > 0) the tile-th of those that are wanted in
+        // two groups of tile rows, row-major, counted off 64 at a time by the lanes;
         // or, in step, the lower triangle in blocks of 8 x 8 tiles (block rows top down, blocks left to right, tiles
         // row-major inside a block): 32 consecutive tiles touch about 12 row blocks of the operands, not 33
         int I, J;
@@ -390,8 +390,22 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
             I = 0;
             J = tile;
         } else if (rect.cb > 0) {
-            const int ntj = dpad / IT, ri = tile / ntj;
-            J = tile - ri * ntj;
+            const int ntj = dpad / IT, all = 2 * rect.cb * ntj;
+            int at = 0;
+            for (int base = 0, before = 0; base < all; base += 64) {
+                const int x = base + lane, r = x / ntj;
+                const bool in = x < all && i8_rect_needs(rect, r < rect.cb ? r : r - rect.cb + rect.gap, x - r * ntj);
+                const unsigned long long m = __ballot(in);
+                const int n = __popcll(m);
+                if (tile < before + n) {
+                    const int rank = before + __popcll(m & ((1ull << lane) - 1));
+                    at = base + __builtin_ctzll(__ballot(in && rank == tile));
+                    break;
+                }
+                before += n;
+            }
+            const int ri = __builtin_amdgcn_readfirstlane(at) / ntj;
+            J = __builtin_amdgcn_readfirstlane(at) - ri * ntj;
             I = ri < rect.cb ? ri : ri - rect.cb + rect.gap;
         } else if (ls.full > 0) {
             const int nt = dpad / IT;
@@ -421,7 +435,9 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
             while (I * (I + 1) / 2 > tile) --I;
             J = tile - I * (I + 1) / 2;
         }
-        const bool tri = rect.cb == 0;       // only the lower triangle is wanted (and stored)
+        // only the lower triangle is wanted (and stored): everywhere, or, of two groups of tile rows, in the block of the
+        // zero offset (a tile that reaches past that block stores everything)
+        const bool tri = rect.cb == 0 || (!rect.half && I == J && 2 * I + 2 <= rect.c64);
         const int i0 = I * IT, j0 = J * TN;
         double* __restrict__ out = Hpart + (int64_t)piece * d * d;
 
@@ -525,6 +541,17 @@ struct I8Plan { int nt, wgs; int64_t ksteps, items, per_wg; I8Lockstep ls; };
 constexpr size_t I8_INSTEP_MIN_BYTES = (size_t)256 << 20;
 constexpr int I8_MAX_PIECES = 8;
 
+// tiles of a launch
+static int64_t i8_tiles(int64_t nt, const I8Rect& rect)
+{
+    if (rect.half) return nt;
+    if (rect.cb == 0) return nt * (nt + 1) / 2;
+    int64_t n = 0;
+    for (int r = 0; r < 2 * rect.cb; ++r)
+        for (int J = 0; J < nt; ++J) n += i8_rect_needs(rect, r < rect.cb ? r : r - rect.cb + rect.gap, J);
+    return n;
+}
+
 static bool i8_instep_wanted(int d, int64_t n, I8Rect rect)
 {
     const int64_t nt = i8_dpad(d) / IT;
@@ -537,7 +564,7 @@ int xxt_i8_wanted_splits(int d, int64_t n, I8Rect rect)
     if (rect.cb > 0) {
         // a list of tile rows has fewer tiles than the triangle that the context's count of slabs is made for: enough
         // pieces per tile that every workgroup gets a range
-        const int64_t nt = i8_dpad(d) / IT, tiles = rect.half ? nt : 2 * rect.cb * nt;
+        const int64_t tiles = i8_tiles(i8_dpad(d) / IT, rect);
         const int64_t want = (I8_WGS + tiles - 1) / tiles + 1;
         return (int)(want < fit ? want : (fit < 2 ? 2 : fit));
     }
@@ -550,7 +577,7 @@ static I8Plan i8_plan(int d, int64_t n, int splits, I8Rect rect)
     I8Plan p;
     p.nt = i8_dpad(d) / IT;
     p.ksteps = i8_ksteps(n);
-    const int64_t tiles = rect.half ? p.nt : rect.cb > 0 ? (int64_t)2 * rect.cb * p.nt : (int64_t)p.nt * (p.nt + 1) / 2;
+    const int64_t tiles = i8_tiles(p.nt, rect);
     if (i8_instep_wanted(d, n, rect)) {
         // Whole rounds of one tile per workgroup, then the rem tiles left over in `pieces` parts each (part j of a
         // tile goes to slab j): the number of parts that ends soonest, where a slab more is charged what clearing

@@ -1,0 +1,29 @@
+"""Tap offsets form only the tiles that the assembly reads (csrc/hessian_i8.hip, i8_rect_needs): channel counts whose taps fill whole
+128-row tiles, end inside one, or lie across them, with enough pixels that a tile is cut into several pieces."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("c,k", [(64, 3), (128, 2), (128, 3), (192, 3), (256, 2), (320, 2), (320, 3), (384, 3)])
+def test_hessian_by_offsets_matches_the_unfolded_sum(c, k):
+    import paper_2509_05576_amd as fobq
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * c + k)
+    maps = torch.relu(torch.randn((6, 12, 15, c), generator=g, device="cuda"))
+    pad = k // 2
+    M = torch.nn.functional.pad(maps, (0, 0, pad, pad, pad, pad)).double()
+    ho, wo = M.shape[1] - k + 1, M.shape[2] - k + 1
+    taps = [M[:, y:y + ho, x:x + wo, :].reshape(-1, c) for y in range(k) for x in range(k)]
+    X = torch.stack(taps, 2).reshape(taps[0].shape[0], -1)
+    want = (X.T.contiguous() @ X) * (2.0 / X.shape[0])
+    with fobq.Ctx(0) as ctx:
+        ctx.set_hessian_mode(fobq.HESSIAN_INT8_SLICES)
+        H = torch.full((c * k * k, c * k * k), float("nan"), dtype=torch.float64, device="cuda")
+        ctx.hessian_conv(maps, k, 1, pad, H_out=H)
+        torch.cuda.synchronize()
+    diag = want.diagonal().sqrt()
+    # the digit products' own bound (19 of 25 products of 40-bit numbers), as for the other forms of this mode
+    assert float(((H - want).abs() / (diag[:, None] * diag[None, :])).max()) <= 1e-12
+    assert torch.equal(H, H.T)
