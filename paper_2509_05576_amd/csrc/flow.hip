@@ -919,18 +919,31 @@ __device__ __forceinline__ void flow_columns(const FlowElimP& p, double* lds, in
     }
     __syncthreads();
     if (more) {
-        double acc[NR];
+        // the share of the next block's columns, rows of D times a 64 x 64 tile: of 32 rows as one 16 x 16 tile a wavefront on the
+        // matrix cores (with 16 rows half the wavefronts have one and wait for 16 dependent products: 983 -> 998 us for
+        // 1000 x 2048), of fewer as the steps went.  20 layers of up to 1024 rows in one call 363 -> 348 us.
+        double* cout = p.corr + ((int64_t)((blk + 1) & 1) * p.NG * NB + NB * g + (s % PER) * RS) * 64;
+        if constexpr (NR == 4) {
+            const int fr = lane & 15, fq = lane >> 4, m0 = (wave >> 2) * 16, n0 = (wave & 3) * 16;
+            const int ra = here(fq * RS + m0 + fr), rb = here(fq * 64 + n0 + fr);
+            d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int r = 0; r < NR; ++r) acc[r] = 0.0;
+            for (int ks = 0; ks < 16; ++ks) acc = mfma4(Ds[ra + ks * 4 * RS], Vs[rb + ks * 256], acc);
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const double v = Vs[k * 64 + lane];
+            for (int v = 0; v < 4; ++v) st_shared(cout + (m0 + 4 * v + fq) * 64 + n0 + fr, acc[v]);
+        } else {
+            double acc[NR];
 #pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r] = fma(chain_readlane(mydiff[r], k), v, acc[r]);
+            for (int r = 0; r < NR; ++r) acc[r] = 0.0;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const double v = Vs[k * 64 + lane];
+#pragma unroll
+                for (int r = 0; r < NR; ++r) acc[r] = fma(chain_readlane(mydiff[r], k), v, acc[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < NR; ++r) st_shared(cout + (wave * NR + r) * 64 + lane, acc[r]);
         }
-        double* cout = p.corr + ((int64_t)((blk + 1) & 1) * p.NG * NB + NB * g + r0) * 64 + lane;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) st_shared(cout + r * 64, acc[r]);
         if (blk + 2 < f.T) {
             double* dt = p.dt + ((int64_t)blk * p.NG + g) * TILE;
 #pragma unroll
