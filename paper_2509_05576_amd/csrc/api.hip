@@ -278,7 +278,9 @@ static int read_flags(fobq_ctx* ctx, const int* dev_flags)
 {
     int* h = ctx->h_flags;
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
-    FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
+    if (!ctx->flags_sent)
+        FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
+    ctx->flags_sent = false;
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
     if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for three quarters of a minute and was given up");
     if (h[FLAG_BADPERM]) return set_err(ctx, FOBQ_EINVAL, "perm_in is not a permutation of 0..d_col-1");
@@ -935,11 +937,11 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     // launches each would be a bubble of about 4 us), here on the clearing kernel.
     FOBQ_TRY(launch_clear_words(s, ctx->flags.p, FLAG_COUNT, ctx->words.p, ctx->words_len, ctx->sync_ev[EV_FORK]),
              "clear flags and loss");
-    FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
-    int rc = enqueue_grid_scores(ctx, ctx->side, p.W, R, d, opts, p.ob, out->scales, out->zeros, ctx->sync_ev[EV_JOIN]);
+    // damp, Cholesky, inverse: before the side stream's launches, which take the host longer than the device takes to get here
+    int rc = enqueue_inverse(ctx, p.H, d, opts->damp, opts->damp_abs);
     if (rc) return rc;
-    // damp, Cholesky, inverse
-    rc = enqueue_inverse(ctx, p.H, d, opts->damp, opts->damp_abs);
+    FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
+    rc = enqueue_grid_scores(ctx, ctx->side, p.W, R, d, opts, p.ob, out->scales, out->zeros, ctx->sync_ev[EV_JOIN]);
     if (rc) return rc;
     FOBQ_TRY(hipStreamWaitEvent(s, ctx->sync_ev[EV_JOIN], 0), "stream wait");
     // column scores, order
@@ -1036,11 +1038,12 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
     }
     {
         StageScope sc(ctx, FOBQ_STAGE_EMIT);
-        if (out->codes || out->Q)
-            FOBQ_TRY(launch_emit(s, codesT, Rp, R, d, steps, p.ob.invperm, scale, zero, G, opts->group,
-                                 out->codes, out->Q, lossrow, out->loss), "emit");
+        const bool emit = out->codes || out->Q;
+        if (emit)
+            FOBQ_TRY(launch_emit(s, codesT, Rp, R, d, steps, p.ob.invperm, scale, zero, G, opts->group, out->codes, out->Q, lossrow, out->loss,
+                                 EmitTail{perm, out->perm, ctx->flags.as<int>(), ctx->h_flags, ctx->h_flags ? FLAG_COUNT : 0}), "emit");
         else if (out->loss) FOBQ_TRY(launch_loss(s, lossrow, R, out->loss), "loss");
-        if (out->perm)
+        if (out->perm && !emit)
             FOBQ_TRY(hipMemcpyAsync(out->perm, perm, (size_t)d * sizeof(int), hipMemcpyDeviceToDevice, s), "copy perm");
         if (out->W_work && !p.flow)
             FOBQ_TRY(hipMemcpyAsync(out->W_work, Wp, (size_t)R * d * sizeof(double), hipMemcpyDeviceToDevice, s), "copy W_work");
@@ -1111,7 +1114,9 @@ static int quantize_enqueue(fobq_ctx* ctx, const float* W, int64_t d_row, int64_
     rc = enqueue_layer_launches(ctx, p);
     // a failure past this point has work in flight on both streams that reads W / H and writes the outputs
     // and the context's scratch: wait for it, so that the caller may free its buffers and use the context again
-    return rc ? drain_after_failure(ctx, rc) : FOBQ_OK;
+    if (rc) return drain_after_failure(ctx, rc);
+    ctx->flags_sent = (out->codes || out->Q) && ctx->h_flags;
+    return FOBQ_OK;
 }
 
 // carve `bytes` (rounded up to 256) out of a pool laid out from `*off`; base == null: only the size is wanted

@@ -117,6 +117,7 @@ struct fobq_ctx {
                             // that live longer (FLAG_WORD_NONFINITE: an accumulation)
     int cus = 256;          // compute units of the device (fobq_create)
     int* h_flags = nullptr; // pinned host memory that the status flags are read back into (made by fobq_create)
+    bool flags_sent = false;    // the enqueued layer's last launch writes them there itself
     unsigned char* static_scratch = nullptr;   // this GPU's copy of the library's static scratch array
     int flow_looks = fobq::FLOW_LOOKS;   // (test hook: fobq_debug_wait_looks)
     int fail_countdown = 0; // test hook: > 0 = the n-th status check from now reports an injected failure
@@ -338,9 +339,11 @@ hipError_t launch_dyn_select(hipStream_t s, double* Wp, int R, int d, int t, dou
 hipError_t launch_step(hipStream_t s, double* Wp, int R, int d, int t, double* A,
                        const double* scale, const double* zero, int G, int group, const int* perm, int bits,
                        uint8_t* codesT, int Rp, double* lossrow, int* flag);   // *flag = 1 when the pivot is not > 0
+// what a layer's last launch does besides: the order to the caller (perm_out may be null), the status words to pinned host memory
+struct EmitTail { const int* perm = nullptr; int* perm_out = nullptr; const int* flags = nullptr; int* host_flags = nullptr; int n_flags = 0; };
 hipError_t launch_emit(hipStream_t s, const uint8_t* codesT, int Rp, int R, int d, int steps,
                        const int* invperm, const double* scale, const double* zero, int G, int group,
-                       uint8_t* codes, float* Q, const double* lossrow, double* loss);   // loss may be null
+                       uint8_t* codes, float* Q, const double* lossrow, double* loss, EmitTail tail);   // loss may be null
 hipError_t launch_loss(hipStream_t s, const double* lossrow, int R, double* loss);
 hipError_t launch_hinv_work(hipStream_t s, const double* A, int d, int steps, double* out);
 hipError_t launch_fill_i32(hipStream_t s, int* p, int64_t n, int v);

@@ -672,8 +672,9 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
                                                    const int* __restrict__ invperm, const double* __restrict__ scale,
                                                    const double* __restrict__ zero, int G, int gs,
                                                    uint8_t* __restrict__ codes, float* __restrict__ Q,
-                                                   const double* __restrict__ lossrow, double* __restrict__ loss)
+                                                   const double* __restrict__ lossrow, double* __restrict__ loss, EmitTail tail)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < tail.n_flags) tail.host_flags[threadIdx.x] = tail.flags[threadIdx.x];
     if (loss && blockIdx.x == 0 && blockIdx.y == 0) {       // uniform over the workgroup
         __shared__ double part[256];
         double s = 0.0;
@@ -689,6 +690,7 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
     const int c = blockIdx.x * 256 + threadIdx.x;
     const int i = blockIdx.y;
     if (c >= d) return;
+    if (tail.perm_out && i == 0) tail.perm_out[c] = tail.perm[c];
     int t = invperm[c];
     uint8_t code = 0;
     double q = 0.0;
@@ -703,11 +705,11 @@ __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ c
 
 hipError_t launch_emit(hipStream_t s, const uint8_t* codesT, int Rp, int R, int d, int steps,
                        const int* invperm, const double* scale, const double* zero, int G, int group,
-                       uint8_t* codes, float* Q, const double* lossrow, double* loss)
+                       uint8_t* codes, float* Q, const double* lossrow, double* loss, EmitTail tail)
 {
     const int gs = group > 0 ? group : d;
     hipLaunchKernelGGL(emit_kernel, dim3((d + 255) / 256, R), dim3(256), 0, s, codesT, Rp, R, d, steps, invperm,
-                       scale, zero, G, gs, codes, Q, lossrow, loss);
+                       scale, zero, G, gs, codes, Q, lossrow, loss, tail);
     return hipGetLastError();
 }
 
