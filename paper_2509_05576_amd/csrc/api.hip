@@ -114,6 +114,12 @@ static hipError_t ensure_sync_event(fobq_ctx* c, size_t i)
     return rc;
 }
 
+// events of a layer in ctx->sync_ev: the fork / join pair that sends the grid and the W-only part of the
+// scores to the side stream and back, then one "pivot rows ready" event per column block, then the start
+// and the end of the column loop.  No event serves two purposes within a layer.
+// (The strips of a convolution by tap offsets are sent to the side stream and back by the first two as well.)
+enum { EV_FORK = 0, EV_JOIN = 1, EV_ROWS0 = 2 };
+
 static int ensure_sync_events(fobq_ctx* ctx, size_t n)
 {
     FOBQ_TRY(ensure_side_stream(ctx), "side stream");
@@ -593,9 +599,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         if (grc) return grc;
     }
     int fresh = 0;
+    bool strips = false;
     if (offsets) {
         FOBQ_TRY(ctx->hcorr.ensure((size_t)d * d * sizeof(double)), "workspace corrections");
         FOBQ_TRY(ctx->strips.ensure(offset_strips_bytes(tab.njobs, (int)c)), "workspace strips");
+        strips = tab.njobs > 0;
+        if (strips) {
+            const int erc = ensure_sync_events(ctx, EV_ROWS0);
+            if (erc) return erc;
+        }
         if (first_call) FOBQ_TRY(launch_clear_words(ctx->stream, ctx->hcorr.p, (int64_t)d * d * 2, nullptr, 0), "clear corrections");
         // the slabs a launch can touch for the first time: the rows of the two base taps, all columns
         auto clear_rect = [&](int64_t n) -> int {
@@ -628,36 +640,52 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         ctx->h_i8_used = true;
     }
     FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>(),
-                             i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax), "pad maps");
-    if (i8) {
-        // the digits of the unfolded input are written out (1.25 bytes per element of the unfolded X, a block of
-        // columns at a time) and the matrix kernel runs on them as it does on a plain X
-        {
-            StageScope sc(ctx, FOBQ_STAGE_SLICE);
-            FOBQ_TRY(launch_i8_chan_shifts(ctx->stream, ctx->maps_pad.as<float>(), (n_img + 1) * hp * wp, (int)c, d,
-                                           ctx->i8amax.as<unsigned>(), have_amax, ctx->i8sh.as<int>(), nonfinite), "channel exponents");
-        }
-        for (int64_t p0 = 0; p0 < npix; p0 += blk) {
-            const int64_t nb = npix - p0 < blk ? npix - p0 : blk;
+                             i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax, strips ? ctx->sync_ev[EV_FORK] : nullptr), "pad maps");
+    if (strips) {
+        // the strips read the padded copy only and are bound by the fp64 pipes, the digits by memory: beside them, on the side stream
+        // (256 channels, 14 x 14 x 128 maps, 3 x 3: 638 -> 605 us)
+        const int rc = [&]() -> int {
+            FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
+            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, ctx->side);
+            FOBQ_TRY(launch_offset_corrections(ctx->side, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, d, tab,
+                                               ctx->strips.as<double>(), ctx->hcorr.as<double>(), ctx->sync_ev[EV_JOIN]), "offset corrections");
+            return FOBQ_OK;
+        }();
+        if (rc) return drain_after_failure(ctx, rc);
+    }
+    const int rc = [&]() -> int {
+        if (i8) {
+            // the digits of the unfolded input are written out (1.25 bytes per element of the unfolded X, a block of
+            // columns at a time) and the matrix kernel runs on them as it does on a plain X
             {
                 StageScope sc(ctx, FOBQ_STAGE_SLICE);
-                FOBQ_TRY(launch_i8_slice_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k,
-                                              stride, (int)ho, (int)wo, npix, p0, nb, ctx->i8sh.as<int>(),
-                                              ctx->i8planes.as<signed char>()), "integer slices (convolution)");
+                FOBQ_TRY(launch_i8_chan_shifts(ctx->stream, ctx->maps_pad.as<float>(), (n_img + 1) * hp * wp, (int)c, d,
+                                               ctx->i8amax.as<unsigned>(), have_amax, ctx->i8sh.as<int>(), nonfinite), "channel exponents");
             }
-            FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
-                                   ctx->Hpart.as<double>(), ctx->h_splits, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect), "xxt (int8)");
+            for (int64_t p0 = 0; p0 < npix; p0 += blk) {
+                const int64_t nb = npix - p0 < blk ? npix - p0 : blk;
+                {
+                    StageScope sc(ctx, FOBQ_STAGE_SLICE);
+                    FOBQ_TRY(launch_i8_slice_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k,
+                                                  stride, (int)ho, (int)wo, npix, p0, nb, ctx->i8sh.as<int>(),
+                                                  ctx->i8planes.as<signed char>()), "integer slices (convolution)");
+                }
+                FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
+                                       ctx->Hpart.as<double>(), ctx->h_splits, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect), "xxt (int8)");
+            }
+        } else {
+            FOBQ_TRY(launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
+                                     (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
+                                     stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
+            if (fresh > 0) ctx->h_zeroed = fresh;
         }
-        if (offsets) {
-            StageScope sc(ctx, FOBQ_STAGE_FINALIZE);
-            FOBQ_TRY(launch_offset_corrections(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, d, tab,
-                                               ctx->strips.as<double>(), ctx->hcorr.as<double>()), "offset corrections");
-        }
-    } else {
-        FOBQ_TRY(launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
-                                 (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
-                                 stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
-        if (fresh > 0) ctx->h_zeroed = fresh;
+        return FOBQ_OK;
+    }();
+    if (rc) return strips ? drain_after_failure(ctx, rc) : rc;
+    // whatever comes next on the context's stream (the corrections' use, another call's padded copy) finds the strips done
+    if (strips) {
+        const hipError_t e = hipStreamWaitEvent(ctx->stream, ctx->sync_ev[EV_JOIN], 0);
+        if (e != hipSuccess) return drain_after_failure(ctx, hip_err(ctx, e, "stream wait"));
     }
     ctx->h_n += npix;
     return FOBQ_OK;
@@ -919,11 +947,6 @@ struct LayerPlan {
     bool flow;           // all columns in blocks of 64: elimination and column loop are one launch
     OrderBufs ob;
 };
-
-// events of a layer in ctx->sync_ev: the fork / join pair that sends the grid and the W-only part of the
-// scores to the side stream and back, then one "pivot rows ready" event per column block, then the start
-// and the end of the column loop.  No event serves two purposes within a layer.
-enum { EV_FORK = 0, EV_JOIN = 1, EV_ROWS0 = 2 };
 
 // All launches of a layer (no allocation in here: a failure leaves work in flight, see quantize_enqueue).
 static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)

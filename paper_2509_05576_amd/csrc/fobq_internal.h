@@ -189,7 +189,8 @@ hipError_t launch_clear_slabs(hipStream_t s, double* Hpart, int d, int first, in
 // the channel maxima along
 struct PadPlan { int64_t rows; int parts, run, wgs, active; bool vec, maxima; };
 PadPlan pad_maps_plan(int64_t n_img, int h, int w, int c, int pad, bool aligned, bool maxima);
-hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took);
+hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took,
+                           hipEvent_t done = nullptr);
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                            int ho, int wo, int64_t npix, double* Hpart, int splits, int fresh,
                            LaunchEvents ev = LaunchEvents());
@@ -252,7 +253,7 @@ bool offset_tables_build(int k, int pad, int h, int w, OffsetTables* tab);
 size_t offset_strips_bytes(int njobs, int c);
 hipError_t launch_clear_slab_rows(hipStream_t s, double* Hpart, int d, int first, int count, int row0, int n0, int row1, int n1);
 hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int d,
-                                     const OffsetTables& tab, double* strips, double* corr);
+                                     const OffsetTables& tab, double* strips, double* corr, hipEvent_t done);
 hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, int c,
                                            int k, const double* corr, const int* poison);
 

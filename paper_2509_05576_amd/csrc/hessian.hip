@@ -156,13 +156,14 @@ PadPlan pad_maps_plan(int64_t n_img, int h, int w, int c, int pad, bool aligned,
 }
 
 // amax: null, or c words that hold zeros; *took (if amax): whether the maxima were taken (else the caller's own pass does it)
-hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took)
+hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, int w, int c, int pad, float* out, unsigned* amax, bool* took,
+                           hipEvent_t done)
 {
     const PadPlan p = pad_maps_plan(n_img, h, w, c, pad, ((reinterpret_cast<uintptr_t>(maps) | reinterpret_cast<uintptr_t>(out)) & 15) == 0, amax != nullptr);
     if (took) *took = p.maxima;
     auto launch = [&](auto whole, auto split) {
-        hipLaunchKernelGGL((p.parts > 1 ? split : whole), dim3(p.wgs), dim3(256), 0, s, maps, n_img, h, w, c, pad, out, p.rows, p.parts, p.run,
-                           p.active, amax);
+        hipExtLaunchKernelGGL((p.parts > 1 ? split : whole), dim3(p.wgs), dim3(256), 0, s, nullptr, done, 0, maps, n_img, h, w, c, pad, out, p.rows,
+                              p.parts, p.run, p.active, amax);
     };
     if (p.vec && p.maxima) launch(pad_maps_kernel<true, true, false>, pad_maps_kernel<true, true, true>);
     else if (p.vec)        launch(pad_maps_kernel<true, false, false>, pad_maps_kernel<true, false, true>);
