@@ -1204,7 +1204,9 @@ FlowElimPlan flow_eliminate_plan(int cus, int d, int R)
     const int64_t T = (d + NB - 1) / NB, NG = (R + NB - 1) / NB;
     p.nr = column_rows(cus, R, T);
     const int64_t parts = NG * (8 / p.nr);
-    const double w1 = work_u((double)T), w2 = work_columns((double)T, (double)NG, p.nr, d), w3 = work_groups((double)T, (double)NG);
+    // (a third more for queue 1 than its work: its workgroups go over to the other queues when it is empty, and those wait for its
+    // rows until then.  2048 x 4608 with 1, 1.3, 1.7 and 2.2 times the work 4546, 4419, 4544 and 4840 us, 1000 x 2048 959, 957, 963, 975)
+    const double w1 = 1.3 * work_u((double)T), w2 = work_columns((double)T, (double)NG, p.nr, d), w3 = work_groups((double)T, (double)NG);
     const int64_t k1 = 2 * T, k2 = parts + (parts + 1) / 2, k3 = NG + NG * T / 6;
     const int avail = flow_grid(cus, T * (T + 9 * NG)) - 1;
     if (k1 + k2 + k3 <= avail) {
