@@ -284,8 +284,8 @@ static int read_flags(fobq_ctx* ctx, const int* dev_flags)
 {
     int* h = ctx->h_flags;
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
-    if (!ctx->flags_sent)
-        FOBQ_TRY(hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "read status flags");
+    FOBQ_TRY(ctx->flags_sent ? hipSuccess : hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream),
+             "read status flags");
     ctx->flags_sent = false;
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
     if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for three quarters of a minute and was given up");
@@ -1066,8 +1066,7 @@ static int enqueue_layer_launches(fobq_ctx* ctx, const LayerPlan& p)
             FOBQ_TRY(launch_emit(s, codesT, Rp, R, d, steps, p.ob.invperm, scale, zero, G, opts->group, out->codes, out->Q, lossrow, out->loss,
                                  EmitTail{perm, out->perm, ctx->flags.as<int>(), ctx->h_flags, ctx->h_flags ? FLAG_COUNT : 0}), "emit");
         else if (out->loss) FOBQ_TRY(launch_loss(s, lossrow, R, out->loss), "loss");
-        if (out->perm && !emit)
-            FOBQ_TRY(hipMemcpyAsync(out->perm, perm, (size_t)d * sizeof(int), hipMemcpyDeviceToDevice, s), "copy perm");
+        FOBQ_TRY(!out->perm || emit ? hipSuccess : hipMemcpyAsync(out->perm, perm, (size_t)d * sizeof(int), hipMemcpyDeviceToDevice, s), "copy perm");
         if (out->W_work && !p.flow)
             FOBQ_TRY(hipMemcpyAsync(out->W_work, Wp, (size_t)R * d * sizeof(double), hipMemcpyDeviceToDevice, s), "copy W_work");
         if (out->Hinv_work) FOBQ_TRY(launch_hinv_work(s, p.flow ? ctx->Hinv.as<double>() : A, d, steps, out->Hinv_work), "copy Hinv_work");
