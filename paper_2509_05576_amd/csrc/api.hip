@@ -717,15 +717,12 @@ int fobq_hessian_finalize(fobq_ctx* ctx, double* H_out)
         const int* poison = ctx->h_i8_used ? ctx->flags.as<int>() + FLAG_WORD_NONFINITE : nullptr;
         if (ctx->h_offsets)
             FOBQ_TRY(launch_hessian_finalize_offsets(ctx->stream, ctx->Hpart.as<double>(), ctx->h_zeroed, d, 2.0 / (double)ctx->h_n,
-                                                     ctx->H.as<double>(), ctx->h_conv_c, ctx->h_conv_k, ctx->hcorr.as<double>(),
+                                                     ctx->H.as<double>(), H_out, ctx->h_conv_c, ctx->h_conv_k, ctx->hcorr.as<double>(),
                                                      poison), "hessian finalize (tap offsets)");
         else
             FOBQ_TRY(launch_hessian_finalize(ctx->stream, ctx->Hpart.as<double>(), ctx->h_zeroed, d,
-                                             2.0 / (double)ctx->h_n, ctx->H.as<double>(), ctx->h_conv_c > 0 ? ctx->h_conv_c : 0,
+                                             2.0 / (double)ctx->h_n, ctx->H.as<double>(), H_out, ctx->h_conv_c > 0 ? ctx->h_conv_c : 0,
                                              ctx->h_conv_k * ctx->h_conv_k, poison), "hessian finalize");
-        if (H_out)
-            FOBQ_TRY(hipMemcpyAsync(H_out, ctx->H.p, (size_t)d * d * sizeof(double), hipMemcpyDeviceToDevice,
-                                    ctx->stream), "copy H");
     }
     ctx->h_final = true;
     return FOBQ_OK;

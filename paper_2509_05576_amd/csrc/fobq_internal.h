@@ -194,7 +194,8 @@ hipError_t launch_pad_maps(hipStream_t s, const float* maps, int n_img, int h, i
 hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                            int ho, int wo, int64_t npix, double* Hpart, int splits, int fresh,
                            LaunchEvents ev = LaunchEvents());
-hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H,
+// (H2: null, or a second place for H)
+hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H, double* H2,
                                    int conv_c, int conv_kk, const int* poison);   // *poison != 0: H = NaN
 
 // hessian_i8.hip: X X^T by exact integer slices on the int8 matrix cores
@@ -254,7 +255,7 @@ size_t offset_strips_bytes(int njobs, int c);
 hipError_t launch_clear_slab_rows(hipStream_t s, double* Hpart, int d, int first, int count, int row0, int n0, int row1, int n1);
 hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int d,
                                      const OffsetTables& tab, double* strips, double* corr, hipEvent_t done);
-hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, int c,
+hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, double* H2, int c,
                                            int k, const double* corr, const int* poison);
 
 // flow.hip: damped H -> upper tiles of Hinv = (H + lambda I)^-1, lambda = damp * mean(diag H) + damp_abs, in one launch.  tiles, gt:

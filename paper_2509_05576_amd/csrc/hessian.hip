@@ -766,7 +766,7 @@ hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp
 // poison (may be null): a word that is non-zero when an input of the integer-slice path held an Inf or NaN;
 // H then becomes NaN throughout, as the floating-point sum would have made the rows concerned.
 __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
-                                                               double factor, double* __restrict__ H,
+                                                               double factor, double* __restrict__ H, double* __restrict__ H2,
                                                                const int* __restrict__ poison)
 {
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
@@ -778,12 +778,16 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)a * d + b] = s;
     H[(int64_t)b * d + a] = s;
+    if (H2) {
+        H2[(int64_t)a * d + b] = s;
+        H2[(int64_t)b * d + a] = s;
+    }
 }
 
 // Convolution mode: the slabs are in tap-major row order; H is written in (c, ky, kx) order.
 __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
-                                                                    double factor, double* __restrict__ H, int c,
-                                                                    int kk, const int* __restrict__ poison)
+                                                                    double factor, double* __restrict__ H, double* __restrict__ H2,
+                                                                    int c, int kk, const int* __restrict__ poison)
 {
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
     const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
@@ -796,6 +800,10 @@ __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)a * d + b] = s;
     H[(int64_t)b * d + a] = s;
+    if (H2) {
+        H2[(int64_t)a * d + b] = s;
+        H2[(int64_t)b * d + a] = s;
+    }
 }
 
 // conv_c > 0: the slabs were accumulated in convolution mode with conv_c channels and conv_kk taps
@@ -816,7 +824,7 @@ __global__ __launch_bounds__(256) void hessian_group_slabs_kernel(double* __rest
     Hpart[(int64_t)k0 * d * d + at] = s;
 }
 
-hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H,
+hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H, double* H2,
                                    int conv_c, int conv_kk, const int* poison)
 {
     dim3 grid((d + 15) / 16, (d + 15) / 16), block(256);
@@ -828,10 +836,10 @@ hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int
         sstride = SLAB_GROUP;
     }
     if (conv_c > 0)
-        hipLaunchKernelGGL(hessian_finalize_conv_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, conv_c, conv_kk,
+        hipLaunchKernelGGL(hessian_finalize_conv_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
                            poison);
     else
-        hipLaunchKernelGGL(hessian_finalize_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, poison);
+        hipLaunchKernelGGL(hessian_finalize_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, poison);
     return hipGetLastError();
 }
 

@@ -70,9 +70,12 @@ __global__ __launch_bounds__(256) void row_shift_kernel(const float* __restrict_
         auto mag4 = [](const uint4& a) {
             return max(max(a.x & 0x7fffffffu, a.y & 0x7fffffffu), max(a.z & 0x7fffffffu, a.w & 0x7fffffffu));
         };
-        for (; j + 768 < n4; j += 1024) {
-            const uint4 a = x4[j], b = x4[j + 256], c = x4[j + 512], e = x4[j + 768];
-            m = max(max(m, mag4(a)), max(mag4(b), max(mag4(c), mag4(e))));
+        for (; j + 1792 < n4; j += 2048) {         // 8 loads in flight
+            uint4 a[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[u] = x4[j + 256 * u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m = max(m, mag4(a[u]));
         }
         for (; j < n4; j += 256) m = max(m, mag4(x4[j]));
         for (int64_t k = (n4 << 2) + threadIdx.x; k < n; k += 256) m = max(m, __float_as_uint(x[k]) & 0x7fffffffu);

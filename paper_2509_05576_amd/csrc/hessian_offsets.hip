@@ -178,8 +178,8 @@ __global__ __launch_bounds__(256) void offset_apply_kernel(OffsetTables tab, con
 // corrections.  Every entry is taken in its canonical orientation (offset pointing down, or right within a row;
 // for the zero offset the lower triangle of the block), so H comes out exactly symmetric.
 __global__ __launch_bounds__(256) void hessian_finalize_offsets_kernel(const double* __restrict__ Hpart, int splits, int d,
-                                                                       double factor, double* __restrict__ H, int c, int k,
-                                                                       const double* __restrict__ corr,
+                                                                       double factor, double* __restrict__ H, double* __restrict__ H2,
+                                                                       int c, int k, const double* __restrict__ corr,
                                                                        const int* __restrict__ poison)
 {
     const int col = blockIdx.x * 16 + (threadIdx.x & 15);
@@ -204,6 +204,10 @@ __global__ __launch_bounds__(256) void hessian_finalize_offsets_kernel(const dou
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)row * d + col] = s;
     H[(int64_t)col * d + row] = s;
+    if (H2) {
+        H2[(int64_t)row * d + col] = s;
+        H2[(int64_t)col * d + row] = s;
+    }
 }
 
 // full rows [row0, row0 + n0) and [row1, row1 + n1) of `count` slabs from slab `first` on
@@ -236,11 +240,11 @@ hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_i
     return hipGetLastError();
 }
 
-hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, int c,
+hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, double* H2, int c,
                                            int k, const double* corr, const int* poison)
 {
     hipLaunchKernelGGL(hessian_finalize_offsets_kernel, dim3((d + 15) / 16, (d + 15) / 16), dim3(256), 0, s, Hpart, splits, d,
-                       factor, H, c, k, corr, poison);
+                       factor, H, H2, c, k, corr, poison);
     return hipGetLastError();
 }
 
