@@ -1222,6 +1222,10 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         return set_err(ctx, FOBQ_ENOMEM, "cannot allocate pinned host memory for the batch descriptors");
     }
     FOBQ_TRY(ctx->batch_desc.ensure(desc_bytes), "workspace batch descriptors");
+    {
+        const int erc = ensure_sync_events(ctx, EV_ROWS0);
+        if (erc) return erc;
+    }
     unsigned char* hb = static_cast<unsigned char*>(ctx->h_batch);
     BatchLayer* hd = static_cast<BatchLayer*>(ctx->h_batch);
     int max_pairs = 1, max_chunks = 1;
@@ -1277,9 +1281,12 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     const BatchLayer* dl = reinterpret_cast<const BatchLayer*>(db);
     int rc = [&]() -> int {
         FOBQ_TRY(hipMemcpyAsync(ctx->batch_desc.p, hb, sent_bytes, hipMemcpyHostToDevice, s), "upload batch descriptors");
-        FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs), "grid (batch)");
-        FOBQ_TRY(launch_batch_sens_partial(s, dl, n_layers, max_chunks), "sensitivity (batch)");
+        FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs, ctx->sync_ev[EV_FORK]), "grid (batch)");
         FOBQ_TRY(launch_flow_batch_inverse(s, db + off_inv, reinterpret_cast<const uint16_t*>(db + off_inv_of), arrivals, plan.inv_wgs), "inverse (batch)");
+        // the column sums need the weights and their grids only: beside the inverse, as for a single layer
+        FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
+        FOBQ_TRY(launch_batch_sens_partial(ctx->side, dl, n_layers, max_chunks, ctx->sync_ev[EV_JOIN]), "sensitivity (batch)");
+        FOBQ_TRY(hipStreamWaitEvent(s, ctx->sync_ev[EV_JOIN], 0), "stream wait");
         FOBQ_TRY(launch_batch_order(s, dl, n_layers), "order (batch)");
         FOBQ_TRY(launch_flow_batch_eliminate(s, db + off_elim, reinterpret_cast<const uint16_t*>(db + off_elim_of), arrivals + 1,
                                             plan.elim_wgs, plan.nr),

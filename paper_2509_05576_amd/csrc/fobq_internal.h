@@ -305,8 +305,8 @@ hipError_t launch_flow_batch_eliminate(hipStream_t s, const void* desc, const ui
 
 // the rest of a batched call: quant.hip; grids have one dimension over the layers
 hipError_t launch_batch_order(hipStream_t s, const BatchLayer* layers, int n);
-hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs);
-hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks);
+hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs, hipEvent_t done);
+hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks, hipEvent_t done);
 hipError_t launch_batch_emit(hipStream_t s, const BatchLayer* layers, int n, int64_t max_weights);
 
 // per-row baseline (obq.hip)

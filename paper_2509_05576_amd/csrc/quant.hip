@@ -907,15 +907,15 @@ __global__ __launch_bounds__(256) void batch_emit_kernel(const BatchLayer* __res
     }
 }
 
-hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs)
+hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs, hipEvent_t done)
 {
-    hipLaunchKernelGGL(batch_grid_kernel, dim3((max_pairs + 3) / 4, n), dim3(256), 0, s, layers);
+    hipExtLaunchKernelGGL(batch_grid_kernel, dim3((max_pairs + 3) / 4, n), dim3(256), 0, s, nullptr, done, 0, layers);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks)
+hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks, hipEvent_t done)
 {
-    hipLaunchKernelGGL(batch_sens_partial_kernel, dim3(max_chunks, n), dim3(256), 0, s, layers);
+    hipExtLaunchKernelGGL(batch_sens_partial_kernel, dim3(max_chunks, n), dim3(256), 0, s, nullptr, done, 0, layers);
     return hipGetLastError();
 }
 
