@@ -356,6 +356,29 @@ static std::vector<DevBuf*> all_buffers(fobq_ctx* ctx)
             &ctx->S, &ctx->Spart, &ctx->perm, &ctx->invperm, &ctx->maps_pad, &ctx->i8planes, &ctx->i8sh, &ctx->i8amax, &ctx->batch_pool, &ctx->batch_desc, &ctx->obq, &ctx->hcorr, &ctx->strips};
 }
 
+// The slabs of Hpart that the launches of one call need: the first launch of an accumulation stores, into `fresh` slabs (h_zeroed
+// once it is enqueued); what later launches can touch beyond those, or beyond what is there, is cleared.  need, need_last: slabs of
+// the call's launches and of its shorter last one (0: none); clear(first, count) enqueues.
+template <class Clear>
+static int prepare_slabs(fobq_ctx* ctx, int need, int need_last, int* fresh, int* have, Clear clear)
+{
+    *fresh = ctx->h_zeroed == 0 ? need : 0;
+    *have = std::max(ctx->h_zeroed, *fresh);
+    const int most = std::max(need, need_last);
+    if (most > *have) {
+        FOBQ_TRY(clear(*have, most - *have), "clear Hessian accumulator");
+        *have = most;
+    }
+    return FOBQ_OK;
+}
+
+static int prepare_slabs(fobq_ctx* ctx, int64_t n, int64_t blk, bool conv, bool i8, int* fresh, int* have)
+{
+    auto touched = [&](int64_t m) { return i8 ? xxt_i8_slabs_touched((int)ctx->h_d, m, ctx->h_splits) : xxt_slabs_touched((int)ctx->h_d, m, ctx->h_splits, conv); };
+    return prepare_slabs(ctx, touched(n < blk ? n : blk), n > blk && n % blk ? touched(n % blk) : 0, fresh, have, [&](int first, int count) {
+        return launch_clear_slabs(ctx->stream, ctx->Hpart.as<double>(), (int)ctx->h_d, first, count); });
+}
+
 extern "C" {
 
 int fobq_create(fobq_ctx** out, int device, void* hip_stream)
@@ -455,21 +478,6 @@ int fobq_hessian_begin(fobq_ctx* ctx, int64_t d_col)
     return FOBQ_OK;
 }
 
-// clears the slabs of Hpart that a launch over n calibration columns can touch for the first time; *fresh: the fp64 kernel's
-// first launch needs no clearing, but the number of its slabs (h_zeroed once it is enqueued)
-static int clear_slabs(fobq_ctx* ctx, int64_t n, bool conv, bool i8, int* fresh)
-{
-    const int need = i8 ? xxt_i8_slabs_touched((int)ctx->h_d, n, ctx->h_splits)
-                        : xxt_slabs_touched((int)ctx->h_d, n, ctx->h_splits, conv);
-    *fresh = !i8 && ctx->h_zeroed == 0 ? need : 0;
-    if (need > ctx->h_zeroed && *fresh == 0) {
-        FOBQ_TRY(launch_clear_slabs(ctx->stream, ctx->Hpart.as<double>(), (int)ctx->h_d, ctx->h_zeroed, need - ctx->h_zeroed),
-                 "clear Hessian accumulator");
-        ctx->h_zeroed = need;
-    }
-    return FOBQ_OK;
-}
-
 // Before its first launch an accumulation may still take more slabs than fobq_hessian_begin reserved (the digit-product
 // kernel wants some for a wide layer with a long calibration dimension, and for a convolution taken by tap offsets, whose
 // few tiles are cut into more pieces each); a failure leaves no accumulation open.
@@ -509,9 +517,8 @@ int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld
         const int grc = grow_i8_slabs(ctx, n < blk ? n : blk);
         if (grc) return grc;
     }
-    int fresh = 0;
-    int rc = clear_slabs(ctx, n < blk ? n : blk, false, i8, &fresh);
-    if (!rc && n > blk && n % blk) rc = clear_slabs(ctx, n % blk, false, i8, &fresh);    // the shorter last launch
+    int fresh = 0, have = 0;
+    int rc = prepare_slabs(ctx, n, blk, false, i8, &fresh, &have);
     if (rc) return rc;
     ctx->h_conv_c = -1;
     if (i8) {
@@ -530,12 +537,14 @@ int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld
                          "integer slices");
             }
             FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
-                                   ctx->Hpart.as<double>(), ctx->h_splits, stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (int8)");
+                                   ctx->Hpart.as<double>(), ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (int8)");
+            ctx->h_zeroed = have;
+            fresh = 0;
         }
     } else {
         FOBQ_TRY(launch_xxt(ctx->stream, X, ld, d, n, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
                             stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt");
-        if (fresh > 0) ctx->h_zeroed = fresh;
+        ctx->h_zeroed = have;
     }
     ctx->h_n += n;
     return FOBQ_OK;
@@ -598,7 +607,7 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         const int grc = grow_i8_slabs(ctx, npix < blk ? npix : blk, rect);
         if (grc) return grc;
     }
-    int fresh = 0;
+    int fresh = 0, have = 0;
     bool strips = false;
     if (offsets) {
         FOBQ_TRY(ctx->hcorr.ensure((size_t)d * d * sizeof(double)), "workspace corrections");
@@ -609,23 +618,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
             if (erc) return erc;
         }
         if (first_call) FOBQ_TRY(launch_clear_words(ctx->stream, ctx->hcorr.p, (int64_t)d * d * 2, nullptr, 0), "clear corrections");
-        // the slabs a launch can touch for the first time: the rows of the two base taps, all columns
-        auto clear_rect = [&](int64_t n) -> int {
-            const int need = xxt_i8_slabs_touched(d, n, ctx->h_splits, rect);
-            if (need > ctx->h_zeroed) {
-                const int last = d - rect_gap * 128 < rect_cb * 128 ? d - rect_gap * 128 : rect_cb * 128;     // rows past d do not exist
-                FOBQ_TRY(launch_clear_slab_rows(ctx->stream, ctx->Hpart.as<double>(), d, ctx->h_zeroed, need - ctx->h_zeroed, 0,
-                                                rect_cb * 128, rect_gap * 128, last), "clear Hessian accumulator");
-                ctx->h_zeroed = need;
-            }
-            return FOBQ_OK;
-        };
-        int rc = clear_rect(npix < blk ? npix : blk);
-        if (!rc && npix > blk && npix % blk) rc = clear_rect(npix % blk);
+        // of the slabs: the rows of the two base taps, all columns
+        const int last = d - rect_gap * 128 < rect_cb * 128 ? d - rect_gap * 128 : rect_cb * 128;     // rows past d do not exist
+        const int rc = prepare_slabs(ctx, xxt_i8_slabs_touched(d, npix < blk ? npix : blk, ctx->h_splits, rect),
+                                     npix > blk && npix % blk ? xxt_i8_slabs_touched(d, npix % blk, ctx->h_splits, rect) : 0, &fresh, &have,
+                                     [&](int first, int count) {
+            return launch_clear_slab_rows(ctx->stream, ctx->Hpart.as<double>(), d, first, count, 0, rect_cb * 128, rect_gap * 128, last); });
         if (rc) return rc;
     } else {
-        int rc = clear_slabs(ctx, npix < blk ? npix : blk, true, i8, &fresh);
-        if (!rc && npix > blk && npix % blk) rc = clear_slabs(ctx, npix % blk, true, i8, &fresh);    // the shorter last launch
+        const int rc = prepare_slabs(ctx, npix, blk, true, i8, &fresh, &have);
         if (rc) return rc;
     }
     ctx->h_conv_c = (int)c;
@@ -671,13 +672,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
                                                   ctx->i8planes.as<signed char>()), "integer slices (convolution)");
                 }
                 FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
-                                       ctx->Hpart.as<double>(), ctx->h_splits, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect), "xxt (int8)");
+                                       ctx->Hpart.as<double>(), ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect), "xxt (int8)");
+                ctx->h_zeroed = have;
+                fresh = 0;
             }
         } else {
             FOBQ_TRY(launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
                                      (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
                                      stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
-            if (fresh > 0) ctx->h_zeroed = fresh;
+            ctx->h_zeroed = have;
         }
         return FOBQ_OK;
     }();

@@ -234,7 +234,7 @@ hipError_t launch_i8_chan_shifts(hipStream_t s, const float* padded, int64_t pix
 hipError_t launch_i8_slice_conv(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int k, int stride,
                                 int ho, int wo, int64_t npix, int64_t pix0, int64_t n, const int* sh, signed char* planes);
 hipError_t launch_xxt_i8(hipStream_t s, const signed char* planes, const int* sh, int d, int64_t n, double* Hpart,
-                         int splits, LaunchEvents ev = LaunchEvents(), I8Rect rect = I8Rect());
+                         int splits, int fresh, LaunchEvents ev = LaunchEvents(), I8Rect rect = I8Rect());   // fresh: as for launch_xxt
 // hessian_offsets.hip: Hessian of a stride-1 convolution by tap offsets (two block rows from the digit-product kernel,
 // the other blocks by corrections over single rows and columns of the padded maps)
 constexpr int OFFSET_MAX_TAPS = 9, OFFSET_MAX_JOBS = 128, OFFSET_MAX_PAIRS = 81, OFFSET_MAX_TERMS = 384;
