@@ -1231,8 +1231,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     }
     unsigned char* hb = static_cast<unsigned char*>(ctx->h_batch);
     BatchLayer* hd = static_cast<BatchLayer*>(ctx->h_batch);
-    int max_pairs = 1, max_chunks = 1;
-    int64_t max_weights = 1;
+    int max_pairs = 1, max_chunks = 1, max_tiles = 1;
     size_t pool = 0;
     pool_take(nullptr, &pool, (size_t)n_layers * 4 * sizeof(int));          // status words
     for (int l = 0; l < n_layers; ++l) {
@@ -1253,7 +1252,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         batch_layout(&L, nullptr, &pool);
         max_pairs = std::max(max_pairs, L.R * L.G);
         max_chunks = std::max(max_chunks, L.chunks);
-        max_weights = std::max(max_weights, (int64_t)L.R * L.d);
+        max_tiles = std::max(max_tiles, (L.R + 15) / 16 * ((L.d + 63) / 64));
     }
     FOBQ_TRY(ctx->batch_pool.ensure(pool), "workspace batch pool");
     size_t off = 0;
@@ -1294,7 +1293,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         FOBQ_TRY(launch_flow_batch_eliminate(s, db + off_elim, reinterpret_cast<const uint16_t*>(db + off_elim_of), arrivals + 1,
                                             plan.elim_wgs, plan.nr),
                  "eliminate and columns (batch)");
-        FOBQ_TRY(launch_batch_emit(s, dl, n_layers, max_weights), "emit (batch)");
+        FOBQ_TRY(launch_batch_emit(s, dl, n_layers, max_tiles), "emit (batch)");
         int* hflags = reinterpret_cast<int*>(hb + desc_bytes);      // behind the descriptors
         FOBQ_TRY(hipMemcpyAsync(hflags, flags, (size_t)n_layers * 4 * sizeof(int), hipMemcpyDeviceToHost, s), "read status flags");
         FOBQ_TRY(hipStreamSynchronize(s), "synchronize");

@@ -307,7 +307,7 @@ hipError_t launch_flow_batch_eliminate(hipStream_t s, const void* desc, const ui
 hipError_t launch_batch_order(hipStream_t s, const BatchLayer* layers, int n);
 hipError_t launch_batch_grid(hipStream_t s, const BatchLayer* layers, int n, int max_pairs, hipEvent_t done);
 hipError_t launch_batch_sens_partial(hipStream_t s, const BatchLayer* layers, int n, int max_chunks, hipEvent_t done);
-hipError_t launch_batch_emit(hipStream_t s, const BatchLayer* layers, int n, int64_t max_weights);
+hipError_t launch_batch_emit(hipStream_t s, const BatchLayer* layers, int n, int max_tiles);   // max_tiles: of 16 rows x 64 columns
 
 // per-row baseline (obq.hip)
 constexpr int OBQ_MAX_D = 4096;        // columns: a row's weights, pivot row and flags live in LDS
