@@ -40,8 +40,8 @@ namespace fobq {
 
 constexpr int TILE = NB * NB;                        // doubles of a published tile
 constexpr int FLOW_LDS = SWEEP_LDS + 4 * NB * DL;    // doubles: two double-buffered operand tiles, or the chain's blocks
-// words of a launch, all zero before it: counters, then one word per tile (T x T), then two per diagonal block for the
-// sums that are handed to the chain
+// words of a launch, all zero before it: counters, then one word per tile (T x T), then three per diagonal block: for the two
+// sums that are handed to the chain and for the sum of tile (k - 2, k) that goes into them
 enum { FW_ROLE = 0, FW_QUEUE1 = 1, FW_QUEUE2 = 2, FW_QUEUE3 = 3, FW_ABORT = 4, FW_HEAD = 16 };
 
 __device__ __forceinline__ double ld_shared(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -50,7 +50,8 @@ __device__ __forceinline__ int ld_word(const int* p) { return __hip_atomic_load(
 __device__ __forceinline__ void st_word(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // what both launches have: d columns in T blocks; tiles: T x T published tiles, [row of tiles][column of tiles][64][64];
-// gt: T tiles, the transposed block inverses, then T tiles for the sums D(k, 0) (see Queue1); stalled: status word for a launch that gave up
+// gt: T tiles, the transposed block inverses, then T tiles for the sums D(k, 0) (see Queue1), then T for
+// those of tiles (k - 2, k) (sum_tile); stalled: status word for a launch that gave up
 struct FlowP {
     int d, T;
     int n1, n2, n3;      // workgroups that serve queue 1 / 2 / 3 first (the chain's workgroup not counted)
@@ -101,7 +102,7 @@ __device__ __forceinline__ void flow_wait(const FlowP& f, const int* word, bool 
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");    // (keeps the loads that follow behind the last look)
 }
 
-// All threads: what the workgroup has stored with st_shared is visible before the word is set.
+// All threads: what the workgroup has stored with st_shared or st_pair is visible before the word is set.
 __device__ __forceinline__ void flow_publish(int* word)
 {
     __builtin_amdgcn_s_waitcnt(0);
@@ -469,6 +470,10 @@ struct SumR {      // R_qi^T R_qj; X_qi^T X_qj; R_qi^T X_qj
 // other six are formed beside it).
 // A wavefront's 16 x 16 tiles of the diagonal block (row tile >= column tile): one before the first sweep, wavefronts
 // 1 and 2 one more during it.
+// What a block takes, in us (256 x 2304, inverse / elimination, 12.5 / 13.3 in all): waiting for the sums 0.4, product with the
+// inverse 0.6, tile to LDS and memory 1.0 / 1.3, product off the diagonal block 1.0, that to LDS 0.3, the block 7.4, loads and stores
+// of its results 1.2 / 1.7, their way to memory 0.5.  (15.3 with 8-byte exchange, an L2 write-back per word, and the sums behind
+// tile (k - 2, k)'s own publication.)
 __device__ __forceinline__ void chain_tiles(int wave, int (&rt)[2], int (&ct)[2])
 {
     rt[0] = wave < 4 ? wave : wave == 4 ? 1 : wave == 6 ? 3 : 2;
@@ -1096,8 +1101,8 @@ int64_t flow_inverse_words(int d) { return flow_words((d + NB - 1) / NB); }
 // A part of columns with 1, 2 or 4 rows per wavefront.
 static const double PART_US[3] = {7.5, 11.0, 18.0};
 // Rows per wavefront of a part of columns (1, 2 or 4).  A part takes PART_US (measured), on top of which its successor
-// waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15 us
-// each), with many the workgroups are all busy and what counts is the time per row.  Twice the pure work over all
+// waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15.3 us
+// each when the line was drawn, 12.5 to 13.3 since), with many the workgroups are all busy and what counts is the time per row.  Twice the pure work over all
 // workgroups against the chains; measured at 1 / 2 / 4 rows, elimination and columns: 256 x 2304 0.54 / 0.58 / 0.74 ms,
 // 2048 x 512 0.16 / 0.15 / 0.19, 1024 x 4608 2.10 / 1.90 / 1.81, 8192 x 256 0.35 / 0.32 / 0.22.
 static int column_rows(int cus, int64_t R, int64_t T)
@@ -1137,8 +1142,10 @@ static FlowInverseP inverse_params(const double* H, int d, double damp, double d
     p.f.looks = looks;
     p.f.d = d;
     p.f.T = (d + NB - 1) / NB;
-    // two rows of tiles in flight keep the chain fed (64 to 160 workgroups give the same times at d = 2304 .. 4608)
-    p.f.n1 = std::max(1, std::min(2 * p.f.T, wgs / 2));
+    // two rows of tiles and a half in flight keep the chain fed; where the products bound the launch, queue 1 feeds queue 2 and its
+    // workgroups go over to that when it is empty, so it has most of them (2048 x 4608, the layer, with 2/5, 1/2, 3/5, 7/10 and 9/10
+    // of the workgroups: 4631, 4418, 4333, 4240 and 4247 us)
+    p.f.n1 = std::max(1, std::min(5 * p.f.T / 2, wgs * 7 / 10));
     p.f.n2 = std::max(1, wgs - 1 - p.f.n1);          // the others: queue 2 (there is no third)
     p.f.n3 = 0;
     p.f.words = words; p.f.tiles = tiles; p.f.gt = gt; p.f.notpd = notpd; p.f.stalled = stalled;
@@ -1238,8 +1245,8 @@ hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
 // ---- several small layers (fobq_quantize_layers_batched) ----------------------------------------------------------
 // A layer of at most 4 blocks is bound by its chain (about 18 us a block in the inverse, 15 to 20 in the elimination); the
 // layers' chains run side by side, and the launch ends when the device has worked off the parts of the longest ones.  20
-// layers of 64 .. 1024 rows and 64 .. 256 columns: inverse 75 us (one workgroup per layer, a panel at a time: 311),
-// elimination with columns 169 us (191 + 311 before, in launches of their own); the call 398 us, 1033 before.
+// layers of 64 .. 1024 rows and 64 .. 256 columns: inverse 66 us (one workgroup per layer, a panel at a time: 311),
+// elimination with columns 150 us (191 + 311 before, in launches of their own); the call 319 us, 1033 before.
 static_assert(sizeof(FlowInverseP) <= FLOW_DESC_BYTES && sizeof(FlowElimP) <= FLOW_DESC_BYTES, "descriptor size");
 constexpr int BATCH_INVERSE_WGS = 8;      // a layer of 4 blocks: the chain, and 25 tiles of R, X and Hinv
 

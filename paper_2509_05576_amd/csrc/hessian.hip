@@ -772,8 +772,7 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
     const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
     if (a >= d || b >= d || b > a) return;
-    double s = 0.0;
-    for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)a * d + b];
+    double s = slab_sum(Hpart + (int64_t)a * d + b, splits, (int64_t)sstride * d * d);
     s *= factor;
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)a * d + b] = s;
@@ -794,8 +793,7 @@ __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double
     if (a >= d || b >= d || b > a) return;
     const int ai = (a % kk) * c + a / kk, bi = (b % kk) * c + b / kk;
     const int hi = max(ai, bi), lo = min(ai, bi);
-    double s = 0.0;
-    for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)hi * d + lo];
+    double s = slab_sum(Hpart + (int64_t)hi * d + lo, splits, (int64_t)sstride * d * d);
     s *= factor;
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)a * d + b] = s;
@@ -819,9 +817,7 @@ __global__ __launch_bounds__(256) void hessian_group_slabs_kernel(double* __rest
     if (a >= d || b >= d || b > a) return;
     const int k0 = blockIdx.z * SLAB_GROUP, k1 = min(splits, k0 + SLAB_GROUP);
     const int64_t at = (int64_t)a * d + b;
-    double s = 0.0;
-    for (int k = k0; k < k1; ++k) s += Hpart[(int64_t)k * d * d + at];
-    Hpart[(int64_t)k0 * d * d + at] = s;
+    Hpart[(int64_t)k0 * d * d + at] = slab_sum(Hpart + (int64_t)k0 * d * d + at, k1 - k0, (int64_t)d * d);
 }
 
 hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int d, double factor, double* H, double* H2,
