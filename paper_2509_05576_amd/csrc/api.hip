@@ -608,12 +608,16 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         if (grc) return grc;
     }
     int fresh = 0, have = 0;
-    bool strips = false;
+    bool strips = false, beside = false;     // beside: the strips on the side stream
     if (offsets) {
         FOBQ_TRY(ctx->hcorr.ensure((size_t)d * d * sizeof(double)), "workspace corrections");
         FOBQ_TRY(ctx->strips.ensure(offset_strips_bytes(tab.njobs, (int)c)), "workspace strips");
         strips = tab.njobs > 0;
-        if (strips) {
+        // (a stream under capture keeps everything to itself: the events that ride on launches are not recorded there)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (ctx->stream) FOBQ_TRY(hipStreamIsCapturing(ctx->stream, &capture), "capture status");
+        beside = strips && capture == hipStreamCaptureStatusNone;
+        if (beside) {
             const int erc = ensure_sync_events(ctx, EV_ROWS0);
             if (erc) return erc;
         }
@@ -641,18 +645,19 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         ctx->h_i8_used = true;
     }
     FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>(),
-                             i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax, strips ? ctx->sync_ev[EV_FORK] : nullptr), "pad maps");
+                             i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax, beside ? ctx->sync_ev[EV_FORK] : nullptr), "pad maps");
     if (strips) {
         // the strips read the padded copy only and are bound by the fp64 pipes, the digits by memory: beside them, on the side stream
         // (256 channels, 14 x 14 x 128 maps, 3 x 3: 638 -> 605 us)
         const int rc = [&]() -> int {
-            FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
-            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, ctx->side);
-            FOBQ_TRY(launch_offset_corrections(ctx->side, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, d, tab,
-                                               ctx->strips.as<double>(), ctx->hcorr.as<double>(), ctx->sync_ev[EV_JOIN]), "offset corrections");
+            hipStream_t on = beside ? ctx->side : ctx->stream;
+            if (beside) FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
+            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, on);
+            FOBQ_TRY(launch_offset_corrections(on, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, d, tab,
+                                               ctx->strips.as<double>(), ctx->hcorr.as<double>(), beside ? ctx->sync_ev[EV_JOIN] : nullptr), "offset corrections");
             return FOBQ_OK;
         }();
-        if (rc) return drain_after_failure(ctx, rc);
+        if (rc) return beside ? drain_after_failure(ctx, rc) : rc;
     }
     const int rc = [&]() -> int {
         if (i8) {
@@ -684,9 +689,9 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         }
         return FOBQ_OK;
     }();
-    if (rc) return strips ? drain_after_failure(ctx, rc) : rc;
+    if (rc) return beside ? drain_after_failure(ctx, rc) : rc;
     // whatever comes next on the context's stream (the corrections' use, another call's padded copy) finds the strips done
-    if (strips) {
+    if (beside) {
         const hipError_t e = hipStreamWaitEvent(ctx->stream, ctx->sync_ev[EV_JOIN], 0);
         if (e != hipSuccess) return drain_after_failure(ctx, hip_err(ctx, e, "stream wait"));
     }
