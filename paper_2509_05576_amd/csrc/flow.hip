@@ -27,8 +27,8 @@
 // Measured with a kernel that does nothing else: 1.85 us from the first store of a 32 KB tile to its last load by a workgroup on
 // another XCD, and 16 TB/s when 256 workgroups read published tiles this way, against 9.6 TB/s that the products want at the
 // full matrix rate.
-// Registers: the inverse 166 VGPRs; the elimination, with the chain, the tiles and the column parts in one body, 192, and 145 to
-// 165 SGPRs kept in lanes of vector registers (no scratch in either).
+// Registers: the inverse 192 VGPRs; the elimination, with the chain, the tiles and the column parts in one body, 199, and 145 to
+// 155 SGPRs kept in lanes of vector registers (no scratch in either).
 #include <string.h>
 
 #include <algorithm>
