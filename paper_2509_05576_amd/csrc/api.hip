@@ -283,10 +283,11 @@ static int ensure_host_flags(fobq_ctx* ctx)
 static int read_flags(fobq_ctx* ctx, const int* dev_flags)
 {
     int* h = ctx->h_flags;
+    const bool sent = ctx->flags_sent;
+    ctx->flags_sent = false;                 // whatever comes of this call: the words sent are this layer's
     if (!h) return set_err(ctx, FOBQ_ESTATE, "the context has no host buffer for the status flags");
-    FOBQ_TRY(ctx->flags_sent ? hipSuccess : hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream),
+    FOBQ_TRY(sent ? hipSuccess : hipMemcpyAsync(h, dev_flags, FLAG_COUNT * sizeof(int), hipMemcpyDeviceToHost, ctx->stream),
              "read status flags");
-    ctx->flags_sent = false;
     FOBQ_TRY(hipStreamSynchronize(ctx->stream), "synchronize");
     if (h[FLAG_STALLED]) return set_err(ctx, FOBQ_EHIP, "a factorization launch drew no tile for three quarters of a minute and was given up");
     if (h[FLAG_BADPERM]) return set_err(ctx, FOBQ_EINVAL, "perm_in is not a permutation of 0..d_col-1");
