@@ -1147,6 +1147,13 @@ static int quantize_enqueue(fobq_ctx* ctx, const float* W, int64_t d_row, int64_
     return FOBQ_OK;
 }
 
+// The end of a layer: waits and reports.  A check that fails before the wait leaves the layer in flight.
+static int finish_layer(fobq_ctx* ctx)
+{
+    const int rc = read_flags(ctx);
+    return (rc && rc != FOBQ_EINVAL && rc != FOBQ_ENOTPD) ? drain_after_failure(ctx, rc) : rc;
+}
+
 // carve `bytes` (rounded up to 256) out of a pool laid out from `*off`; base == null: only the size is wanted
 static void* pool_take(unsigned char* base, size_t* off, size_t bytes)
 {
@@ -1321,7 +1328,7 @@ int fobq_quantize_layer(fobq_ctx* ctx, const float* W, int64_t d_row, int64_t d_
 {
     int rc = quantize_enqueue(ctx, W, d_row, d_col, H, opts, out);
     if (rc) return rc;
-    return read_flags(ctx);
+    return finish_layer(ctx);
 }
 
 int fobq_quantize_layer_enqueue(fobq_ctx* ctx, const float* W, int64_t d_row, int64_t d_col, const double* H,
@@ -1343,7 +1350,7 @@ int fobq_finish(fobq_ctx* ctx)
         return FOBQ_OK;
     }
     ctx->pending = false;
-    return read_flags(ctx);
+    return finish_layer(ctx);
 }
 
 int fobq_profile_enable(fobq_ctx* ctx, int on)

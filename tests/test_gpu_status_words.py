@@ -35,3 +35,27 @@ def test_calls_after_a_failed_check_read_their_own_words():
                     call()
                 assert e.value.code == code, nth
         assert 10 < nth < 99
+
+
+@pytest.mark.parametrize("wait", [True, False])
+def test_a_failed_call_has_waited_for_its_work(wait):
+    import paper_2509_05576_amd as fobq
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    W = torch.randn((64, 1024), generator=g, device="cuda")
+    H = torch.eye(1024, dtype=torch.float64, device="cuda")
+    s = torch.cuda.Stream()
+    with fobq.Ctx(0, stream=s.cuda_stream) as ctx:
+        out = ctx.quantize_layer(W, H)
+        torch.cuda.synchronize()
+        for nth in range(1, 100):
+            fobq.fobq_debug_fail_after(ctx.handle, nth)
+            try:
+                ctx.quantize_layer(W, H, out=out, wait=wait)
+                if not wait:
+                    ctx.finish()
+                break
+            except fobq.FobqError as e:
+                assert e.code == fobq.EHIP
+                assert s.query(), str(e)
+        assert 10 < nth < 99
