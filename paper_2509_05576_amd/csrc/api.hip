@@ -647,15 +647,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
     }
     FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>(),
                              i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax, beside ? ctx->sync_ev[EV_FORK] : nullptr), "pad maps");
+    // the strips read the padded copy only and are bound by the fp64 pipes, the digits by memory: beside them, on the side stream
+    // (256 channels, 14 x 14 x 128 maps, 3 x 3: 638 -> 605 us)
+    hipStream_t strips_on = beside ? ctx->side : ctx->stream;
     if (strips) {
-        // the strips read the padded copy only and are bound by the fp64 pipes, the digits by memory: beside them, on the side stream
-        // (256 channels, 14 x 14 x 128 maps, 3 x 3: 638 -> 605 us)
         const int rc = [&]() -> int {
-            hipStream_t on = beside ? ctx->side : ctx->stream;
             if (beside) FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
-            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, on);
-            FOBQ_TRY(launch_offset_corrections(on, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, d, tab,
-                                               ctx->strips.as<double>(), ctx->hcorr.as<double>(), beside ? ctx->sync_ev[EV_JOIN] : nullptr), "offset corrections");
+            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, strips_on);
+            FOBQ_TRY(launch_offset_strips(strips_on, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, tab,
+                                          ctx->strips.as<double>()), "offset strips");
             return FOBQ_OK;
         }();
         if (rc) return beside ? drain_after_failure(ctx, rc) : rc;
@@ -687,6 +687,13 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
                                      (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
                                      stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
             ctx->h_zeroed = have;
+        }
+        if (strips) {
+            // what the strips add is enqueued last, so that a call that failed above can be made again (the device gets there beside
+            // the products all the same)
+            StageScope sc(ctx, FOBQ_STAGE_FINALIZE, strips_on);
+            FOBQ_TRY(launch_offset_apply(strips_on, (int)c, d, tab, ctx->strips.as<double>(), ctx->hcorr.as<double>(),
+                                         beside ? ctx->sync_ev[EV_JOIN] : nullptr), "offset corrections");
         }
         return FOBQ_OK;
     }();

@@ -267,8 +267,9 @@ struct OffsetTables {
 bool offset_tables_build(int k, int pad, int h, int w, OffsetTables* tab);
 size_t offset_strips_bytes(int njobs, int c);
 hipError_t launch_clear_slab_rows(hipStream_t s, double* Hpart, int d, int first, int count, int row0, int n0, int row1, int n1);
-hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int d,
-                                     const OffsetTables& tab, double* strips, double* corr, hipEvent_t done);
+// (both only where the tables have jobs)
+hipError_t launch_offset_strips(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, const OffsetTables& tab, double* strips);
+hipError_t launch_offset_apply(hipStream_t s, int c, int d, const OffsetTables& tab, const double* strips, double* corr, hipEvent_t done);
 hipError_t launch_hessian_finalize_offsets(hipStream_t s, const double* Hpart, int splits, int d, double factor, double* H, double* H2, int c,
                                            int k, const double* corr, const int* poison);
 

@@ -225,17 +225,21 @@ hipError_t launch_clear_slab_rows(hipStream_t s, double* Hpart, int d, int first
     return hipGetLastError();
 }
 
-// the strips of one call (overwritten; offset_strips_bytes of scratch), then their signed sums into the correction matrix
+// the strips of one call (overwritten; offset_strips_bytes of scratch), and their signed sums into the correction matrix
 size_t offset_strips_bytes(int njobs, int c) { return (size_t)offset_parts(njobs, c) * (njobs > 0 ? njobs : 1) * c * c * sizeof(double); }
 
-hipError_t launch_offset_corrections(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, int d,
-                                     const OffsetTables& tab, double* strips, double* corr, hipEvent_t done)
+hipError_t launch_offset_strips(hipStream_t s, const float* padded, int n_img, int hp, int wp, int c, const OffsetTables& tab, double* strips)
 {
-    if (tab.njobs == 0) return hipSuccess;
     const int parts = offset_parts(tab.njobs, c);
     hipLaunchKernelGGL(offset_strip_kernel, dim3(c / 64, c / 64, tab.njobs * parts), dim3(512), 0, s, padded, n_img, hp, wp, c,
                        tab, parts, strips);
-    hipExtLaunchKernelGGL(offset_apply_kernel, dim3((c * c + 255) / 256, tab.npairs), dim3(256), 0, s, nullptr, done, 0, tab, strips, parts, c, d, corr);
+    return hipGetLastError();
+}
+
+hipError_t launch_offset_apply(hipStream_t s, int c, int d, const OffsetTables& tab, const double* strips, double* corr, hipEvent_t done)
+{
+    hipExtLaunchKernelGGL(offset_apply_kernel, dim3((c * c + 255) / 256, tab.npairs), dim3(256), 0, s, nullptr, done, 0, tab, strips,
+                          offset_parts(tab.njobs, c), c, d, corr);
     return hipGetLastError();
 }
 
