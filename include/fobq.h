@@ -118,6 +118,9 @@ int fobq_workspace_bytes(fobq_ctx* ctx, int64_t* bytes);
  *               context, and, if H_out != NULL (device, d_col x d_col fp64),
  *               copies it there.  Enqueues and returns.
  * Errors: EINVAL on bad sizes/NULL, ESTATE on wrong call order, ENOMEM, EHIP.
+ * An accumulate call that fails leaves the accumulation as it was, so that the call can be made
+ * again, or, if products of it may have been added, closes it: accumulate and finalize then
+ * fail with ESTATE until the next begin.
  */
 int fobq_hessian_begin(fobq_ctx* ctx, int64_t d_col);
 

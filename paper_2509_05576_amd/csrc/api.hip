@@ -496,6 +496,20 @@ static int grow_i8_slabs(fobq_ctx* ctx, int64_t n_launch, I8Rect rect = I8Rect()
     return FOBQ_OK;
 }
 
+// A launch that adds into the sum, and the end of an accumulate call that failed: with products of it in the sum the sum is of no
+// use, and the accumulation is closed; without any it is as it was, and the call can be made again.
+static hipError_t adds(bool* added, hipError_t launched)
+{
+    if (launched == hipSuccess) *added = true;
+    return launched;
+}
+
+static int failed_accumulate(fobq_ctx* ctx, int rc, bool added)
+{
+    if (added) ctx->h_d = 0;
+    return rc;
+}
+
 int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld)
 {
     if (!ctx) return FOBQ_EINVAL;
@@ -522,31 +536,37 @@ int fobq_hessian_accumulate(fobq_ctx* ctx, const float* X, int64_t n, int64_t ld
     int rc = prepare_slabs(ctx, n, blk, false, i8, &fresh, &have);
     if (rc) return rc;
     ctx->h_conv_c = -1;
-    if (i8) {
-        int* nonfinite = ctx->flags.as<int>() + FLAG_WORD_NONFINITE;
-        if (!ctx->h_i8_used) FOBQ_TRY(launch_clear_words(ctx->stream, nonfinite, 1, nullptr, 0), "clear flag");
-        ctx->h_i8_used = true;
-        {
-            StageScope sc(ctx, FOBQ_STAGE_SLICE);
-            FOBQ_TRY(launch_i8_row_shifts(ctx->stream, X, ld, d, n, ctx->i8sh.as<int>(), nonfinite), "row exponents");
-        }
-        for (int64_t c0 = 0; c0 < n; c0 += blk) {
-            const int64_t nb = n - c0 < blk ? n - c0 : blk;
+    bool added = false;
+    rc = [&]() -> int {
+        if (i8) {
+            int* nonfinite = ctx->flags.as<int>() + FLAG_WORD_NONFINITE;
+            if (!ctx->h_i8_used) FOBQ_TRY(launch_clear_words(ctx->stream, nonfinite, 1, nullptr, 0), "clear flag");
+            ctx->h_i8_used = true;
             {
                 StageScope sc(ctx, FOBQ_STAGE_SLICE);
-                FOBQ_TRY(launch_i8_slice(ctx->stream, X + c0, ld, d, nb, ctx->i8sh.as<int>(), ctx->i8planes.as<signed char>()),
-                         "integer slices");
+                FOBQ_TRY(launch_i8_row_shifts(ctx->stream, X, ld, d, n, ctx->i8sh.as<int>(), nonfinite), "row exponents");
             }
-            FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
-                                   ctx->Hpart.as<double>(), ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (int8)");
+            for (int64_t c0 = 0; c0 < n; c0 += blk) {
+                const int64_t nb = n - c0 < blk ? n - c0 : blk;
+                {
+                    StageScope sc(ctx, FOBQ_STAGE_SLICE);
+                    FOBQ_TRY(launch_i8_slice(ctx->stream, X + c0, ld, d, nb, ctx->i8sh.as<int>(), ctx->i8planes.as<signed char>()),
+                             "integer slices");
+                }
+                FOBQ_TRY(adds(&added, launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
+                                                    ctx->Hpart.as<double>(), ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT))),
+                         "xxt (int8)");
+                ctx->h_zeroed = have;
+                fresh = 0;
+            }
+        } else {
+            FOBQ_TRY(adds(&added, launch_xxt(ctx->stream, X, ld, d, n, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
+                                             stage_launch_events(ctx, FOBQ_STAGE_XXT))), "xxt");
             ctx->h_zeroed = have;
-            fresh = 0;
         }
-    } else {
-        FOBQ_TRY(launch_xxt(ctx->stream, X, ld, d, n, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
-                            stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt");
-        ctx->h_zeroed = have;
-    }
+        return FOBQ_OK;
+    }();
+    if (rc) return failed_accumulate(ctx, rc, added);
     ctx->h_n += n;
     return FOBQ_OK;
 }
@@ -660,6 +680,7 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         }();
         if (rc) return beside ? drain_after_failure(ctx, rc) : rc;
     }
+    bool added = false;
     const int rc = [&]() -> int {
         if (i8) {
             // the digits of the unfolded input are written out (1.25 bytes per element of the unfolded X, a block of
@@ -677,15 +698,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
                                                   stride, (int)ho, (int)wo, npix, p0, nb, ctx->i8sh.as<int>(),
                                                   ctx->i8planes.as<signed char>()), "integer slices (convolution)");
                 }
-                FOBQ_TRY(launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb,
-                                       ctx->Hpart.as<double>(), ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect), "xxt (int8)");
+                FOBQ_TRY(adds(&added, launch_xxt_i8(ctx->stream, ctx->i8planes.as<signed char>(), ctx->i8sh.as<int>(), d, nb, ctx->Hpart.as<double>(),
+                                                    ctx->h_splits, fresh, stage_launch_events(ctx, FOBQ_STAGE_XXT), rect)), "xxt (int8)");
                 ctx->h_zeroed = have;
                 fresh = 0;
             }
         } else {
-            FOBQ_TRY(launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
-                                     (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
-                                     stage_launch_events(ctx, FOBQ_STAGE_XXT)), "xxt (convolution)");
+            FOBQ_TRY(adds(&added, launch_xxt_conv(ctx->stream, ctx->maps_pad.as<float>(), (int)n_img, (int)hp, (int)wp, (int)c, k, stride,
+                                                  (int)ho, (int)wo, npix, ctx->Hpart.as<double>(), ctx->h_splits, fresh,
+                                                  stage_launch_events(ctx, FOBQ_STAGE_XXT))), "xxt (convolution)");
             ctx->h_zeroed = have;
         }
         if (strips) {
@@ -695,14 +716,11 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
             FOBQ_TRY(launch_offset_apply(strips_on, (int)c, d, tab, ctx->strips.as<double>(), ctx->hcorr.as<double>(),
                                          beside ? ctx->sync_ev[EV_JOIN] : nullptr), "offset corrections");
         }
+        // whatever comes next on the context's stream (the corrections' use, another call's padded copy) finds the strips done
+        if (beside) FOBQ_TRY(hipStreamWaitEvent(ctx->stream, ctx->sync_ev[EV_JOIN], 0), "stream wait");
         return FOBQ_OK;
     }();
-    if (rc) return beside ? drain_after_failure(ctx, rc) : rc;
-    // whatever comes next on the context's stream (the corrections' use, another call's padded copy) finds the strips done
-    if (beside) {
-        const hipError_t e = hipStreamWaitEvent(ctx->stream, ctx->sync_ev[EV_JOIN], 0);
-        if (e != hipSuccess) return drain_after_failure(ctx, hip_err(ctx, e, "stream wait"));
-    }
+    if (rc) return failed_accumulate(ctx, beside ? drain_after_failure(ctx, rc) : rc, added);
     ctx->h_n += npix;
     return FOBQ_OK;
 }
