@@ -127,6 +127,19 @@ static int ensure_sync_events(fobq_ctx* ctx, size_t n)
     return FOBQ_OK;
 }
 
+// For calls that gain from the side stream but can do without: whether it is there.
+static bool side_at_hand(const fobq_ctx* c) { return c->side && c->sync_ev.size() >= EV_ROWS0; }
+
+// Such a call has kept to its own stream and is enqueued: the second one of a context makes the side stream for those after it, while
+// the device works.  Making one takes the host 0.15 to 0.4 ms (the first three of a process 3 to 4), the strips of 256 channels or
+// the column sums of 20 small layers gain 0.03 from it: not for a context's first call, which is often its only one.
+static void make_side_for_later(fobq_ctx* c)
+{
+    if (c->side_missed++ == 0) return;
+    if (ensure_side_stream(c) != hipSuccess || ensure_sync_event(c, EV_FORK) != hipSuccess || ensure_sync_event(c, EV_JOIN) != hipSuccess)
+        (void)hipGetLastError();             // nothing depends on it
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool ok = true;
@@ -629,7 +642,7 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         if (grc) return grc;
     }
     int fresh = 0, have = 0;
-    bool strips = false, beside = false;     // beside: the strips on the side stream
+    bool strips = false, beside = false, want_side = false;     // beside: the strips on the side stream
     if (offsets) {
         FOBQ_TRY(ctx->hcorr.ensure((size_t)d * d * sizeof(double)), "workspace corrections");
         FOBQ_TRY(ctx->strips.ensure(offset_strips_bytes(tab.njobs, (int)c)), "workspace strips");
@@ -637,11 +650,8 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         // (a stream under capture keeps everything to itself: the events that ride on launches are not recorded there)
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (ctx->stream) FOBQ_TRY(hipStreamIsCapturing(ctx->stream, &capture), "capture status");
-        beside = strips && capture == hipStreamCaptureStatusNone;
-        if (beside) {
-            const int erc = ensure_sync_events(ctx, EV_ROWS0);
-            if (erc) return erc;
-        }
+        want_side = strips && capture == hipStreamCaptureStatusNone;
+        beside = want_side && side_at_hand(ctx);
         if (first_call) FOBQ_TRY(launch_clear_words(ctx->stream, ctx->hcorr.p, (int64_t)d * d * 2, nullptr, 0), "clear corrections");
         // of the slabs: the rows of the two base taps, all columns
         const int last = d - rect_gap * 128 < rect_cb * 128 ? d - rect_gap * 128 : rect_cb * 128;     // rows past d do not exist
@@ -721,6 +731,7 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         return FOBQ_OK;
     }();
     if (rc) return failed_accumulate(ctx, beside ? drain_after_failure(ctx, rc) : rc, added);
+    if (want_side && !beside) make_side_for_later(ctx);
     ctx->h_n += npix;
     return FOBQ_OK;
 }
@@ -1263,10 +1274,6 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         return set_err(ctx, FOBQ_ENOMEM, "cannot allocate pinned host memory for the batch descriptors");
     }
     FOBQ_TRY(ctx->batch_desc.ensure(desc_bytes), "workspace batch descriptors");
-    {
-        const int erc = ensure_sync_events(ctx, EV_ROWS0);
-        if (erc) return erc;
-    }
     unsigned char* hb = static_cast<unsigned char*>(ctx->h_batch);
     BatchLayer* hd = static_cast<BatchLayer*>(ctx->h_batch);
     int max_pairs = 1, max_chunks = 1, max_tiles = 1;
@@ -1321,12 +1328,14 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     const BatchLayer* dl = reinterpret_cast<const BatchLayer*>(db);
     int rc = [&]() -> int {
         FOBQ_TRY(hipMemcpyAsync(ctx->batch_desc.p, hb, sent_bytes, hipMemcpyHostToDevice, s), "upload batch descriptors");
-        FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs, ctx->sync_ev[EV_FORK]), "grid (batch)");
+        const bool beside = side_at_hand(ctx);
+        FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs, beside ? ctx->sync_ev[EV_FORK] : nullptr), "grid (batch)");
         FOBQ_TRY(launch_flow_batch_inverse(s, db + off_inv, reinterpret_cast<const uint16_t*>(db + off_inv_of), arrivals, plan.inv_wgs), "inverse (batch)");
         // the column sums need the weights and their grids only: beside the inverse, as for a single layer
-        FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
-        FOBQ_TRY(launch_batch_sens_partial(ctx->side, dl, n_layers, max_chunks, ctx->sync_ev[EV_JOIN]), "sensitivity (batch)");
-        FOBQ_TRY(hipStreamWaitEvent(s, ctx->sync_ev[EV_JOIN], 0), "stream wait");
+        if (beside) FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");
+        FOBQ_TRY(launch_batch_sens_partial(beside ? ctx->side : s, dl, n_layers, max_chunks, beside ? ctx->sync_ev[EV_JOIN] : nullptr),
+                 "sensitivity (batch)");
+        if (beside) FOBQ_TRY(hipStreamWaitEvent(s, ctx->sync_ev[EV_JOIN], 0), "stream wait");
         FOBQ_TRY(launch_batch_order(s, dl, n_layers), "order (batch)");
         FOBQ_TRY(launch_flow_batch_eliminate(s, db + off_elim, reinterpret_cast<const uint16_t*>(db + off_elim_of), arrivals + 1,
                                             plan.elim_wgs, plan.nr),
@@ -1334,6 +1343,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         FOBQ_TRY(launch_batch_emit(s, dl, n_layers, max_tiles), "emit (batch)");
         int* hflags = reinterpret_cast<int*>(hb + desc_bytes);      // behind the descriptors
         FOBQ_TRY(hipMemcpyAsync(hflags, flags, (size_t)n_layers * 4 * sizeof(int), hipMemcpyDeviceToHost, s), "read status flags");
+        if (!beside) make_side_for_later(ctx);
         FOBQ_TRY(hipStreamSynchronize(s), "synchronize");
         for (int l = 0; l < n_layers; ++l) {
             if (hflags[4 * l + FLAG_STALLED])

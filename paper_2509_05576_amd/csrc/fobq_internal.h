@@ -147,6 +147,7 @@ struct fobq_ctx {
     // second stream: the column loop of block k only needs the pivot rows of blocks <= k, so it
     // runs behind the shared-Hinv elimination on its own stream, ordered by one event per block
     hipStream_t side = nullptr;
+    int side_missed = 0;    // calls that would have used it and kept to the context's stream
     std::vector<hipEvent_t> sync_ev;
 
     bool pending = false;   // a layer was enqueued without the final status read (fobq_finish outstanding)
