@@ -328,8 +328,10 @@ int fobq_debug_offset_tables(int32_t k, int32_t pad, int64_t h, int64_t w, int32
  *                  out, per layer: rows per wavefront of a part of columns, then the workgroups that first serve the
  *                  tiles of the pivot rows, the parts of columns, the sums of 64 rows
  *   FOBQ_PLAN_HESSIAN  in: d_col, calibration columns of one fp64 accumulate call, from feature maps (0 / 1)
- *                  out: tile edge, slabs of an accumulation, slabs that this call can touch */
-typedef enum { FOBQ_PLAN_PAD = 0, FOBQ_PLAN_ELIMINATE = 1, FOBQ_PLAN_HESSIAN = 2 } fobq_plan;
+ *                  out: tile edge, slabs of an accumulation, slabs that this call can touch
+ *   FOBQ_PLAN_SLABS  in: channels, kernel size of a stride-1 convolution, integer slices
+ *                  out: slabs that fobq_hessian_begin reserves, slabs that its form by tap offsets takes (0: another form) */
+typedef enum { FOBQ_PLAN_PAD = 0, FOBQ_PLAN_ELIMINATE = 1, FOBQ_PLAN_HESSIAN = 2, FOBQ_PLAN_SLABS = 3 } fobq_plan;
 
 int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out, int32_t n_out);
 

@@ -342,7 +342,7 @@ def fobq_debug_wait_looks(ctx: int, looks: int) -> None:
     _check(ctx, load_library().fobq_debug_wait_looks(ctypes.c_void_p(ctx), looks))
 
 
-PLAN_PAD, PLAN_ELIMINATE, PLAN_HESSIAN = 0, 1, 2
+PLAN_PAD, PLAN_ELIMINATE, PLAN_HESSIAN, PLAN_SLABS = 0, 1, 2, 3
 
 
 def fobq_debug_plan(what: int, args, n_out: int):

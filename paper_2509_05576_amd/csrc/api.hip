@@ -393,6 +393,30 @@ static int prepare_slabs(fobq_ctx* ctx, int64_t n, int64_t blk, bool conv, bool 
         return launch_clear_slabs(ctx->stream, ctx->Hpart.as<double>(), (int)ctx->h_d, first, count); });
 }
 
+// The tile rows (128 rows each) of a stride-1 convolution by tap offsets that hold the rows of its two base taps: two groups of the
+// same size, apart; false: the convolution does not take this form.
+static bool offset_rect(int64_t c, int k, I8Rect* rect)
+{
+    const int cb = (int)((c + 127) / 128), gap = (int)((k - 1) * c / 128);
+    if (k < 2 || k * k > OFFSET_MAX_TAPS || c % 64 != 0 || gap < cb || (int)((k * c + 127) / 128) - gap != cb) return false;
+    // 64 channels, 3 x 3: the base taps are the first halves of tile rows 0 and 1, formed as one tile row
+    *rect = I8Rect{cb, gap, (c == 64 && k == 3) ? 1 : 0, (int)c / 64, k};
+    return true;
+}
+
+// Slabs that fobq_hessian_begin makes room for: what the fp64 kernel and the triangle of digit products take, and what a convolution
+// of this many columns by tap offsets takes, whose few tiles are cut into more pieces each.  (Without room for those its first call
+// frees the slabs and takes larger ones: 1440 us against 1081 for 256 channels, 14 x 14 x 128 maps, 890 against 253 for 8 maps of 128.)
+static int slabs_reserved(int mode, int d)
+{
+    int slabs = xxt_pick_splits(d);
+    for (int k = 2; k * k <= OFFSET_MAX_TAPS && mode == FOBQ_HESSIAN_INT8_SLICES && d >= I8_MIN_D; ++k) {
+        I8Rect rect;
+        if (d % (k * k) == 0 && offset_rect(d / (k * k), k, &rect)) slabs = std::max(slabs, xxt_i8_wanted_splits(d, 0, rect));
+    }
+    return slabs;
+}
+
 extern "C" {
 
 int fobq_create(fobq_ctx** out, int device, void* hip_stream)
@@ -473,7 +497,7 @@ int fobq_hessian_begin(fobq_ctx* ctx, int64_t d_col)
     if (!g.ok) return set_err(ctx, FOBQ_EHIP, "cannot select device %d", ctx->device);
     const int splits = xxt_pick_splits((int)d_col);
     const size_t dd = (size_t)d_col * d_col * sizeof(double);
-    FOBQ_TRY(ctx->Hpart.ensure(dd * splits), "workspace Hpart");
+    FOBQ_TRY(ctx->Hpart.ensure(dd * slabs_reserved(ctx->h_mode, (int)d_col)), "workspace Hpart");
     FOBQ_TRY(ctx->H.ensure(dd), "workspace H");
     {
         int rc = ensure_flags(ctx);
@@ -493,8 +517,8 @@ int fobq_hessian_begin(fobq_ctx* ctx, int64_t d_col)
 }
 
 // Before its first launch an accumulation may still take more slabs than fobq_hessian_begin reserved (the digit-product
-// kernel wants some for a wide layer with a long calibration dimension, and for a convolution taken by tap offsets, whose
-// few tiles are cut into more pieces each); a failure leaves no accumulation open.
+// kernel wants some for a wide layer with a long calibration dimension; a convolution by tap offsets where the mode was set after
+// begin); a failure leaves no accumulation open.
 static int grow_i8_slabs(fobq_ctx* ctx, int64_t n_launch, I8Rect rect = I8Rect())
 {
     if (ctx->h_n > 0 || ctx->h_zeroed > 0) return FOBQ_OK;
@@ -620,18 +644,15 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
     OffsetTables tab;
     const bool first_call = ctx->h_conv_c == 0;
     bool offsets = false;
-    // the tile rows (128 rows each) that hold the rows of the two base taps: two groups of the same size, apart
-    const int rect_cb = (int)((c + 127) / 128), rect_gap = (int)((k - 1) * c / 128);
-    const bool rect_fits = c % 64 == 0 && rect_gap >= rect_cb && (int)((k * c + 127) / 128) - rect_gap == rect_cb;
-    if (first_call ? (i8 && stride == 1 && k >= 2 && rect_fits) : ctx->h_offsets) {
+    I8Rect rect;
+    if (first_call ? (i8 && stride == 1 && offset_rect(c, k, &rect)) : ctx->h_offsets && offset_rect(c, k, &rect)) {
         offsets = stride == 1 && offset_tables_build(k, pad, (int)h, (int)w, &tab);
         if (!offsets && !first_call)
             return set_err(ctx, FOBQ_ESTATE, "this accumulation takes the convolution by tap offsets (stride 1): a later call "
                                              "must have stride 1 and a map of at least k x k");
     }
     if (offsets) i8 = true;
-    // 64 channels, 3 x 3: the base taps are the first halves of tile rows 0 and 1, formed as one tile row
-    const I8Rect rect = offsets ? I8Rect{rect_cb, rect_gap, (c == 64 && k == 3) ? 1 : 0, (int)c / 64, k} : I8Rect();
+    else rect = I8Rect();
     const int64_t blk = i8 ? i8_block_columns(d) : npix;
     FOBQ_TRY(ctx->maps_pad.ensure((size_t)(n_img + 1) * hp * wp * c * sizeof(float)), "workspace padded maps");
     if (i8) {
@@ -654,11 +675,11 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
         beside = want_side && side_at_hand(ctx);
         if (first_call) FOBQ_TRY(launch_clear_words(ctx->stream, ctx->hcorr.p, (int64_t)d * d * 2, nullptr, 0), "clear corrections");
         // of the slabs: the rows of the two base taps, all columns
-        const int last = d - rect_gap * 128 < rect_cb * 128 ? d - rect_gap * 128 : rect_cb * 128;     // rows past d do not exist
+        const int last = d - rect.gap * 128 < rect.cb * 128 ? d - rect.gap * 128 : rect.cb * 128;     // rows past d do not exist
         const int rc = prepare_slabs(ctx, xxt_i8_slabs_touched(d, npix < blk ? npix : blk, ctx->h_splits, rect),
                                      npix > blk && npix % blk ? xxt_i8_slabs_touched(d, npix % blk, ctx->h_splits, rect) : 0, &fresh, &have,
                                      [&](int first, int count) {
-            return launch_clear_slab_rows(ctx->stream, ctx->Hpart.as<double>(), d, first, count, 0, rect_cb * 128, rect_gap * 128, last); });
+            return launch_clear_slab_rows(ctx->stream, ctx->Hpart.as<double>(), d, first, count, 0, rect.cb * 128, rect.gap * 128, last); });
         if (rc) return rc;
     } else {
         const int rc = prepare_slabs(ctx, npix, blk, true, i8, &fresh, &have);
@@ -947,6 +968,14 @@ int fobq_debug_plan(int32_t what, const int64_t* in, int32_t n_in, int64_t* out,
         if (in[0] < 1 || in[0] > MAX_DCOL || in[1] < 1 || in[1] >= (1ll << 31) - 64) return FOBQ_EINVAL;
         const int splits = xxt_pick_splits((int)in[0]);
         out[0] = xxt_tile((int)in[0], in[1]); out[1] = splits; out[2] = xxt_slabs_touched((int)in[0], in[1], splits, in[2] != 0);
+        return FOBQ_OK;
+    }
+    if (what == FOBQ_PLAN_SLABS && n_in == 2 && n_out == 2) {
+        if (in[0] < 1 || in[1] < 1 || in[1] > 64 || in[0] > MAX_DCOL / (in[1] * in[1])) return FOBQ_EINVAL;
+        const int d = (int)(in[0] * in[1] * in[1]);
+        I8Rect rect;
+        out[0] = slabs_reserved(FOBQ_HESSIAN_INT8_SLICES, d);
+        out[1] = d >= I8_MIN_D && offset_rect(in[0], (int)in[1], &rect) ? xxt_i8_wanted_splits(d, 0, rect) : 0;
         return FOBQ_OK;
     }
     if (what == FOBQ_PLAN_ELIMINATE && n_in >= 3 && n_in % 2 == 1 && n_in / 2 <= BATCH_MAX_LAYERS && n_out == 4 * (n_in / 2)) {

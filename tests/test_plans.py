@@ -68,3 +68,15 @@ def test_short_hessian_calls_take_the_small_tiles(d, conv):
         tile, slabs, touched = fobq.fobq_debug_plan(fobq.PLAN_HESSIAN, [d, n, conv], 3)
         assert tile == wide if wide and n >= (4096 if wide == 160 else 24576) else tile in (64, 128)
         assert 1 <= touched <= slabs
+
+
+# slabs grown by a first call are freed and taken again in it, 0.3 ms
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("c", list(range(64, 1025, 64)) + [2048, 32, 48, 100, 65, 3])
+def test_a_first_call_by_tap_offsets_finds_its_slabs(c, k):
+    if c * k * k > 32768:
+        return
+    reserved, wanted = fobq.fobq_debug_plan(fobq.PLAN_SLABS, [c, k], 2)
+    assert reserved >= max(wanted, 1)
+    if c % 64 or k not in (2, 3) or c * k * k < 384:
+        assert wanted == 0
