@@ -57,8 +57,8 @@ __device__ __forceinline__ double pivot_rsqrt(double x)
 
 // Lane K of every row of 16 lanes, to the whole row (DPP row_newbcast, which 64-bit operations take).  The compiler does not see
 // into the asm and so does not keep the two wait states that DPP wants between a vector instruction and the one that reads its
-// result across lanes: every statement brings its own where the value may be that young, and row_product hands on a factor
-// that is old enough for any number of uses.
+// result across lanes: every statement brings its own where the value may be that young, and row_factor hands on a factor
+// that is old enough for any number of uses.  That nothing lands in between (a copy, a spill) the build checks in its listing.
 template <int K>
 __device__ __forceinline__ double row_lane(double v)
 {
