@@ -23,6 +23,7 @@ def test_hessian_by_offsets_in_a_graph():
                 ctx.hessian_conv(buf, k, 1, 1, H_out=H)
                 s.synchronize()
                 want.append(H.clone())
+        assert ctx.hessian_form() == fobq.FORM_INT8_TAP_OFFSETS
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=s):
