@@ -783,7 +783,12 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
     }
 }
 
-// Convolution mode: the slabs are in tap-major row order; H is written in (c, ky, kx) order.
+// Convolution mode: the slabs are in tap-major row order; H is written in (c, ky, kx) order.  ONE: the slabs one after another.  The
+// gather takes a line of a slab for an entry or two, and finds it in the L2 again for the taps beside it only while all threads are
+// at the same slab: with four of them in flight 576 columns (3 x 3) 58 -> 62 us for the call, 900 99 -> 103, 1200 (5 x 5) 130 -> 150.
+// A slab of up to 256 columns stays in the L2, and rows of a 1 x 1 kernel are read whole: there four (147 columns 61 -> 60 us, 512 of a
+// 1 x 1 kernel 50 -> 43).
+template <bool ONE>
 __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
                                                                     double factor, double* __restrict__ H, double* __restrict__ H2,
                                                                     int c, int kk, const int* __restrict__ poison)
@@ -793,7 +798,11 @@ __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double
     if (a >= d || b >= d || b > a) return;
     const int ai = (a % kk) * c + a / kk, bi = (b % kk) * c + b / kk;
     const int hi = max(ai, bi), lo = min(ai, bi);
-    double s = slab_sum(Hpart + (int64_t)hi * d + lo, splits, (int64_t)sstride * d * d);
+    double s = 0.0;
+    if (ONE)
+        for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)hi * d + lo];
+    else
+        s = slab_sum(Hpart + (int64_t)hi * d + lo, splits, (int64_t)sstride * d * d);
     s *= factor;
     if (poison && *poison) s = __builtin_nan("");
     H[(int64_t)a * d + b] = s;
@@ -831,8 +840,11 @@ hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int
         splits = groups;
         sstride = SLAB_GROUP;
     }
-    if (conv_c > 0)
-        hipLaunchKernelGGL(hessian_finalize_conv_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
+    if (conv_c > 0 && conv_kk > 1 && d > 256)
+        hipLaunchKernelGGL(hessian_finalize_conv_kernel<true>, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
+                           poison);
+    else if (conv_c > 0)
+        hipLaunchKernelGGL(hessian_finalize_conv_kernel<false>, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
                            poison);
     else
         hipLaunchKernelGGL(hessian_finalize_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, poison);
