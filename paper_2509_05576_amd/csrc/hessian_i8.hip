@@ -23,6 +23,7 @@
 // (tile, k-step) items, or, for wide layers whose digits no cache holds, whole tiles in step with the others).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fobq_internal.h"
@@ -296,8 +297,10 @@ __device__ __forceinline__ void lds_copy_block(const signed char* __restrict__ s
 // (Tried and slower: 128 x 64 tiles with 4 wavefronts, a ring of three LDS stages and the next k-step's
 // fragments prefetched into a second register set -- the compiler shuffles accumulators between the two
 // register files in that loop, 1.38 ms against 0.80 on the 2304 x 25088 layer.)
+// The ranges: items, tile after tile, tile_steps of them a tile (its ksteps, or more, so that no range lies across two tiles: see
+// i8_plan; items past ksteps are none), per_wg to a workgroup.
 __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restrict__ P, const int* __restrict__ sh, int d,
-                                                        int dpad, int64_t ksteps, double* __restrict__ Hpart, int64_t per_wg,
+                                                        int dpad, int64_t ksteps, int64_t tile_steps, double* __restrict__ Hpart, int64_t per_wg,
                                                         int64_t items, int classes, int fresh, I8Rect rect, I8Lockstep ls)
 {
     constexpr int TN = IT, NB = TN / 32;  // row blocks of the B operand
@@ -340,8 +343,8 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
         npieces = ls.full + (int)(vpos < units ? (units - vpos + gridDim.x - 1) / gridDim.x : 0);
     } else {
         if (g0 >= g1) return;
-        t_first = (int)(g0 / ksteps);
-        t_last = (int)((g1 - 1) / ksteps);
+        t_first = (int)(g0 / tile_steps);
+        t_last = (int)((g1 - 1) / tile_steps);
         npieces = t_last - t_first + 1;
     }
 
@@ -369,15 +372,15 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
             }
         } else {
             tile = npieces == 2 ? t_last - pi : t_first + pi;
-            const int64_t tile_first = (int64_t)tile * ksteps;
+            const int64_t tile_first = (int64_t)tile * tile_steps;
             c_begin = max(g0, tile_first) - tile_first;
-            c_end = min(g1, tile_first + ksteps) - tile_first;
+            c_end = min(min(g1, tile_first + tile_steps) - tile_first, ksteps);
             if (npieces == 1) {
                 const int64_t aligned = (c_begin + per_wg - 1) / per_wg * per_wg;
                 if (aligned < c_end) rot = aligned - c_begin;
             }
             piece = (int)(vb - tile_first / per_wg);            // ranges that reached this tile before this one
-            pieces = (int)((min(items, tile_first + ksteps) - 1) / per_wg - tile_first / per_wg) + 1;
+            pieces = (int)((min(items, tile_first + tile_steps) - 1) / per_wg - tile_first / per_wg) + 1;
         }
         const int64_t len = c_end - c_begin;
         if (len <= 0) continue;                                 // the same for the whole workgroup
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
 }
 
 
-struct I8Plan { int nt, wgs; int64_t ksteps, items, per_wg; I8Lockstep ls; };
+struct I8Plan { int nt, wgs; int64_t ksteps, tile_steps, items, per_wg; I8Lockstep ls; };
 
 // Digits that fit the 256 MB memory-side cache are served from it however the workgroups walk them; beyond that,
 // with at least one tile per workgroup, the ranges below leave every workgroup at a k-step of its own and every
@@ -595,7 +598,7 @@ static I8Plan i8_plan(int d, int64_t n, int splits, I8Rect rect)
 {
     I8Plan p;
     p.nt = i8_dpad(d) / IT;
-    p.ksteps = i8_ksteps(n);
+    p.ksteps = p.tile_steps = i8_ksteps(n);
     const int64_t tiles = i8_tiles(p.nt, rect);
     if (i8_instep_wanted(d, n, rect)) {
         // Whole rounds of one tile per workgroup, then the rem tiles left over in `pieces` parts each (part j of a
@@ -630,6 +633,18 @@ static I8Plan i8_plan(int d, int64_t n, int splits, I8Rect rect)
     const int64_t min_len = splits > 1 ? (p.ksteps + splits - 2) / (splits - 1) : p.ksteps;
     if (p.per_wg < min_len) p.per_wg = min_len;
     if (p.per_wg < 1) p.per_wg = 1;
+    // A range across two tiles folds twice, which takes a workgroup some 20 k-steps, and its tiles reach one slab more.  Few tiles, most of
+    // them cut, are dealt a piece to a workgroup instead where the longest piece is at most 40 k-steps more than an even range
+    // (pieces / ranges, the call: 128 channels, 3136 pixels 117 / 145 us, 256 channels, 25088 352 / 376, 4 calls of 6272 pixels 560 / 645;
+    // 40 more: 320 channels, 12544 546 / 542, 109 more: 448 channels, 12544 956 / 904).
+    if (rect.cb > 0 && tiles <= I8_WGS) {
+        const int64_t most = std::min<int64_t>({I8_WGS / tiles, splits, p.ksteps}), len = (p.ksteps + most - 1) / most;
+        if (len <= p.per_wg + 40) {
+            p.per_wg = len;
+            p.tile_steps = (p.ksteps + len - 1) / len * len;
+            p.items = tiles * p.tile_steps;
+        }
+    }
     p.wgs = (int)((p.items + p.per_wg - 1) / p.per_wg);
     return p;
 }
@@ -638,6 +653,7 @@ int xxt_i8_slabs_touched(int d, int64_t n, int splits, I8Rect rect)
 {
     const I8Plan pl = i8_plan(d, n, splits, rect);
     if (pl.ls.full > 0) return pl.ls.pieces > 1 ? pl.ls.pieces : 1;
+    if (pl.tile_steps % pl.per_wg == 0) return (int)(pl.tile_steps / pl.per_wg);       // (no range reaches into two tiles)
     const int64_t p = (pl.ksteps + pl.per_wg - 1) / pl.per_wg + 1;
     return (int)(p < splits ? p : splits);
 }
@@ -697,10 +713,10 @@ hipError_t launch_xxt_i8(hipStream_t s, const signed char* planes, const int* sh
 {
     const I8Plan pl = i8_plan(d, n, splits, rect);
     // pieces per tile, rounded: the number of classes of ranges (see the kernel)
-    int classes = (int)((pl.ksteps + pl.per_wg / 2) / pl.per_wg);
+    int classes = (int)((pl.tile_steps + pl.per_wg / 2) / pl.per_wg);
     classes = classes < 1 || pl.ls.full > 0 ? 1 : (classes > pl.wgs ? pl.wgs : classes);
     hipExtLaunchKernelGGL(xxt_i8_kernel, dim3(pl.wgs), dim3(512), 0, s, ev.start, ev.stop, 0, planes, sh, d, i8_dpad(d),
-                          pl.ksteps, Hpart, pl.per_wg, pl.items, classes, fresh, rect, pl.ls);
+                          pl.ksteps, pl.tile_steps, Hpart, pl.per_wg, pl.items, classes, fresh, rect, pl.ls);
     return hipGetLastError();
 }
 

@@ -7,9 +7,10 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-# (320 channels, 2 x 2: the base taps' tile rows overlap, so the whole triangle is formed)
+# (320 channels, 2 x 2: the base taps' tile rows overlap, so the whole triangle is formed; from 448 channels on the long calls deal ranges
+# that lie across tiles, the short ones and those of fewer channels a piece of a tile to a workgroup; 1024, 2 x 2: more tiles than workgroups)
 @pytest.mark.parametrize("images", [[6], [3, 37]])
-@pytest.mark.parametrize("c,k", [(64, 3), (128, 2), (128, 3), (192, 3), (256, 2), (320, 2), (320, 3), (384, 3)])
+@pytest.mark.parametrize("c,k", [(64, 3), (128, 2), (128, 3), (192, 3), (256, 2), (320, 2), (320, 3), (384, 3), (448, 3), (1024, 2)])
 def test_hessian_by_offsets_matches_the_unfolded_sum(c, k, images):
     import paper_2509_05576_amd as fobq
     g = torch.Generator(device="cuda")
