@@ -699,7 +699,8 @@ int fobq_hessian_accumulate_conv(fobq_ctx* ctx, const float* maps, int64_t n_img
     FOBQ_TRY(launch_pad_maps(ctx->stream, maps, (int)n_img, (int)h, (int)w, (int)c, pad, ctx->maps_pad.as<float>(),
                              i8 ? ctx->i8amax.as<unsigned>() : nullptr, &have_amax, beside ? ctx->sync_ev[EV_FORK] : nullptr), "pad maps");
     // the strips read the padded copy only and are bound by the fp64 pipes, the digits by memory: beside them, on the side stream
-    // (256 channels, 14 x 14 x 128 maps, 3 x 3: 638 -> 605 us)
+    // (3 x 3, the call: 256 channels, 64 maps of 14 x 14 368 -> 358 us, 64 of 7 x 7 205 -> 193; 512, 4 of 28 x 28 491 -> 467; 64, 64 of 28 x 28
+    // 233 -> 217; few pixels are even: 192 channels, 8 maps of 14 x 14 123 -> 125)
     hipStream_t strips_on = beside ? ctx->side : ctx->stream;
     if (strips) {
         const int rc = [&]() -> int {

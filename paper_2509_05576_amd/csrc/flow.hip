@@ -1098,13 +1098,17 @@ __global__ __launch_bounds__(NT, 2) void flow_eliminate_batch_kernel(const FlowE
 }
 
 int64_t flow_inverse_words(int d) { return flow_words((d + NB - 1) / NB); }
-// A part of columns with 1, 2 or 4 rows per wavefront.
-static const double PART_US[3] = {7.5, 11.0, 18.0};
-// Rows per wavefront of a part of columns (1, 2 or 4).  A part takes PART_US (measured), on top of which its successor
-// waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks (15.3 us
-// each when the line was drawn, 12.5 to 13.3 since), with many the workgroups are all busy and what counts is the time per row.  Twice the pure work over all
-// workgroups against the chains; measured at 1 / 2 / 4 rows, elimination and columns: 256 x 2304 0.54 / 0.58 / 0.74 ms,
-// 2048 x 512 0.16 / 0.15 / 0.19, 1024 x 4608 2.10 / 1.90 / 1.81, 8192 x 256 0.35 / 0.32 / 0.22.
+// The weights of a part of columns with 1, 2 or 4 rows per wavefront and of a diagonal block in the rules below, in us as they were when the
+// lines were drawn.  Now a part takes 7.2 to 8.0, 10.1 to 11.4 and 14.1 to 15.7, a block 12.5 to 13.3.  With those in their place 22 of 306
+// shapes (16 .. 65535 rows, 64 .. 8192 columns) would take more rows; of 17 of them measured none gains and most lose (layer, now /
+// so: 512 x 3072 1494 / 1565 us, 1000 x 1792 804 / 824, 2048 x 1280 618 / 686, 3000 x 512 315 / 335), so the weights stay.
+static const double PART_US[3] = {7.5, 11.0, 18.0}, BLOCK_US = 15.3;
+// Rows per wavefront of a part of columns (1, 2 or 4).  A part takes its own time, on top of which its successor
+// waits about 2.5 us for it: with few rows the part's time is on a second chain beside the chain of the diagonal blocks, with many the
+// workgroups are all busy and what counts is the time per row.  Twice the pure work over all
+// workgroups against the chains; measured at 1 / 2 / 4 rows, elimination and columns: 256 x 2304 0.48 / 0.48 / 0.57 ms,
+// 2048 x 512 0.140 / 0.140 / 0.157, 1000 x 2048 0.45 / 0.47 / 0.54, 2048 x 1500 0.45 / 0.40 / 0.43, 1024 x 4608 1.99 / 1.70 / 1.63, 8192 x 256
+// 0.21 / 0.15 / 0.13; 300 x 4608 1.31 / 1.35 / 1.37, where the rule takes 4.
 static int column_rows(int cus, int64_t R, int64_t T)
 {
     const double NG = (double)((R + NB - 1) / NB), t = (double)T, products = 2.4 * (t * t * t / 6.0 + NG * t * t / 2.0);
@@ -1112,7 +1116,7 @@ static int column_rows(int cus, int64_t R, int64_t T)
     double least = 0.0;
     for (int i = 0; i < 3; ++i) {
         const int nr = 1 << i;
-        const double chains = t * std::max(15.3, PART_US[i] + 2.5), work = 2.0 / (cus - 1) * (products + t * NG * (8 / nr) * PART_US[i]);
+        const double chains = t * std::max(BLOCK_US, PART_US[i] + 2.5), work = 2.0 / (cus - 1) * (products + t * NG * (8 / nr) * PART_US[i]);
         const double time = std::max(chains, work);
         if (i == 0 || time < least) { least = time; best = nr; }
     }
@@ -1142,9 +1146,11 @@ static FlowInverseP inverse_params(const double* H, int d, double damp, double d
     p.f.looks = looks;
     p.f.d = d;
     p.f.T = (d + NB - 1) / NB;
-    // two rows of tiles and a half in flight keep the chain fed; where the products bound the launch, queue 1 feeds queue 2 and its
-    // workgroups go over to that when it is empty, so it has most of them (2048 x 4608, the layer, with 2/5, 1/2, 3/5, 7/10 and 9/10
-    // of the workgroups: 4631, 4418, 4333, 4240 and 4247 us)
+    // Two rows of tiles and a half in flight keep the chain fed: with 1.5, 2, 2.5, 3 and 4 the inverse of 4 to 24 blocks of columns takes the
+    // same (77, 127, 182, 231, 339 us for 4, 8, 12, 16, 24), that of 36 594, 542, 534, 535, 535, of 48 972, 855, 800, 787, 790, of
+    // 64 1732, 1524, 1430, 1407, 1408.  Where the products bound the launch, queue 1 feeds queue 2 and its workgroups go over to that
+    // when it is empty, so it has most of them: with 1/2, 3/5, 7/10 and 4/5 of the workgroups 64 blocks 1522, 1447, 1409, 1401 us, 72 2098,
+    // 2003, 1921, 1891, 96 4840, 4513, 4323, 4240, 128 11500, 10752, 10182, 9910.
     p.f.n1 = std::max(1, std::min(5 * p.f.T / 2, wgs * 7 / 10));
     p.f.n2 = std::max(1, wgs - 1 - p.f.n1);          // the others: queue 2 (there is no third)
     p.f.n3 = 0;
@@ -1188,13 +1194,15 @@ hipError_t launch_flow_inverse(hipStream_t s, int cus, const double* H, int d, d
 }
 
 // What the queues of an elimination have to do, in units of 2.3 us, a rank-64 product of a tile near the chain: tiles of U; parts of
-// columns (measured; of a layer narrower than a block their steps are fewer); sums of 64 rows.  Where there are more groups of
+// columns (3, 5 and 8 units for 1, 2 and 4 rows per wavefront; of a layer narrower than a block their steps are fewer); sums of 64 rows.  Where there are more groups of
 // rows than blocks, the launch consists of parts and sums, and a sum is its products (1.5 units: their tiles come from farther
 // away) and, whatever their number, a ticket, the gather of its weights and its publication (5 us).  Otherwise the products
 // alone: queue 1's workgroups are free for the rest in the later half.  The best share of queue 3 in what queues 2 and 3 have,
 // measured / by these: 65535 x 64 from 0.16 on / 0.16, 65535 x 512 0.30 / 0.34, 4000 x 1024 0.46 / 0.47, 8000 x 2048 0.69 / 0.62;
 // 4096 x 4608 0.68 / 0.69 (6.80 ms; at 0.76 6.99), 2048 x 4608 0.70 to 0.76 / 0.69.  (With the products alone counted everywhere
 // 8 workgroups had the sums of 65535 x 64 and 245 waited for them: 986 us for the layer, 666 with a launch per block, 580 so.)
+// A part of 4 rows has become shorter since, 6.4 units; with 8, 7.2 and 6.4 the layer takes, 65535 x 512 2286, 2343, 2396 us, 20000 x 512 775,
+// 782, 796, 4096 x 4608 5781, 5795, 5865, 8192 x 256 264, 264, 265, 2048 x 4608 4193, 4147, 4148, 30000 x 1500 3906, 3849, 3827.
 static double work_u(double T) { return T * T * T / 6.0; }
 static double work_columns(double T, double NG, int nr, int d)
 {
@@ -1212,7 +1220,8 @@ FlowElimPlan flow_eliminate_plan(int cus, int d, int R)
     p.nr = column_rows(cus, R, T);
     const int64_t parts = NG * (8 / p.nr);
     // (a third more for queue 1 than its work: its workgroups go over to the other queues when it is empty, and those wait for its
-    // rows until then.  2048 x 4608 with 1, 1.3, 1.7 and 2.2 times the work 4546, 4419, 4544 and 4840 us, 1000 x 2048 959, 957, 963, 975)
+    // rows until then.  The layer with 1, 1.15, 1.3, 1.5 and 1.7 times the work: 2048 x 4608 4355, 4255, 4217, 4204, 4337 us, 1024 x 3072 1661,
+    // 1635, 1618, 1606, 1626, 512 x 4096 2500, 2498, 2500, 2504, 2583; 1000 x 2048, 2048 x 2048, 300 x 4608 and tall ones the same to 0.5 %)
     const double w1 = 1.3 * work_u((double)T), w2 = work_columns((double)T, (double)NG, p.nr, d), w3 = work_groups((double)T, (double)NG);
     const int64_t k1 = 2 * T, k2 = parts + (parts + 1) / 2, k3 = NG + NG * T / 6;
     const int avail = flow_grid(cus, T * (T + 9 * NG)) - 1;
@@ -1243,7 +1252,7 @@ hipError_t launch_flow_eliminate(hipStream_t s, int cus, const FlowElimArgs& a)
 }
 
 // ---- several small layers (fobq_quantize_layers_batched) ----------------------------------------------------------
-// A layer of at most 4 blocks is bound by its chain (about 18 us a block in the inverse, 15 to 20 in the elimination); the
+// A layer of at most 4 blocks is bound by its chain (12 to 14 us a block; an inverse of 1, 2, 3 and 4 blocks 37, 52, 64 and 76 us as a call); the
 // layers' chains run side by side, and the launch ends when the device has worked off the parts of the longest ones.  20
 // layers of 64 .. 1024 rows and 64 .. 256 columns: inverse 66 us (one workgroup per layer, a panel at a time: 311),
 // elimination with columns 150 us (191 + 311 before, in launches of their own); the call 319 us, 1033 before.
@@ -1262,7 +1271,7 @@ void flow_batch_deal(int cus, int n, const int* d, const int* R, FlowElimPlan* o
         double chains = 0.0, work = 0.0;
         for (int l = 0; l < n; ++l) {
             const double T = (d[l] + NB - 1) / NB, NG = (R[l] + NB - 1) / NB;
-            chains = std::max(chains, T * std::max(15.3, PART_US[i] + 2.5));
+            chains = std::max(chains, T * std::max(BLOCK_US, PART_US[i] + 2.5));
             work += T * NG * (8 >> i) * PART_US[i] * 2.0 / (cus - 1);
         }
         const double time = std::max(chains, work);

@@ -541,8 +541,8 @@ __global__ __launch_bounds__(512) void xxt_i8_kernel(const signed char* __restri
         }
         // An accumulation's first launch finds nothing in its slabs and stores; where a tile has fewer pieces than the launch has
         // slabs (fresh), its workgroups put zeros into the others in turn.  (Against a launch that clears them all and sums
-        // read and written: 256-channel maps, 3 x 3, 599 -> 555 us the call, 128 channels with stride 2 638 -> 604, 4608 x 24576
-        // 3574 -> 3457.)
+        // read and written, the call: 256-channel maps, 3 x 3, 550 -> 523 us, 128 channels with stride 2 638 -> 599, 512 x 50176 227 -> 187,
+        // 1000 x 3000 115 -> 86, 4608 x 6000 1003 -> 943; 4608 x 24576 3555 -> 3494, within what two runs of it differ by.)
         for (int p = piece + pieces; p < fresh; p += pieces) {
             double* __restrict__ rest = Hpart + (int64_t)p * d * d;
             for (int e = threadIdx.x; e < IT * IT; e += 512) {

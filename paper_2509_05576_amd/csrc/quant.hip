@@ -665,9 +665,6 @@ hipError_t launch_step(hipStream_t s, double* Wp, int R, int d, int t, double* A
 }
 
 // ---------------------------------------------------------------------------
-// Outputs in original column order: codes[i][c] and Q[i][c] = scale * (code - zero)
-// for the column c processed at step invperm[c] < steps; others get code 0, Q 0.
-// Workgroup (0, 0) also adds up the per-row loss terms (loss != null).
 // Codes and Q of RB rows from i0 on and 64 columns from c0 on, in original order: a column's codes of consecutive rows are
 // contiguous (16 bytes a lane), a row's columns come from all over codesT, so they change places in LDS.  (A byte a thread from a
 // line of its own: 20 layers of up to 1024 x 256 323 us against 318 for the call, 2048 x 4608 4422 and 4391.)  Columns with invperm outside 0 .. steps - 1 give 0.
@@ -703,6 +700,10 @@ __device__ __forceinline__ void emit_tile(const uint8_t* __restrict__ codesT, in
     }
 }
 
+// Outputs in original column order: codes[i][c] and Q[i][c] = scale * (code - zero)
+// for the column c processed at step invperm[c] < steps; others get code 0, Q 0.
+// Workgroup (0, 0) also adds up the per-row loss terms (loss != null) and hands out the status words, the first row of workgroups the
+// order (tail).
 template <int RB>
 __global__ __launch_bounds__(256) void emit_kernel(const uint8_t* __restrict__ codesT, int Rp, int R, int d, int steps,
                                                    const int* __restrict__ invperm, const double* __restrict__ scale,
@@ -908,8 +909,8 @@ __global__ __launch_bounds__(256) void batch_order_kernel(const BatchLayer* __re
     if (L.perm_out && j < d) L.perm_out[j] = L.perm[j];
 }
 
-// Codes and dequantized weights of all layers in original column order, and the losses (as emit_kernel); blockIdx.x: 1024
-// weights of a layer
+// Codes and dequantized weights of all layers in original column order, and the losses (as emit_kernel); blockIdx.x: a tile of 16 rows
+// and 64 columns of a layer
 __global__ __launch_bounds__(256) void batch_emit_kernel(const BatchLayer* __restrict__ layers)
 {
     const BatchLayer L = layers[blockIdx.y];

@@ -28,13 +28,6 @@ constexpr int NT = 512;   // threads per workgroup of every kernel that uses the
 constexpr int DL = 66;    // LDS row stride (doubles): conflict-free 8-byte MFMA fragment reads per half-wave
 constexpr int SWEEP_LDS = NB + 16 * DL + 2;   // doubles of LDS that chol_block / elim_block need besides the two tiles
 
-__device__ __forceinline__ double readlane_f64(double v, int lane)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
 // Reciprocal and reciprocal square root of a pivot (a normal, positive number): the hardware
 // approximation r0 (good to about 2^-24) with one third-order correction,
 //   1/x       = r0 (1 + e + e^2 + ...),            e = 1 - x r0
@@ -152,8 +145,7 @@ __device__ __forceinline__ void inv_tile(double* Xm, TF tfetch, int i, int j, in
 //   (after each of b = 0..2: trail(b) on all wavefronts)
 // Called by all NT threads of the workgroup (at least 6 wavefronts); ends with a barrier.
 // `beside` is called by wavefronts 1 .. 7 during the first sweep: the caller's work on tiles of the block that this sweep does
-// not read (it reads the first tile column / row only; the diagonal entries of later tiles that its lanes carry along are not
-// used).  `ahead` is called by every wavefront about 2 us before the end (wavefront 0: after the last sweep).
+// not read (it reads the first tile column / row only).  `ahead` is called by every wavefront about 2 us before the end (wavefront 0: after the last sweep).
 struct Nothing { __device__ void operator()() const {} };
 template <class SW, class TR, class TF, class BS, class AH>
 __device__ __forceinline__ void block_schedule(double* Xm, SW sweep, TR trail, TF tf, BS beside, AH ahead)

@@ -27,7 +27,7 @@ def test_bad_plans_are_refused():
             fobq.fobq_debug_plan(fobq.PLAN_PAD, args, 2)
 
 
-PART_US, GROUP_US, PRODUCT_US = {1: 7.5, 2: 11.0, 4: 18.0}, 5.0, 3.4       # measured on an MI355X: a part of columns, a sum's own time, one of its products
+PART_US, GROUP_US, PRODUCT_US = {1: 7.5, 2: 11.0, 4: 18.0}, 5.0, 3.4       # the rules' weights in us: a part of columns, a sum's own time, one of its products
 
 
 def _queue_us(r, d, nr, n1, n2, n3):
