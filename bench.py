@@ -36,6 +36,15 @@ def _blob_hash(path: str) -> str:
     return hashlib.sha1(b"blob %d\0" % len(data) + data).hexdigest()
 
 
+def hessian_entries_formed(d: int, channels: int = 0) -> float:
+    """Entries of H that the matrix kernel cannot do without: the lower triangle, or (channels > 0) of a k x k convolution by tap offsets
+    one block per offset up to its sign, of the zero offset's block the triangle; the rest of H comes from those by corrections."""
+    if not channels:
+        return d * (d + 1) / 2.0
+    k = round((d // channels) ** 0.5)
+    return channels * (channels + 1) / 2.0 + ((2 * k - 1) ** 2 - 1) // 2 * float(channels) ** 2
+
+
 def measured_traffic(kernel: str, workload: str):
     """HBM bytes per launch of `kernel` on `workload` from the counter runs recorded in profiles/traffic.json
     (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, each scaled by what the same counter reads for a plain device
@@ -372,17 +381,13 @@ def main() -> int:
     offsets = form == fobq.FORM_INT8_TAP_OFFSETS
     if int8:
         # integer-slice formulation: 19 int8 slice products per entry the kernel forms, against the dense int8 peak.
-        # Entries: the lower triangle, d (d + 1) / 2 -- or, for a convolution taken by tap offsets, the two block
-        # rows of c channels that hold every offset, 2 c d (the rest of H comes from them by corrections).
-        channels = spec.conv[2] if (offsets and spec.conv is not None) else 0
-        entries2 = 4.0 * channels * spec.d_col if offsets else float(spec.d_col) * (spec.d_col + 1)    # 2 x entries
-        ops_per_launch = 19.0 * entries2 * n_per_launch
+        ops_per_launch = 19.0 * 2.0 * hessian_entries_formed(spec.d_col, spec.conv[2] if offsets else 0) * n_per_launch
         achieved = ops_per_launch / (avg_ms * 1e-3) / 1e12
         roofline = {"kernel": "xxt_i8_kernel", "bound": "mfma", "achieved": round(achieved, 1), "peak": PEAK_INT8_MFMA_TOPS,
                     "unit": "TOP/s", "frac": round(achieved / PEAK_INT8_MFMA_TOPS, 4),
                     "traffic": measured_traffic("xxt_i8_kernel", spec.name) if launches_per_step == 1 and not args.from_maps else None,
                     "avg_launch_ms": round(avg_ms, 4), "algorithmic_ops_per_launch": ops_per_launch,
-                    "slice_products": 19, "entries_formed": "two block rows (tap offsets)" if offsets else "lower triangle",
+                    "slice_products": 19, "entries_formed": "one block per tap offset" if offsets else "lower triangle",
                     "fp64_equivalent_TFLOPs": round(flops_per_launch / (avg_ms * 1e-3) / 1e12, 2),
                     "fp64_equivalent_over_fp64_mfma_peak": round(flops_per_launch / (avg_ms * 1e-3) / 1e12 / PEAK_FP64_MFMA_TFLOPS, 3)}
         # What the int8 matrix cores sustain on this machine, outside the timed region: the kernel's inner loop
