@@ -32,6 +32,32 @@ __device__ __forceinline__ double slab_sum(const double* __restrict__ p, int n, 
     return s;
 }
 
+// Entry (a, b) of a symmetric matrix of d columns and its mirror image, into H and, if there is one, H2: a workgroup of 256 has a tile of 16 x 16,
+// row threadIdx.x / 16, whose lower triangle alone counts on the diagonal.  TURN: the tile changes places in LDS, so that the mirror image is
+// written 16 entries a row as well (every thread of the workgroup comes here).  Without, a store instruction takes 16 pieces of 4 entries there,
+// twice since H2 is written beside H: 4607 x 700 421 -> 424 us against a copy behind the launch, so 412; 4096 x 600 290, 279, 249; the
+// barrier costs 1 us where the launch takes 4, up to 256 columns.
+template <bool TURN>
+__device__ __forceinline__ void store_symmetric(double s, int d, double* __restrict__ H, double* __restrict__ H2)
+{
+    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+    auto put = [&](int row, int col, double v) {
+        H[(int64_t)row * d + col] = v;
+        if (H2) H2[(int64_t)row * d + col] = v;
+    };
+    const int a = 16 * blockIdx.y + y, b = 16 * blockIdx.x + x;
+    if (a < d && b <= a) put(a, b, s);
+    if constexpr (TURN) {
+        __shared__ double t[16 * 17];
+        t[y * 17 + x] = s;
+        __syncthreads();
+        const int a2 = 16 * blockIdx.y + x, b2 = 16 * blockIdx.x + y;
+        if (a2 < d && b2 <= a2) put(b2, a2, t[x * 17 + y]);
+    } else if (a < d && b <= a) {
+        put(b, a, s);
+    }
+}
+
 // Looks that a wavefront inside a factorization launch waits while nobody in that launch draws a tile before the launch is given
 // up.  A look takes 0.16 to 0.19 us (measured, one workgroup or 256 of them waiting): 43 to 51 seconds.
 constexpr int FLOW_LOOKS = 1 << 28;

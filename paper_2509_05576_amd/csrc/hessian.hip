@@ -765,22 +765,19 @@ hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp
 // H[a][b] = H[b][a] = factor * sum_s Hpart[s][a][b]   for b <= a (lower slabs hold the sums)
 // poison (may be null): a word that is non-zero when an input of the integer-slice path held an Inf or NaN;
 // H then becomes NaN throughout, as the floating-point sum would have made the rows concerned.
+// TURN: see store_symmetric.
+template <bool TURN>
 __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
                                                                double factor, double* __restrict__ H, double* __restrict__ H2,
                                                                const int* __restrict__ poison)
 {
+    if (blockIdx.x > blockIdx.y) return;
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
     const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (a >= d || b >= d || b > a) return;
-    double s = slab_sum(Hpart + (int64_t)a * d + b, splits, (int64_t)sstride * d * d);
-    s *= factor;
+    double s = 0.0;
+    if (a < d && b <= a) s = slab_sum(Hpart + (int64_t)a * d + b, splits, (int64_t)sstride * d * d) * factor;
     if (poison && *poison) s = __builtin_nan("");
-    H[(int64_t)a * d + b] = s;
-    H[(int64_t)b * d + a] = s;
-    if (H2) {
-        H2[(int64_t)a * d + b] = s;
-        H2[(int64_t)b * d + a] = s;
-    }
+    store_symmetric<TURN>(s, d, H, H2);
 }
 
 // Convolution mode: the slabs are in tap-major row order; H is written in (c, ky, kx) order.  ONE: the slabs one after another.  The
@@ -788,29 +785,26 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
 // at the same slab: with four of them in flight 576 columns (3 x 3) 58 -> 62 us for the call, 900 99 -> 103, 1200 (5 x 5) 130 -> 150.
 // A slab of up to 256 columns stays in the L2, and rows of a 1 x 1 kernel are read whole: there four (147 columns 61 -> 60 us, 512 of a
 // 1 x 1 kernel 50 -> 43).
-template <bool ONE>
+template <bool ONE, bool TURN>
 __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
                                                                     double factor, double* __restrict__ H, double* __restrict__ H2,
                                                                     int c, int kk, const int* __restrict__ poison)
 {
+    if (blockIdx.x > blockIdx.y) return;
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
     const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (a >= d || b >= d || b > a) return;
-    const int ai = (a % kk) * c + a / kk, bi = (b % kk) * c + b / kk;
-    const int hi = max(ai, bi), lo = min(ai, bi);
     double s = 0.0;
-    if (ONE)
-        for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)hi * d + lo];
-    else
-        s = slab_sum(Hpart + (int64_t)hi * d + lo, splits, (int64_t)sstride * d * d);
-    s *= factor;
-    if (poison && *poison) s = __builtin_nan("");
-    H[(int64_t)a * d + b] = s;
-    H[(int64_t)b * d + a] = s;
-    if (H2) {
-        H2[(int64_t)a * d + b] = s;
-        H2[(int64_t)b * d + a] = s;
+    if (a < d && b <= a) {
+        const int ai = (a % kk) * c + a / kk, bi = (b % kk) * c + b / kk;
+        const int hi = max(ai, bi), lo = min(ai, bi);
+        if (ONE)
+            for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)hi * d + lo];
+        else
+            s = slab_sum(Hpart + (int64_t)hi * d + lo, splits, (int64_t)sstride * d * d);
+        s *= factor;
     }
+    if (poison && *poison) s = __builtin_nan("");
+    store_symmetric<TURN>(s, d, H, H2);
 }
 
 // conv_c > 0: the slabs were accumulated in convolution mode with conv_c channels and conv_kk taps
@@ -840,14 +834,15 @@ hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int
         splits = groups;
         sstride = SLAB_GROUP;
     }
-    if (conv_c > 0 && conv_kk > 1 && d > 256)
-        hipLaunchKernelGGL(hessian_finalize_conv_kernel<true>, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
-                           poison);
-    else if (conv_c > 0)
-        hipLaunchKernelGGL(hessian_finalize_conv_kernel<false>, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk,
-                           poison);
-    else
-        hipLaunchKernelGGL(hessian_finalize_kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, poison);
+    const bool turn = d > 256;
+    if (conv_c > 0) {
+        const auto kernel = !turn ? hessian_finalize_conv_kernel<false, false>
+                          : conv_kk > 1 ? hessian_finalize_conv_kernel<true, true> : hessian_finalize_conv_kernel<false, true>;
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk, poison);
+    } else {
+        hipLaunchKernelGGL((turn ? hessian_finalize_kernel<true> : hessian_finalize_kernel<false>), grid, block, 0, s, Hpart, splits, sstride, d, factor,
+                           H, H2, poison);
+    }
     return hipGetLastError();
 }
 

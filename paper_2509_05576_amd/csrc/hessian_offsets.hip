@@ -182,32 +182,30 @@ __global__ __launch_bounds__(256) void hessian_finalize_offsets_kernel(const dou
                                                                        int c, int k, const double* __restrict__ corr,
                                                                        const int* __restrict__ poison)
 {
+    if (blockIdx.x > blockIdx.y) return;
     const int col = blockIdx.x * 16 + (threadIdx.x & 15);
     const int row = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (row >= d || col >= d || col > row) return;
-    const int kk = k * k;
-    int ta = row % kk, ch = row / kk, tb = col % kk, ch2 = col / kk;       // H's order: index = channel * k^2 + tap
-    int dy = tb / k - ta / k, dx = tb % k - ta % k;
-    const bool canonical = dy > 0 || (dy == 0 && dx > 0) || (dy == 0 && dx == 0 && ch2 <= ch);
-    if (!canonical) {
-        int t = ta; ta = tb; tb = t;
-        t = ch; ch = ch2; ch2 = t;
-        dy = -dy; dx = -dx;
+    double s = 0.0;
+    if (row < d && col <= row) {
+        const int kk = k * k;
+        int ta = row % kk, ch = row / kk, tb = col % kk, ch2 = col / kk;       // H's order: index = channel * k^2 + tap
+        int dy = tb / k - ta / k, dx = tb % k - ta % k;
+        const bool canonical = dy > 0 || (dy == 0 && dx > 0) || (dy == 0 && dx == 0 && ch2 <= ch);
+        if (!canonical) {
+            int t = ta; ta = tb; tb = t;
+            t = ch; ch = ch2; ch2 = t;
+            dy = -dy; dx = -dx;
+        }
+        const int a0x = dx >= 0 ? 0 : k - 1;
+        const int t0 = a0x, t1 = dy * k + a0x + dx;                             // the base taps a0 = (0, a0x), b0 = a0 + offset
+        const int64_t at = (int64_t)(t0 * c + ch) * d + t1 * c + ch2;
+        // (a gather: one slab at a time, as in hessian_finalize_conv_kernel; 64 channels 111 -> 103 us, 256 173 -> 166)
+        for (int q = 0; q < splits; ++q) s += Hpart[(int64_t)q * d * d + at];
+        if (!(ta / k == 0 && ta % k == a0x)) s += corr[(int64_t)(ta * c + ch) * d + tb * c + ch2];
+        s *= factor;
     }
-    const int a0x = dx >= 0 ? 0 : k - 1;
-    const int t0 = a0x, t1 = dy * k + a0x + dx;                             // the base taps a0 = (0, a0x), b0 = a0 + offset
-    const int64_t at = (int64_t)(t0 * c + ch) * d + t1 * c + ch2;
-    double s = 0.0;             // (a gather: one slab at a time, as in hessian_finalize_conv_kernel; 64 channels 111 -> 103 us, 256 173 -> 166)
-    for (int q = 0; q < splits; ++q) s += Hpart[(int64_t)q * d * d + at];
-    if (!(ta / k == 0 && ta % k == a0x)) s += corr[(int64_t)(ta * c + ch) * d + tb * c + ch2];
-    s *= factor;
     if (poison && *poison) s = __builtin_nan("");
-    H[(int64_t)row * d + col] = s;
-    H[(int64_t)col * d + row] = s;
-    if (H2) {
-        H2[(int64_t)row * d + col] = s;
-        H2[(int64_t)col * d + row] = s;
-    }
+    store_symmetric<true>(s, d, H, H2);
 }
 
 // full rows [row0, row0 + n0) and [row1, row1 + n1) of `count` slabs from slab `first` on
