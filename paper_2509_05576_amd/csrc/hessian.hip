@@ -765,8 +765,8 @@ hipError_t launch_xxt_conv(hipStream_t s, const float* padded, int n_img, int hp
 // H[a][b] = H[b][a] = factor * sum_s Hpart[s][a][b]   for b <= a (lower slabs hold the sums)
 // poison (may be null): a word that is non-zero when an input of the integer-slice path held an Inf or NaN;
 // H then becomes NaN throughout, as the floating-point sum would have made the rows concerned.
-// TURN: see store_symmetric.
-template <bool TURN>
+// TURN: see store_symmetric.  ONE: the slabs one after another, not four in flight (launch_hessian_finalize).
+template <bool ONE, bool TURN>
 __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
                                                                double factor, double* __restrict__ H, double* __restrict__ H2,
                                                                const int* __restrict__ poison)
@@ -775,7 +775,13 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
     const int b = blockIdx.x * 16 + (threadIdx.x & 15);
     const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
     double s = 0.0;
-    if (a < d && b <= a) s = slab_sum(Hpart + (int64_t)a * d + b, splits, (int64_t)sstride * d * d) * factor;
+    if (a < d && b <= a) {
+        if (ONE)
+            for (int k = 0; k < splits; ++k) s += Hpart[(int64_t)k * sstride * d * d + (int64_t)a * d + b];
+        else
+            s = slab_sum(Hpart + (int64_t)a * d + b, splits, (int64_t)sstride * d * d);
+        s *= factor;
+    }
     if (poison && *poison) s = __builtin_nan("");
     store_symmetric<TURN>(s, d, H, H2);
 }
@@ -783,8 +789,7 @@ __global__ __launch_bounds__(256) void hessian_finalize_kernel(const double* __r
 // Convolution mode: the slabs are in tap-major row order; H is written in (c, ky, kx) order.  ONE: the slabs one after another.  The
 // gather takes a line of a slab for an entry or two, and finds it in the L2 again for the taps beside it only while all threads are
 // at the same slab: with four of them in flight 576 columns (3 x 3) 58 -> 62 us for the call, 900 99 -> 103, 1200 (5 x 5) 130 -> 150.
-// A slab of up to 256 columns stays in the L2, and rows of a 1 x 1 kernel are read whole: there four (147 columns 61 -> 60 us, 512 of a
-// 1 x 1 kernel 50 -> 43).
+// A slab of up to 256 columns stays in the L2 (147 columns 61 -> 60 us with four), and rows of a 1 x 1 kernel are read whole.
 template <bool ONE, bool TURN>
 __global__ __launch_bounds__(256) void hessian_finalize_conv_kernel(const double* __restrict__ Hpart, int splits, int sstride, int d,
                                                                     double factor, double* __restrict__ H, double* __restrict__ H2,
@@ -834,14 +839,20 @@ hipError_t launch_hessian_finalize(hipStream_t s, double* Hpart, int splits, int
         splits = groups;
         sstride = SLAB_GROUP;
     }
-    const bool turn = d > 256;
+    // Four slabs in flight where rows are read whole and a tile's pieces of them begin with a line or its half, or all slabs of a tile's
+    // columns stay in the L2; else a line is found there again by the next tile only while all are at the same slab.  One after
+    // another / four, the call: 288 x 900 21.9 / 16.8 us, 420 x 9000 59.0 / 54.2, 511 x 600 30.0 / 30.8, 512 x 20000 122.6 / 114.0, 701 x 900
+    // 32.8 / 33.9, 520 of a 1 x 1 kernel 38.0 / 35.9, 640 x 500 29.9 / 28.9, 768 x 512 32.7 / 33.6, 896 x 700 43.5 / 44.3, 1040 x 512 48.2 / 45.0, 1400 x 700
+    // 65.7 / 63.8; of few slabs 2048 x 512 71.5 / 72.1.
+    const bool turn = d > 256, rows = conv_c <= 0 || conv_kk == 1;
+    const bool four = d <= 256 || (rows && (d <= 504 || (d % 8 == 0 && (d <= 640 || (d >= 1000 && splits >= 8)))));
     if (conv_c > 0) {
         const auto kernel = !turn ? hessian_finalize_conv_kernel<false, false>
-                          : conv_kk > 1 ? hessian_finalize_conv_kernel<true, true> : hessian_finalize_conv_kernel<false, true>;
+                          : four ? hessian_finalize_conv_kernel<false, true> : hessian_finalize_conv_kernel<true, true>;
         hipLaunchKernelGGL(kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, conv_c, conv_kk, poison);
     } else {
-        hipLaunchKernelGGL((turn ? hessian_finalize_kernel<true> : hessian_finalize_kernel<false>), grid, block, 0, s, Hpart, splits, sstride, d, factor,
-                           H, H2, poison);
+        const auto kernel = !turn ? hessian_finalize_kernel<false, false> : four ? hessian_finalize_kernel<false, true> : hessian_finalize_kernel<true, true>;
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, Hpart, splits, sstride, d, factor, H, H2, poison);
     }
     return hipGetLastError();
 }

@@ -21,7 +21,7 @@ def _check(fobq, ctx, H, buf, X):
     assert torch.equal(a.Q, b.Q) and torch.equal(a.perm, b.perm) and torch.equal(a.loss, b.loss)
 
 
-@pytest.mark.parametrize("mode,d", [(m, d) for m in ("f64", "i8") for d in (1, 15, 16, 17, 255, 256, 257, 272, 273, 400, 511, 1041)])
+@pytest.mark.parametrize("mode,d", [(m, d) for m in ("f64", "i8") for d in (1, 15, 16, 17, 255, 256, 257, 272, 273, 400, 511, 640, 1041)])
 def test_both_copies_from_x(mode, d):
     import paper_2509_05576_amd as fobq
     X = torch.randn((d, 700), generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
@@ -34,7 +34,7 @@ def test_both_copies_from_x(mode, d):
 
 
 @pytest.mark.parametrize("mode", ["f64", "i8"])
-@pytest.mark.parametrize("c,k,stride", [(3, 7, 2), (29, 3, 1), (255, 1, 1), (257, 1, 2), (45, 3, 2), (64, 3, 1), (128, 2, 1)])
+@pytest.mark.parametrize("c,k,stride", [(3, 7, 2), (29, 3, 1), (255, 1, 1), (257, 1, 2), (512, 1, 1), (45, 3, 2), (64, 3, 1), (128, 2, 1)])
 def test_both_copies_from_maps(mode, c, k, stride):
     import paper_2509_05576_amd as fobq
     maps = torch.randn((5, 14, 13, c), generator=torch.Generator(device="cuda").manual_seed(c), device="cuda")
