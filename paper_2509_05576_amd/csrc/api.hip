@@ -1307,6 +1307,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     unsigned char* hb = static_cast<unsigned char*>(ctx->h_batch);
     BatchLayer* hd = static_cast<BatchLayer*>(ctx->h_batch);
     int max_pairs = 1, max_chunks = 1, max_tiles = 1, max_d = 1;
+    int64_t rows = 0;
     size_t pool = 0;
     pool_take(nullptr, &pool, (size_t)n_layers * 4 * sizeof(int));          // status words
     for (int l = 0; l < n_layers; ++l) {
@@ -1328,6 +1329,7 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
         max_pairs = std::max(max_pairs, L.R * L.G);
         max_chunks = std::max(max_chunks, L.chunks);
         max_d = std::max(max_d, L.d);
+        rows += L.R;
         max_tiles = std::max(max_tiles, (L.R + 15) / 16 * ((L.d + 63) / 64));
     }
     FOBQ_TRY(ctx->batch_pool.ensure(pool), "workspace batch pool");
@@ -1360,9 +1362,10 @@ int fobq_quantize_layers_batched(fobq_ctx* ctx, int32_t n_layers, const fobq_lay
     int rc = [&]() -> int {
         FOBQ_TRY(hipMemcpyAsync(ctx->batch_desc.p, hb, sent_bytes, hipMemcpyHostToDevice, s), "upload batch descriptors");
         // The column sums need the weights and their grids only: beside the inverse, as for a single layer, on the side stream.  Two blocks
-        // of columns or many layers make an inverse that is worth the two waits between the streams (beside / in front of it: 1024 x 256 191 /
-        // 207 us, 128 x 128 121 / 134, 16 layers of 64 x 64 323 / 329; one of 64 x 64 107 / 100, of 1024 x 64 113 / 108, 4 of 16 x 16 146 / 139).
-        const bool want_side = max_d > 64 || n_layers >= 16, beside = want_side && side_at_hand(ctx);
+        // of columns or many layers make an inverse that is worth the two waits between the streams, many rows make sums that are (beside / not:
+        // 1024 x 256 191 / 207 us, 128 x 128 121 / 134, 16 layers of 64 x 64 323 / 329, 4 of 16000 x 64 324 / 332, of 6000 x 64 196 / 199; one of
+        // 16000 x 64 207 / 212, of 12000 x 64 173 / 170, of 64 x 64 107 / 100, of 1024 x 64 113 / 108, 4 of 4096 x 16 137 / 134, of 16 x 16 146 / 139).
+        const bool want_side = max_d > 64 || n_layers >= 16 || rows >= 16000, beside = want_side && side_at_hand(ctx);
         FOBQ_TRY(launch_batch_grid(s, dl, n_layers, max_pairs, beside ? ctx->sync_ev[EV_FORK] : nullptr), "grid (batch)");
         FOBQ_TRY(launch_flow_batch_inverse(s, db + off_inv, reinterpret_cast<const uint16_t*>(db + off_inv_of), arrivals, plan.inv_wgs), "inverse (batch)");
         if (beside) FOBQ_TRY(hipStreamWaitEvent(ctx->side, ctx->sync_ev[EV_FORK], 0), "stream wait");

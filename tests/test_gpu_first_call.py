@@ -14,11 +14,11 @@ def _maps(seed, c=128):
     return torch.relu(torch.randn((8, 12, 12, c), generator=g, device="cuda"))
 
 
-def _layers(seed):
+def _layers(seed, shapes):
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     Ws, Hs = [], []
-    for r, d in ((64, 147), (300, 64), (16, 256)):
+    for r, d in shapes:
         X = torch.randn((d, 600), generator=g, device="cuda").double()
         Ws.append(torch.randn((r, d), generator=g, device="cuda"))
         Hs.append((X @ X.T.contiguous() / 300).contiguous())
@@ -33,12 +33,16 @@ def _hessian(fobq, ctx, seed):
     return [H]
 
 
-def _batch(fobq, ctx, seed):
-    Ws, Hs = _layers(seed)
+def _batch(fobq, ctx, seed, shapes=((64, 147), (300, 64), (16, 256))):
+    Ws, Hs = _layers(seed, shapes)
     return [t for o in ctx.quantize_layers_batched(Ws, Hs) for t in (o.codes, o.Q, o.perm, o.scales, o.zeros, o.loss)]
 
 
-@pytest.mark.parametrize("call", [_hessian, _batch])
+def _tall(fobq, ctx, seed):                  # one block of columns, and enough rows for the side stream
+    return _batch(fobq, ctx, seed, ((15000, 40), (1000, 64)))
+
+
+@pytest.mark.parametrize("call", [_hessian, _batch, _tall])
 def test_a_first_call_makes_no_stream(call):
     import paper_2509_05576_amd as fobq
     said = []
@@ -54,7 +58,7 @@ def test_a_first_call_makes_no_stream(call):
     assert 5 < nth < 99 and not any("side stream" in m or "event" in m for m in said), said
 
 
-@pytest.mark.parametrize("call", [_hessian, _batch])
+@pytest.mark.parametrize("call", [_hessian, _batch, _tall])
 def test_calls_without_and_with_the_side_stream_agree(call):
     import paper_2509_05576_amd as fobq
     wrong = []
